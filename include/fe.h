@@ -46,7 +46,12 @@
  *   lo[M * (nmax-1)]      lo_k of hop k in lo[m*(nmax-1) + k], k < N-1;
  *   hi[M * (nmax-1)]      hi_k likewise.  0 <= lo_k < hi_k < 2^30 and
  *                         sum_k hi_k < 2^30.
- *   Every such hop is counted exactly.  Algorithm 1's list for hop k matters
+ *   Every such hop is counted exactly.  By default the counters walk
+ *   per-type event lists of the stream, which each call builds in library
+ *   workspace (about 16 B per event), and need no lists of their own; calls
+ *   those do not take (FE_PARAM_TYPE_DISPATCH = 0, FE_PARAM_SEGMENTS > 0,
+ *   more than 4096 types or 2^30 events, or no memory for them) run the
+ *   machines event by event.  There, Algorithm 1's list for hop k matters
  *   only through the ticks that pass its test, a union of windows of which
  *   at most hi_k/(hi_k-lo_k+1)+1 are live at once.  Candidates whose hops
  *   all have at most 8 live windows keep their lists in registers; the
@@ -92,8 +97,11 @@ typedef enum fe_param {
                                  0 = per-candidate sequential walk             */
     FE_PARAM_TIMING = 4,     /* 1 = time every kernel launch with HIP events on
                                 the context's stream (fe_get_kernel_stats)     */
-    FE_PARAM_TYPE_DISPATCH = 5, /* 1 (default) = per-type dispatch: a lane steps
-                                only the events of its own episode's types
+    FE_PARAM_TYPE_DISPATCH = 5, /* 1 (default) = per-type dispatch: a candidate
+                                meets only the events of its own types, from
+                                per-type lists where the call takes those; in
+                                the event-by-event kernels a lane steps only
+                                the events of its own episode's types
                                 (for waves whose candidates share their first
                                 N-1 types, those events wave-wide plus each
                                 lane's own last-type events); 0 = every event

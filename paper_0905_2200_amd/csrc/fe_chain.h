@@ -1,0 +1,91 @@
+// fe_chain.h -- counting by chains over per-type event lists: the stream
+// index, its descriptors and the launchers (fe_chain.hip).  Not public.
+#pragma once
+
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include "fe_const.h"
+
+namespace fe {
+
+// Types an index may hold: the sort keeps three words of LDS per type in
+// each wave (48 KiB at this limit).  Streams with more take the Map kernels.
+constexpr int CHAIN_TYPES = 4096;
+// Guard entries behind every type's list: a search reads four entries at once.
+constexpr int LIST_PAD = 4;
+
+// One type's events in the index.
+struct TypeIdx {
+    int start;  // first entry of its list in et / ei
+    int count;  // events
+    int boff;   // its bucket table in tab: nb + 2 entries
+    int nb;     // buckets
+    int sh;     // bucket of tick t: (t - t0) >> sh
+    int t0;     // the stream's first tick
+    int pad[2];
+};
+
+// Per-type event lists of a stream (in stream order) and, per type, the
+// position of the first event of each power-of-two stretch of ticks.
+struct ChainIdx {
+    const int *et;       // ticks, LIST_PAD guards of INT_MAX after each list
+    const int *ei;       // stream indices, same layout
+    const int *tab;      // bucket tables
+    const TypeIdx *ty;   // [num_types]
+};
+
+// Device layout of an index over n events of T types, in ints.
+struct IndexPlan {
+    int n = 0, T = 0, nch = 0, chunk = 0;
+    int64_t o_et = 0, o_ei = 0, o_tab = 0, o_ty = 0, o_hist = 0, o_scan = 0, ints = 0;
+};
+IndexPlan index_plan(int64_t n, int T);
+ChainIdx index_view(const IndexPlan &p, int *base);
+
+// Candidate rows with strides: node k of candidate m has type
+// ty[m*ts + k*tk], hop k (lo, hi] = lo[m*hs + k*hk], hi[m*hs + k*hk]; its
+// size is len[m], or N when len is null.
+struct Rows {
+    const int *ty, *lo, *hi, *len;
+    int ts, tk, hs, hk, N;
+    int M;
+};
+
+// One stream's table to count; the two-pass form writes both outputs.
+struct ChainJob {
+    ChainIdx ix;
+    Rows rows;
+    int theta;
+    int *upper;  // relaxed counts
+    int *exact;  // exact counts
+    int P;       // segments per candidate
+    int4 *seg;   // [P][M] segment results (P > 1): completions, last one's index
+    // incremental form (count_io set): the events before `from`, whose tick
+    // is *t_from, are counted; adds the rest to the carry
+    int *count_io, *last_io;
+    const int *t_from;
+    int from;
+};
+
+enum ChainMode { CHAIN_EXACT = 0, CHAIN_RELAXED = 1, CHAIN_TWO_PASS = 2 };
+
+// Validates the stream and (rows.M > 0) the candidate rows into *status, and
+// starts the index with the per-chunk type histograms; *wmax: the largest
+// sum of hi among the candidates (may be null).
+void launch_index_check(const IndexPlan &p, const int *ids, const int *ticks, int *base,
+                        const Rows &rows, int nmax, int num_types, int *status, int *wmax,
+                        hipStream_t s);
+// The rest of the index; the first kernel also copies *status to hstat (a
+// pinned host word, may be null); base_index is added to the stored indices.
+void launch_index_types(const IndexPlan &p, const int *ticks, int *base, const int *status,
+                        int *hstat, hipStream_t s);
+void launch_index_lists(const IndexPlan &p, const int *ids, const int *ticks, int *base,
+                        const int *status, int base_index, hipStream_t s);
+// Counts every row of one job (status non-zero: nothing is written).
+void launch_chain(const ChainJob &job, ChainMode mode, int nmax, const int *status,
+                  hipStream_t s);
+// *out = the number of v[0..M) that are at least theta.
+void launch_count_ge(const int *v, int M, int theta, int *out, const int *status, hipStream_t s);
+
+}  // namespace fe

@@ -1,0 +1,642 @@
+// fe_chain.hip -- the stream index (per-type event lists) and the counting
+// kernels that walk it (fe_walk.h).
+#include "fe_chain.h"
+#include "fe_internal.h"
+#include "fe_walk.h"
+
+namespace fe {
+
+// ------------------------------------------------------------------ index
+// A stable counting sort by type: one wave per chunk of consecutive events
+// counts its types, the counts are scanned type by type, and the wave then
+// places its events; a last kernel fills each type's bucket table.
+namespace {
+
+constexpr int MAX_CHUNKS = 4096;
+constexpr int SMALL_SCAN = 16384;  // counts scanned by one block
+
+int64_t align64(int64_t x) { return (x + 63) & ~(int64_t)63; }
+
+// buckets of a type with c events: at most 2c + 2 (see k_ix_types)
+__host__ __device__ __forceinline__ int64_t tab_room(int64_t n, int64_t T) { return 2 * n + 4 * T; }
+
+}  // namespace
+
+IndexPlan index_plan(int64_t n, int T)
+{
+    IndexPlan p;
+    p.n = (int)n;
+    p.T = T;
+    int64_t chunk = (n + MAX_CHUNKS - 1) / MAX_CHUNKS;
+    if (chunk < 512) chunk = 512;
+    p.chunk = (int)((chunk + WAVE - 1) / WAVE * WAVE);
+    p.nch = (int)((n + p.chunk - 1) / p.chunk);
+    int64_t o = 0;
+    auto take = [&](int64_t ints) {
+        const int64_t at = o;
+        o += align64(ints);
+        return at;
+    };
+    p.o_et = take(n + (int64_t)LIST_PAD * T);
+    p.o_ei = take(n + (int64_t)LIST_PAD * T);
+    p.o_tab = take(tab_room(n, T));
+    p.o_ty = take((int64_t)T * (sizeof(TypeIdx) / sizeof(int)));
+    p.o_hist = take((int64_t)T * p.nch);
+    p.o_scan = take((int64_t)T * p.nch + scan_scratch_ints((int64_t)T * p.nch) + 1);
+    p.ints = o;
+    return p;
+}
+
+ChainIdx index_view(const IndexPlan &p, int *base)
+{
+    ChainIdx v;
+    v.et = base + p.o_et;
+    v.ei = base + p.o_ei;
+    v.tab = base + p.o_tab;
+    v.ty = (const TypeIdx *)(base + p.o_ty);
+    return v;
+}
+
+namespace {
+
+// Blocks [0, nch): stream checks (ticks non-decreasing and in range, ids in
+// range) and the chunk's type counts, hist[type*nch + chunk].  Blocks after
+// them: candidate checks, 64 rows each.
+__global__ __launch_bounds__(WAVE) void k_ix_check(const int *__restrict__ ids,
+                                                   const int *__restrict__ ticks, int n, int T,
+                                                   int chunk, int nch, int *__restrict__ hist,
+                                                   Rows rows, int nmax, int num_types,
+                                                   int *status, int *wmax)
+{
+    extern __shared__ int sh[];
+    const int lane = threadIdx.x;
+    int bits = 0;
+    if ((int)blockIdx.x < nch) {
+        const int c = blockIdx.x;
+        for (int e = lane; e < T; e += WAVE) sh[e] = 0;
+        __syncthreads();
+        const int b = c * chunk, e = b + chunk < n ? b + chunk : n;
+        for (int i = b + lane; i < e; i += WAVE) {
+            const int id = ids[i], t = ticks[i];
+            if (id < 0 || id >= num_types || t < 0 || t >= TICK_LIMIT) bits |= ST_RANGE;
+            else if (T) atomicAdd(&sh[id], 1);
+            if (i > 0 && ticks[i - 1] > t) bits |= ST_UNSORTED;
+        }
+        __syncthreads();
+        for (int e2 = lane; e2 < T; e2 += WAVE) hist[(int64_t)e2 * nch + c] = sh[e2];
+    } else {
+        const int m = ((int)blockIdx.x - nch) * WAVE + lane;
+        int W = 0;
+        if (m < rows.M) {
+            const int N = rows.len ? rows.len[m] : rows.N;
+            bool ok = N >= 1 && N <= nmax;
+            int64_t w = 0;
+            for (int k = 0; ok && k < N; ++k) {
+                const int t = rows.ty[(int64_t)m * rows.ts + k * rows.tk];
+                ok = t >= 0 && t < num_types;
+                if (ok && k < N - 1) {
+                    const int l = rows.lo[(int64_t)m * rows.hs + k * rows.hk];
+                    const int h = rows.hi[(int64_t)m * rows.hs + k * rows.hk];
+                    ok = l >= 0 && l < h && h < TICK_LIMIT;
+                    w += h;
+                }
+            }
+            if (!ok || w >= TICK_LIMIT) bits |= ST_BADCAND;
+            else W = (int)w;
+        }
+        if (wmax) {
+            for (int off = 32; off >= 1; off >>= 1) {
+                const int o = __shfl_xor(W, off);
+                W = o > W ? o : W;
+            }
+            if (lane == 0) atomicMax(wmax, W);
+        }
+    }
+    for (int off = 32; off >= 1; off >>= 1) bits |= __shfl_xor(bits, off);
+    if (bits && lane == 0) atomicOr(status, bits);
+}
+
+constexpr int TYB = 1024;  // threads of the type kernel
+
+// exclusive prefix of v over the block, and the block's total
+__device__ __forceinline__ int64_t block_prefix(int64_t v, int64_t *sh, int64_t &tot)
+{
+    const int lane = threadIdx.x & (WAVE - 1), wv = threadIdx.x >> 6;
+    int64_t x = v;
+#pragma unroll
+    for (int off = 1; off < WAVE; off <<= 1) {
+        const int64_t y = __shfl_up(x, off);
+        if (lane >= off) x += y;
+    }
+    if (lane == WAVE - 1) sh[wv] = x;
+    __syncthreads();
+    int64_t base = 0, all = 0;
+    for (int k = 0; k < TYB / WAVE; ++k) {
+        base += k < wv ? sh[k] : 0;
+        all += sh[k];
+    }
+    __syncthreads();
+    tot = all;
+    return base + x - v;
+}
+
+// One block.  Small indexes: scans the counts itself (hist to off).  Then,
+// per type: its list's place, the buckets of its table (a power of two of
+// ticks wide, so many that a bucket holds half an event to one on average)
+// and the list's guards.
+__global__ __launch_bounds__(TYB) void k_ix_types(const int *__restrict__ ticks, int n, int T,
+                                                  int nch, const int *__restrict__ hist,
+                                                  int *__restrict__ off, int scan_here,
+                                                  int *__restrict__ et, int *__restrict__ ei,
+                                                  TypeIdx *__restrict__ ty, const int *status,
+                                                  int *hstat)
+{
+    __shared__ int64_t sh[TYB / WAVE];
+    const int st = *status;
+    if (threadIdx.x == 0 && hstat) *hstat = st;
+    if (st) return;
+    const int64_t H = (int64_t)T * nch;
+    int64_t tot;
+    if (scan_here) {
+        const int64_t per = (H + TYB - 1) / TYB;
+        const int64_t b = threadIdx.x * per, e = b + per < H ? b + per : H;
+        int64_t s = 0;
+        for (int64_t i = b; i < e; ++i) s += hist[i];
+        int64_t run = block_prefix(s, sh, tot);
+        for (int64_t i = b; i < e; ++i) {
+            off[i] = (int)run;
+            run += hist[i];
+        }
+        __syncthreads();
+    }
+    const int t0 = ticks[0];
+    const int span = ticks[n - 1] - t0;
+    int64_t boff = 0;
+    for (int e0 = 0; e0 < T; e0 += TYB) {
+        const int e = e0 + threadIdx.x;
+        TypeIdx x{};
+        if (e < T) {
+            const int a = off[(int64_t)e * nch], b = e + 1 < T ? off[(int64_t)(e + 1) * nch] : n;
+            x.start = a + LIST_PAD * e;
+            x.count = b - a;
+            x.t0 = t0;
+            const int64_t most = 2 * (int64_t)x.count;
+            while (((int64_t)span >> x.sh) + 1 > (most > 1 ? most : 1)) ++x.sh;
+            x.nb = (span >> x.sh) + 1;
+            for (int j = 0; j < LIST_PAD; ++j) {
+                et[x.start + x.count + j] = FAR_TICK;
+                ei[x.start + x.count + j] = FAR_TICK;
+            }
+        }
+        const int64_t room = e < T ? (int64_t)x.nb + 2 : 0;
+        const int64_t at = boff + block_prefix(room, sh, tot);
+        boff += tot;
+        if (e < T) {
+            x.boff = (int)at;
+            ty[e] = x;
+        }
+    }
+}
+
+// One wave per chunk: 64 events at a time, each lane's rank among the
+// events of its type from a bit mask per type.
+__global__ __launch_bounds__(WAVE) void k_ix_lists(const int *__restrict__ ids,
+                                                   const int *__restrict__ ticks, int n, int T,
+                                                   int chunk, int nch,
+                                                   const int *__restrict__ off,
+                                                   int *__restrict__ et, int *__restrict__ ei,
+                                                   const int *status, int base_index)
+{
+    extern __shared__ unsigned long long sm[];
+    if (*status) return;
+    unsigned long long *mask = sm;
+    int *cur = (int *)(sm + T);
+    const int lane = threadIdx.x, c = blockIdx.x;
+    for (int e = lane; e < T; e += WAVE) {
+        mask[e] = 0;
+        cur[e] = off[(int64_t)e * nch + c] + LIST_PAD * e;
+    }
+    __syncthreads();
+    const int b = c * chunk, e = b + chunk < n ? b + chunk : n;
+    for (int i0 = b; i0 < e; i0 += WAVE) {
+        const int i = i0 + lane;
+        const bool in = i < e;
+        const int id = in ? ids[i] : 0, t = in ? ticks[i] : 0;
+        if (in) atomicOr(&mask[id], 1ull << lane);
+        __syncthreads();
+        const unsigned long long m = mask[id];
+        const int rank = below(m);
+        const int at = cur[id] + rank;
+        __syncthreads();
+        if (in) {
+            et[at] = t;
+            ei[at] = base_index + i;
+            if (rank == 0) {
+                cur[id] += __builtin_popcountll(m);
+                mask[id] = 0;
+            }
+        }
+        __syncthreads();
+    }
+}
+
+// tab[boff + b] = events of the type before bucket b.  Each position fills
+// the buckets after its predecessor's, up to its own; the end of the list
+// fills the rest.  Long stretches are filled by the whole wave.
+__global__ __launch_bounds__(256) void k_ix_tab(const int *__restrict__ et,
+                                                const TypeIdx *__restrict__ ty,
+                                                int *__restrict__ tab, const int *status)
+{
+    if (*status) return;
+    const TypeIdx x = ty[blockIdx.x];
+    const int lane = __lane_id();
+    const int w0 = (int)(blockIdx.y * (blockDim.x / WAVE) + (threadIdx.x >> 6));
+    const int64_t step = (int64_t)gridDim.y * blockDim.x;
+    for (int64_t p0 = (int64_t)w0 * WAVE; p0 <= x.count; p0 += step) {
+        const int64_t p = p0 + lane;
+        int b0 = 0, b1 = -1;  // buckets b0..b1 are this position's
+        if (p <= x.count) {
+            b0 = p ? ((et[x.start + p - 1] - x.t0) >> x.sh) + 1 : 0;
+            b1 = p < x.count ? (et[x.start + p] - x.t0) >> x.sh : x.nb + 1;
+        }
+        const bool wide = b1 - b0 >= 16;
+        if (!wide)
+            for (int b = b0; b <= b1; ++b) tab[x.boff + b] = (int)p;
+        unsigned long long m = bal(wide);
+        while (m) {
+            const int j = (int)__builtin_ctzll(m);
+            m &= m - 1;
+            const int c0 = rdl(b0, j), c1 = rdl(b1, j);
+            for (int b = c0 + lane; b <= c1; b += WAVE) tab[x.boff + b] = (int)(p0 + j);
+        }
+    }
+}
+
+}  // namespace
+
+void launch_index_check(const IndexPlan &p, const int *ids, const int *ticks, int *base,
+                        const Rows &rows, int nmax, int num_types, int *status, int *wmax,
+                        hipStream_t s)
+{
+    const int cb = (rows.M + WAVE - 1) / WAVE;
+    if (p.nch + cb == 0) return;
+    hipLaunchKernelGGL(k_ix_check, dim3((unsigned)(p.nch + cb)), dim3(WAVE),
+                       (size_t)p.T * sizeof(int), s, ids, ticks, p.n, p.T, p.chunk, p.nch,
+                       base + p.o_hist, rows, nmax, num_types, status, wmax);
+}
+
+void launch_index_types(const IndexPlan &p, const int *ticks, int *base, const int *status,
+                        int *hstat, hipStream_t s)
+{
+    const int64_t H = (int64_t)p.T * p.nch;
+    const bool here = H <= SMALL_SCAN;
+    if (!here)
+        launch_scan_excl(base + p.o_hist, H, base + p.o_scan, base + p.o_scan + H, s);
+    hipLaunchKernelGGL(k_ix_types, dim3(1), dim3(TYB), 0, s, ticks, p.n, p.T, p.nch,
+                       base + p.o_hist, base + p.o_scan, here ? 1 : 0, base + p.o_et,
+                       base + p.o_ei, (TypeIdx *)(base + p.o_ty), status, hstat);
+}
+
+void launch_index_lists(const IndexPlan &p, const int *ids, const int *ticks, int *base,
+                        const int *status, int base_index, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_ix_lists, dim3((unsigned)p.nch), dim3(WAVE),
+                       (size_t)p.T * (sizeof(unsigned long long) + sizeof(int)), s, ids, ticks,
+                       p.n, p.T, p.chunk, p.nch, base + p.o_scan, base + p.o_et, base + p.o_ei,
+                       status, base_index);
+    int64_t parts = (int64_t)p.n / p.T / 1024 + 1;
+    if (parts > 256) parts = 256;
+    hipLaunchKernelGGL(k_ix_tab, dim3((unsigned)p.T, (unsigned)parts), dim3(256), 0, s,
+                       base + p.o_et, (const TypeIdx *)(base + p.o_ty), base + p.o_tab, status);
+}
+
+// ------------------------------------------------------------------ counting
+namespace {
+
+constexpr int FCAP = 2 * WAVE;  // completions waiting (64 and one batch's)
+
+// Takes node N-2's entries, finds each one's first event of the last type
+// and counts the completions (s, i) greedily.  Only the first event matters:
+// a later one of the same entry has the same s and comes after it.
+//   DUAL: the same also from rf, the state the segment's own run began in;
+// both runs are the same from their first common completion on.
+template <bool REL, bool DUAL> struct Count {
+    const ChainIdx &ix;
+    const NodeRow &row;
+    int N, a1;       // completions of chains from [.., a1) of node 0's list count
+    int *fq;         // FCAP (chain start, completing event) positions
+    int fh = 0, fn = 0;
+    int r, cnt = 0;
+    int rf = -1, cntf = 0;
+
+    __device__ __forceinline__ Count(const ChainIdx &x, const NodeRow &w, int N_, int a1_, int *q,
+                                     int r0)
+        : ix(x), row(w), N(N_), a1(a1_), fq(q), r(r0)
+    {
+    }
+
+    // the greedy choice among 64 completions in order (valid: their lanes),
+    // after one at rr: an entry whose chain starts after its predecessor's
+    // completion is always taken; the others depend on the last one taken
+    __device__ __forceinline__ void choose(unsigned long long valid, int s, int i, int &rr,
+                                           int &c) const
+    {
+        const int lane = __lane_id();
+        int ip = __shfl_up(i, 1);
+        ip = lane == 0 ? rr : ip;
+        unsigned long long conf = bal(s <= ip) & valid;
+        unsigned long long sel = valid & ~conf;
+        while (conf) {
+            const int j = (int)__builtin_ctzll(conf);
+            conf &= conf - 1;
+            const unsigned long long lower = sel & ((1ull << j) - 1ull);
+            const int last = lower ? rdl(i, 63 - __builtin_clzll(lower)) : rr;
+            if (rdl(s, j) > last) sel |= 1ull << j;
+        }
+        c += __builtin_popcountll(sel);
+        if (sel) rr = rdl(i, 63 - __builtin_clzll(sel));
+    }
+    __device__ __forceinline__ void drain(int n)
+    {
+        const int lane = __lane_id();
+        const bool on = lane < n;
+        const int q = (fh + lane) & (FCAP - 1);
+        const int ap = on ? fq[q] : 0, dp = on ? fq[FCAP + q] : 0;
+        const int s = on ? ix.ei[rdl(row.start, 0) + ap] : FAR_TICK;
+        const int i = on ? ix.ei[rdl(row.start, N - 1) + dp] : FAR_TICK;
+        const unsigned long long valid = bal(on);
+        choose(valid, s, i, r, cnt);
+        if (DUAL) choose(valid, s, i, rf, cntf);
+        fh = (fh + n) & (FCAP - 1);
+        fn -= n;
+    }
+    __device__ __forceinline__ void finish()
+    {
+        if (fn) drain(fn);
+    }
+    __device__ __forceinline__ void operator()(int, bool on, int t, int apos, int i, bool first,
+                                               int L0)
+    {
+        const int lo = rdl(row.lo, N - 2), hi = rdl(row.hi, N - 2);
+        const int start = rdl(row.start, N - 1), boff = rdl(row.boff, N - 1);
+        t = on ? t : row.t0;
+        const int x = REL ? t : t + lo + 1;
+        const int b = bucket(x, row.t0, rdl(row.sh, N - 1), rdl(row.nb, N - 1));
+        if (!first) L0 = ix.tab[boff + b];
+        else if (!on) L0 = 0;
+        Place<REL> pl;
+        find<REL>(ix, start, boff, b, L0, on, x, i, pl);
+        const bool pass = on & (pl.tick() <= t + hi) & (apos < a1);
+        const unsigned long long m = bal(pass);
+        if (m == 0) return;
+        if (pass) {
+            const int q = (fh + fn + below(m)) & (FCAP - 1);
+            fq[q] = apos;
+            fq[FCAP + q] = pl.p();
+        }
+        __builtin_amdgcn_wave_barrier();
+        fn += __builtin_popcountll(m);
+        if (fn >= WAVE) drain(WAVE);
+    }
+};
+
+// Sum of the row's hop widths (an occurrence spans at most this).
+__device__ __forceinline__ int row_width(const NodeRow &row, int N)
+{
+    int W = 0;
+    for (int k = 0; k < N - 1; ++k) W += rdl(row.hi, k);
+    return W;
+}
+
+// Where the walk over chains from [.., a1) of node 0's list may end: past
+// every event within W ticks of the last one (their entries bound those of
+// the chains counted); a bucket's end, so possibly a few more.
+__device__ __forceinline__ int look_ahead(const ChainIdx &ix, const NodeRow &row, int N, int a1)
+{
+    const int start = rdl(row.start, 0), count = rdl(row.count, 0);
+    if (N <= 2 || a1 >= count || a1 <= 0) return a1;
+    const int x = ix.et[start + a1 - 1] + row_width(row, N);
+    const int b = bucket(x, row.t0, rdl(row.sh, 0), rdl(row.nb, 0));
+    const int e = __builtin_amdgcn_readfirstlane(ix.tab[rdl(row.boff, 0) + b + 1]);
+    return e > a1 ? e : a1;
+}
+
+// Counts the chains from [a0, a1) of node 0's list after a completion at
+// index r (DUAL: and, into rf/cntf, after none).
+template <bool REL, bool DUAL>
+__device__ __forceinline__ void count_range(const ChainIdx &ix, const NodeRow &row, int N, int a0,
+                                            int a1, int *lds, int &r, int &cnt, int &rf,
+                                            int &cntf)
+{
+    if (a0 >= a1) return;
+    if (N == 1) {
+        // every event is a completion
+        const int last =
+            __builtin_amdgcn_readfirstlane(ix.ei[rdl(row.start, 0) + a1 - 1]);
+        cnt += a1 - a0;
+        r = last;
+        if (DUAL) {
+            cntf += a1 - a0;
+            rf = last;
+        }
+        return;
+    }
+    Count<REL, DUAL> sink(ix, row, N, a1, lds, r);
+    if (DUAL) sink.rf = rf;
+    walk<REL>(ix, row, N - 2, a0, look_ahead(ix, row, N, a1), lds + 2 * FCAP, sink);
+    sink.finish();
+    r = sink.r;
+    cnt += sink.cnt;
+    if (DUAL) {
+        rf = sink.rf;
+        cntf += sink.cntf;
+    }
+}
+
+__host__ __device__ constexpr int chain_lds(bool rel, int nmax)
+{
+    return 2 * FCAP + (nmax > 2 ? nmax - 2 : 0) * ring_ints(rel);
+}
+
+// Segment p of P of a list of c events.
+__device__ __forceinline__ int seg_at(int c, int p, int P) { return (int)((int64_t)p * c / P); }
+
+// One wave per (segment, candidate).  P = 1 writes the counts; P > 1 the
+// segment's own count (after no completion), its last completion's index
+// and its first chain's.
+//   A batch of 64 node-0 events is one coalesced read of their ticks and two
+// of the next list (its bucket, four entries), so the kernel is bound by the
+// latency of those reads at few waves and by the lists' bytes at many.  Why
+// not the Map kernels' scan: a wave there reads every event of the stream
+// for 64 candidates, here only its candidate's first list and the few
+// entries that pass.  20011 episodes of 1-8 nodes over 3.0e5 events of 200
+// types: 22.6 -> 0.25 ms a call; 5000 relaxed of 5-8 nodes over 1.06e6 events
+// of 128 types: 13.2 -> 0.58 ms; 1e5 of 3 nodes over 9.7e6 events, both
+// passes: 81 -> 42 ms; 3000 with 9 to 19 live windows a list: 26 -> 0.08 ms.
+template <int MODE> __global__ __launch_bounds__(WAVE) void k_chain(ChainJob j, const int *status)
+{
+    extern __shared__ int lds[];
+    if (*status) return;
+    const int M = j.rows.M;
+    const int p = (int)(blockIdx.x / (unsigned)M), m = (int)(blockIdx.x - (unsigned)p * (unsigned)M);
+    const int lane = __lane_id();
+    NodeRow row;
+    int dr = -1, dc = 0;
+    if (j.P > 1) {
+        // (MODE is EXACT or RELAXED; theta > 0 with upper set: survivors only)
+        constexpr bool REL = MODE == CHAIN_RELAXED;
+        if (!REL && j.upper && j.upper[m] < j.theta) return;
+        const int N = load_row(j.ix, j.rows, m, row);
+        const int c = rdl(row.count, 0);
+        const int a0 = seg_at(c, p, j.P), a1 = seg_at(c, p + 1, j.P);
+        int r = -1, cnt = 0;
+        count_range<REL, false>(j.ix, row, N, a0, a1, lds, r, cnt, dr, dc);
+        const int first = a0 < a1 ? j.ix.ei[rdl(row.start, 0) + a0] : FAR_TICK;
+        if (lane == 0) j.seg[(int64_t)p * M + m] = make_int4(cnt, r, first, 0);
+        return;
+    }
+    const int N = load_row(j.ix, j.rows, m, row);
+    if (j.count_io) {
+        // chains that start after the last completion, and no more than the
+        // episode's width before the first new event: the others have been
+        // counted or can complete at no new event
+        int last = j.last_io[m];
+        last = last < j.from ? last : j.from - 1;
+        const int start = rdl(row.start, 0);
+        const int x = j.t_from[0] - row_width(row, N);
+        int lo = 0, hi = rdl(row.count, 0);
+        const int c = hi;
+        while (lo < hi) {
+            const int mid = (lo + hi) >> 1;
+            const bool before = (j.ix.ei[start + mid] <= last) | (j.ix.et[start + mid] < x);
+            if (bal(before) != 0) lo = mid + 1;
+            else hi = mid;
+        }
+        int r = last, cnt = 0;
+        count_range<MODE == CHAIN_RELAXED, false>(j.ix, row, N, lo, c, lds, r, cnt, dr, dc);
+        if (lane == 0 && cnt) {
+            j.count_io[m] += cnt;
+            j.last_io[m] = r;
+        }
+        return;
+    }
+    const int c = rdl(row.count, 0);
+    bool take = true;
+    if (MODE != CHAIN_EXACT) {
+        int r = -1, cnt = 0;
+        count_range<true, false>(j.ix, row, N, 0, c, lds, r, cnt, dr, dc);
+        if (lane == 0) j.upper[m] = cnt;
+        take = cnt >= j.theta;
+    }
+    if (MODE != CHAIN_RELAXED) {
+        int r = -1, cnt = 0;
+        if (take) count_range<false, false>(j.ix, row, N, 0, c, lds, r, cnt, dr, dc);
+        if (lane == 0) j.exact[m] = take ? cnt : -1;
+    }
+}
+
+// One wave per 64 candidates: their segments' results in order.  A
+// segment's own run stands when its first chain starts after the last
+// completion before it; otherwise the wave runs it again from there until
+// it meets its own run (a common completion), a growing stretch at a time.
+template <bool REL> __global__ __launch_bounds__(WAVE) void k_stitch(ChainJob j, const int *status)
+{
+    extern __shared__ int lds[];
+    if (*status) return;
+    const int M = j.rows.M, lane = __lane_id();
+    const int m = (int)blockIdx.x * WAVE + lane;
+    bool on = m < M;
+    int *out = REL ? j.upper : j.exact;
+    if (!REL && j.upper && on && j.upper[m] < j.theta) {
+        out[m] = -1;
+        on = false;
+    }
+    int tot = 0, r = -1;
+    for (int p = 0; p < j.P; ++p) {
+        const int4 g = on ? j.seg[(int64_t)p * M + m] : make_int4(0, -1, FAR_TICK, 0);
+        const bool again = on & (g.x > 0) & (r >= g.z);
+        if (on && !again && g.x > 0) {
+            tot += g.x;
+            r = g.y;
+        }
+        unsigned long long todo = bal(again);
+        while (todo) {
+            const int q = (int)__builtin_ctzll(todo);
+            todo &= todo - 1;
+            const int mq = (int)blockIdx.x * WAVE + q;
+            NodeRow row;
+            const int N = load_row(j.ix, j.rows, mq, row);
+            const int c = rdl(row.count, 0);
+            const int a1 = seg_at(c, p + 1, j.P);
+            int b = seg_at(c, p, j.P), len = WAVE;
+            int rr = rdl(r, q), cnt = 0, rf = -1, cntf = 0;
+            while (b < a1 && (rf != rr)) {
+                const int e = a1 - b < len ? a1 : b + len;
+                count_range<REL, true>(j.ix, row, N, b, e, lds, rr, cnt, rf, cntf);
+                b = e;
+                len *= 2;
+            }
+            const int gx = rdl(g.x, q), gy = rdl(g.y, q);
+            if (lane == q) {
+                if (rf == rr && rf >= 0) {
+                    tot += cnt + (gx - cntf);
+                    r = gy;
+                } else {
+                    tot += cnt;
+                    r = rr;
+                }
+            }
+        }
+    }
+    if (on) out[m] = tot;
+}
+
+template <int MODE> void chain_mode(const ChainJob &j, int nmax, const int *status, hipStream_t s)
+{
+    const size_t lds = (size_t)chain_lds(MODE != CHAIN_EXACT, nmax) * sizeof(int);
+    hipLaunchKernelGGL((k_chain<MODE>), dim3((unsigned)((int64_t)j.P * j.rows.M)), dim3(WAVE), lds,
+                       s, j, status);
+    if (j.P > 1)
+        hipLaunchKernelGGL((k_stitch<MODE == CHAIN_RELAXED>),
+                           dim3((unsigned)((j.rows.M + WAVE - 1) / WAVE)), dim3(WAVE), lds, s, j,
+                           status);
+}
+
+}  // namespace
+
+namespace {
+__global__ __launch_bounds__(256) void k_count_ge(const int *v, int M, int theta, int *out,
+                                                  const int *status)
+{
+    if (*status) return;
+    int c = 0;
+    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < M; i += gridDim.x * blockDim.x)
+        c += v[i] >= theta ? 1 : 0;
+    for (int off = 32; off >= 1; off >>= 1) c += __shfl_xor(c, off);
+    if (__lane_id() == 0 && c) atomicAdd(out, c);
+}
+}  // namespace
+
+void launch_count_ge(const int *v, int M, int theta, int *out, const int *status, hipStream_t s)
+{
+    launch_fill(out, 0, 1, s);
+    if (M <= 0) return;
+    int blocks = (M + 1023) / 1024;
+    if (blocks > 256) blocks = 256;
+    hipLaunchKernelGGL(k_count_ge, dim3(blocks), dim3(256), 0, s, v, M, theta, out, status);
+}
+
+void launch_chain(const ChainJob &job, ChainMode mode, int nmax, const int *status, hipStream_t s)
+{
+    if (job.rows.M <= 0) return;
+    if (mode == CHAIN_TWO_PASS && job.P == 1) return chain_mode<CHAIN_TWO_PASS>(job, nmax, status, s);
+    ChainJob j = job;
+    if (mode != CHAIN_EXACT) chain_mode<CHAIN_RELAXED>(j, nmax, status, s);
+    if (mode != CHAIN_RELAXED) {
+        // (exact alone: every candidate is taken)
+        if (mode == CHAIN_EXACT) j.upper = nullptr;
+        chain_mode<CHAIN_EXACT>(j, nmax, status, s);
+    }
+}
+
+}  // namespace fe

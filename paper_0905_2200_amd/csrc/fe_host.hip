@@ -2,6 +2,7 @@
 // candidate grouping, launch planning, two-pass elimination and the
 // level-wise mining driver.
 #include "fe.h"
+#include "fe_chain.h"
 #include "fe_hostalgo.h"
 #include "fe_internal.h"
 
@@ -116,6 +117,8 @@ struct fe_ctx {
     Buf keys, hist, wmax, pk, orig, tileW, lam, tbl, flags, sel, nsel, status, small, cmask;
     Buf mtypes, mlen, mlo, mhi, mup, mex, msel, mn, mkey, tscr, tinfo, mfk, mfo, mfsel, pbc;
     Buf deep;  // window rings of the deep-class exact launches
+    Buf cidx, cseg;           // stream index and segment results of chain counting
+    hipEvent_t checked = nullptr;  // the input checks of the call have run
     Buf skey, sup;  // keys and relaxed counts of a level's elimination sample
     // This device's copy of the fixed scratch array (fe_count_noalloc), and
     // while such a call runs, the bump arena its workspace is carved from.
@@ -636,6 +639,112 @@ int stream_info(fe_ctx *c, const int32_t *ids, const int32_t *ticks, int n, int 
     return FE_OK;
 }
 
+// ---- chain counting (fe_walk.h): per-type event lists of the stream are
+// built by each call and every candidate is counted by one wave (or one per
+// segment of its first list).
+
+// The calls it takes: per-type dispatch on, no segment count asked for, and
+// a stream whose lists can be built (the others take the Map kernels).
+bool chain_takes(const fe_ctx *c, int64_t n, int num_types)
+{
+    return c->param[FE_PARAM_TYPE_DISPATCH] != 0 && c->param[FE_PARAM_SEGMENTS] == 0 && n > 0 &&
+           n <= ((int64_t)1 << 30) && num_types <= CHAIN_TYPES;
+}
+
+// Segments per candidate: the hybrid rule's crossover (choose_P) decides
+// between one and several; several are as many as the target number of waves
+// takes, with at least 512 events of a list of average length in each.
+int chain_P(const fe_ctx *c, int64_t M, int64_t n, int num_types, int nmax, bool exact)
+{
+    const int64_t tiles = (M + WAVE - 1) / WAVE;
+    const int pa = exact ? FE_PARAM_CROSSOVER_A : FE_PARAM_CROSSOVER_A_RELAXED;
+    const int pb = exact ? FE_PARAM_CROSSOVER_B : FE_PARAM_CROSSOVER_B_RELAXED;
+    const double cross = (double)c->param[pa] / std::max(nmax, 1) + (double)c->param[pb];
+    if ((double)tiles >= cross) return 1;
+    int64_t P = std::max<int64_t>(2, (c->param[FE_PARAM_TARGET_WAVES] + M - 1) / M);
+    P = std::min<int64_t>(P, n / ((int64_t)512 * num_types));
+    P = std::min<int64_t>(P, ((int64_t)1 << 30) / M);
+    return (int)std::max<int64_t>(1, std::min<int64_t>(P, 4096));
+}
+
+Rows table_rows(const CandIn &cin, int M)
+{
+    Rows r{};
+    r.ty = cin.types;
+    r.lo = cin.lo;
+    r.hi = cin.hi;
+    r.len = cin.len;
+    r.ts = cin.nmax;
+    r.tk = 1;
+    r.hs = cin.nmax - 1;
+    r.hk = 1;
+    r.M = M;
+    return r;
+}
+
+// Waits for the input checks enqueued on the stream (status word to
+// c->host[0]) while the launches behind them go on.
+int wait_checks(fe_ctx *c)
+{
+    HIPCHK(c, hipGetLastError());
+    HIPCHK(c, hipEventSynchronize(c->checked));
+    const int bits = *(volatile int *)c->host;
+    if (bits) {
+        launch_fill(P<int>(c->status), 0, 1, c->stream);
+        return fail(c, status_code(bits), "%s", status_text(bits));
+    }
+    return FE_OK;
+}
+
+// One call's counting by chains; taken = false (nothing enqueued) when its
+// workspace cannot be had.
+int chain_call(fe_ctx *c, const int *ids, const int *ticks, int64_t n, int num_types,
+               const CandIn &cin, int M, ChainMode mode, int theta, int *upper, int *exact,
+               int *nsurv, bool &taken)
+{
+    hipStream_t s = c->stream;
+    int rc;
+    taken = false;
+    const IndexPlan ip = index_plan(n, num_types);
+    const int Pn = chain_P(c, M, n, num_types, cin.nmax, mode == CHAIN_EXACT);
+    if (ensure(c, c->cidx, (size_t)ip.ints * sizeof(int)) ||
+        ensure(c, c->cseg, Pn > 1 ? (size_t)Pn * M * sizeof(int4) : 4))
+        return FE_OK;
+    if ((rc = ensure_host(c, 4))) return rc;
+    if (!c->checked)
+        HIPCHK(c, hipEventCreateWithFlags(&c->checked, hipEventDisableTiming));
+    taken = true;
+    int *base = P<int>(c->cidx);
+    ChainJob j{};
+    j.ix = index_view(ip, base);
+    j.rows = table_rows(cin, M);
+    j.theta = theta;
+    j.upper = upper;
+    j.exact = exact;
+    j.P = Pn;
+    j.seg = P<int4>(c->cseg);
+    const int *st = P<int>(c->status);
+    {
+        KTimer kt(c, "index", 0);
+        launch_index_check(ip, ids, ticks, base, j.rows, cin.nmax, num_types, P<int>(c->status),
+                           nullptr, s);
+        launch_index_types(ip, ticks, base, st, c->host, s);
+        HIPCHK(c, hipEventRecord(c->checked, s));
+        launch_index_lists(ip, ids, ticks, base, st, 0, s);
+    }
+    c->stats.map_launches += mode == CHAIN_TWO_PASS ? 2 : 1;
+    c->stats.segments_max = std::max<int64_t>(c->stats.segments_max, Pn);
+    {
+        const char *name = mode == CHAIN_EXACT     ? "map_exact_chain"
+                           : mode == CHAIN_RELAXED ? "map_relaxed_chain"
+                                                   : "map_two_pass_chain";
+        KTimer kt(c, name, (double)M * (double)n);
+        launch_chain(j, mode, cin.nmax, st, s);
+        if (nsurv) launch_count_ge(upper, M, theta, nsurv, st, s);
+    }
+    return wait_checks(c);
+}
+
 int count_impl(fe_ctx *c, const int32_t *ids, const int32_t *ticks, const StreamInfo &si,
                int32_t num_types, const CandIn &cin, int32_t M, int mode, int32_t *out)
 {
@@ -745,9 +854,10 @@ extern "C" int fe_destroy(fe_ctx *c)
                    &c->lam,  &c->tbl,  &c->flags, &c->sel, &c->nsel,  &c->status, &c->small, &c->cmask,
                    &c->mtypes, &c->mlen, &c->mlo, &c->mhi, &c->mup, &c->mex, &c->msel, &c->mn,
                    &c->mkey, &c->tscr, &c->tinfo, &c->mfk, &c->mfo, &c->mfsel, &c->pbc,
-                   &c->deep, &c->skey, &c->sup};
+                   &c->deep, &c->skey, &c->sup, &c->cidx, &c->cseg};
     for (Buf *b : bufs)
         if (b->p) (void)hipFree(b->p);
+    if (c->checked) (void)hipEventDestroy(c->checked);
     for (auto &p : c->pending) {
         (void)hipEventDestroy(p.a);
         (void)hipEventDestroy(p.b);
@@ -863,10 +973,17 @@ extern "C" int fe_count(fe_ctx *c, const int32_t *ids, const int32_t *ticks, int
     if (M > 0 && !counts_out) return fail(c, FE_EINVAL, "null output");
     HIPCHK(c, hipSetDevice(c->device));
     c->stats = fe_stats{};
-    StreamInfo si;
-    if ((rc = stream_info(c, ids, ticks, (int)n, num_types, si))) return rc;
     CandIn cin{types, len, lo, hi, nmax};
-    rc = count_impl(c, ids, ticks, si, num_types, cin, M, mode, counts_out);
+    bool taken = false;
+    if (M > 0 && chain_takes(c, n, num_types))
+        rc = chain_call(c, ids, ticks, n, num_types, cin, M,
+                        mode == FE_EXACT ? CHAIN_EXACT : CHAIN_RELAXED, 0, counts_out, counts_out,
+                        nullptr, taken);
+    if (!taken) {
+        StreamInfo si;
+        if ((rc = stream_info(c, ids, ticks, (int)n, num_types, si))) return rc;
+        rc = count_impl(c, ids, ticks, si, num_types, cin, M, mode, counts_out);
+    }
     c->stats.last_call_ms = now_ms() - t0;
     return rc;
 }
@@ -937,9 +1054,17 @@ extern "C" int fe_count_two_pass(fe_ctx *c, const int32_t *ids, const int32_t *t
     if (M > 0 && (!upper_out || !exact_out)) return fail(c, FE_EINVAL, "null output");
     HIPCHK(c, hipSetDevice(c->device));
     c->stats = fe_stats{};
+    CandIn cin{types, len, lo, hi, nmax};
+    bool taken = false;
+    if (M > 0 && chain_takes(c, n, num_types))
+        rc = chain_call(c, ids, ticks, n, num_types, cin, M, CHAIN_TWO_PASS, theta, upper_out,
+                        exact_out, n_survivors_out, taken);
+    if (taken) {
+        c->stats.last_call_ms = now_ms() - t0;
+        return rc;
+    }
     StreamInfo si;
     if ((rc = stream_info(c, ids, ticks, (int)n, num_types, si))) return rc;
-    CandIn cin{types, len, lo, hi, nmax};
     rc = two_pass_impl(c, ids, ticks, si, num_types, cin, M, theta, upper_out, exact_out,
                        n_survivors_out);
     c->stats.last_call_ms = now_ms() - t0;

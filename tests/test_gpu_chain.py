@@ -1,0 +1,174 @@
+"""Counting by chains over per-type lists (the default of fe_count and
+fe_count_two_pass) where it can go wrong, against the CPU oracle, bit for bit:
+entries with more following events than a batch holds, crowded buckets, ties
+in the ticks, list lengths around a batch and a read of four, segments whose
+first chains start before an earlier segment's last completion, types up to
+the lists' limit and beyond it, and ticks at the ends of their range."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_0905_2200_amd import synth
+from tests.gpu_util import banner, have_gpu, oracle_counts
+
+pytestmark = [pytest.mark.gpu, pytest.mark.skipif(not have_gpu(), reason="needs a GPU")]
+
+EXACT, RELAXED = 0, 1
+IVS = [(0, 50), (50, 100), (100, 200), (190, 200), (0, 1), (7, 9)]
+
+
+@pytest.fixture(scope="module")
+def fe():
+    from paper_0905_2200_amd import fe as fe_mod
+    return fe_mod
+
+
+@pytest.fixture(scope="module")
+def ctx(fe):
+    c = fe.Context(0)
+    yield c
+    c.close()
+
+
+def _check(ctx, ids_h, ticks_h, T, cand, what):
+    ids, ticks = ctx.stream_tensors(ids_h, ticks_h)
+    cd = ctx.cand_tensors(cand)
+    seen = 0
+    for mode in (EXACT, RELAXED):
+        want = oracle_counts(ids_h, ticks_h, T, cand, mode)
+        got = ctx.count(ids, ticks, T, cd, mode).cpu().numpy()
+        bad = np.nonzero(got != want)[0]
+        assert bad.size == 0, (what, mode, bad[:5], got[bad[:5]], want[bad[:5]])
+        seen = max(seen, int(want.max()) if want.size else 0)
+    for theta in (1, max(1, seen // 4)):
+        up, ex, ns = ctx.count_two_pass(ids, ticks, T, cd, theta)
+        wu, we = oracle.two_pass(ids_h, ticks_h, T, cand["types"], cand["len"], cand["lo"],
+                                 cand["hi"], theta, projection=True)
+        assert np.array_equal(up.cpu().numpy(), wu), (what, theta)
+        assert np.array_equal(ex.cpu().numpy(), we), (what, theta)
+        assert int(ns.item()) == int((wu >= theta).sum()), (what, theta)
+    return seen
+
+
+def _all_sizes(rng, T, M, ivs=IVS):
+    return synth.pack(synth.random_episodes(rng, M, T, 8, ivs, n_min=1))
+
+
+@pytest.mark.parametrize("n", [1, 2, 3, 4, 5, 63, 64, 65, 66, 127, 128, 129, 191, 513, 4099])
+def test_short_lists(ctx, n):
+    # one and two types: lists of n and about n/2 events
+    rng = np.random.default_rng(n)
+    for T in (1, 2, 3):
+        ids_h = rng.integers(0, T, n).astype(np.int32)
+        ticks_h = np.cumsum(rng.integers(0, 30, n)).astype(np.int32)
+        banner("short lists: n=%d T=%d" % (n, T))
+        _check(ctx, ids_h, ticks_h, T, _all_sizes(rng, T, 200), "n=%d T=%d" % (n, T))
+
+
+@pytest.mark.parametrize("gap", [0, 1, 2, 5])
+def test_more_followers_than_a_batch(ctx, gap):
+    # type 1 fires in runs far longer than a batch within one interval of a
+    # lone type 0 event; at gap 0 the whole run shares its tick (one bucket)
+    rng = np.random.default_rng(50 + gap)
+    ids, ticks, t = [], [], 0
+    for run in (1, 3, 4, 5, 63, 64, 65, 127, 128, 129, 200, 333):
+        for first in (0, 2):
+            ids += [first] + [1] * run + [2]
+            ticks += [t] + list(t + 1 + gap * np.arange(run)) + [t + 2 + gap * run]
+            t = ticks[-1] + int(rng.integers(0, 40))
+    ids_h, ticks_h = np.array(ids, np.int32), np.array(ticks, np.int32)
+    eps = [((a, b, c)[:n], (lo, lo2)[:n - 1], (hi, hi2)[:n - 1]) for n in (2, 3)
+           for a in range(3) for b in range(3) for c in range(3)
+           for lo, hi in ((0, 40), (0, 3000), (10, 500)) for lo2, hi2 in ((0, 2000), (3, 70))]
+    banner("more followers than a batch: gap %d" % gap)
+    assert _check(ctx, ids_h, ticks_h, 3, synth.pack(eps), "gap=%d" % gap) > 3
+
+
+@pytest.mark.parametrize("T,mean_gap", [(2, 1), (3, 4), (5, 20), (16, 3)])
+def test_dense_segments(ctx, fe, T, mean_gap):
+    # a completion every few events: at most segment boundaries a chain is open
+    rng = np.random.default_rng(70 + T)
+    n = 40_000
+    ids_h = rng.integers(0, T, n).astype(np.int32)
+    ticks_h = np.cumsum(rng.integers(0, 2 * mean_gap + 1, n)).astype(np.int32)
+    cand = synth.pack(synth.random_episodes(rng, 300, T, 5, IVS, n_min=1))
+    banner("dense segments: T=%d gap=%d" % (T, mean_gap))
+    _check(ctx, ids_h, ticks_h, T, cand, "T=%d" % T)
+    assert ctx.stats()["segments_max"] >= 2
+    # the whole-stream form of the same counts
+    ids, ticks = ctx.stream_tensors(ids_h, ticks_h)
+    keys = (fe.PARAM_CROSSOVER_A, fe.PARAM_CROSSOVER_B, fe.PARAM_CROSSOVER_A_RELAXED,
+            fe.PARAM_CROSSOVER_B_RELAXED)
+    saved = [ctx.get_param(p) for p in keys]
+    cut = [ctx.count(ids, ticks, T, cand, m).cpu().numpy() for m in (EXACT, RELAXED)]
+    try:
+        for p in keys:
+            ctx.set_param(p, 0)
+        for m in (EXACT, RELAXED):
+            assert np.array_equal(ctx.count(ids, ticks, T, cand, m).cpu().numpy(), cut[m])
+            assert ctx.stats()["segments_max"] == 1
+    finally:
+        for p, v in zip(keys, saved):
+            ctx.set_param(p, v)
+
+
+@pytest.mark.parametrize("T", [1000, 1025, 4096, 4097, 9000])
+def test_many_types(ctx, T):
+    # (beyond 4096 types the Map kernels count)
+    rng = np.random.default_rng(T)
+    n = 20_000
+    hot = rng.choice(T, 40, replace=False)
+    ids_h = np.where(rng.random(n) < 0.8, rng.choice(hot, n), rng.integers(0, T, n)).astype(np.int32)
+    ticks_h = np.cumsum(rng.integers(0, 8, n)).astype(np.int32)
+    eps = synth.random_episodes(rng, 300, 40, 4, IVS, n_min=1)
+    eps = [(tuple(int(hot[e]) for e in ty), lo, hi) for ty, lo, hi in eps]
+    eps += synth.random_episodes(rng, 100, T, 3, IVS, n_min=1)
+    eps += [((T - 1,), (), ()), ((T - 1, 0), (0,), (90,))]
+    banner("many types: T=%d" % T)
+    _check(ctx, ids_h, ticks_h, T, synth.pack(eps), "T=%d" % T)
+
+
+def test_tick_range_ends(ctx):
+    # all events at either end of the tick range, and the widest hops
+    top = (1 << 30) - 1
+    rng = np.random.default_rng(9)
+    t = np.concatenate([np.sort(rng.integers(0, 300, 500)),
+                        np.sort(top - rng.integers(0, 300, 500)), [top] * 20])
+    ids_h = rng.integers(0, 4, t.size).astype(np.int32)
+    eps = synth.random_episodes(rng, 300, 4, 4, IVS, n_min=1)
+    eps += [((a, b), (lo,), (hi,)) for a in range(4) for b in range(4)
+            for lo, hi in ((0, top), (top - 300, top), (top - 1, top), (0, top - 299))]
+    banner("tick range ends")
+    _check(ctx, ids_h, t.astype(np.int32), 4, synth.pack(eps), "range ends")
+
+
+@pytest.mark.parametrize("seed", range(8))
+def test_random_streams(ctx, seed):
+    # uneven rates, bursts and ties, every size and interval
+    rng = np.random.default_rng(3000 + seed)
+    T = int(rng.integers(2, 40))
+    n = int(rng.integers(3_000, 30_000))
+    w = rng.lognormal(0.0, 1.5, T)
+    ids_h = rng.choice(T, n, p=w / w.sum()).astype(np.int32)
+    gaps = rng.integers(0, int(rng.integers(2, 60)), n)
+    gaps[rng.random(n) < 0.3 * (seed % 3)] = 0
+    ticks_h = np.cumsum(gaps).astype(np.int32)
+    banner("random streams: seed=%d T=%d n=%d" % (seed, T, n))
+    _check(ctx, ids_h, ticks_h, T, _all_sizes(rng, T, 700), "seed=%d" % seed)
+
+
+@pytest.mark.parametrize("mode", [EXACT, RELAXED])
+def test_errors_write_nothing(ctx, fe, mode):
+    ids, ticks = ctx.stream_tensors([0, 1, 0, 1], [0, 5, 3, 9])
+    ok = ctx.stream_tensors([0, 1, 0, 1], [0, 5, 6, 9])
+    out = ctx.torch.full((1,), -7, dtype=ctx.torch.int32, device=ctx.device)
+    good = synth.pack([((0, 1), (0,), (10,))])
+    for stream, cand, code in (((ids, ticks), good, fe.FE_EUNSORTED),
+                               (ok, synth.pack([((0, 2), (0,), (10,))]), fe.FE_EINVAL),
+                               ((ids + 5, ok[1]), good, fe.FE_ERANGE)):
+        with pytest.raises(fe.FeError) as e:
+            ctx.count(stream[0], stream[1], 2, cand, mode, out=out)
+        assert e.value.code == code
+        ctx.torch.cuda.synchronize()
+        assert out.item() == -7
+    assert ctx.count(ok[0], ok[1], 2, good, mode).item() == 2
