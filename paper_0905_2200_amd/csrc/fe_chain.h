@@ -88,4 +88,38 @@ void launch_chain(const ChainJob &job, ChainMode mode, int nmax, const int *stat
 // *out = the number of v[0..M) that are at least theta.
 void launch_count_ge(const int *v, int M, int theta, int *out, const int *status, hipStream_t s);
 
+// ---- mining: join siblings (the candidates one frequent episode is joined
+// into differ in their last node and hop alone)
+
+// 32-bit words of a mask over T types
+constexpr int mask_words(int T) { return (T + 31) / 32; }
+
+struct SibJob {
+    ChainIdx ix;
+    const int *F;                // frequent episodes' keys, sorted, w ints each
+    int w, m;                    // m nodes
+    const int64_t *first, *off;  // episode a's siblings end like F[first[a] + c]; outputs off[a] + c
+    int *out;                    // exact counts
+    // masks[h][list entry][word]: types with an event in hop h's window
+    const unsigned *mask;
+    int64_t hop;  // words of one hop's masks
+    int words;
+    const int *ivlo, *ivhi;  // the interval set (device)
+    int n_iv;
+    // node 1's entries of every pair: (first type's rank * n_iv + hop) *
+    // sd_stride + the second type's place in the lists; sd_n: their numbers
+    const int *sd_t, *sd_a, *sd_p, *sd_n;
+    int64_t sd_stride;
+    const int *rank;  // [num_types] rank among the frequent types
+    int nF;
+};
+
+void launch_masks(const IndexPlan &p, const int *base, const int *ivlo, const int *ivhi, int n_iv,
+                  unsigned *mask, hipStream_t s);
+void launch_seeds(const ChainIdx &ix, const int *F1, int nF, const int *ivlo, const int *ivhi,
+                  int n_iv, int *sd_t, int *sd_a, int *sd_p, int *sd_n, int64_t stride,
+                  hipStream_t s);
+// cnt episodes, `longest` siblings at most.
+void launch_siblings(const SibJob &j, int64_t cnt, int64_t longest, hipStream_t s);
+
 }  // namespace fe

@@ -117,6 +117,7 @@ struct fe_ctx {
     Buf keys, hist, wmax, pk, orig, tileW, lam, tbl, flags, sel, nsel, status, small, cmask;
     Buf mtypes, mlen, mlo, mhi, mup, mex, msel, mn, mkey, tscr, tinfo, mfk, mfo, mfsel, pbc;
     Buf deep;  // window rings of the deep-class exact launches
+    Buf smask, sseed, sivl;    // miner: window masks, pairs' entries, intervals and ranks
     Buf cidx, cseg;           // stream index and segment results of chain counting
     hipEvent_t checked = nullptr;  // the input checks of the call have run
     Buf skey, sup;  // keys and relaxed counts of a level's elimination sample
@@ -682,6 +683,20 @@ Rows table_rows(const CandIn &cin, int M)
     return r;
 }
 
+// Rows of m-node episode keys (E1, lo1, hi1, E2, ...).
+Rows key_rows(const int *key, int m, int64_t M)
+{
+    Rows r{};
+    r.ty = key;
+    r.lo = key + 1;
+    r.hi = key + 2;
+    r.ts = r.hs = 3 * m - 2;
+    r.tk = r.hk = 3;
+    r.N = m;
+    r.M = (int)M;
+    return r;
+}
+
 // Waits for the input checks enqueued on the stream (status word to
 // c->host[0]) while the launches behind them go on.
 int wait_checks(fe_ctx *c)
@@ -854,7 +869,8 @@ extern "C" int fe_destroy(fe_ctx *c)
                    &c->lam,  &c->tbl,  &c->flags, &c->sel, &c->nsel,  &c->status, &c->small, &c->cmask,
                    &c->mtypes, &c->mlen, &c->mlo, &c->mhi, &c->mup, &c->mex, &c->msel, &c->mn,
                    &c->mkey, &c->tscr, &c->tinfo, &c->mfk, &c->mfo, &c->mfsel, &c->pbc,
-                   &c->deep, &c->skey, &c->sup, &c->cidx, &c->cseg};
+                   &c->deep, &c->skey, &c->sup, &c->cidx, &c->cseg,
+                   &c->smask, &c->sseed, &c->sivl};
     for (Buf *b : bufs)
         if (b->p) (void)hipFree(b->p);
     if (c->checked) (void)hipEventDestroy(c->checked);
@@ -1238,8 +1254,14 @@ int dev_pack(fe_ctx *c, const int *key_d, int m, int64_t M, const int *up, int t
 // relaxed pass over a sample of the level's candidates (every 64th block of
 // 64 consecutive ones, so join siblings stay together); ns sampled, nk of
 // them with upper >= theta.
-int sample_survival(fe_ctx *c, const int *ids, const int *ticks, const StreamInfo &si, int level,
-                    int64_t M, int wbound, int bbound, int theta, int64_t &ns, int64_t &nk)
+struct MineChains;
+int chain_rows(fe_ctx *c, const MineChains &mc, const Rows &rows, int num_types, ChainMode mode,
+               int theta, int *up, int *ex, const char *name);
+bool chains_on(const MineChains &mc);
+
+int sample_survival(fe_ctx *c, const int *ids, const int *ticks, const StreamInfo &si,
+                    const MineChains &mc, int num_types, int level, int64_t M, int wbound,
+                    int bbound, int theta, int64_t &ns, int64_t &nk)
 {
     int rc;
     hipStream_t s = c->stream;
@@ -1250,6 +1272,16 @@ int sample_survival(fe_ctx *c, const int *ids, const int *ticks, const StreamInf
     if ((rc = ensure(c, c->skey, (size_t)ns * wk * sizeof(int)))) return rc;
     if ((rc = ensure(c, c->sup, (size_t)ns * sizeof(int)))) return rc;
     launch_sample_keys(P<int>(c->mkey), wk, M, P<int>(c->skey), s);
+    if (chains_on(mc)) {
+        if ((rc = chain_rows(c, mc, key_rows(P<int>(c->skey), level, ns), num_types, CHAIN_RELAXED,
+                             theta, P<int>(c->sup), P<int>(c->sup), "sample_relaxed_chain")))
+            return rc;
+        launch_count_ge(P<int>(c->sup), (int)ns, theta, P<int>(c->mn), P<int>(c->status), s);
+        HIPCHK(c, hipMemcpyAsync(c->host, P<int>(c->mn), sizeof(int), hipMemcpyDeviceToHost, s));
+        HIPCHK(c, hipStreamSynchronize(s));
+        nk = c->host[0];
+        return FE_OK;
+    }
     std::vector<GroupDesc> groups;
     int64_t kept = 0;
     if ((rc = dev_pack(c, P<int>(c->skey), level, ns, nullptr, 0, false, wbound, bbound, groups,
@@ -1262,6 +1294,119 @@ int sample_survival(fe_ctx *c, const int *ids, const int *ticks, const StreamInf
     HIPCHK(c, hipMemcpyAsync(c->host, P<int>(c->mn), sizeof(int), hipMemcpyDeviceToHost, s));
     HIPCHK(c, hipStreamSynchronize(s));
     nk = c->host[0];
+    return FE_OK;
+}
+
+// What the miner keeps on the device over its levels when it counts by chains.
+struct MineChains {
+    IndexPlan ip;
+    ChainIdx ix;
+    bool on = false;
+    int n_iv = 0, nF = 0;
+    int tried = 0;    // siblings: 0 not set up yet, 1 ready, -1 not possible
+    SibJob sib{};
+};
+
+bool chains_on(const MineChains &mc) { return mc.on; }
+
+// Index of the stream, with its checks (synchronises).
+int mine_index(fe_ctx *c, const int *ids, const int *ticks, int64_t n, int num_types,
+               MineChains &mc)
+{
+    hipStream_t s = c->stream;
+    int rc;
+    mc.ip = index_plan(n, num_types);
+    if (ensure(c, c->cidx, (size_t)mc.ip.ints * sizeof(int))) return FE_OK;
+    if ((rc = ensure_host(c, 4))) return rc;
+    if (!c->checked) HIPCHK(c, hipEventCreateWithFlags(&c->checked, hipEventDisableTiming));
+    int *base = P<int>(c->cidx);
+    const int *st = P<int>(c->status);
+    {
+        KTimer kt(c, "index", 0);
+        launch_index_check(mc.ip, ids, ticks, base, Rows{}, 1, num_types, P<int>(c->status),
+                           nullptr, s);
+        launch_index_types(mc.ip, ticks, base, st, c->host, s);
+        HIPCHK(c, hipEventRecord(c->checked, s));
+        launch_index_lists(mc.ip, ids, ticks, base, st, 0, s);
+    }
+    if ((rc = wait_checks(c))) return rc;
+    mc.ix = index_view(mc.ip, base);
+    mc.on = true;
+    return FE_OK;
+}
+
+// The masks and the pairs' entries that sibling counting reads, made once a
+// run, when a level first takes one exact pass; they take at most 2 and 16 GiB.
+int sibling_setup(fe_ctx *c, MineChains &mc, const std::vector<int> &F1, const std::vector<int> &ilo,
+                  const std::vector<int> &ihi, int num_types)
+{
+    hipStream_t s = c->stream;
+    mc.tried = -1;
+    const int64_t places = mc.ip.n + (int64_t)LIST_PAD * num_types;
+    const int words = mask_words(num_types), n_iv = (int)ilo.size(), nF = (int)F1.size();
+    const int64_t mask_ints = places * words * n_iv;
+    const int64_t pairs = (int64_t)nF * nF * n_iv, sd = (int64_t)nF * n_iv * places;
+    if (mask_ints > ((int64_t)1 << 29) || (int64_t)words * n_iv > 65535 ||
+        sd > ((int64_t)1 << 32) / 3 || pairs >= ((int64_t)1 << 31))
+        return FE_OK;
+    if (ensure(c, c->smask, (size_t)mask_ints * sizeof(int)) ||
+        ensure(c, c->sseed, (size_t)(3 * sd + pairs) * sizeof(int)) ||
+        ensure(c, c->sivl, (size_t)(2 * n_iv + num_types + nF) * sizeof(int)))
+        return FE_OK;
+    std::vector<int> h(2 * n_iv + num_types + nF, 0);
+    std::copy(ilo.begin(), ilo.end(), h.begin());
+    std::copy(ihi.begin(), ihi.end(), h.begin() + n_iv);
+    for (int k = 0; k < nF; ++k) {
+        h[2 * n_iv + F1[k]] = k;
+        h[2 * n_iv + num_types + k] = F1[k];
+    }
+    HIPCHK(c, hipMemcpyAsync(c->sivl.p, h.data(), h.size() * sizeof(int), hipMemcpyHostToDevice, s));
+    SibJob &j = mc.sib;
+    j.ix = mc.ix;
+    j.mask = (const unsigned *)c->smask.p;
+    j.hop = places * words;
+    j.words = words;
+    j.ivlo = P<int>(c->sivl);
+    j.ivhi = j.ivlo + n_iv;
+    j.n_iv = n_iv;
+    j.rank = j.ivlo + 2 * n_iv;
+    j.nF = nF;
+    int *t = P<int>(c->sseed);
+    j.sd_t = t;
+    j.sd_a = t + sd;
+    j.sd_p = t + 2 * sd;
+    j.sd_n = t + 3 * sd;
+    j.sd_stride = places;
+    KTimer kt(c, "sibling_setup", 0);
+    launch_masks(mc.ip, P<int>(c->cidx), j.ivlo, j.ivhi, n_iv, (unsigned *)c->smask.p, s);
+    launch_seeds(mc.ix, j.rank + num_types, nF, j.ivlo, j.ivhi, n_iv, t, t + sd, t + 2 * sd,
+                 t + 3 * sd, places, s);
+    // (h is pageable: its copy has been staged when the call returns)
+    HIPCHK(c, hipGetLastError());
+    mc.tried = 1;
+    return FE_OK;
+}
+
+// Every row of `rows` by chains (both counts, or one of them).
+int chain_rows(fe_ctx *c, const MineChains &mc, const Rows &rows, int num_types, ChainMode mode,
+               int theta, int *up, int *ex, const char *name)
+{
+    int rc;
+    const int Pn = chain_P(c, rows.M, mc.ip.n, num_types, rows.N, mode == CHAIN_EXACT);
+    if ((rc = ensure(c, c->cseg, Pn > 1 ? (size_t)Pn * rows.M * sizeof(int4) : 4))) return rc;
+    ChainJob j{};
+    j.ix = mc.ix;
+    j.rows = rows;
+    j.theta = theta;
+    j.upper = up;
+    j.exact = ex;
+    j.P = Pn;
+    j.seg = P<int4>(c->cseg);
+    c->stats.map_launches += mode == CHAIN_TWO_PASS ? 2 : 1;
+    c->stats.segments_max = std::max<int64_t>(c->stats.segments_max, Pn);
+    KTimer kt(c, name, (double)rows.M * (double)mc.ip.n);
+    launch_chain(j, mode, rows.N, P<int>(c->status), c->stream);
+    HIPCHK(c, hipGetLastError());
     return FE_OK;
 }
 
@@ -1290,8 +1435,12 @@ extern "C" int fe_mine(fe_ctx *c, const int32_t *ids, const int32_t *ticks, int6
     HIPCHK(c, hipSetDevice(c->device));
     c->stats = fe_stats{};
     hipStream_t s = c->stream;
-    StreamInfo si;
-    if ((rc = stream_info(c, ids, ticks, (int)n, num_types, si))) return rc;
+    MineChains mc;
+    mc.n_iv = n_iv;
+    if (chain_takes(c, n, num_types) && c->param[FE_PARAM_HOST_TILING] == 0)
+        if ((rc = mine_index(c, ids, ticks, n, num_types, mc))) return rc;
+    StreamInfo si{};
+    if (!mc.on && (rc = stream_info(c, ids, ticks, (int)n, num_types, si))) return rc;
 
     std::vector<LevelOut> levels;
     // level 1: a one-node episode occurs at every event of its type
@@ -1361,7 +1510,23 @@ extern "C" int fe_mine(fe_ctx *c, const int32_t *ids, const int32_t *ticks, int6
         int bbound = 1;  // largest window bound of the interval set
         for (int k = 0; k < n_iv; ++k) bbound = std::max(bbound, window_bound(ilo[k], ihi[k]));
         const int wk = 3 * level - 2;  // ints per key
-        if ((rc = ensure(c, c->mkey, std::max<size_t>(M * wk, 1) * sizeof(int)))) return rc;
+        const int64_t emode = c->param[FE_PARAM_ELIMINATION];
+        const double r1 = (double)c->param[FE_PARAM_PASS1_COST] / 1000.0;
+        const bool large = emode == 2 && !htile && (int64_t)M >= c->param[FE_PARAM_SAMPLE_MIN];
+        // one exact pass over a joined level, siblings together: the
+        // candidates' keys are only written out when something asks for them
+        bool sib = mc.on && djoin && (emode == 0 || (large && r1 >= 1.0));
+        if (sib && !mc.tried &&
+            (rc = sibling_setup(c, mc, levels[0].types, ilo, ihi, num_types)))
+            return rc;
+        sib = sib && mc.tried > 0;
+        const bool keys_on = !sib || c->param[FE_PARAM_KEEP_CANDIDATES] != 0;
+        if (keys_on && (rc = ensure(c, c->mkey, std::max<size_t>(M * wk, 1) * sizeof(int))))
+            return rc;
+        int64_t longest = 0;  // most siblings of one episode
+        if (sib)
+            for (size_t a = 0; a + 1 < joff.size(); ++a)
+                longest = std::max(longest, joff[a + 1] - joff[a]);
         if (djoin) {
             const int64_t cnt = (int64_t)F.count();
             const size_t fb = F.key.size() * sizeof(int), ob = (size_t)(cnt + 1) * sizeof(int64_t);
@@ -1373,9 +1538,10 @@ extern "C" int fe_mine(fe_ctx *c, const int32_t *ids, const int32_t *ticks, int6
                                      hipMemcpyHostToDevice, s));
             HIPCHK(c, hipMemcpyAsync((char *)c->mfo.p + ob, joff.data(), ob,
                                      hipMemcpyHostToDevice, s));
-            launch_join(P<int>(c->mfk), 3 * F.m - 2, (const int64_t *)c->mfo.p,
-                        (const int64_t *)((char *)c->mfo.p + ob), cnt, (int64_t)M,
-                        P<int>(c->mkey), s);
+            if (keys_on)
+                launch_join(P<int>(c->mfk), 3 * F.m - 2, (const int64_t *)c->mfo.p,
+                            (const int64_t *)((char *)c->mfo.p + ob), cnt, (int64_t)M,
+                            P<int>(c->mkey), s);
             HIPCHK(c, hipGetLastError());
             // (F, jfirst and joff outlive the stream synchronisation below)
         } else {
@@ -1386,24 +1552,46 @@ extern "C" int fe_mine(fe_ctx *c, const int32_t *ids, const int32_t *ticks, int6
         }
         HostPack hp;
         ivec order;
-        const int64_t emode = c->param[FE_PARAM_ELIMINATION];
         bool elim = emode != 0;
         int64_t smp_n = 0, smp_kept = 0;
-        if (emode == 2 && !htile && (int64_t)M >= c->param[FE_PARAM_SAMPLE_MIN]) {
+        if (large) {
             // two passes pay when the relaxed pass (cost r per candidate,
             // relative to the exact one) prunes more than r of the level;
             // with r >= 1 nothing can, and no sample is taken
-            const double r = (double)c->param[FE_PARAM_PASS1_COST] / 1000.0;
             elim = false;
-            if (r < 1.0) {
-                if ((rc = sample_survival(c, ids, ticks, si, level, (int64_t)M, wbound, bbound,
-                                          theta, smp_n, smp_kept)))
+            if (r1 < 1.0) {
+                if ((rc = sample_survival(c, ids, ticks, si, mc, num_types, level, (int64_t)M,
+                                          wbound, bbound, theta, smp_n, smp_kept)))
                     return rc;
-                elim = (double)smp_kept < (1.0 - r) * (double)smp_n;
+                elim = (double)smp_kept < (1.0 - r1) * (double)smp_n;
             }
         }
         int64_t kept = 0;  // candidates of the exact pass (device tiling)
-        if (!htile) {
+        int *nkept_d = P<int>(c->mn) + 1;  // the same, still on the device (chains)
+        if (mc.on) {
+            if (sib) {
+                SibJob j = mc.sib;
+                j.F = P<int>(c->mfk);
+                j.m = F.m;
+                j.w = 3 * F.m - 2;
+                const int64_t cnt = (int64_t)F.count();
+                j.first = (const int64_t *)c->mfo.p;
+                j.off = j.first + cnt + 1;
+                j.out = ex;
+                c->stats.map_launches++;
+                char kname[40];
+                snprintf(kname, sizeof kname, "map_exact_siblings_n%d", level);
+                KTimer kt(c, kname, (double)M * (double)n);
+                launch_siblings(j, cnt, longest, s);
+                HIPCHK(c, hipGetLastError());
+            } else if ((rc = chain_rows(c, mc, key_rows(P<int>(c->mkey), level, (int64_t)M),
+                                        num_types, elim ? CHAIN_TWO_PASS : CHAIN_EXACT, theta, up,
+                                        ex, elim ? "map_two_pass_chain" : "map_exact_chain"))) {
+                return rc;
+            }
+            if (elim) launch_count_ge(up, (int)M, theta, nkept_d, P<int>(c->status), s);
+            else if (c->param[FE_PARAM_KEEP_CANDIDATES]) launch_fill(up, -1, (int64_t)M, s);
+        } else if (!htile) {
             // prune and tile on the device: pass 1 (Algorithm 3) over every
             // candidate, then pass 2 (Algorithm 1) over those with
             // upper >= theta (Algorithm 4), or over all in one-pass mode
@@ -1451,7 +1639,7 @@ extern "C" int fe_mine(fe_ctx *c, const int32_t *ids, const int32_t *ticks, int6
             // one pass: Algorithm 1 over every candidate, no relaxed count
             launch_fill(up, -1, (int64_t)M, s);
         }
-        const int64_t nsurv = !htile ? kept : elim ? (int64_t)order.size() : (int64_t)M;
+        int64_t nsurv = !htile ? kept : elim ? (int64_t)order.size() : (int64_t)M;
         // pass 2 (Algorithm 1) over the survivors; the others keep -1
         if (htile) launch_fill(ex, -1, (int64_t)M, s);
         if (htile && nsurv > 0) {
@@ -1467,20 +1655,31 @@ extern "C" int fe_mine(fe_ctx *c, const int32_t *ids, const int32_t *ticks, int6
             if ((rc = launch_groups(c, ids, ticks, si, hp.groups, true, ex))) return rc;
         }
         // frequent = exact >= theta
-        launch_fill(P<int>(c->mn), 0, 1, s);
-        launch_compact(ex, (int)M, theta, nullptr, P<int>(c->msel), P<int>(c->mn), s);
-        launch_gather2(up, ex, P<int>(c->msel), P<int>(c->mn), (int)M, up + M, ex + M, s);
+        if (mc.on) {
+            // (in candidate order, which is key order)
+            if ((rc = ensure(c, c->tscr, (size_t)pick_scratch_ints((int64_t)M) * sizeof(int))))
+                return rc;
+            launch_pick(up, ex, (int64_t)M, theta, P<int>(c->tscr), P<int>(c->mn),
+                        P<int>(c->msel), elim ? up + M : nullptr, ex + M, s);
+        } else {
+            launch_fill(P<int>(c->mn), 0, 1, s);
+            launch_compact(ex, (int)M, theta, nullptr, P<int>(c->msel), P<int>(c->mn), s);
+            launch_gather2(up, ex, P<int>(c->msel), P<int>(c->mn), (int)M, up + M, ex + M, s);
+        }
         int cnts[2];
-        HIPCHK(c, hipMemcpyAsync(cnts, P<int>(c->mn), sizeof(int), hipMemcpyDeviceToHost, s));
+        HIPCHK(c, hipMemcpyAsync(cnts, P<int>(c->mn), 2 * sizeof(int), hipMemcpyDeviceToHost, s));
         HIPCHK(c, hipStreamSynchronize(s));
+        if (mc.on) nsurv = elim ? cnts[1] : (int64_t)M;
         cnts[1] = (int)nsurv;
         const int nf = cnts[0];
-        std::vector<int> fsel(nf), fup(nf), fex(nf);
+        std::vector<int> fsel(nf), fup(nf, -1), fex(nf);
         if (nf > 0) {
-            HIPCHK(c, hipMemcpyAsync(fsel.data(), P<int>(c->msel), nf * sizeof(int),
-                                     hipMemcpyDeviceToHost, s));
-            HIPCHK(c, hipMemcpyAsync(fup.data(), up + M, nf * sizeof(int), hipMemcpyDeviceToHost,
-                                     s));
+            if (!djoin || !mc.on)
+                HIPCHK(c, hipMemcpyAsync(fsel.data(), P<int>(c->msel), nf * sizeof(int),
+                                         hipMemcpyDeviceToHost, s));
+            if (elim || !mc.on)
+                HIPCHK(c, hipMemcpyAsync(fup.data(), up + M, nf * sizeof(int),
+                                         hipMemcpyDeviceToHost, s));
             HIPCHK(c, hipMemcpyAsync(fex.data(), ex + M, nf * sizeof(int), hipMemcpyDeviceToHost,
                                      s));
             HIPCHK(c, hipStreamSynchronize(s));
@@ -1514,7 +1713,13 @@ extern "C" int fe_mine(fe_ctx *c, const int32_t *ids, const int32_t *ticks, int6
             // the frequent keys come back from the device
             if (nf > 0) {
                 if ((rc = ensure(c, c->mfsel, (size_t)nf * wk * sizeof(int)))) return rc;
-                launch_gather_keys(P<int>(c->mkey), wk, P<int>(c->msel), nf, P<int>(c->mfsel), s);
+                if (keys_on)
+                    launch_gather_keys(P<int>(c->mkey), wk, P<int>(c->msel), nf, P<int>(c->mfsel),
+                                       s);
+                else
+                    launch_join_sel(P<int>(c->mfk), 3 * F.m - 2, (const int64_t *)c->mfo.p,
+                                    (const int64_t *)c->mfo.p + F.count() + 1,
+                                    (int64_t)F.count(), P<int>(c->msel), nf, P<int>(c->mfsel), s);
                 HIPCHK(c, hipMemcpyAsync(NF.key.data(), c->mfsel.p, (size_t)nf * wk * sizeof(int),
                                          hipMemcpyDeviceToHost, s));
                 HIPCHK(c, hipStreamSynchronize(s));
@@ -1523,7 +1728,7 @@ extern "C" int fe_mine(fe_ctx *c, const int32_t *ids, const int32_t *ticks, int6
             for (int i = 0; i < nf; ++i)
                 std::memcpy(NF.key.data() + (size_t)i * wk, C.at(fsel[i]), wk * sizeof(int));
         }
-        {
+        if (!mc.on || !djoin) {
             HTimer ht(c, "host_sort");
             // (the join writes candidates in key order; the compaction that
             // found the frequent ones does not keep it)

@@ -130,6 +130,14 @@ void launch_tile_lanes(int64_t M, const int *scratch, const int *info, int *orig
 // first/off from the host's range search), and a gather of selected keys.
 void launch_join(const int *F, int w, const int64_t *first, const int64_t *off, int64_t cnt,
                  int64_t M, int *out, hipStream_t s);
+// The same for the listed candidates alone.
+void launch_join_sel(const int *F, int w, const int64_t *first, const int64_t *off, int64_t cnt,
+                     const int *sel, int nsel, int *out, hipStream_t s);
+// The candidates with ex >= theta, in order: their indices (sel), ex and
+// (out_up set) up there; *total their number.
+int64_t pick_scratch_ints(int64_t M);
+void launch_pick(const int *up, const int *ex, int64_t M, int theta, int *scratch, int *total,
+                 int *sel, int *out_up, int *out_ex, hipStream_t s);
 void launch_gather_keys(const int *key, int w, const int *sel, int nsel, int *out, hipStream_t s);
 // Sample of a level for the elimination decision: every SAMPLE_STRIDE-th
 // block of 64 consecutive candidates; sample_count(M) candidates.

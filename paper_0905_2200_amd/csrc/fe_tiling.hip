@@ -55,6 +55,11 @@ struct ClassFlag {
     int c;
     __device__ int operator()(int64_t i) const { return cls[i] == c ? 1 : 0; }
 };
+struct AtLeast {
+    const int *a;
+    int theta;
+    __device__ int operator()(int64_t i) const { return a[i] >= theta ? 1 : 0; }
+};
 struct Arr {
     const int *a;
     __device__ int operator()(int64_t i) const { return a[i]; }
@@ -380,6 +385,45 @@ __global__ void k_join(const int *__restrict__ F, int w, const int64_t *__restri
     for (int k = 0; k < w; ++k) o[3 + k] = be[k];
 }
 
+// Candidate j of the join, without the others: alpha is the last a with
+// off[a] <= j.
+__global__ void k_join_sel(const int *__restrict__ F, int w, const int64_t *__restrict__ first,
+                           const int64_t *__restrict__ off, int64_t cnt,
+                           const int *__restrict__ sel, int nsel, int *__restrict__ out)
+{
+    const int i = blockIdx.x * TB + threadIdx.x;
+    if (i >= nsel) return;
+    const int64_t j = sel[i];
+    int64_t lo = 0, hi = cnt;
+    while (hi - lo > 1) {
+        const int64_t mid = (lo + hi) >> 1;
+        if (off[mid] <= j) lo = mid;
+        else hi = mid;
+    }
+    const int *al = F + lo * w, *be = F + (first[lo] + (j - off[lo])) * w;
+    int *o = out + (int64_t)i * (w + 3);
+    o[0] = al[0];
+    o[1] = al[1];
+    o[2] = al[2];
+    for (int k = 0; k < w; ++k) o[3 + k] = be[k];
+}
+
+// The values of at least theta, in order: their indices and both arrays'
+// values there.
+__global__ void k_pick(const int *__restrict__ up, const int *__restrict__ ex, int64_t M,
+                       int theta, const int *__restrict__ pos, int *__restrict__ sel,
+                       int *__restrict__ out_up, int *__restrict__ out_ex)
+{
+    const int64_t i = blockIdx.x * (int64_t)TB + threadIdx.x;
+    if (i >= M) return;
+    const int x = ex[i];
+    if (x < theta) return;
+    const int at = pos[i];
+    sel[at] = (int)i;
+    out_ex[at] = x;
+    if (out_up) out_up[at] = up[i];
+}
+
 __global__ void k_gather_keys(const int *__restrict__ key, int w, const int *__restrict__ sel,
                               int nsel, int *__restrict__ out)
 {
@@ -423,6 +467,25 @@ int64_t scan_scratch_ints(int64_t n) { return (n + CHUNK - 1) / CHUNK + 1; }
 void launch_scan_excl(const int *in, int64_t n, int *out, int *scratch, hipStream_t s)
 {
     scan(Arr{in}, nullptr, n, out, scratch + 1, scratch, s);
+}
+
+int64_t pick_scratch_ints(int64_t M) { return M + (M + CHUNK - 1) / CHUNK; }
+
+void launch_pick(const int *up, const int *ex, int64_t M, int theta, int *scratch, int *total,
+                 int *sel, int *out_up, int *out_ex, hipStream_t s)
+{
+    scan(AtLeast{ex, theta}, nullptr, M, scratch, scratch + M, total, s);
+    if (M > 0)
+        hipLaunchKernelGGL(k_pick, dim3((unsigned)((M + TB - 1) / TB)), dim3(TB), 0, s, up, ex, M,
+                           theta, scratch, sel, out_up, out_ex);
+}
+
+void launch_join_sel(const int *F, int w, const int64_t *first, const int64_t *off, int64_t cnt,
+                     const int *sel, int nsel, int *out, hipStream_t s)
+{
+    if (nsel <= 0) return;
+    hipLaunchKernelGGL(k_join_sel, dim3((unsigned)((nsel + TB - 1) / TB)), dim3(TB), 0, s, F, w,
+                       first, off, cnt, sel, nsel, out);
 }
 
 void launch_join(const int *F, int w, const int64_t *first, const int64_t *off, int64_t cnt,

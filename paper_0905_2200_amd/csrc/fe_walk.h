@@ -46,12 +46,12 @@ struct NodeRow {
 };
 
 // Row m of a table into lanes 0..N-1 (N returned; wave-uniform).
-__device__ __forceinline__ int load_row(const ChainIdx &ix, const Rows &rows, int m, NodeRow &r)
+__device__ __forceinline__ int load_row(const ChainIdx &ix, const Rows &rows, int64_t m, NodeRow &r)
 {
     const int lane = __lane_id();
     const int N = rows.len ? __builtin_amdgcn_readfirstlane(rows.len[m]) : rows.N;
     const int k = lane < N ? lane : 0;
-    const TypeIdx ty = ix.ty[rows.ty[(int64_t)m * rows.ts + k * rows.tk]];
+    const TypeIdx ty = ix.ty[rows.ty[m * rows.ts + k * rows.tk]];
     r.start = ty.start;
     r.count = ty.count;
     r.boff = ty.boff;
@@ -60,8 +60,8 @@ __device__ __forceinline__ int load_row(const ChainIdx &ix, const Rows &rows, in
     r.t0 = __builtin_amdgcn_readfirstlane(ty.t0);
     r.lo = r.hi = 0;
     if (lane < N - 1) {
-        r.lo = rows.lo[(int64_t)m * rows.hs + lane * rows.hk];
-        r.hi = rows.hi[(int64_t)m * rows.hs + lane * rows.hk];
+        r.lo = rows.lo[m * rows.hs + lane * rows.hk];
+        r.hi = rows.hi[m * rows.hs + lane * rows.hk];
     }
     return N;
 }
@@ -126,37 +126,55 @@ __device__ __forceinline__ void find(const ChainIdx &ix, int start, int boff, in
     pl.k = pl.k < 4 ? pl.k : 3;  // (lanes off)
 }
 
-// One wave's rings in LDS: ring q (1..) at base + (q-1)*QCAP*F ints: ticks,
-// node-0 positions and, relaxed, stream indices.
-template <bool REL> __device__ __forceinline__ int *ring(int *base, int q)
-{
-    return base + (q - 1) * QCAP * (REL ? 3 : 2);
-}
-__host__ __device__ constexpr int ring_ints(bool rel) { return QCAP * (rel ? 3 : 2); }
+// What an entry carries besides its tick and its chain's first event's
+// position in node 0's list: nothing (the exact counter), its own stream
+// index (the relaxed counter) or its own position in its list.
+enum Carry { CARRY_NONE = 0, CARRY_INDEX = 1, CARRY_POS = 2 };
 
-// Entries of node E, in order, from node 0's events [a, aend) of the row's
-// first list (aend is either the list's end or past every tick that an entry
-// wanted from [a, ...) can reach).  sink(n, t, apos, i): the next n <= 64
-// entries, one per lane: tick, position of the chain's first event in node
-// 0's list, and (relaxed) the entry's own stream index.
-template <bool REL, class Sink>
+// One wave's rings in LDS: ring q (1..) at base + (q-1)*ring_ints: ticks,
+// node-0 positions and, with a carry, a third word.
+__host__ __device__ constexpr int ring_ints(bool third) { return QCAP * (third ? 3 : 2); }
+
+// Entries of node 1, kept in memory for every pair (mining): their ticks,
+// chains' first positions and own positions.
+struct Seeds {
+    const int *t, *a, *p;
+};
+
+// Entries of node E, in order, from the source [a, aend): node 0's events of
+// the row's first list (aend is either the list's end or past every tick that
+// an entry wanted from [a, ...) can reach), or, SEED, all of a pair's entries
+// of node 1.  sink(n, on, t, apos, own, first, L0): the next n <= 64 entries,
+// one per lane (on): tick, position of the chain's first event in node 0's
+// list, the carried word; first: straight from the source, L0 then being the
+// next list's table at their buckets.
+template <Carry CARRY, bool SEED, class Sink>
 __device__ __forceinline__ void walk(const ChainIdx &ix, const NodeRow &row, int E, int a,
-                                     int aend, int *lds, Sink &sink)
+                                     int aend, int *lds, Sink &sink, const Seeds &seed = Seeds())
 {
+    constexpr bool REL = CARRY == CARRY_INDEX;
+    constexpr bool THIRD = CARRY != CARRY_NONE;
+    constexpr int S = SEED ? 1 : 0;  // the source's node
     const int lane = __lane_id();
     const int start0 = rdl(row.start, 0);
+    auto ring = [&](int q) { return lds + (q - 1 - S) * ring_ints(THIRD); };
     // lane q: ring q's first slot, its entries, and how many events of its
     // first entry's range have been put out already (an entry with more than
     // a batch's worth is put out in parts)
     int qh = 0, qn = 0, sk = 0;
     // the next batch of node 0's events, loaded while this one is worked on
     int pa = -1, pt = 0, ptn = 0, pL = 0;
-    const int x0 = REL ? 0 : rdl(row.lo, 0) + 1;
-    const int boff1 = rdl(row.boff, 1), nb1 = rdl(row.nb, 1), sh1 = rdl(row.sh, 1);
+    const int x0 = REL ? 0 : rdl(row.lo, S) + 1;
+    const int boff1 = rdl(row.boff, S + 1), nb1 = rdl(row.nb, S + 1), sh1 = rdl(row.sh, S + 1);
     auto load_t = [&](int at) {
         const int pos = at + lane < aend ? at + lane : aend - 1;
-        pt = ix.et[start0 + pos];
-        ptn = ix.et[start0 + pos + 1];
+        if constexpr (SEED) {
+            pt = seed.t[pos];
+            ptn = pos + 1 < aend ? seed.t[pos + 1] : FAR_TICK;
+        } else {
+            pt = ix.et[start0 + pos];
+            ptn = ix.et[start0 + pos + 1];
+        }
     };
     auto load_L = [&] { pL = ix.tab[boff1 + bucket(pt + x0, row.t0, sh1, nb1)]; };
     for (;;) {
@@ -166,7 +184,7 @@ __device__ __forceinline__ void walk(const ChainIdx &ix, const NodeRow &row, int
         if (ready) {
             k = 63 - __builtin_clzll(ready);
         } else if (a < aend) {
-            k = 0;
+            k = S;
         } else {
             const unsigned long long some = bal(qn > 0);
             if (!some) break;
@@ -175,11 +193,11 @@ __device__ __forceinline__ void walk(const ChainIdx &ix, const NodeRow &row, int
             flush = true;
         }
         int t, tn = FAR_TICK, apos, i = 0, in = FAR_TICK, n, L0 = 0;
-        if (k == 0) {
+        if (k == S) {
             n = aend - a < WAVE ? aend - a : WAVE;
             if (pa != a) {
                 load_t(a);
-                load_L();
+                if (!SEED || E > S) load_L();
             }
             t = pt;
             tn = ptn;
@@ -189,32 +207,36 @@ __device__ __forceinline__ void walk(const ChainIdx &ix, const NodeRow &row, int
                 i = ix.ei[start0 + apos];
                 in = ix.ei[start0 + apos + 1];
             }
+            if constexpr (SEED) {
+                if (E == S) i = seed.p[apos];
+                apos = seed.a[apos];
+            }
             pa = a + WAVE;
             if (pa < aend) load_t(pa);
         } else {
             const int h = rdl(qh, k), c = rdl(qn, k);
-            const int *q = ring<REL>(lds, k);
+            const int *q = ring(k);
             n = (flush || k == E) ? c : c - 1;
             n = n < WAVE ? n : WAVE;
             const int s0 = (h + lane) & (QCAP - 1), s1 = (h + lane + 1) & (QCAP - 1);
             t = q[s0];
             apos = q[QCAP + s0];
             if (lane + 1 < c) tn = q[s1];
+            if constexpr (THIRD) i = q[2 * QCAP + s0];
             if constexpr (REL) {
-                i = q[2 * QCAP + s0];
                 if (lane + 1 < c) in = q[2 * QCAP + s1];
             }
         }
         bool on = lane < n;
         if (k == E) {
-            sink(n, on, t, apos, i, k == 0, L0);
-            if (k == 0) {
+            sink(n, on, t, apos, i, k == S, L0);
+            if (k == S) {
                 a += n;
             } else {
                 qh = lane == k ? (qh + n) & (QCAP - 1) : qh;
                 qn = lane == k ? qn - n : qn;
             }
-            if (k == 0 && pa < aend) load_L();
+            if (!SEED && k == S && pa < aend) load_L();
             continue;
         }
         const int lo = rdl(row.lo, k), hi = rdl(row.hi, k);
@@ -227,7 +249,7 @@ __device__ __forceinline__ void walk(const ChainIdx &ix, const NodeRow &row, int
             lim = tl < lim ? tl : lim;
         }
         const int b = bucket(x, row.t0, rdl(row.sh, k + 1), rdl(row.nb, k + 1));
-        if (k != 0) L0 = ix.tab[boff + b];
+        if (k != S) L0 = ix.tab[boff + b];
         else if (!on) L0 = 0;
         Place<REL> pl;
         find<REL>(ix, start, boff, b, L0, on, x, i, pl);
@@ -315,33 +337,34 @@ __device__ __forceinline__ void walk(const ChainIdx &ix, const NodeRow &row, int
             }
         }
         if (tot) {
-            int *q = ring<REL>(lds, k + 1);
+            int *q = ring(k + 1);
             const int tail = rdl(qh, k + 1) + rdl(qn, k + 1) + excl;
             if (c > 0) {
                 const int s0 = tail & (QCAP - 1);
                 q[s0] = pl.tick();
                 q[QCAP + s0] = apos;
-                if constexpr (REL) q[2 * QCAP + s0] = pl.index();
+                if constexpr (THIRD) q[2 * QCAP + s0] = REL ? pl.index() : pl.p();
             }
             for (int j = 1; bal(c > j) != 0; ++j) {
                 if (c > j) {
                     const int s0 = (tail + j) & (QCAP - 1);
                     q[s0] = ix.et[start + pl.p() + j];
                     q[QCAP + s0] = apos;
-                    if constexpr (REL) q[2 * QCAP + s0] = ix.ei[start + pl.p() + j];
+                    if constexpr (THIRD)
+                        q[2 * QCAP + s0] = REL ? ix.ei[start + pl.p() + j] : pl.p() + j;
                 }
             }
             qn = lane == k + 1 ? qn + tot : qn;
             __builtin_amdgcn_wave_barrier();
         }
         sk = lane == k ? put_skip : sk;
-        if (k == 0) {
+        if (k == S) {
             a += nc;
         } else {
             qh = lane == k ? (qh + nc) & (QCAP - 1) : qh;
             qn = lane == k ? qn - nc : qn;
         }
-        if (k == 0 && pa < aend) load_L();
+        if (k == S && pa < aend) load_L();
     }
 }
 
