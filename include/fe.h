@@ -324,7 +324,9 @@ typedef struct fe_job {
 
 typedef struct fe_batch fe_batch;
 
-/* Launch shape of a batch, picked by fe_batch_autotune or set by hand. */
+/* Launch shape of a batch's event-by-event launches, picked by
+ * fe_batch_autotune or set by hand (a batch counted over per-type lists, the
+ * default, has one shape: a wave per candidate). */
 typedef struct fe_batch_tuning {
     int32_t seg_events;   /* target events per work item (segment length)    */
     int32_t waves_per_cu; /* persistent waves launched per compute unit      */
@@ -334,7 +336,11 @@ typedef struct fe_batch_tuning {
 } fe_batch_tuning;
 
 /* Plan the two-pass count (Algorithm 4) of R recordings as one batch:
- * validates every stream and candidate table (synchronises), tiles every
+ * validates every stream and candidate table (synchronises) and lays out the
+ * recordings' per-type lists, which each run builds anew before one launch
+ * counts every candidate of every recording, the longest recordings first.
+ * With FE_PARAM_TYPE_DISPATCH = 0, more than 4096 types or no memory for the
+ * lists it instead tiles every
  * recording's candidates, splits long recordings into MapConcatenate
  * segments, orders all (tile, segment) work items heaviest first, and
  * captures one HIP graph per episode size: a persistent relaxed launch over
@@ -343,12 +349,12 @@ typedef struct fe_batch_tuning {
  * candidate tables must stay unchanged and valid while the batch exists. */
 int fe_batch_create(fe_ctx *ctx, int32_t R, const fe_job *jobs, fe_batch **out);
 
-/* Replay the batch's graphs on the context's stream (asynchronous). */
+/* Enqueue the batch on the context's stream (asynchronous). */
 int fe_batch_run(fe_batch *b);
 
 /* Time `reps` runs for each launch shape of a small grid (segment length x
  * persistent waves per CU x waves per workgroup), keep the fastest; *best
- * receives it.
+ * receives it (counting over per-type lists: the one shape is timed).
  * Synchronises. */
 int fe_batch_autotune(fe_batch *b, int32_t reps, fe_batch_tuning *best);
 int fe_batch_set_tuning(fe_batch *b, const fe_batch_tuning *t);
@@ -379,7 +385,8 @@ typedef struct fe_server_config {
     int32_t max_inflight;  /* rounds on the device at once (>= 1)              */
     int32_t max_round;     /* requests per round (>= 1)                        */
     int32_t seg_events;    /* target events per work item (0: 16384)           */
-    int32_t waves_per_cu;  /* persistent waves per compute unit (0: 16)        */
+    int32_t waves_per_cu;  /* persistent waves per compute unit (0: 16); both
+                              for the event-by-event launches                 */
 } fe_server_config;
 
 typedef struct fe_request {

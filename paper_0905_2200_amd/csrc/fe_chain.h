@@ -38,10 +38,37 @@ struct ChainIdx {
 // Device layout of an index over n events of T types, in ints.
 struct IndexPlan {
     int n = 0, T = 0, nch = 0, chunk = 0;
-    int64_t o_et = 0, o_ei = 0, o_tab = 0, o_ty = 0, o_hist = 0, o_scan = 0, ints = 0;
+    int64_t o_et = 0, o_ei = 0, o_tab = 0, o_ty = 0, o_hist = 0, o_off = 0, o_scan = 0, ints = 0;
 };
-IndexPlan index_plan(int64_t n, int T);
+// alone: one stream a call (the counts of a large one are scanned by many
+// blocks); else one of several indexed together, each scanned by one block.
+IndexPlan index_plan(int64_t n, int T, bool alone);
 ChainIdx index_view(const IndexPlan &p, int *base);
+
+// One stream to index; base_index is added to the stored indices.
+struct IndexJob {
+    const int *ids, *ticks;
+    int n, T, chunk, nch, base_index;
+    int *et, *ei, *tab, *hist, *off;
+    TypeIdx *ty;
+    int first_chunk, first_type;  // over the jobs before it
+};
+IndexJob index_job(const IndexPlan &p, const int *ids, const int *ticks, int *base, int base_index);
+
+// Streams indexed by one launch each step: `one`, or jobs[0..njobs).
+struct IndexSet {
+    IndexJob one;
+    const IndexJob *jobs = nullptr;  // device
+    int njobs = 1;
+    int chunks = 0, types = 0;  // of all jobs
+    int most_types = 0, parts = 1;
+    bool alone = true;
+    int64_t scan = 0;           // counts of a stream indexed alone
+    int *scan_scratch = nullptr;
+};
+// blocks a type that fill the bucket tables
+int index_parts(const IndexJob &j);
+IndexSet index_set(const IndexPlan &p, const IndexJob &j, int *base);
 
 // Candidate rows with strides: node k of candidate m has type
 // ty[m*ts + k*tk], hop k (lo, hi] = lo[m*hs + k*hk], hi[m*hs + k*hk]; its
@@ -70,21 +97,27 @@ struct ChainJob {
 
 enum ChainMode { CHAIN_EXACT = 0, CHAIN_RELAXED = 1, CHAIN_TWO_PASS = 2 };
 
-// Validates the stream and (rows.M > 0) the candidate rows into *status, and
-// starts the index with the per-chunk type histograms; *wmax: the largest
-// sum of hi among the candidates (may be null).
-void launch_index_check(const IndexPlan &p, const int *ids, const int *ticks, int *base,
-                        const Rows &rows, int nmax, int num_types, int *status, int *wmax,
-                        hipStream_t s);
+// Validates the streams and (rows.M > 0) the candidate rows into *status, and
+// starts the index with the per-chunk type histograms (T = 0 in the plan:
+// the checks alone); *wmax: the largest sum of hi among the candidates (may
+// be null).
+void launch_index_check(const IndexSet &x, const Rows &rows, int nmax, int num_types, int *status,
+                        int *wmax, hipStream_t s);
 // The rest of the index; the first kernel also copies *status to hstat (a
-// pinned host word, may be null); base_index is added to the stored indices.
-void launch_index_types(const IndexPlan &p, const int *ticks, int *base, const int *status,
-                        int *hstat, hipStream_t s);
-void launch_index_lists(const IndexPlan &p, const int *ids, const int *ticks, int *base,
-                        const int *status, int base_index, hipStream_t s);
+// pinned host word, may be null).
+void launch_index_types(const IndexSet &x, const int *status, int *hstat, hipStream_t s);
+void launch_index_lists(const IndexSet &x, const int *status, hipStream_t s);
+// lam[0] = first index with tick >= ticks[from] - *wmax, lam[1] = *status
+// (lam: pinned host words).
+void launch_look_back(const int *ticks, int from, const int *wmax, const int *status, int *lam,
+                      hipStream_t s);
 // Counts every row of one job (status non-zero: nothing is written).
 void launch_chain(const ChainJob &job, ChainMode mode, int nmax, const int *status,
                   hipStream_t s);
+// Both counts of every row of several jobs (device array; P = 1), whose rows
+// are numbered first[0..njobs]: job q has rows first[q] to first[q + 1].
+void launch_chains(const ChainJob *jobs, const int64_t *first, int njobs, int64_t total, int nmax,
+                   const int *status, hipStream_t s);
 // *out = the number of v[0..M) that are at least theta.
 void launch_count_ge(const int *v, int M, int theta, int *out, const int *status, hipStream_t s);
 

@@ -22,12 +22,14 @@ __host__ __device__ __forceinline__ int64_t tab_room(int64_t n, int64_t T) { ret
 
 }  // namespace
 
-IndexPlan index_plan(int64_t n, int T)
+IndexPlan index_plan(int64_t n, int T, bool alone)
 {
     IndexPlan p;
     p.n = (int)n;
     p.T = T;
     int64_t chunk = (n + MAX_CHUNKS - 1) / MAX_CHUNKS;
+    // (several together: one block scans a stream's counts, 32 a thread)
+    if (!alone) chunk = n * T / (32 * 1024);
     if (chunk < 512) chunk = 512;
     p.chunk = (int)((chunk + WAVE - 1) / WAVE * WAVE);
     p.nch = (int)((n + p.chunk - 1) / p.chunk);
@@ -37,14 +39,53 @@ IndexPlan index_plan(int64_t n, int T)
         o += align64(ints);
         return at;
     };
+    const int64_t H = (int64_t)T * p.nch;
     p.o_et = take(n + (int64_t)LIST_PAD * T);
     p.o_ei = take(n + (int64_t)LIST_PAD * T);
     p.o_tab = take(tab_room(n, T));
     p.o_ty = take((int64_t)T * (sizeof(TypeIdx) / sizeof(int)));
-    p.o_hist = take((int64_t)T * p.nch);
-    p.o_scan = take((int64_t)T * p.nch + scan_scratch_ints((int64_t)T * p.nch) + 1);
+    p.o_hist = take(H);
+    p.o_off = take(H);
+    p.o_scan = take(alone && H > SMALL_SCAN ? scan_scratch_ints(H) + 1 : 0);
     p.ints = o;
     return p;
+}
+
+IndexJob index_job(const IndexPlan &p, const int *ids, const int *ticks, int *base, int base_index)
+{
+    IndexJob j{};
+    j.ids = ids;
+    j.ticks = ticks;
+    j.n = p.n;
+    j.T = p.T;
+    j.chunk = p.chunk;
+    j.nch = p.nch;
+    j.base_index = base_index;
+    j.et = base + p.o_et;
+    j.ei = base + p.o_ei;
+    j.tab = base + p.o_tab;
+    j.hist = base + p.o_hist;
+    j.off = base + p.o_off;
+    j.ty = (TypeIdx *)(base + p.o_ty);
+    return j;
+}
+
+int index_parts(const IndexJob &j)
+{
+    const int64_t parts = j.T ? (int64_t)j.n / j.T / 1024 + 1 : 1;
+    return (int)(parts < 256 ? parts : 256);
+}
+
+IndexSet index_set(const IndexPlan &p, const IndexJob &j, int *base)
+{
+    IndexSet x;
+    x.one = j;
+    x.chunks = j.nch;
+    x.types = x.most_types = j.T;
+    x.parts = index_parts(j);
+    x.scan = (int64_t)j.T * j.nch;
+    x.scan_scratch = base + p.o_scan;
+    return x;
 }
 
 ChainIdx index_view(const IndexPlan &p, int *base)
@@ -59,33 +100,47 @@ ChainIdx index_view(const IndexPlan &p, int *base)
 
 namespace {
 
-// Blocks [0, nch): stream checks (ticks non-decreasing and in range, ids in
-// range) and the chunk's type counts, hist[type*nch + chunk].  Blocks after
-// them: candidate checks, 64 rows each.
-__global__ __launch_bounds__(WAVE) void k_ix_check(const int *__restrict__ ids,
-                                                   const int *__restrict__ ticks, int n, int T,
-                                                   int chunk, int nch, int *__restrict__ hist,
-                                                   Rows rows, int nmax, int num_types,
+// The job of a block, by its number among all jobs' chunks or types (FIRST
+// reads a job's first).
+template <class First>
+__device__ __forceinline__ IndexJob job_of(const IndexSet &x, int block, First first)
+{
+    if (!x.jobs) return x.one;
+    int lo = 0, hi = x.njobs;  // the last job that starts by block
+    while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (first(x.jobs[mid]) <= block) lo = mid;
+        else hi = mid;
+    }
+    return x.jobs[lo];
+}
+
+// Blocks [0, chunks): stream checks (ticks non-decreasing and in range, ids
+// in range) and the chunk's type counts, hist[type*nch + chunk].  Blocks
+// after them: candidate checks, 64 rows each.
+__global__ __launch_bounds__(WAVE) void k_ix_check(IndexSet x, Rows rows, int nmax, int num_types,
                                                    int *status, int *wmax)
 {
     extern __shared__ int sh[];
     const int lane = threadIdx.x;
     int bits = 0;
-    if ((int)blockIdx.x < nch) {
-        const int c = blockIdx.x;
+    if ((int)blockIdx.x < x.chunks) {
+        const IndexJob j = job_of(x, blockIdx.x, [](const IndexJob &q) { return q.first_chunk; });
+        const int c = (int)blockIdx.x - j.first_chunk;
+        const int T = j.T, types = T ? T : num_types;
         for (int e = lane; e < T; e += WAVE) sh[e] = 0;
         __syncthreads();
-        const int b = c * chunk, e = b + chunk < n ? b + chunk : n;
+        const int b = c * j.chunk, e = b + j.chunk < j.n ? b + j.chunk : j.n;
         for (int i = b + lane; i < e; i += WAVE) {
-            const int id = ids[i], t = ticks[i];
-            if (id < 0 || id >= num_types || t < 0 || t >= TICK_LIMIT) bits |= ST_RANGE;
+            const int id = j.ids[i], t = j.ticks[i];
+            if (id < 0 || id >= types || t < 0 || t >= TICK_LIMIT) bits |= ST_RANGE;
             else if (T) atomicAdd(&sh[id], 1);
-            if (i > 0 && ticks[i - 1] > t) bits |= ST_UNSORTED;
+            if (i > 0 && j.ticks[i - 1] > t) bits |= ST_UNSORTED;
         }
         __syncthreads();
-        for (int e2 = lane; e2 < T; e2 += WAVE) hist[(int64_t)e2 * nch + c] = sh[e2];
+        for (int e2 = lane; e2 < T; e2 += WAVE) j.hist[(int64_t)e2 * j.nch + c] = sh[e2];
     } else {
-        const int m = ((int)blockIdx.x - nch) * WAVE + lane;
+        const int m = ((int)blockIdx.x - x.chunks) * WAVE + lane;
         int W = 0;
         if (m < rows.M) {
             const int N = rows.len ? rows.len[m] : rows.N;
@@ -140,21 +195,22 @@ __device__ __forceinline__ int64_t block_prefix(int64_t v, int64_t *sh, int64_t 
     return base + x - v;
 }
 
-// One block.  Small indexes: scans the counts itself (hist to off).  Then,
-// per type: its list's place, the buckets of its table (a power of two of
-// ticks wide, so many that a bucket holds half an event to one on average)
-// and the list's guards.
-__global__ __launch_bounds__(TYB) void k_ix_types(const int *__restrict__ ticks, int n, int T,
-                                                  int nch, const int *__restrict__ hist,
-                                                  int *__restrict__ off, int scan_here,
-                                                  int *__restrict__ et, int *__restrict__ ei,
-                                                  TypeIdx *__restrict__ ty, const int *status,
+// One block a stream.  Scans the counts (hist to off) unless many blocks
+// have.  Then, per type: its list's place, the buckets of its table (a power
+// of two of ticks wide, so many that a bucket holds half an event to one on
+// average) and the list's guards.
+__global__ __launch_bounds__(TYB) void k_ix_types(IndexSet x, int scan_here, const int *status,
                                                   int *hstat)
 {
     __shared__ int64_t sh[TYB / WAVE];
     const int st = *status;
-    if (threadIdx.x == 0 && hstat) *hstat = st;
+    if (threadIdx.x == 0 && blockIdx.x == 0 && hstat) *hstat = st;
     if (st) return;
+    const IndexJob j = x.jobs ? x.jobs[blockIdx.x] : x.one;
+    const int n = j.n, T = j.T, nch = j.nch;
+    const int *hist = j.hist;
+    int *off = j.off, *et = j.et, *ei = j.ei;
+    TypeIdx *ty = j.ty;
     const int64_t H = (int64_t)T * nch;
     int64_t tot;
     if (scan_here) {
@@ -169,14 +225,15 @@ __global__ __launch_bounds__(TYB) void k_ix_types(const int *__restrict__ ticks,
         }
         __syncthreads();
     }
-    const int t0 = ticks[0];
-    const int span = ticks[n - 1] - t0;
+    const int t0 = n ? j.ticks[0] : 0;
+    const int span = n ? j.ticks[n - 1] - t0 : 0;
     int64_t boff = 0;
     for (int e0 = 0; e0 < T; e0 += TYB) {
         const int e = e0 + threadIdx.x;
         TypeIdx x{};
         if (e < T) {
-            const int a = off[(int64_t)e * nch], b = e + 1 < T ? off[(int64_t)(e + 1) * nch] : n;
+            const int a = n ? off[(int64_t)e * nch] : 0;
+            const int b = n && e + 1 < T ? off[(int64_t)(e + 1) * nch] : n;
             x.start = a + LIST_PAD * e;
             x.count = b - a;
             x.t0 = t0;
@@ -200,28 +257,25 @@ __global__ __launch_bounds__(TYB) void k_ix_types(const int *__restrict__ ticks,
 
 // One wave per chunk: 64 events at a time, each lane's rank among the
 // events of its type from a bit mask per type.
-__global__ __launch_bounds__(WAVE) void k_ix_lists(const int *__restrict__ ids,
-                                                   const int *__restrict__ ticks, int n, int T,
-                                                   int chunk, int nch,
-                                                   const int *__restrict__ off,
-                                                   int *__restrict__ et, int *__restrict__ ei,
-                                                   const int *status, int base_index)
+__global__ __launch_bounds__(WAVE) void k_ix_lists(IndexSet x, const int *status)
 {
     extern __shared__ unsigned long long sm[];
     if (*status) return;
+    const IndexJob j = job_of(x, blockIdx.x, [](const IndexJob &q) { return q.first_chunk; });
+    const int T = j.T, n = j.n, chunk = j.chunk, nch = j.nch;
     unsigned long long *mask = sm;
     int *cur = (int *)(sm + T);
-    const int lane = threadIdx.x, c = blockIdx.x;
+    const int lane = threadIdx.x, c = (int)blockIdx.x - j.first_chunk;
     for (int e = lane; e < T; e += WAVE) {
         mask[e] = 0;
-        cur[e] = off[(int64_t)e * nch + c] + LIST_PAD * e;
+        cur[e] = j.off[(int64_t)e * nch + c] + LIST_PAD * e;
     }
     __syncthreads();
     const int b = c * chunk, e = b + chunk < n ? b + chunk : n;
     for (int i0 = b; i0 < e; i0 += WAVE) {
         const int i = i0 + lane;
         const bool in = i < e;
-        const int id = in ? ids[i] : 0, t = in ? ticks[i] : 0;
+        const int id = in ? j.ids[i] : 0, t = in ? j.ticks[i] : 0;
         if (in) atomicOr(&mask[id], 1ull << lane);
         __syncthreads();
         const unsigned long long m = mask[id];
@@ -229,8 +283,8 @@ __global__ __launch_bounds__(WAVE) void k_ix_lists(const int *__restrict__ ids,
         const int at = cur[id] + rank;
         __syncthreads();
         if (in) {
-            et[at] = t;
-            ei[at] = base_index + i;
+            j.et[at] = t;
+            j.ei[at] = j.base_index + i;
             if (rank == 0) {
                 cur[id] += __builtin_popcountll(m);
                 mask[id] = 0;
@@ -243,12 +297,13 @@ __global__ __launch_bounds__(WAVE) void k_ix_lists(const int *__restrict__ ids,
 // tab[boff + b] = events of the type before bucket b.  Each position fills
 // the buckets after its predecessor's, up to its own; the end of the list
 // fills the rest.  Long stretches are filled by the whole wave.
-__global__ __launch_bounds__(256) void k_ix_tab(const int *__restrict__ et,
-                                                const TypeIdx *__restrict__ ty,
-                                                int *__restrict__ tab, const int *status)
+__global__ __launch_bounds__(256) void k_ix_tab(IndexSet s, const int *status)
 {
     if (*status) return;
-    const TypeIdx x = ty[blockIdx.x];
+    const IndexJob j = job_of(s, blockIdx.x, [](const IndexJob &q) { return q.first_type; });
+    const TypeIdx x = j.ty[(int)blockIdx.x - j.first_type];
+    const int *et = j.et;
+    int *tab = j.tab;
     const int lane = __lane_id();
     const int w0 = (int)(blockIdx.y * (blockDim.x / WAVE) + (threadIdx.x >> 6));
     const int64_t step = (int64_t)gridDim.y * blockDim.x;
@@ -264,50 +319,67 @@ __global__ __launch_bounds__(256) void k_ix_tab(const int *__restrict__ et,
             for (int b = b0; b <= b1; ++b) tab[x.boff + b] = (int)p;
         unsigned long long m = bal(wide);
         while (m) {
-            const int j = (int)__builtin_ctzll(m);
+            const int q = (int)__builtin_ctzll(m);
             m &= m - 1;
-            const int c0 = rdl(b0, j), c1 = rdl(b1, j);
-            for (int b = c0 + lane; b <= c1; b += WAVE) tab[x.boff + b] = (int)(p0 + j);
+            const int c0 = rdl(b0, q), c1 = rdl(b1, q);
+            for (int b = c0 + lane; b <= c1; b += WAVE) tab[x.boff + b] = (int)(p0 + q);
         }
     }
 }
 
 }  // namespace
 
-void launch_index_check(const IndexPlan &p, const int *ids, const int *ticks, int *base,
-                        const Rows &rows, int nmax, int num_types, int *status, int *wmax,
-                        hipStream_t s)
+void launch_index_check(const IndexSet &x, const Rows &rows, int nmax, int num_types, int *status,
+                        int *wmax, hipStream_t s)
 {
     const int cb = (rows.M + WAVE - 1) / WAVE;
-    if (p.nch + cb == 0) return;
-    hipLaunchKernelGGL(k_ix_check, dim3((unsigned)(p.nch + cb)), dim3(WAVE),
-                       (size_t)p.T * sizeof(int), s, ids, ticks, p.n, p.T, p.chunk, p.nch,
-                       base + p.o_hist, rows, nmax, num_types, status, wmax);
+    if (x.chunks + cb == 0) return;
+    hipLaunchKernelGGL(k_ix_check, dim3((unsigned)(x.chunks + cb)), dim3(WAVE),
+                       (size_t)x.most_types * sizeof(int), s, x, rows, nmax, num_types, status,
+                       wmax);
 }
 
-void launch_index_types(const IndexPlan &p, const int *ticks, int *base, const int *status,
-                        int *hstat, hipStream_t s)
+void launch_index_types(const IndexSet &x, const int *status, int *hstat, hipStream_t s)
 {
-    const int64_t H = (int64_t)p.T * p.nch;
-    const bool here = H <= SMALL_SCAN;
-    if (!here)
-        launch_scan_excl(base + p.o_hist, H, base + p.o_scan, base + p.o_scan + H, s);
-    hipLaunchKernelGGL(k_ix_types, dim3(1), dim3(TYB), 0, s, ticks, p.n, p.T, p.nch,
-                       base + p.o_hist, base + p.o_scan, here ? 1 : 0, base + p.o_et,
-                       base + p.o_ei, (TypeIdx *)(base + p.o_ty), status, hstat);
+    const bool here = !x.alone || x.scan <= SMALL_SCAN;
+    if (!here) launch_scan_excl(x.one.hist, x.scan, x.one.off, x.scan_scratch, s);
+    hipLaunchKernelGGL(k_ix_types, dim3((unsigned)x.njobs), dim3(TYB), 0, s, x, here ? 1 : 0,
+                       status, hstat);
 }
 
-void launch_index_lists(const IndexPlan &p, const int *ids, const int *ticks, int *base,
-                        const int *status, int base_index, hipStream_t s)
+void launch_index_lists(const IndexSet &x, const int *status, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_ix_lists, dim3((unsigned)p.nch), dim3(WAVE),
-                       (size_t)p.T * (sizeof(unsigned long long) + sizeof(int)), s, ids, ticks,
-                       p.n, p.T, p.chunk, p.nch, base + p.o_scan, base + p.o_et, base + p.o_ei,
-                       status, base_index);
-    int64_t parts = (int64_t)p.n / p.T / 1024 + 1;
-    if (parts > 256) parts = 256;
-    hipLaunchKernelGGL(k_ix_tab, dim3((unsigned)p.T, (unsigned)parts), dim3(256), 0, s,
-                       base + p.o_et, (const TypeIdx *)(base + p.o_ty), base + p.o_tab, status);
+    if (x.chunks > 0)
+        hipLaunchKernelGGL(k_ix_lists, dim3((unsigned)x.chunks), dim3(WAVE),
+                           (size_t)x.most_types * (sizeof(unsigned long long) + sizeof(int)), s,
+                           x, status);
+    hipLaunchKernelGGL(k_ix_tab, dim3((unsigned)x.types, (unsigned)x.parts), dim3(256), 0, s, x,
+                       status);
+}
+
+namespace {
+__global__ void k_look_back(const int *ticks, int from, const int *wmax, const int *status,
+                            int *lam)
+{
+    const int st = *status;
+    int a = 0, b = from;
+    if (!st) {
+        const int x = ticks[from] - *wmax;
+        while (a < b) {
+            const int mid = (a + b) >> 1;
+            if (ticks[mid] < x) a = mid + 1;
+            else b = mid;
+        }
+    }
+    lam[0] = a;
+    lam[1] = st;
+}
+}  // namespace
+
+void launch_look_back(const int *ticks, int from, const int *wmax, const int *status, int *lam,
+                      hipStream_t s)
+{
+    hipLaunchKernelGGL(k_look_back, dim3(1), dim3(1), 0, s, ticks, from, wmax, status, lam);
 }
 
 // ------------------------------------------------------------------ counting
@@ -487,13 +559,10 @@ __device__ __forceinline__ int seg_at(int c, int p, int P) { return (int)((int64
 // types: 22.6 -> 0.25 ms a call; 5000 relaxed of 5-8 nodes over 1.06e6 events
 // of 128 types: 13.2 -> 0.58 ms; 1e5 of 3 nodes over 9.7e6 events, both
 // passes: 81 -> 42 ms; 3000 with 9 to 19 live windows a list: 26 -> 0.08 ms.
-template <int MODE> __global__ __launch_bounds__(WAVE) void k_chain(ChainJob j, const int *status)
+template <int MODE>
+__device__ __forceinline__ void chain_item(const ChainJob &j, int64_t item, int *lds)
 {
-    extern __shared__ int lds[];
-    if (*status) return;
     const int M = j.rows.M;
-    const int64_t item = grid_item();
-    if (item >= (int64_t)j.P * M) return;
     const int p = (int)((unsigned)item / (unsigned)M), m = (int)((unsigned)item - (unsigned)p * (unsigned)M);
     const int lane = __lane_id();
     NodeRow row;
@@ -549,6 +618,33 @@ template <int MODE> __global__ __launch_bounds__(WAVE) void k_chain(ChainJob j, 
         if (take) count_range<false, false>(j.ix, row, N, 0, c, lds, r, cnt, dr, dc);
         if (lane == 0) j.exact[m] = take ? cnt : -1;
     }
+}
+
+template <int MODE> __global__ __launch_bounds__(WAVE) void k_chain(ChainJob j, const int *status)
+{
+    extern __shared__ int lds[];
+    if (*status) return;
+    const int64_t item = grid_item();
+    if (item < (int64_t)j.P * j.rows.M) chain_item<MODE>(j, item, lds);
+}
+
+// The same for the rows of several jobs.
+template <int MODE>
+__global__ __launch_bounds__(WAVE) void k_chains(const ChainJob *jobs, const int64_t *first,
+                                                 int njobs, int64_t total, const int *status)
+{
+    extern __shared__ int lds[];
+    if (*status) return;
+    const int64_t item = grid_item();
+    if (item >= total) return;
+    int lo = 0, hi = njobs;
+    while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (first[mid] <= item) lo = mid;
+        else hi = mid;
+    }
+    const ChainJob j = jobs[lo];
+    chain_item<MODE>(j, item - first[lo], lds);
 }
 
 // One wave per 64 candidates: their segments' results in order.  A
@@ -653,6 +749,15 @@ void launch_chain(const ChainJob &job, ChainMode mode, int nmax, const int *stat
         if (mode == CHAIN_EXACT) j.upper = nullptr;
         chain_mode<CHAIN_EXACT>(j, nmax, status, s);
     }
+}
+
+void launch_chains(const ChainJob *jobs, const int64_t *first, int njobs, int64_t total, int nmax,
+                   const int *status, hipStream_t s)
+{
+    if (total <= 0) return;
+    hipLaunchKernelGGL((k_chains<CHAIN_TWO_PASS>), grid_of(total), dim3(WAVE),
+                       (size_t)chain_lds(true, nmax) * sizeof(int), s, jobs, first, njobs, total,
+                       status);
 }
 
 // ------------------------------------------------------------------ siblings

@@ -720,7 +720,7 @@ int chain_call(fe_ctx *c, const int *ids, const int *ticks, int64_t n, int num_t
     hipStream_t s = c->stream;
     int rc;
     taken = false;
-    const IndexPlan ip = index_plan(n, num_types);
+    const IndexPlan ip = index_plan(n, num_types, true);
     const int Pn = chain_P(c, M, n, num_types, cin.nmax, mode == CHAIN_EXACT);
     if (ensure(c, c->cidx, (size_t)ip.ints * sizeof(int)) ||
         ensure(c, c->cseg, Pn > 1 ? (size_t)Pn * M * sizeof(int4) : 4))
@@ -741,11 +741,11 @@ int chain_call(fe_ctx *c, const int *ids, const int *ticks, int64_t n, int num_t
     const int *st = P<int>(c->status);
     {
         KTimer kt(c, "index", 0);
-        launch_index_check(ip, ids, ticks, base, j.rows, cin.nmax, num_types, P<int>(c->status),
-                           nullptr, s);
-        launch_index_types(ip, ticks, base, st, c->host, s);
+        const IndexSet x = index_set(ip, index_job(ip, ids, ticks, base, 0), base);
+        launch_index_check(x, j.rows, cin.nmax, num_types, P<int>(c->status), nullptr, s);
+        launch_index_types(x, st, c->host, s);
         HIPCHK(c, hipEventRecord(c->checked, s));
-        launch_index_lists(ip, ids, ticks, base, st, 0, s);
+        launch_index_lists(x, st, s);
     }
     c->stats.map_launches += mode == CHAIN_TWO_PASS ? 2 : 1;
     c->stats.segments_max = std::max<int64_t>(c->stats.segments_max, Pn);
@@ -758,6 +758,63 @@ int chain_call(fe_ctx *c, const int *ids, const int *ticks, int64_t n, int num_t
         if (nsurv) launch_count_ge(upper, M, theta, nsurv, st, s);
     }
     return wait_checks(c);
+}
+
+// The incremental count by chains: the checks over the whole stream, then an
+// index of the part that a new completion can reach back to.
+int chain_resume(fe_ctx *c, const int *ids, const int *ticks, int64_t n, int num_types,
+                 const CandIn &cin, int M, bool exact, int from, int *count_io, int *last_io,
+                 bool &taken)
+{
+    hipStream_t s = c->stream;
+    int rc;
+    taken = false;
+    if ((rc = ensure_host(c, 4))) return rc;
+    if (ensure(c, c->small, sizeof(int))) return FE_OK;
+    if (!c->checked)
+        HIPCHK(c, hipEventCreateWithFlags(&c->checked, hipEventDisableTiming));
+    int *wmax = P<int>(c->small);
+    const int *st = P<int>(c->status);
+    const Rows rows = table_rows(cin, M);
+    const IndexPlan cp = index_plan(n, 0, true);
+    IndexSet x = index_set(cp, index_job(cp, ids, ticks, nullptr, 0), nullptr);
+    launch_fill(wmax, 0, 1, s);
+    launch_index_check(x, rows, cin.nmax, num_types, P<int>(c->status), wmax, s);
+    launch_look_back(ticks, from, wmax, st, c->host + 1, s);
+    HIPCHK(c, hipEventRecord(c->checked, s));
+    HIPCHK(c, hipGetLastError());
+    HIPCHK(c, hipEventSynchronize(c->checked));
+    const int lam = ((volatile int *)c->host)[1], bits = ((volatile int *)c->host)[2];
+    if (bits) {
+        taken = true;
+        launch_fill(P<int>(c->status), 0, 1, s);
+        return fail(c, status_code(bits), "%s", status_text(bits));
+    }
+    const IndexPlan ip = index_plan(n - lam, num_types, true);
+    if (ensure(c, c->cidx, (size_t)ip.ints * sizeof(int))) return FE_OK;
+    taken = true;
+    int *base = P<int>(c->cidx);
+    {
+        KTimer kt(c, "index", 0);
+        x = index_set(ip, index_job(ip, ids + lam, ticks + lam, base, lam), base);
+        launch_index_check(x, Rows{}, 1, num_types, P<int>(c->status), nullptr, s);
+        launch_index_types(x, st, nullptr, s);
+        launch_index_lists(x, st, s);
+    }
+    ChainJob j{};
+    j.ix = index_view(ip, base);
+    j.rows = rows;
+    j.P = 1;
+    j.count_io = count_io;
+    j.last_io = last_io;
+    j.t_from = ticks + from;
+    j.from = from;
+    c->stats.map_launches++;
+    KTimer kt(c, exact ? "resume_exact_chain" : "resume_relaxed_chain",
+              (double)M * (double)(n - from));
+    launch_chain(j, exact ? CHAIN_EXACT : CHAIN_RELAXED, cin.nmax, st, s);
+    HIPCHK(c, hipGetLastError());
+    return FE_OK;
 }
 
 int count_impl(fe_ctx *c, const int32_t *ids, const int32_t *ticks, const StreamInfo &si,
@@ -1101,10 +1158,18 @@ extern "C" int fe_count_resume(fe_ctx *c, const int32_t *ids, const int32_t *tic
     if (M > 0 && (!count_io || !last_io)) return fail(c, FE_EINVAL, "null carry arrays");
     HIPCHK(c, hipSetDevice(c->device));
     c->stats = fe_stats{};
+    const CandIn cin{types, len, lo, hi, nmax};
+    bool taken = false;
+    if (M > 0 && from < n && chain_takes(c, n, num_types))
+        rc = chain_resume(c, ids, ticks, n, num_types, cin, M, mode == FE_EXACT, (int)from,
+                          count_io, last_io, taken);
+    if (taken) {
+        c->stats.last_call_ms = now_ms() - t0;
+        return rc;
+    }
     StreamInfo si;
     if ((rc = stream_info(c, ids, ticks, (int)n, num_types, si))) return rc;
     if (M > 0 && from < n) {
-        CandIn cin{types, len, lo, hi, nmax};
         const Resume rs{(int)from, count_io, last_io};
         rc = run_pass(c, ids, ticks, si, num_types, cin, nullptr, nullptr, M, mode == FE_EXACT,
                       nullptr, &rs);
@@ -1315,7 +1380,7 @@ int mine_index(fe_ctx *c, const int *ids, const int *ticks, int64_t n, int num_t
 {
     hipStream_t s = c->stream;
     int rc;
-    mc.ip = index_plan(n, num_types);
+    mc.ip = index_plan(n, num_types, true);
     if (ensure(c, c->cidx, (size_t)mc.ip.ints * sizeof(int))) return FE_OK;
     if ((rc = ensure_host(c, 4))) return rc;
     if (!c->checked) HIPCHK(c, hipEventCreateWithFlags(&c->checked, hipEventDisableTiming));
@@ -1323,11 +1388,11 @@ int mine_index(fe_ctx *c, const int *ids, const int *ticks, int64_t n, int num_t
     const int *st = P<int>(c->status);
     {
         KTimer kt(c, "index", 0);
-        launch_index_check(mc.ip, ids, ticks, base, Rows{}, 1, num_types, P<int>(c->status),
-                           nullptr, s);
-        launch_index_types(mc.ip, ticks, base, st, c->host, s);
+        const IndexSet x = index_set(mc.ip, index_job(mc.ip, ids, ticks, base, 0), base);
+        launch_index_check(x, Rows{}, 1, num_types, P<int>(c->status), nullptr, s);
+        launch_index_types(x, st, c->host, s);
         HIPCHK(c, hipEventRecord(c->checked, s));
-        launch_index_lists(mc.ip, ids, ticks, base, st, 0, s);
+        launch_index_lists(x, st, s);
     }
     if ((rc = wait_checks(c))) return rc;
     mc.ix = index_view(mc.ip, base);
@@ -1849,9 +1914,144 @@ struct fe_batch {
     std::vector<Level> levels;
     hipStream_t cap = nullptr;
     int ncu = 256;
+    // counting by chains: an index of every stream (made by each run) and
+    // one job per recording
+    bool chain = false;
+    Buf ixd, cjobs;
+    IndexSet set;
+    const ChainJob *chain_jobs = nullptr;
+    const int64_t *chain_first = nullptr;
+    int64_t total = 0;
+    int nmax = 1;
 };
 
 namespace {
+
+// Descriptors of streams indexed and counted together, as host bytes and the
+// offsets of its parts: IndexJob[R], ChainJob[R], int64_t first[R + 1].
+struct ChainBlock {
+    std::vector<char> bytes;
+    size_t o_chain = 0, o_first = 0;
+    IndexSet set;
+    int64_t total = 0;
+    int nmax = 1;
+};
+constexpr size_t chain_block_bytes(size_t R)
+{
+    return R * (sizeof(IndexJob) + sizeof(ChainJob)) + (R + 1) * sizeof(int64_t) + 16;
+}
+
+// ij: the streams' index jobs (first_chunk and first_type are filled in);
+// cj: their counts.
+ChainBlock chain_block(std::vector<IndexJob> &ij, const std::vector<ChainJob> &cj, int nmax)
+{
+    ChainBlock b;
+    const size_t R = ij.size();
+    std::vector<int64_t> first(R + 1, 0);
+    IndexSet &x = b.set;
+    x.alone = false;
+    x.njobs = (int)R;
+    for (size_t r = 0; r < R; ++r) {
+        ij[r].first_chunk = x.chunks;
+        ij[r].first_type = x.types;
+        x.chunks += ij[r].nch;
+        x.types += ij[r].T;
+        x.most_types = std::max(x.most_types, ij[r].T);
+        x.parts = std::max(x.parts, index_parts(ij[r]));
+        first[r + 1] = first[r] + cj[r].rows.M;
+    }
+    b.total = first[R];
+    b.nmax = nmax;
+    const auto al = [](size_t v) { return (v + 7) & ~(size_t)7; };
+    b.o_chain = al(R * sizeof(IndexJob));
+    b.o_first = al(b.o_chain + R * sizeof(ChainJob));
+    b.bytes.resize(b.o_first + (R + 1) * sizeof(int64_t));
+    if (R) {
+        std::memcpy(b.bytes.data(), ij.data(), R * sizeof(IndexJob));
+        std::memcpy(b.bytes.data() + b.o_chain, cj.data(), R * sizeof(ChainJob));
+    }
+    std::memcpy(b.bytes.data() + b.o_first, first.data(), (R + 1) * sizeof(int64_t));
+    return b;
+}
+
+void launch_chain_block(const IndexSet &set, const ChainJob *jobs, const int64_t *first,
+                        int64_t total, int nmax, int *status, hipStream_t s)
+{
+    if (set.njobs == 0) return;
+    launch_index_check(set, Rows{}, 1, 1, status, nullptr, s);
+    launch_index_types(set, status, nullptr, s);
+    launch_index_lists(set, status, s);
+    launch_chains(jobs, first, set.njobs, total, nmax, status, s);
+}
+
+// Plans a batch counted by chains: checks every stream and table (one wait)
+// and lays out the indexes and jobs, longest recordings first, so that their
+// candidates' waves start first.  b->chain stays false when there is no
+// memory for the indexes.
+int batch_chain_plan(fe_batch *b)
+{
+    fe_ctx *c = b->c;
+    hipStream_t s = c->stream;
+    const size_t R = b->jobs.size();
+    std::vector<size_t> order(R);
+    for (size_t r = 0; r < R; ++r) order[r] = r;
+    std::stable_sort(order.begin(), order.end(),
+                     [&](size_t x, size_t y) { return b->jobs[x].n > b->jobs[y].n; });
+    std::vector<IndexPlan> plan(R);
+    int64_t ints = 0;
+    int nmax = 1;
+    for (size_t r = 0; r < R; ++r) {
+        const fe_job &j = b->jobs[order[r]];
+        plan[r] = index_plan(j.n, j.num_types, false);
+        ints += plan[r].ints;
+        nmax = std::max(nmax, j.nmax);
+    }
+    if (ensure(c, b->ixd, (size_t)ints * sizeof(int)) ||
+        ensure(c, b->cjobs, chain_block_bytes(R)))
+        return FE_OK;
+    std::vector<IndexJob> ij(R);
+    std::vector<ChainJob> cj(R);
+    int *at = P<int>(b->ixd);
+    for (size_t r = 0; r < R; ++r) {
+        const fe_job &j = b->jobs[order[r]];
+        ij[r] = index_job(plan[r], j.ids, j.ticks, at, 0);
+        ChainJob &q = cj[r];
+        q = ChainJob{};
+        q.ix = index_view(plan[r], at);
+        q.rows = table_rows(CandIn{j.types, j.len, j.lo, j.hi, j.nmax}, j.M);
+        q.theta = j.theta;
+        q.upper = j.upper_out;
+        q.exact = j.exact_out;
+        q.P = 1;
+        at += plan[r].ints;
+    }
+    ChainBlock blk = chain_block(ij, cj, nmax);
+    char *d = (char *)b->cjobs.p;
+    HIPCHK(c, hipMemcpyAsync(d, blk.bytes.data(), blk.bytes.size(), hipMemcpyHostToDevice, s));
+    b->set = blk.set;
+    b->set.jobs = (const IndexJob *)d;
+    b->chain_jobs = (const ChainJob *)(d + blk.o_chain);
+    b->chain_first = (const int64_t *)(d + blk.o_first);
+    b->total = blk.total;
+    b->nmax = nmax;
+    if (R) launch_index_check(b->set, Rows{}, 1, 1, P<int>(c->status), nullptr, s);
+    for (size_t r = 0; r < R; ++r) {
+        const fe_job &j = b->jobs[order[r]];
+        IndexSet none;
+        none.njobs = 0;
+        launch_index_check(none, cj[r].rows, j.nmax, j.num_types, P<int>(c->status), nullptr, s);
+    }
+    HIPCHK(c, hipGetLastError());
+    HIPCHK(c, hipMemcpyAsync(c->host, c->status.p, sizeof(int), hipMemcpyDeviceToHost, s));
+    HIPCHK(c, hipStreamSynchronize(s));
+    const int bits = c->host[0];
+    if (bits) {
+        launch_fill(P<int>(c->status), 0, 1, s);
+        return fail(c, status_code(bits), "%s", status_text(bits));
+    }
+    b->chain = true;
+    return FE_OK;
+}
 
 void batch_free_graphs(fe_batch *b)
 {
@@ -2112,6 +2312,15 @@ extern "C" int fe_batch_create(fe_ctx *c, int32_t R, const fe_job *jobs, fe_batc
         fe_batch_destroy(b);
         return code;
     };
+    bool chains = c->param[FE_PARAM_TYPE_DISPATCH] != 0;
+    for (int r = 0; r < R; ++r)
+        chains = chains && (jobs[r].n == 0 || chain_takes(c, jobs[r].n, jobs[r].num_types)) &&
+                 jobs[r].num_types <= CHAIN_TYPES;
+    if (chains && (rc = batch_chain_plan(b))) return bail(rc);
+    if (b->chain) {
+        *out = b;
+        return FE_OK;
+    }
     // validate the streams and learn their spans
     for (int r = 0; r < R; ++r)
         if ((rc = stream_info(c, jobs[r].ids, jobs[r].ticks, (int)jobs[r].n, jobs[r].num_types,
@@ -2196,6 +2405,12 @@ extern "C" int fe_batch_run(fe_batch *b)
     if (!b) return FE_EINVAL;
     fe_ctx *c = b->c;
     HIPCHK(c, hipSetDevice(c->device));
+    if (b->chain) {
+        launch_chain_block(b->set, b->chain_jobs, b->chain_first, b->total, b->nmax,
+                           P<int>(c->status), c->stream);
+        HIPCHK(c, hipGetLastError());
+        return FE_OK;
+    }
     for (auto &L : b->levels) HIPCHK(c, hipGraphLaunch(L.x, c->stream));
     return FE_OK;
 }
@@ -2209,7 +2424,7 @@ extern "C" int fe_batch_set_tuning(fe_batch *b, const fe_batch_tuning *t)
     b->tun.seg_events = t->seg_events;
     b->tun.waves_per_cu = t->waves_per_cu;
     b->tun.waves_per_block = wpb;
-    return batch_plan(b);
+    return b->chain ? FE_OK : batch_plan(b);
 }
 
 extern "C" int fe_batch_get_tuning(const fe_batch *b, fe_batch_tuning *t)
@@ -2231,6 +2446,22 @@ extern "C" int fe_batch_autotune(fe_batch *b, int32_t reps, fe_batch_tuning *bes
     hipEvent_t e0, e1;
     HIPCHK(c, hipEventCreate(&e0));
     HIPCHK(c, hipEventCreate(&e1));
+    if (b->chain) {
+        // one launch shape: a wave per candidate
+        if ((rc = fe_batch_run(b))) return rc;  // warm-up
+        HIPCHK(c, hipEventRecord(e0, c->stream));
+        for (int r = 0; r < reps; ++r)
+            if ((rc = fe_batch_run(b))) return rc;
+        HIPCHK(c, hipEventRecord(e1, c->stream));
+        HIPCHK(c, hipEventSynchronize(e1));
+        float ms = 0.f;
+        HIPCHK(c, hipEventElapsedTime(&ms, e0, e1));
+        (void)hipEventDestroy(e0);
+        (void)hipEventDestroy(e1);
+        b->tun.run_ms = ms / reps;
+        if (best) *best = b->tun;
+        return FE_OK;
+    }
     for (int sg : segs)
         for (int wp : wpcs)
         for (int wb : wpbs) {
@@ -2265,7 +2496,7 @@ extern "C" int fe_batch_destroy(fe_batch *b)
     batch_free_graphs(b);
     Buf *bufs[] = {&b->pk,    &b->origd, &b->tileWd, &b->tilesd, &b->jobsd,  &b->itemsd,
                    &b->listsd, &b->lamd, &b->tbld,   &b->flagsr, &b->flagsx, &b->qctr,
-                   &b->deepd};
+                   &b->deepd,  &b->ixd,  &b->cjobs};
     for (Buf *x : bufs)
         if (x->p) (void)hipFree(x->p);
     if (b->cap) (void)hipStreamDestroy(b->cap);
@@ -2308,6 +2539,10 @@ struct fe_server {
     std::vector<int> tile_key;      // group key per packed tile
     std::vector<int> tile_w;        // widest W per packed tile
     int ntiles = 0;
+    // the same as a plain table, for rounds counted by chains
+    Buf rowsd;
+    Rows rows{};
+    int nmax = 1, maxtypes = 0;
     // arrays
     struct Arr {
         Buf ids, ticks;
@@ -2335,6 +2570,7 @@ struct fe_server {
         int round = -1, rsize = 0;
         int ns = 0, nf = 0;
         int64_t foot = 0;
+        bool chain = false;  // counted by chains (a round is all of one kind)
         std::vector<int> up, ex;
     };
     std::unordered_map<uint64_t, Req *> reqs;
@@ -2365,6 +2601,8 @@ struct fe_server {
 
 namespace {
 
+size_t align_up(size_t x) { return (x + 255) & ~(size_t)255; }
+
 // Device state one request needs inside a lane's arena (slot tables, look-
 // back starts, flags, work items, tile lists).
 int64_t req_arena_bytes(const fe_server *sv, int n)
@@ -2380,11 +2618,70 @@ int64_t req_arena_bytes(const fe_server *sv, int n)
     return tot + 4096;
 }
 
-size_t align_up(size_t x) { return (x + 255) & ~(size_t)255; }
+// The same for a request counted by chains: its window's index and its
+// share of the round's descriptors.
+int64_t req_chain_bytes(const fe_server *sv, int n)
+{
+    const IndexPlan p = index_plan(n, sv->maxtypes, false);
+    return (p.ints + 64) * (int64_t)sizeof(int) + (int64_t)chain_block_bytes(1);
+}
+
+// One round counted by chains: the windows' indexes, then every candidate of
+// every request in one launch.
+int server_launch_chain(fe_server *sv, fe_server::Lane &ln)
+{
+    fe_ctx *c = sv->c;
+    const int R = (int)ln.reqs.size(), M = sv->M;
+    std::vector<IndexJob> ij(R);
+    std::vector<ChainJob> cj(R);
+    char *ar = (char *)ln.arena.p;
+    size_t off = align_up(chain_block_bytes(R));
+    for (int r = 0; r < R; ++r) {
+        fe_server::Req *q = ln.reqs[r];
+        const fe_server::Arr &A = sv->arr[q->r.array];
+        const IndexPlan p = index_plan(q->b - q->a, sv->maxtypes, false);
+        int *base = (int *)(ar + off);
+        off = align_up(off + (size_t)p.ints * sizeof(int));
+        if (off > ln.arena.cap) return fail(c, FE_EINTERNAL, "round exceeds its lane arena");
+        ij[r] = index_job(p, (const int *)A.ids.p + q->a, (const int *)A.ticks.p + q->a, base, 0);
+        cj[r] = ChainJob{};
+        cj[r].ix = index_view(p, base);
+        cj[r].rows = sv->rows;
+        cj[r].theta = q->r.theta;
+        cj[r].upper = P<int>(ln.outd) + (int64_t)r * 2 * M;
+        cj[r].exact = cj[r].upper + M;
+        cj[r].P = 1;
+    }
+    const ChainBlock blk = chain_block(ij, cj, sv->nmax);
+    if (blk.bytes.size() > ln.stage_cap) {
+        if (ln.hstage) HIPCHK(c, hipHostFree(ln.hstage));
+        ln.hstage = nullptr;
+        HIPCHK(c, hipHostMalloc((void **)&ln.hstage, blk.bytes.size() * 2));
+        ln.stage_cap = blk.bytes.size() * 2;
+    }
+    std::memcpy(ln.hstage, blk.bytes.data(), blk.bytes.size());
+    hipStream_t s = ln.s;
+    if (sv->apending) HIPCHK(c, hipStreamWaitEvent(s, sv->aev, 0));
+    HIPCHK(c, hipMemcpyAsync(ar, ln.hstage, blk.bytes.size(), hipMemcpyHostToDevice, s));
+    launch_fill(P<int>(ln.statd), 0, 1, s);
+    IndexSet set = blk.set;
+    set.jobs = (const IndexJob *)ar;
+    launch_chain_block(set, (const ChainJob *)(ar + blk.o_chain),
+                       (const int64_t *)(ar + blk.o_first), blk.total, blk.nmax,
+                       P<int>(ln.statd), s);
+    HIPCHK(c, hipMemcpyAsync(ln.hout, ln.outd.p, (size_t)R * 2 * M * sizeof(int),
+                             hipMemcpyDeviceToHost, s));
+    HIPCHK(c, hipMemcpyAsync(ln.hout + (size_t)R * 2 * M, ln.statd.p, sizeof(int),
+                             hipMemcpyDeviceToHost, s));
+    HIPCHK(c, hipEventRecord(ln.done, s));
+    HIPCHK(c, hipGetLastError());
+    return FE_OK;
+}
 
 // Plan and enqueue one round on a lane.
 int server_launch(fe_server *sv, fe_server::Lane &ln)
 {
+    if (ln.reqs[0]->chain) return server_launch_chain(sv, ln);
     fe_ctx *c = sv->c;
     const int R = (int)ln.reqs.size();
     const int T = sv->ntiles;
@@ -2666,6 +2963,7 @@ void server_loop(fe_server *sv)
             const int64_t now = steady_ns();
             while (!sv->pending.empty() && (int)free_lane->reqs.size() < sv->cfg.max_round) {
                 fe_server::Req *q = sv->pending.front();
+                if (!free_lane->reqs.empty() && free_lane->reqs[0]->chain != q->chain) break;
                 if (!free_lane->reqs.empty() && used + q->foot > lane_budget) {
                     sv->st.budget_closed++;
                     break;
@@ -2803,6 +3101,22 @@ extern "C" int fe_server_create(fe_ctx *c, const fe_server_config *cfg, const in
         tileW.insert(tileW.end(), hp.tileW.begin(), hp.tileW.end());
         sv->ntiles += hp.tiles;
     }
+    sv->nmax = nm;
+    sv->maxtypes = maxtypes;
+    {
+        const size_t th = (size_t)M * (nm - 1);
+        if ((rc = ensure(c, sv->rowsd, ((size_t)M * (nm + 1) + 2 * th) * sizeof(int))))
+            return bail(rc);
+        int *d = P<int>(sv->rowsd);
+        HIPCHK(c, hipMemcpy(d, ty.data(), (size_t)M * nm * sizeof(int), hipMemcpyHostToDevice));
+        HIPCHK(c, hipMemcpy(d + (size_t)M * nm, ln.data(), M * sizeof(int), hipMemcpyHostToDevice));
+        int *dl = d + (size_t)M * (nm + 1);
+        if (nm > 1) {
+            HIPCHK(c, hipMemcpy(dl, lov.data(), th * sizeof(int), hipMemcpyHostToDevice));
+            HIPCHK(c, hipMemcpy(dl + th, hiv.data(), th * sizeof(int), hipMemcpyHostToDevice));
+        }
+        sv->rows = table_rows(CandIn{d, d + (size_t)M * nm, dl, dl + th, nm}, M);
+    }
     if ((rc = ensure(c, sv->pk, rec.size() * sizeof(int)))) return bail(rc);
     if ((rc = ensure(c, sv->origd, orig.size() * sizeof(int)))) return bail(rc);
     if ((rc = ensure(c, sv->tileWd, tileW.size() * sizeof(int)))) return bail(rc);
@@ -2835,7 +3149,11 @@ extern "C" int fe_server_create(fe_ctx *c, const fe_server_config *cfg, const in
                                                         g.dcap, (int)cfg->capacity).bytes);
     // lanes: stream, completion event, arena sized to the lane's budget
     const int64_t lane_budget = std::max<int64_t>(1, cfg->hbm_budget / cfg->max_inflight);
-    const int64_t max_one = req_arena_bytes(sv, (int)cfg->capacity);
+    int64_t max_one = req_arena_bytes(sv, (int)cfg->capacity);
+    // (a window whose index exceeds the budget is counted event by event)
+    if (maxtypes <= CHAIN_TYPES)
+        max_one = std::max(max_one, std::min(cfg->hbm_budget,
+                                             req_chain_bytes(sv, (int)cfg->capacity)));
     const int64_t arena = std::max<int64_t>(lane_budget, max_one) + (64 << 10);
     sv->lanes.resize(cfg->max_inflight);
     for (auto &L : sv->lanes) {
@@ -2919,6 +3237,14 @@ extern "C" int fe_server_submit(fe_server *sv, const fe_request *rq, uint64_t *t
         q->b = (int)(std::lower_bound(h.begin(), h.end(), rq->t_end) - h.begin());
     }
     q->foot = req_arena_bytes(sv, q->b - q->a) + 2 * (int64_t)sv->M * 4;
+    if (c->param[FE_PARAM_TYPE_DISPATCH] != 0 && sv->maxtypes <= CHAIN_TYPES &&
+        q->b - q->a <= (1 << 30)) {
+        const int64_t f = req_chain_bytes(sv, q->b - q->a) + 2 * (int64_t)sv->M * 4;
+        if (f <= sv->cfg.hbm_budget) {
+            q->foot = f;
+            q->chain = true;
+        }
+    }
     std::lock_guard<std::mutex> lk(sv->mu);
     q->ticket = sv->next_ticket++;
     sv->reqs[q->ticket] = q;
@@ -3033,7 +3359,7 @@ extern "C" int fe_server_destroy(fe_server *sv)
     if (sv->astage) (void)hipHostFree(sv->astage);
     if (sv->aev) (void)hipEventDestroy(sv->aev);
     if (sv->astream) (void)hipStreamDestroy(sv->astream);
-    Buf *bs[] = {&sv->pk, &sv->origd, &sv->tileWd};
+    Buf *bs[] = {&sv->pk, &sv->origd, &sv->tileWd, &sv->rowsd};
     for (Buf *x : bs)
         if (x->p) (void)hipFree(x->p);
     for (auto &kv : sv->reqs) delete kv.second;

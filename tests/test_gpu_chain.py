@@ -172,3 +172,85 @@ def test_errors_write_nothing(ctx, fe, mode):
         ctx.torch.cuda.synchronize()
         assert out.item() == -7
     assert ctx.count(ok[0], ok[1], 2, good, mode).item() == 2
+
+
+def test_batch_of_uneven_jobs(ctx, fe):
+    # recordings without events, tables without rows, one candidate, every
+    # table width, and more candidates than one launch row of waves
+    rng = np.random.default_rng(17)
+    recs = []
+    for n, T, M, nmax in ((0, 5, 40, 3), (1, 1, 1, 1), (5_000, 90, 900, 8), (20_000, 3, 300, 2),
+                          (700, 64, 0, 4), (0, 2, 3, 1), (12_345, 16, 2_000, 5)):
+        ids_h = rng.integers(0, T, n).astype(np.int32)
+        ticks_h = np.cumsum(rng.integers(0, 12, n)).astype(np.int32)
+        eps = synth.random_episodes(rng, M, T, nmax, IVS, n_min=1)
+        recs.append((ids_h, ticks_h, T, synth.pack(eps, nmax=nmax), 2 if n else 1))
+    dev = [{"ids": a, "ticks": b, "num_types": T, "cand": ctx.cand_tensors(c), "theta": th}
+           for (i, t, T, c, th) in recs for a, b in [ctx.stream_tensors(i, t)]]
+    banner("batch of uneven jobs")
+    b = fe.Batch(ctx, dev)
+    for _ in range(2):
+        b.run()
+        ctx.sync()
+        for r, (i, t, T, c, th) in enumerate(recs):
+            if c["M"] == 0:
+                continue
+            wu, we = oracle.two_pass(i, t, T, c["types"], c["len"], c["lo"], c["hi"], th,
+                                     projection=True)
+            assert np.array_equal(b.upper[r].cpu().numpy(), wu), r
+            assert np.array_equal(b.exact[r].cpu().numpy(), we), r
+    b.close()
+
+
+@pytest.mark.parametrize("mode", [EXACT, RELAXED])
+def test_resume_at_ties(ctx, mode):
+    # every cut inside a run of equal ticks, and increments shorter than the
+    # episodes' width
+    rng = np.random.default_rng(23)
+    T, n = 4, 3_000
+    ids_h = rng.integers(0, T, n).astype(np.int32)
+    ticks_h = np.cumsum(rng.integers(0, 2, n) * rng.integers(0, 25, n)).astype(np.int32)
+    cand = _all_sizes(rng, T, 300)
+    cd = ctx.cand_tensors(cand)
+    t = ctx.torch
+    cnt = t.zeros(cand["M"], dtype=t.int32, device=ctx.device)
+    last = t.full((cand["M"],), -1, dtype=t.int32, device=ctx.device)
+    ids, ticks = ctx.stream_tensors(ids_h, ticks_h)
+    prev = 0
+    banner("resume at ties")
+    for cut in (1, 2, 5, 64, 65, 200, 201, 202, 900, 1500, 1510, 1511, n):
+        ctx.count_resume(ids[:cut], ticks[:cut], T, cd, mode, prev, cnt, last)
+        want = oracle_counts(ids_h[:cut], ticks_h[:cut], T, cand, mode)
+        assert np.array_equal(cnt.cpu().numpy(), want), cut
+        prev = cut
+
+
+def test_served_arrays_of_different_types(ctx, fe):
+    # candidates of types that an array does not have, empty windows, and
+    # windows whose index passes the budget (counted event by event)
+    rng = np.random.default_rng(29)
+    sizes = [(3, 8_000), (40, 9_000), (40, 0)]
+    arrays = [(rng.integers(0, T, n).astype(np.int32),
+               np.cumsum(rng.integers(0, 9, n)).astype(np.int32)) for T, n in sizes]
+    cand = synth.pack(synth.random_episodes(rng, 400, 40, 6, IVS, n_min=1))
+    for budget in (1 << 30, 400 << 10):
+        sv = fe.Server(ctx, cand, [T for T, _ in sizes], capacity=9_016, hbm_budget=budget,
+                       max_inflight=2, max_round=5)
+        for a, (i, t) in enumerate(arrays):
+            sv.append(a, i, t)
+        reqs = []
+        for k in range(14):
+            a = k % 3
+            t0 = int(rng.integers(0, 30_000))
+            t1 = t0 if k == 3 else t0 + int(rng.integers(1, 30_000))
+            reqs.append((a, t0, t1, 1 + k % 4, sv.submit(a, t0, t1, 1 + k % 4)))
+        banner("served, budget %d" % budget)
+        for a, t0, t1, theta, tkt in reqs:
+            res = sv.wait(tkt)
+            i, t = arrays[a]
+            x, y = np.searchsorted(t, t0, "left"), np.searchsorted(t, t1, "left")
+            wu, we = oracle.two_pass(i[x:y], t[x:y], 40, cand["types"], cand["len"], cand["lo"],
+                                     cand["hi"], theta, projection=True)
+            assert res["status"] == fe.FE_OK and res["n_events"] == y - x
+            assert np.array_equal(res["upper"], wu) and np.array_equal(res["exact"], we), (a, t0, t1)
+        sv.close()
