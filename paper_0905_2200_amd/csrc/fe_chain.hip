@@ -413,6 +413,7 @@ template <bool REL, bool DUAL> struct Count {
     int fh = 0, fn = 0;
     int r, cnt = 0;
     int rf = -1, cntf = 0;
+    int s1 = FAR_TICK;  // first event of the first completion's chain
 
     __device__ __forceinline__ Count(const ChainIdx &x, const NodeRow &w, int N_, int a1_, int *q,
                                      int r0)
@@ -450,6 +451,7 @@ template <bool REL, bool DUAL> struct Count {
         const int s = on ? ix.ei[rdl(row.start, 0) + ap] : FAR_TICK;
         const int i = on ? ix.ei[rdl(row.start, N - 1) + dp] : FAR_TICK;
         const unsigned long long valid = bal(on);
+        if (s1 == FAR_TICK) s1 = rdl(s, 0);
         choose(valid, s, i, r, cnt);
         if (DUAL) choose(valid, s, i, rf, cntf);
         fh = (fh + n) & (FCAP - 1);
@@ -459,7 +461,7 @@ template <bool REL, bool DUAL> struct Count {
     {
         if (fn) drain(fn);
     }
-    __device__ __forceinline__ void operator()(int, bool on, int t, int apos, int i, bool first,
+    __device__ __forceinline__ void operator()(int, bool on, int t, int apos, int own, bool first,
                                                int L0)
     {
         const int lo = rdl(row.lo, N - 2), hi = rdl(row.hi, N - 2);
@@ -469,8 +471,8 @@ template <bool REL, bool DUAL> struct Count {
         const int b = bucket(x, row.t0, rdl(row.sh, N - 1), rdl(row.nb, N - 1));
         if (!first) L0 = ix.tab[boff + b];
         else if (!on) L0 = 0;
-        Place<REL> pl;
-        find<REL>(ix, start, boff, b, L0, on, x, i, pl);
+        Place pl;
+        find<REL>(ix, start, boff, b, L0, on, x, rdl(row.start, N - 2) + own, pl);
         const bool pass = on & (pl.tick() <= t + hi) & (apos < a1);
         const unsigned long long m = bal(pass);
         if (m == 0) return;
@@ -507,11 +509,12 @@ __device__ __forceinline__ int look_ahead(const ChainIdx &ix, const NodeRow &row
 }
 
 // Counts the chains from [a0, a1) of node 0's list after a completion at
-// index r (DUAL: and, into rf/cntf, after none).
+// index r (DUAL: and, into rf/cntf, after none).  s1: the first event of the
+// first chain that completes (unless N = 1, where none can be cut off).
 template <bool REL, bool DUAL>
 __device__ __forceinline__ void count_range(const ChainIdx &ix, const NodeRow &row, int N, int a0,
                                             int a1, int *lds, int &r, int &cnt, int &rf,
-                                            int &cntf)
+                                            int &cntf, int &s1)
 {
     if (a0 >= a1) return;
     if (N == 1) {
@@ -528,9 +531,9 @@ __device__ __forceinline__ void count_range(const ChainIdx &ix, const NodeRow &r
     }
     Count<REL, DUAL> sink(ix, row, N, a1, lds, r);
     if (DUAL) sink.rf = rf;
-    walk<REL ? CARRY_INDEX : CARRY_NONE, false>(ix, row, N - 2, a0, look_ahead(ix, row, N, a1),
-                                                lds + 2 * FCAP, sink);
+    walk<REL, REL, false>(ix, row, N - 2, a0, look_ahead(ix, row, N, a1), lds + 2 * FCAP, sink);
     sink.finish();
+    s1 = sink.s1;
     r = sink.r;
     cnt += sink.cnt;
     if (DUAL) {
@@ -549,7 +552,7 @@ __device__ __forceinline__ int seg_at(int c, int p, int P) { return (int)((int64
 
 // One wave per (segment, candidate).  P = 1 writes the counts; P > 1 the
 // segment's own count (after no completion), its last completion's index
-// and its first chain's.
+// and the first event of its first completed chain.
 //   A batch of 64 node-0 events is one coalesced read of their ticks and two
 // of the next list (its bucket, four entries), so the kernel is bound by the
 // latency of those reads at few waves and by the lists' bytes at many.  Why
@@ -566,7 +569,7 @@ __device__ __forceinline__ void chain_item(const ChainJob &j, int64_t item, int 
     const int p = (int)((unsigned)item / (unsigned)M), m = (int)((unsigned)item - (unsigned)p * (unsigned)M);
     const int lane = __lane_id();
     NodeRow row;
-    int dr = -1, dc = 0;
+    int dr = -1, dc = 0, s1 = FAR_TICK;
     if (j.P > 1) {
         // (MODE is EXACT or RELAXED; theta > 0 with upper set: survivors only)
         constexpr bool REL = MODE == CHAIN_RELAXED;
@@ -575,9 +578,8 @@ __device__ __forceinline__ void chain_item(const ChainJob &j, int64_t item, int 
         const int c = rdl(row.count, 0);
         const int a0 = seg_at(c, p, j.P), a1 = seg_at(c, p + 1, j.P);
         int r = -1, cnt = 0;
-        count_range<REL, false>(j.ix, row, N, a0, a1, lds, r, cnt, dr, dc);
-        const int first = a0 < a1 ? j.ix.ei[rdl(row.start, 0) + a0] : FAR_TICK;
-        if (lane == 0) j.seg[(int64_t)p * M + m] = make_int4(cnt, r, first, 0);
+        count_range<REL, false>(j.ix, row, N, a0, a1, lds, r, cnt, dr, dc, s1);
+        if (lane == 0) j.seg[(int64_t)p * M + m] = make_int4(cnt, r, s1, 0);
         return;
     }
     const int N = load_row(j.ix, j.rows, m, row);
@@ -598,7 +600,7 @@ __device__ __forceinline__ void chain_item(const ChainJob &j, int64_t item, int 
             else hi = mid;
         }
         int r = last, cnt = 0;
-        count_range<MODE == CHAIN_RELAXED, false>(j.ix, row, N, lo, c, lds, r, cnt, dr, dc);
+        count_range<MODE == CHAIN_RELAXED, false>(j.ix, row, N, lo, c, lds, r, cnt, dr, dc, s1);
         if (lane == 0 && cnt) {
             j.count_io[m] += cnt;
             j.last_io[m] = r;
@@ -609,13 +611,13 @@ __device__ __forceinline__ void chain_item(const ChainJob &j, int64_t item, int 
     bool take = true;
     if (MODE != CHAIN_EXACT) {
         int r = -1, cnt = 0;
-        count_range<true, false>(j.ix, row, N, 0, c, lds, r, cnt, dr, dc);
+        count_range<true, false>(j.ix, row, N, 0, c, lds, r, cnt, dr, dc, s1);
         if (lane == 0) j.upper[m] = cnt;
         take = cnt >= j.theta;
     }
     if (MODE != CHAIN_RELAXED) {
         int r = -1, cnt = 0;
-        if (take) count_range<false, false>(j.ix, row, N, 0, c, lds, r, cnt, dr, dc);
+        if (take) count_range<false, false>(j.ix, row, N, 0, c, lds, r, cnt, dr, dc, s1);
         if (lane == 0) j.exact[m] = take ? cnt : -1;
     }
 }
@@ -648,8 +650,8 @@ __global__ __launch_bounds__(WAVE) void k_chains(const ChainJob *jobs, const int
 }
 
 // One wave per 64 candidates: their segments' results in order.  A
-// segment's own run stands when its first chain starts after the last
-// completion before it; otherwise the wave runs it again from there until
+// segment's own run stands when the first chain it completes starts after
+// the last completion before it (the run would take it too); otherwise the wave runs it again from there until
 // it meets its own run (a common completion), a growing stretch at a time.
 template <bool REL> __global__ __launch_bounds__(WAVE) void k_stitch(ChainJob j, const int *status)
 {
@@ -681,10 +683,10 @@ template <bool REL> __global__ __launch_bounds__(WAVE) void k_stitch(ChainJob j,
             const int c = rdl(row.count, 0);
             const int a1 = seg_at(c, p + 1, j.P);
             int b = seg_at(c, p, j.P), len = WAVE;
-            int rr = rdl(r, q), cnt = 0, rf = -1, cntf = 0;
+            int rr = rdl(r, q), cnt = 0, rf = -1, cntf = 0, s1 = 0;
             while (b < a1 && (rf != rr)) {
                 const int e = a1 - b < len ? a1 : b + len;
-                count_range<REL, true>(j.ix, row, N, b, e, lds, rr, cnt, rf, cntf);
+                count_range<REL, true>(j.ix, row, N, b, e, lds, rr, cnt, rf, cntf, s1);
                 b = e;
                 len *= 2;
             }
@@ -842,7 +844,7 @@ __global__ __launch_bounds__(WAVE) void k_seeds(ChainIdx ix, const int *__restri
     row.lo = lane == 0 ? ivlo[k] : 0;
     row.hi = lane == 0 ? ivhi[k] : 0;
     SeedOut out{sd_t, sd_a, sd_p, ak * stride + rdl(ty.start, 1)};
-    walk<CARRY_POS, false>(ix, row, 1, 0, rdl(row.count, 0), lds, out);
+    walk<false, true, false>(ix, row, 1, 0, rdl(row.count, 0), lds, out);
     if (lane == 0) sd_n[item] = out.n;
 }
 
@@ -966,7 +968,7 @@ __device__ __forceinline__ void count_siblings(const SibJob &j, int64_t al, int 
     const int64_t at = ak * j.sd_stride + rdl(row.start, 1);
     const int c1 = j.sd_n[ak * j.nF + j.rank[key[3]]];
     const Seeds seed{j.sd_t + at, j.sd_a + at, j.sd_p + at};
-    walk<CARRY_POS, true>(j.ix, row, m - 1, 0, c1, lds, sink, seed);
+    walk<false, true, true>(j.ix, row, m - 1, 0, c1, lds, sink, seed);
 #pragma unroll
     for (int g = 0; g < G; ++g) {
         const int c = g0 + g * WAVE + lane;

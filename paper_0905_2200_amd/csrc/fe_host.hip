@@ -654,7 +654,10 @@ bool chain_takes(const fe_ctx *c, int64_t n, int num_types)
 
 // Segments per candidate: the hybrid rule's crossover (choose_P) decides
 // between one and several; several are as many as the target number of waves
-// takes, with at least 512 events of a list of average length in each.
+// takes, or as make a segment's share of all lists (12 B an event: tick and
+// bucket table) fit in one XCD's 4 MiB L2 -- the waves of one segment run
+// together, over the same stretch of time of every list -- with at least 512
+// events of a list of average length in each.
 int chain_P(const fe_ctx *c, int64_t M, int64_t n, int num_types, int nmax, bool exact)
 {
     const int64_t tiles = (M + WAVE - 1) / WAVE;
@@ -663,6 +666,7 @@ int chain_P(const fe_ctx *c, int64_t M, int64_t n, int num_types, int nmax, bool
     const double cross = (double)c->param[pa] / std::max(nmax, 1) + (double)c->param[pb];
     if ((double)tiles >= cross) return 1;
     int64_t P = std::max<int64_t>(2, (c->param[FE_PARAM_TARGET_WAVES] + M - 1) / M);
+    P = std::max<int64_t>(P, 12 * n / ((int64_t)3 << 20));
     P = std::min<int64_t>(P, n / ((int64_t)512 * num_types));
     P = std::min<int64_t>(P, ((int64_t)1 << 30) / M);
     return (int)std::max<int64_t>(1, std::min<int64_t>(P, 4096));

@@ -68,17 +68,13 @@ __device__ __forceinline__ int load_row(const ChainIdx &ix, const Rows &rows, in
 
 // A lane's place in a list: entries L..L+3, of which the first k come before
 // the wanted one at p = L + k.
-template <bool REL> struct Place {
+struct Place {
     int L, k;
-    v4i v, w;  // ticks; stream indices (relaxed)
+    v4i v;  // ticks
     __device__ __forceinline__ int p() const { return L + k; }
     __device__ __forceinline__ int tick() const
     {
         return k == 0 ? v[0] : k == 1 ? v[1] : k == 2 ? v[2] : v[3];
-    }
-    __device__ __forceinline__ int index() const
-    {
-        return k == 0 ? w[0] : k == 1 ? w[1] : k == 2 ? w[2] : w[3];
     }
 };
 
@@ -89,22 +85,19 @@ __device__ __forceinline__ int bucket(int x, int t0, int sh, int nb)
     return b < nb ? b : nb;
 }
 
-// First entry of the list with tick >= x (relaxed: with index > i, all of
-// whose predecessors have ticks <= x).  L0: the list's table at x's bucket.
-// Bounds: L0 <= count and LIST_PAD guards follow the list, so the four
-// entries read always exist; the guards (INT_MAX) stop every search.
+// First entry of the list with tick >= x.  L0: the list's table at x's
+// bucket b.  Bounds: L0 <= count and LIST_PAD guards follow the list, so the
+// four entries read always exist; the guards (INT_MAX) stop every search.
+//   REL: the first entry after the event at ei[self], whose tick is x; only
+// entries of the same tick can come before it, so indices are read there
+// alone (the stream's indices are half of its lists' bytes).
 template <bool REL>
 __device__ __forceinline__ void find(const ChainIdx &ix, int start, int boff, int b, int L0,
-                                     bool on, int x, int i, Place<REL> &pl)
+                                     bool on, int x, int self, Place &pl)
 {
     pl.L = L0;
     pl.v = *(const v4i *)(ix.et + start + L0);
-    if constexpr (REL) {
-        pl.w = *(const v4i *)(ix.ei + start + L0);
-        pl.k = (pl.w[0] <= i) + (pl.w[1] <= i) + (pl.w[2] <= i) + (pl.w[3] <= i);
-    } else {
-        pl.k = (pl.v[0] < x) + (pl.v[1] < x) + (pl.v[2] < x) + (pl.v[3] < x);
-    }
+    pl.k = (pl.v[0] < x) + (pl.v[1] < x) + (pl.v[2] < x) + (pl.v[3] < x);
     const bool slow = on & (pl.k == 4);
     if (__builtin_expect(bal(slow) != 0, 0)) {
         // a crowded bucket: binary search in the rest of it
@@ -112,27 +105,41 @@ __device__ __forceinline__ void find(const ChainIdx &ix, int start, int boff, in
             int lo = L0 + 4, hi = ix.tab[boff + b + 1];
             while (lo < hi) {
                 const int mid = (lo + hi) >> 1;
-                const bool before =
-                    REL ? ix.ei[start + mid] <= i : ix.et[start + mid] < x;
+                const bool before = ix.et[start + mid] < x;
                 lo = before ? mid + 1 : lo;
                 hi = before ? hi : mid;
             }
             pl.L = lo;
             pl.k = 0;
             pl.v = *(const v4i *)(ix.et + start + lo);
-            if constexpr (REL) pl.w = *(const v4i *)(ix.ei + start + lo);
         }
     }
     pl.k = pl.k < 4 ? pl.k : 3;  // (lanes off)
+    if constexpr (REL) {
+        const bool tie = on & (pl.tick() == x);
+        if (__builtin_expect(bal(tie) != 0, 0)) {
+            // (the entries of tick x end by the bucket's end)
+            if (tie) {
+                const int i = ix.ei[self];
+                int lo = pl.p(), hi = ix.tab[boff + b + 1];
+                while (lo < hi) {
+                    const int mid = (lo + hi) >> 1;
+                    const bool before = ix.ei[start + mid] <= i;
+                    lo = before ? mid + 1 : lo;
+                    hi = before ? hi : mid;
+                }
+                pl.L = lo;
+                pl.k = 0;
+                pl.v = *(const v4i *)(ix.et + start + lo);
+            }
+        }
+    }
 }
 
-// What an entry carries besides its tick and its chain's first event's
-// position in node 0's list: nothing (the exact counter), its own stream
-// index (the relaxed counter) or its own position in its list.
-enum Carry { CARRY_NONE = 0, CARRY_INDEX = 1, CARRY_POS = 2 };
-
 // One wave's rings in LDS: ring q (1..) at base + (q-1)*ring_ints: ticks,
-// node-0 positions and, with a carry, a third word.
+// positions of the chains' first events in node 0's list and, where something
+// asks for it (the relaxed counter's ties, the siblings' masks), the entries'
+// positions in their own list.
 __host__ __device__ constexpr int ring_ints(bool third) { return QCAP * (third ? 3 : 2); }
 
 // Entries of node 1, kept in memory for every pair (mining): their ticks,
@@ -146,18 +153,17 @@ struct Seeds {
 // an entry wanted from [a, ...) can reach), or, SEED, all of a pair's entries
 // of node 1.  sink(n, on, t, apos, own, first, L0): the next n <= 64 entries,
 // one per lane (on): tick, position of the chain's first event in node 0's
-// list, the carried word; first: straight from the source, L0 then being the
-// next list's table at their buckets.
-template <Carry CARRY, bool SEED, class Sink>
+// list, own position (POS); first: straight from the source, L0 then being
+// the next list's table at their buckets.
+template <bool REL, bool POS, bool SEED, class Sink>
 __device__ __forceinline__ void walk(const ChainIdx &ix, const NodeRow &row, int E, int a,
                                      int aend, int *lds, Sink &sink, const Seeds &seed = Seeds())
 {
-    constexpr bool REL = CARRY == CARRY_INDEX;
-    constexpr bool THIRD = CARRY != CARRY_NONE;
+    static_assert(POS || !REL, "the relaxed counter's ties need the positions");
     constexpr int S = SEED ? 1 : 0;  // the source's node
     const int lane = __lane_id();
     const int start0 = rdl(row.start, 0);
-    auto ring = [&](int q) { return lds + (q - 1 - S) * ring_ints(THIRD); };
+    auto ring = [&](int q) { return lds + (q - 1 - S) * ring_ints(POS); };
     // lane q: ring q's first slot, its entries, and how many events of its
     // first entry's range have been put out already (an entry with more than
     // a batch's worth is put out in parts)
@@ -192,7 +198,7 @@ __device__ __forceinline__ void walk(const ChainIdx &ix, const NodeRow &row, int
             k = (int)__builtin_ctzll(some);
             flush = true;
         }
-        int t, tn = FAR_TICK, apos, i = 0, in = FAR_TICK, n, L0 = 0;
+        int t, tn = FAR_TICK, apos, own = 0, next = 0, n, L0 = 0;
         if (k == S) {
             n = aend - a < WAVE ? aend - a : WAVE;
             if (pa != a) {
@@ -203,13 +209,12 @@ __device__ __forceinline__ void walk(const ChainIdx &ix, const NodeRow &row, int
             tn = ptn;
             L0 = pL;
             apos = a + lane < aend ? a + lane : aend - 1;
-            if constexpr (REL) {
-                i = ix.ei[start0 + apos];
-                in = ix.ei[start0 + apos + 1];
-            }
             if constexpr (SEED) {
-                if (E == S) i = seed.p[apos];
+                if (E == S) own = seed.p[apos];
                 apos = seed.a[apos];
+            } else {
+                own = apos;
+                next = apos + 1;
             }
             pa = a + WAVE;
             if (pa < aend) load_t(pa);
@@ -222,14 +227,12 @@ __device__ __forceinline__ void walk(const ChainIdx &ix, const NodeRow &row, int
             t = q[s0];
             apos = q[QCAP + s0];
             if (lane + 1 < c) tn = q[s1];
-            if constexpr (THIRD) i = q[2 * QCAP + s0];
-            if constexpr (REL) {
-                if (lane + 1 < c) in = q[2 * QCAP + s1];
-            }
+            if constexpr (POS) own = q[2 * QCAP + s0];
+            if constexpr (REL) next = q[2 * QCAP + s1];
         }
         bool on = lane < n;
         if (k == E) {
-            sink(n, on, t, apos, i, k == S, L0);
+            sink(n, on, t, apos, own, k == S, L0);
             if (k == S) {
                 a += n;
             } else {
@@ -244,15 +247,13 @@ __device__ __forceinline__ void walk(const ChainIdx &ix, const NodeRow &row, int
         t = on ? t : row.t0;
         const int x = REL ? t : t + lo + 1;
         int lim = t + hi;
-        if constexpr (!REL) {
-            const int tl = tn == FAR_TICK ? FAR_TICK : tn + lo;
-            lim = tl < lim ? tl : lim;
-        }
+        const int tl = REL || tn == FAR_TICK ? tn : tn + lo;
+        lim = tl < lim ? tl : lim;
         const int b = bucket(x, row.t0, rdl(row.sh, k + 1), rdl(row.nb, k + 1));
         if (k != S) L0 = ix.tab[boff + b];
         else if (!on) L0 = 0;
-        Place<REL> pl;
-        find<REL>(ix, start, boff, b, L0, on, x, i, pl);
+        Place pl;
+        find<REL>(ix, start, boff, b, L0, on, x, rdl(row.start, k) + own, pl);
         const int skip = rdl(sk, k);
         if (__builtin_expect(skip != 0, 0)) {
             if (lane == 0) {
@@ -260,35 +261,32 @@ __device__ __forceinline__ void walk(const ChainIdx &ix, const NodeRow &row, int
                 pl.L = pl.p() + skip;
                 pl.k = 0;
                 pl.v = *(const v4i *)(ix.et + start + pl.L);
-                if constexpr (REL) pl.w = *(const v4i *)(ix.ei + start + pl.L);
             }
         }
-        // events of the range among the four at hand; more: the last is one
+        // events of the range among the four at hand; more: the last is one,
+        // or (relaxed) one shares the next entry's tick and is in this range
+        // only if it comes before that entry's event
         int c = 0;
-        bool more = false;
-        if constexpr (REL) {
+        bool tie = false;
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
-                c += ((j >= pl.k) & (pl.v[j] <= lim) & (pl.w[j] <= in)) ? 1 : 0;
-            more = on & (pl.v[3] <= lim) & (pl.w[3] <= in);
-        } else {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) c += ((j >= pl.k) & (pl.v[j] <= lim)) ? 1 : 0;
-            more = on & (pl.v[3] <= lim);
+        for (int j = 0; j < 4; ++j) {
+            c += ((j >= pl.k) & (pl.v[j] <= lim)) ? 1 : 0;
+            if constexpr (REL) tie |= (j >= pl.k) & (pl.v[j] == tn) & (pl.v[j] <= lim);
         }
+        const bool more = on & ((pl.v[3] <= lim) | tie);
         c = on ? c : 0;
         if (__builtin_expect(bal(more) != 0, 0)) {
             if (more) {
                 // (a guard ends every range; at most a batch is put out at once)
-                int q = pl.L + 4, step = 4;
-                const int top = pl.p() + WAVE;
+                const int in = REL && tn != FAR_TICK ? ix.ei[rdl(row.start, k) + next] : FAR_TICK;
                 auto in_range = [&](int p) {
                     const int te = ix.et[start + p];
-                    if constexpr (REL) return (te <= lim) & (ix.ei[start + p] <= in);
+                    if constexpr (REL)
+                        return (te <= lim) & ((te != tn) || ix.ei[start + p] <= in);
                     else return te <= lim;
                 };
-                const int cnt = rdl(row.count, k + 1);
-                int e = q;  // entries before e are in range
+                const int cnt = rdl(row.count, k + 1), top = pl.p() + WAVE;
+                int e = pl.p(), step = 4;  // entries before e are in range
                 while (e + step <= cnt && e < top && in_range(e + step - 1)) {
                     e += step;
                     step *= 2;
@@ -343,15 +341,14 @@ __device__ __forceinline__ void walk(const ChainIdx &ix, const NodeRow &row, int
                 const int s0 = tail & (QCAP - 1);
                 q[s0] = pl.tick();
                 q[QCAP + s0] = apos;
-                if constexpr (THIRD) q[2 * QCAP + s0] = REL ? pl.index() : pl.p();
+                if constexpr (POS) q[2 * QCAP + s0] = pl.p();
             }
             for (int j = 1; bal(c > j) != 0; ++j) {
                 if (c > j) {
                     const int s0 = (tail + j) & (QCAP - 1);
                     q[s0] = ix.et[start + pl.p() + j];
                     q[QCAP + s0] = apos;
-                    if constexpr (THIRD)
-                        q[2 * QCAP + s0] = REL ? ix.ei[start + pl.p() + j] : pl.p() + j;
+                    if constexpr (POS) q[2 * QCAP + s0] = pl.p() + j;
                 }
             }
             qn = lane == k + 1 ? qn + tot : qn;
