@@ -461,25 +461,20 @@ template <bool REL, bool DUAL> struct Count {
     {
         if (fn) drain(fn);
     }
-    __device__ __forceinline__ void operator()(int, bool on, int t, int apos, int own, bool first,
-                                               int L0)
+    static constexpr bool SEARCHES = true;
+    __device__ __forceinline__ void operator()(int, bool on, int t, int src, int own, int L)
     {
-        const int lo = rdl(row.lo, N - 2), hi = rdl(row.hi, N - 2);
-        const int start = rdl(row.start, N - 1), boff = rdl(row.boff, N - 1);
-        t = on ? t : row.t0;
-        const int x = REL ? t : t + lo + 1;
-        const int b = bucket(x, row.t0, rdl(row.sh, N - 1), rdl(row.nb, N - 1));
-        if (!first) L0 = ix.tab[boff + b];
-        else if (!on) L0 = 0;
-        Place pl;
-        find<REL>(ix, start, boff, b, L0, on, x, rdl(row.start, N - 2) + own, pl);
-        const bool pass = on & (pl.tick() <= t + hi) & (apos < a1);
+        const Hop h = hop_of(ix, row, N - 2);
+        if (L < 0 || N > 2) L = table_at<REL>(h, t);
+        int p, c;
+        events_of<REL, true>(h, on, t, FAR_TICK, own, 0, L, 0, p, c);
+        const bool pass = (c != 0) & (src < a1);
         const unsigned long long m = bal(pass);
         if (m == 0) return;
         if (pass) {
             const int q = (fh + fn + below(m)) & (FCAP - 1);
-            fq[q] = apos;
-            fq[FCAP + q] = pl.p();
+            fq[q] = src;
+            fq[FCAP + q] = p;
         }
         __builtin_amdgcn_wave_barrier();
         fn += __builtin_popcountll(m);
@@ -531,7 +526,7 @@ __device__ __forceinline__ void count_range(const ChainIdx &ix, const NodeRow &r
     }
     Count<REL, DUAL> sink(ix, row, N, a1, lds, r);
     if (DUAL) sink.rf = rf;
-    walk<REL, REL, false>(ix, row, N - 2, a0, look_ahead(ix, row, N, a1), lds + 2 * FCAP, sink);
+    walk<REL, false>(ix, row, N - 2, a0, look_ahead(ix, row, N, a1), lds + 2 * FCAP, sink);
     sink.finish();
     s1 = sink.s1;
     r = sink.r;
@@ -542,9 +537,9 @@ __device__ __forceinline__ void count_range(const ChainIdx &ix, const NodeRow &r
     }
 }
 
-__host__ __device__ constexpr int chain_lds(bool rel, int nmax)
+__host__ __device__ constexpr int chain_lds(int nmax)
 {
-    return 2 * FCAP + (nmax > 2 ? nmax - 2 : 0) * ring_ints(rel);
+    return 2 * FCAP + (nmax > 2 ? nmax - 2 : 0) * RING_INTS;
 }
 
 // Segment p of P of a list of c events.
@@ -707,7 +702,7 @@ template <bool REL> __global__ __launch_bounds__(WAVE) void k_stitch(ChainJob j,
 
 template <int MODE> void chain_mode(const ChainJob &j, int nmax, const int *status, hipStream_t s)
 {
-    const size_t lds = (size_t)chain_lds(MODE != CHAIN_EXACT, nmax) * sizeof(int);
+    const size_t lds = (size_t)chain_lds(nmax) * sizeof(int);
     hipLaunchKernelGGL((k_chain<MODE>), grid_of((int64_t)j.P * j.rows.M), dim3(WAVE), lds, s, j,
                        status);
     if (j.P > 1)
@@ -758,7 +753,7 @@ void launch_chains(const ChainJob *jobs, const int64_t *first, int njobs, int64_
 {
     if (total <= 0) return;
     hipLaunchKernelGGL((k_chains<CHAIN_TWO_PASS>), grid_of(total), dim3(WAVE),
-                       (size_t)chain_lds(true, nmax) * sizeof(int), s, jobs, first, njobs, total,
+                       (size_t)chain_lds(nmax) * sizeof(int), s, jobs, first, njobs, total,
                        status);
 }
 
@@ -809,13 +804,13 @@ struct SeedOut {
     int *t, *a, *p;
     int64_t base;
     int n = 0;
-    __device__ __forceinline__ void operator()(int c, bool on, int tk, int apos, int own, bool,
-                                               int)
+    static constexpr bool SEARCHES = false;
+    __device__ __forceinline__ void operator()(int c, bool on, int tk, int src, int own, int)
     {
         if (on) {
             const int64_t at = base + n + __lane_id();
             t[at] = tk;
-            a[at] = apos;
+            a[at] = src;
             p[at] = own;
         }
         n += c;
@@ -844,8 +839,11 @@ __global__ __launch_bounds__(WAVE) void k_seeds(ChainIdx ix, const int *__restri
     row.lo = lane == 0 ? ivlo[k] : 0;
     row.hi = lane == 0 ? ivhi[k] : 0;
     SeedOut out{sd_t, sd_a, sd_p, ak * stride + rdl(ty.start, 1)};
-    walk<false, true, false>(ix, row, 1, 0, rdl(row.count, 0), lds, out);
-    if (lane == 0) sd_n[item] = out.n;
+    walk<false, false>(ix, row, 1, 0, rdl(row.count, 0), lds, out);
+    if (lane == 0) {
+        sd_t[out.base + out.n] = FAR_TICK;  // (a list has its guards' room)
+        sd_n[item] = out.n;
+    }
 }
 
 constexpr int SIB = 2;  // siblings a lane counts
@@ -866,11 +864,11 @@ template <int G> struct Siblings {
     unsigned off[G], bit[G];
     int hm = 0;           // widest hi
     int mb = -1;          // no lane's rb is larger
-    __device__ __forceinline__ void operator()(int n, bool on, int t, int apos, int own, bool,
-                                               int)
+    static constexpr bool SEARCHES = false;
+    const int *seed_a;  // the source's positions in node 0's list
+    __device__ __forceinline__ void operator()(int n, bool, int t, int src, int own, int)
     {
-        apos = on ? apos : 0;
-        own = on ? own : 0;
+        const int apos = at(seed_a, src);
         const int st = ix.et[start0 + apos];
         constexpr int U = 8;
         for (int e0 = 0; e0 < n; e0 += U) {
@@ -936,6 +934,7 @@ __device__ __forceinline__ void count_siblings(const SibJob &j, int64_t al, int 
     const int lane = __lane_id();
     const int start_m = rdl(row.start, m - 1);
     Siblings<G> sink{j, j.ix, j.mask + (int64_t)start_m * j.words, rdl(row.start, 0)};
+    const int *key = j.F + al * j.w;
 #pragma unroll
     for (int g = 0; g < G; ++g) {
         const int c = g0 + g * WAVE + lane;
@@ -961,14 +960,14 @@ __device__ __forceinline__ void count_siblings(const SibJob &j, int64_t al, int 
         sink.hm = hx > sink.hm ? hx : sink.hm;
     }
     // the pair (node 0, hop 0, node 1)'s entries
-    const int *key = j.F + al * j.w;
     int k0 = 0;
     for (int k = 1; k < j.n_iv; ++k) k0 = (j.ivlo[k] == key[1] && j.ivhi[k] == key[2]) ? k : k0;
     const int64_t ak = (int64_t)j.rank[key[0]] * j.n_iv + k0;
-    const int64_t at = ak * j.sd_stride + rdl(row.start, 1);
+    const int64_t sd = ak * j.sd_stride + rdl(row.start, 1);
     const int c1 = j.sd_n[ak * j.nF + j.rank[key[3]]];
-    const Seeds seed{j.sd_t + at, j.sd_a + at, j.sd_p + at};
-    walk<false, true, true>(j.ix, row, m - 1, 0, c1, lds, sink, seed);
+    const Seeds seed{j.sd_t + sd, j.sd_a + sd, j.sd_p + sd};
+    sink.seed_a = seed.a;
+    walk<false, true>(j.ix, row, m - 1, 0, c1, lds, sink, seed);
 #pragma unroll
     for (int g = 0; g < G; ++g) {
         const int c = g0 + g * WAVE + lane;
@@ -1023,7 +1022,7 @@ void launch_seeds(const ChainIdx &ix, const int *F1, int nF, const int *ivlo, co
                   hipStream_t s)
 {
     hipLaunchKernelGGL(k_seeds, grid_of((int64_t)nF * nF * n_iv), dim3(WAVE),
-                       (size_t)ring_ints(true) * sizeof(int), s, ix, F1, nF, ivlo, ivhi, n_iv,
+                       (size_t)RING_INTS * sizeof(int), s, ix, F1, nF, ivlo, ivhi, n_iv,
                        sd_t, sd_a, sd_p, sd_n, stride);
 }
 
@@ -1031,7 +1030,7 @@ void launch_siblings(const SibJob &j, int64_t cnt, int64_t longest, hipStream_t 
 {
     if (cnt <= 0 || longest <= 0) return;
     hipLaunchKernelGGL(k_siblings, grid_of(cnt, (longest + SIB * WAVE - 1) / (SIB * WAVE)),
-                       dim3(WAVE), (size_t)(j.m > 2 ? j.m - 2 : 1) * ring_ints(true) * sizeof(int),
+                       dim3(WAVE), (size_t)(j.m > 2 ? j.m - 2 : 1) * RING_INTS * sizeof(int),
                        s, j, cnt);
 }
 

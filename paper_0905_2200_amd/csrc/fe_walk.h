@@ -19,7 +19,12 @@
 //   Layout: a wave takes one candidate (or one shared prefix); lane k holds
 // node k's list and hop, read with v_readlane.  Between stages entries wait in
 // rings of 128 in LDS, and the deepest stage with a full batch goes first, so
-// every batch but the last few has 64 entries and no ring overflows.
+// every batch but the last few has 64 entries and no ring overflows.  The
+// walk is bound by instruction issue, nearly all of it in the source stage's
+// loop, so that stage has a loop of its own with its list's values in scalar
+// registers, entries wait as two positions (their ticks are read again by the
+// few that get on), and everything unusual -- a crowded bucket, a tie, more
+// events than the four at hand -- is behind one test.
 #pragma once
 
 #include "fe_chain.h"
@@ -66,18 +71,6 @@ __device__ __forceinline__ int load_row(const ChainIdx &ix, const Rows &rows, in
     return N;
 }
 
-// A lane's place in a list: entries L..L+3, of which the first k come before
-// the wanted one at p = L + k.
-struct Place {
-    int L, k;
-    v4i v;  // ticks
-    __device__ __forceinline__ int p() const { return L + k; }
-    __device__ __forceinline__ int tick() const
-    {
-        return k == 0 ? v[0] : k == 1 ? v[1] : k == 2 ? v[2] : v[3];
-    }
-};
-
 // bucket of tick x >= t0 in a list's table
 __device__ __forceinline__ int bucket(int x, int t0, int sh, int nb)
 {
@@ -85,65 +78,147 @@ __device__ __forceinline__ int bucket(int x, int t0, int sh, int nb)
     return b < nb ? b : nb;
 }
 
-// First entry of the list with tick >= x.  L0: the list's table at x's
-// bucket b.  Bounds: L0 <= count and LIST_PAD guards follow the list, so the
-// four entries read always exist; the guards (INT_MAX) stop every search.
-//   REL: the first entry after the event at ei[self], whose tick is x; only
-// entries of the same tick can come before it, so indices are read there
-// alone (the stream's indices are half of its lists' bytes).
-template <bool REL>
-__device__ __forceinline__ void find(const ChainIdx &ix, int start, int boff, int b, int L0,
-                                     bool on, int x, int self, Place &pl)
+// list[i] at a 32-bit byte offset (lists hold fewer than 2^30 entries)
+__device__ __forceinline__ int at(const int *list, int i)
 {
-    pl.L = L0;
-    pl.v = *(const v4i *)(ix.et + start + L0);
-    pl.k = (pl.v[0] < x) + (pl.v[1] < x) + (pl.v[2] < x) + (pl.v[3] < x);
-    const bool slow = on & (pl.k == 4);
-    if (__builtin_expect(bal(slow) != 0, 0)) {
-        // a crowded bucket: binary search in the rest of it
-        if (slow) {
-            int lo = L0 + 4, hi = ix.tab[boff + b + 1];
-            while (lo < hi) {
-                const int mid = (lo + hi) >> 1;
-                const bool before = ix.et[start + mid] < x;
-                lo = before ? mid + 1 : lo;
-                hi = before ? hi : mid;
-            }
-            pl.L = lo;
-            pl.k = 0;
-            pl.v = *(const v4i *)(ix.et + start + lo);
-        }
+    return *(const int *)((const char *)list + (size_t)((unsigned)i << 2));
+}
+__device__ __forceinline__ v4i at4(const int *list, int i)
+{
+    return *(const v4i *)((const char *)list + (size_t)((unsigned)i << 2));
+}
+
+// A hop (wave-uniform): from node k's list to the next node's.
+struct Hop {
+    const int *et, *ei;    // the next list
+    const int *tab;        // its bucket table
+    const int *own;        // stream indices of node k's list
+    int lo, hi, count, nb, sh, t0;
+};
+__device__ __forceinline__ Hop hop_of(const ChainIdx &ix, const NodeRow &row, int k)
+{
+    Hop h;
+    const int start = rdl(row.start, k + 1);
+    h.et = ix.et + start;
+    h.ei = ix.ei + start;
+    h.tab = ix.tab + rdl(row.boff, k + 1);
+    h.own = ix.ei + rdl(row.start, k);
+    h.lo = rdl(row.lo, k);
+    h.hi = rdl(row.hi, k);
+    h.count = rdl(row.count, k + 1);
+    h.nb = rdl(row.nb, k + 1);
+    h.sh = rdl(row.sh, k + 1);
+    h.t0 = row.t0;
+    return h;
+}
+// the tick a hop's events start at, and its place in the table
+template <bool REL> __device__ __forceinline__ int from_tick(const Hop &h, int t)
+{
+    return REL ? t : t + h.lo + 1;
+}
+template <bool REL> __device__ __forceinline__ int table_at(const Hop &h, int t)
+{
+    return at(h.tab, bucket(from_tick<REL>(h, t), h.t0, h.sh, h.nb));
+}
+
+// The events of the next list chained to an entry: positions [p, p + c).
+// Exact: ticks in (t + lo, min(t + hi, tn + lo)]; relaxed: events after the
+// entry's (own: its position), up to tick t + hi and up to the next entry's
+// event (tick tn, position next).  FIRST: the next entry is left out of it and
+// c only tells whether there is an event.  L: the table at the first tick's
+// bucket.
+//   Four entries from L on are read at once (L <= count, and LIST_PAD guards
+// of INT_MAX, which stop every search, follow a list); relaxed, indices are
+// only read where ticks are equal.  skip: events of lane 0's entry that have
+// been put out already.
+template <bool REL, bool FIRST>
+__device__ __forceinline__ void events_of(const Hop &h, bool on, int t, int tn, int own, int next,
+                                          int L, int skip, int &p, int &c)
+{
+    const int x = from_tick<REL>(h, t);
+    int lim = t + h.hi;
+    if constexpr (!FIRST) {
+        const int tl = REL ? tn : __builtin_elementwise_add_sat(tn, h.lo);
+        lim = tl < lim ? tl : lim;
     }
-    pl.k = pl.k < 4 ? pl.k : 3;  // (lanes off)
+    const v4i v = at4(h.et, L);
+    const int k = (v[0] < x) + (v[1] < x) + (v[2] < x) + (v[3] < x);
+    const int m = (v[0] <= lim) + (v[1] <= lim) + (v[2] <= lim) + (v[3] <= lim);
+    p = L + k;
+    c = m > k ? m - k : 0;
+    bool odd = v[3] < x;
+    if constexpr (!FIRST) odd |= v[3] <= lim;
     if constexpr (REL) {
-        const bool tie = on & (pl.tick() == x);
-        if (__builtin_expect(bal(tie) != 0, 0)) {
-            // (the entries of tick x end by the bucket's end)
-            if (tie) {
-                const int i = ix.ei[self];
-                int lo = pl.p(), hi = ix.tab[boff + b + 1];
-                while (lo < hi) {
-                    const int mid = (lo + hi) >> 1;
-                    const bool before = ix.ei[start + mid] <= i;
-                    lo = before ? mid + 1 : lo;
-                    hi = before ? hi : mid;
+        odd |= (v[0] == t) | (v[1] == t) | (v[2] == t) | (v[3] == t);
+        if constexpr (!FIRST) odd |= (v[0] == tn) | (v[1] == tn) | (v[2] == tn) | (v[3] == tn);
+    }
+    c = on ? c : 0;
+    odd &= on;
+    if (skip) odd |= __lane_id() == 0;
+    if (__builtin_expect(bal(odd) != 0, 0)) {
+        if (odd) {
+            const int end = at(h.tab, bucket(x, h.t0, h.sh, h.nb) + 1);  // the bucket's end
+            int q = p;
+            if (v[3] < x) {
+                int z = end;
+                while (q < z) {
+                    const int mid = (q + z) >> 1;
+                    const bool before = at(h.et, mid) < x;
+                    q = before ? mid + 1 : q;
+                    z = before ? z : mid;
                 }
-                pl.L = lo;
-                pl.k = 0;
-                pl.v = *(const v4i *)(ix.et + start + lo);
+            }
+            if constexpr (REL) {
+                if (at(h.et, q) == t) {
+                    // (the entries of tick t end by the bucket's end)
+                    const int i = at(h.own, own);
+                    int z = end;
+                    while (q < z) {
+                        const int mid = (q + z) >> 1;
+                        const bool before = at(h.ei, mid) <= i;
+                        q = before ? mid + 1 : q;
+                        z = before ? z : mid;
+                    }
+                }
+            }
+            if constexpr (FIRST) {
+                p = q;
+                c = at(h.et, q) <= lim ? 1 : 0;
+            } else {
+                // (those entries were in range: the place exists)
+                p = q = q + (__lane_id() == 0 ? skip : 0);
+                const int in = REL && tn != FAR_TICK ? at(h.own, next) : FAR_TICK;
+                auto in_range = [&](int e) {
+                    const int te = at(h.et, e);
+                    if constexpr (REL) return (te <= lim) & ((te != tn) || at(h.ei, e) <= in);
+                    else return te <= lim;
+                };
+                // (a guard ends every range; at most a batch is put out at once)
+                int step = 4;  // entries before q are in range
+                while (q + step <= h.count && q < p + WAVE && in_range(q + step - 1)) {
+                    q += step;
+                    step *= 2;
+                }
+                int z = q + step <= h.count ? q + step - 1 : h.count;  // z is not (or the end)
+                if (q >= p + WAVE) z = q;
+                while (q < z) {
+                    const int mid = (q + z) >> 1;
+                    const bool r = in_range(mid);
+                    q = r ? mid + 1 : q;
+                    z = r ? z : mid;
+                }
+                c = q - p < WAVE ? q - p : WAVE;
             }
         }
     }
 }
 
-// One wave's rings in LDS: ring q (1..) at base + (q-1)*ring_ints: ticks,
-// positions of the chains' first events in node 0's list and, where something
-// asks for it (the relaxed counter's ties, the siblings' masks), the entries'
-// positions in their own list.
-__host__ __device__ constexpr int ring_ints(bool third) { return QCAP * (third ? 3 : 2); }
+// One wave's rings in LDS: ring q's entries as their positions in node q's
+// list and their chains' first positions in the source.
+constexpr int RING_INTS = 2 * QCAP;
 
-// Entries of node 1, kept in memory for every pair (mining): their ticks,
-// chains' first positions and own positions.
+// Entries of node 1, kept in memory for every pair (mining): their ticks
+// (FAR_TICK behind the last), chains' first positions and own positions.
 struct Seeds {
     const int *t, *a, *p;
 };
@@ -151,165 +226,60 @@ struct Seeds {
 // Entries of node E, in order, from the source [a, aend): node 0's events of
 // the row's first list (aend is either the list's end or past every tick that
 // an entry wanted from [a, ...) can reach), or, SEED, all of a pair's entries
-// of node 1.  sink(n, on, t, apos, own, first, L0): the next n <= 64 entries,
-// one per lane (on): tick, position of the chain's first event in node 0's
-// list, own position (POS); first: straight from the source, L0 then being
-// the next list's table at their buckets.
-template <bool REL, bool POS, bool SEED, class Sink>
+// of node 1.  sink(n, on, t, src, own, L): the next n <= 64 entries, one per
+// lane (on; the other lanes' values are in range too): tick, position of the
+// chain's first event in the source, own position; L: straight from the
+// source, the sink's list's table at their buckets, else -1.
+template <bool REL, bool SEED, class Sink>
 __device__ __forceinline__ void walk(const ChainIdx &ix, const NodeRow &row, int E, int a,
                                      int aend, int *lds, Sink &sink, const Seeds &seed = Seeds())
 {
-    static_assert(POS || !REL, "the relaxed counter's ties need the positions");
+    static_assert(!SEED || !REL, "pairs' entries are kept for the exact counter");
     constexpr int S = SEED ? 1 : 0;  // the source's node
+    if (a >= aend) return;
     const int lane = __lane_id();
-    const int start0 = rdl(row.start, 0);
-    auto ring = [&](int q) { return lds + (q - 1 - S) * ring_ints(POS); };
+    const int *src_t = SEED ? seed.t : ix.et + rdl(row.start, 0);
+    auto place = [&](int from) { return from + lane < aend ? from + lane : aend - 1; };
+    if (E == S) {
+        const Hop h = hop_of(ix, row, S);
+        int t = at(src_t, place(a)), L = Sink::SEARCHES ? table_at<REL>(h, t) : 0;
+        for (;;) {
+            const int pos = place(a), n = aend - a < WAVE ? aend - a : WAVE;
+            const int t_now = t, L_now = L;
+            if (a + WAVE < aend) t = at(src_t, place(a + WAVE));
+            sink(n, lane < n, t_now, pos, SEED ? at(seed.p, pos) : pos, L_now);
+            a += WAVE;
+            if (a >= aend) return;
+            if (Sink::SEARCHES) L = table_at<REL>(h, t);
+        }
+    }
     // lane q: ring q's first slot, its entries, and how many events of its
     // first entry's range have been put out already (an entry with more than
-    // a batch's worth is put out in parts)
+    // a batch's worth is put out in parts); ring S+1's in scalars
     int qh = 0, qn = 0, sk = 0;
-    // the next batch of node 0's events, loaded while this one is worked on
-    int pa = -1, pt = 0, ptn = 0, pL = 0;
-    const int x0 = REL ? 0 : rdl(row.lo, S) + 1;
-    const int boff1 = rdl(row.boff, S + 1), nb1 = rdl(row.nb, S + 1), sh1 = rdl(row.sh, S + 1);
-    auto load_t = [&](int at) {
-        const int pos = at + lane < aend ? at + lane : aend - 1;
-        if constexpr (SEED) {
-            pt = seed.t[pos];
-            ptn = pos + 1 < aend ? seed.t[pos + 1] : FAR_TICK;
+    int h1 = 0, n1 = 0, sk0 = 0;
+    auto ring = [&](int q) { return lds + (q - 1 - S) * RING_INTS; };
+    // c events from p on of each lane's entry to the ring at slot `tail`, in
+    // entry order; n: entries given, nc: taken whole, tot: events put out,
+    // part: events of the next entry put out in total
+    auto put = [&](int *q, int tail, int n, int p, int c, int src, int skip, int &nc, int &tot,
+                   int &part) {
+        nc = n;
+        part = 0;
+        int excl;
+        const unsigned long long one = bal(c == 1), many = bal(c > 1);
+        if (many == 0) {
+            excl = below(one);
+            tot = __builtin_popcountll(one);
+        } else if (bal(c > 3) == 0) {
+            const unsigned long long b0 = bal((c & 1) != 0), b1 = bal((c & 2) != 0);
+            excl = below(b0) + 2 * below(b1);
+            tot = __builtin_popcountll(b0) + 2 * __builtin_popcountll(b1);
         } else {
-            pt = ix.et[start0 + pos];
-            ptn = ix.et[start0 + pos + 1];
+            excl = 0;
+            tot = WAVE + 1;
         }
-    };
-    auto load_L = [&] { pL = ix.tab[boff1 + bucket(pt + x0, row.t0, sh1, nb1)]; };
-    for (;;) {
-        int k;
-        bool flush = false;
-        const unsigned long long ready = bal(qn >= (lane == E ? WAVE : WAVE + 1));
-        if (ready) {
-            k = 63 - __builtin_clzll(ready);
-        } else if (a < aend) {
-            k = S;
-        } else {
-            const unsigned long long some = bal(qn > 0);
-            if (!some) break;
-            // (every stage before it is done: its entries are the last ones)
-            k = (int)__builtin_ctzll(some);
-            flush = true;
-        }
-        int t, tn = FAR_TICK, apos, own = 0, next = 0, n, L0 = 0;
-        if (k == S) {
-            n = aend - a < WAVE ? aend - a : WAVE;
-            if (pa != a) {
-                load_t(a);
-                if (!SEED || E > S) load_L();
-            }
-            t = pt;
-            tn = ptn;
-            L0 = pL;
-            apos = a + lane < aend ? a + lane : aend - 1;
-            if constexpr (SEED) {
-                if (E == S) own = seed.p[apos];
-                apos = seed.a[apos];
-            } else {
-                own = apos;
-                next = apos + 1;
-            }
-            pa = a + WAVE;
-            if (pa < aend) load_t(pa);
-        } else {
-            const int h = rdl(qh, k), c = rdl(qn, k);
-            const int *q = ring(k);
-            n = (flush || k == E) ? c : c - 1;
-            n = n < WAVE ? n : WAVE;
-            const int s0 = (h + lane) & (QCAP - 1), s1 = (h + lane + 1) & (QCAP - 1);
-            t = q[s0];
-            apos = q[QCAP + s0];
-            if (lane + 1 < c) tn = q[s1];
-            if constexpr (POS) own = q[2 * QCAP + s0];
-            if constexpr (REL) next = q[2 * QCAP + s1];
-        }
-        bool on = lane < n;
-        if (k == E) {
-            sink(n, on, t, apos, own, k == S, L0);
-            if (k == S) {
-                a += n;
-            } else {
-                qh = lane == k ? (qh + n) & (QCAP - 1) : qh;
-                qn = lane == k ? qn - n : qn;
-            }
-            if (!SEED && k == S && pa < aend) load_L();
-            continue;
-        }
-        const int lo = rdl(row.lo, k), hi = rdl(row.hi, k);
-        const int start = rdl(row.start, k + 1), boff = rdl(row.boff, k + 1);
-        t = on ? t : row.t0;
-        const int x = REL ? t : t + lo + 1;
-        int lim = t + hi;
-        const int tl = REL || tn == FAR_TICK ? tn : tn + lo;
-        lim = tl < lim ? tl : lim;
-        const int b = bucket(x, row.t0, rdl(row.sh, k + 1), rdl(row.nb, k + 1));
-        if (k != S) L0 = ix.tab[boff + b];
-        else if (!on) L0 = 0;
-        Place pl;
-        find<REL>(ix, start, boff, b, L0, on, x, rdl(row.start, k) + own, pl);
-        const int skip = rdl(sk, k);
-        if (__builtin_expect(skip != 0, 0)) {
-            if (lane == 0) {
-                // (those entries were in range: the place exists)
-                pl.L = pl.p() + skip;
-                pl.k = 0;
-                pl.v = *(const v4i *)(ix.et + start + pl.L);
-            }
-        }
-        // events of the range among the four at hand; more: the last is one,
-        // or (relaxed) one shares the next entry's tick and is in this range
-        // only if it comes before that entry's event
-        int c = 0;
-        bool tie = false;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            c += ((j >= pl.k) & (pl.v[j] <= lim)) ? 1 : 0;
-            if constexpr (REL) tie |= (j >= pl.k) & (pl.v[j] == tn) & (pl.v[j] <= lim);
-        }
-        const bool more = on & ((pl.v[3] <= lim) | tie);
-        c = on ? c : 0;
-        if (__builtin_expect(bal(more) != 0, 0)) {
-            if (more) {
-                // (a guard ends every range; at most a batch is put out at once)
-                const int in = REL && tn != FAR_TICK ? ix.ei[rdl(row.start, k) + next] : FAR_TICK;
-                auto in_range = [&](int p) {
-                    const int te = ix.et[start + p];
-                    if constexpr (REL)
-                        return (te <= lim) & ((te != tn) || ix.ei[start + p] <= in);
-                    else return te <= lim;
-                };
-                const int cnt = rdl(row.count, k + 1), top = pl.p() + WAVE;
-                int e = pl.p(), step = 4;  // entries before e are in range
-                while (e + step <= cnt && e < top && in_range(e + step - 1)) {
-                    e += step;
-                    step *= 2;
-                }
-                int f = e + step <= cnt ? e + step - 1 : cnt;  // entry f is not (or the end)
-                if (e >= top) f = e;
-                while (e < f) {
-                    const int mid = (e + f) >> 1;
-                    const bool r = in_range(mid);
-                    e = r ? mid + 1 : e;
-                    f = r ? f : mid;
-                }
-                c = e - pl.p();
-                c = c < WAVE ? c : WAVE;
-            }
-        }
-        // the events go to ring k+1 in entry order
-        int excl, tot, nc = n, put_skip = 0;
-        if (bal(c > 1) == 0) {
-            const unsigned long long m = bal(c != 0);
-            excl = below(m);
-            tot = __builtin_popcountll(m);
-        } else {
+        if (__builtin_expect(tot > WAVE, 0)) {
             int inc = c;
 #pragma unroll
             for (int off = 1; off < WAVE; off <<= 1) {
@@ -317,51 +287,123 @@ __device__ __forceinline__ void walk(const ChainIdx &ix, const NodeRow &row, int
                 inc += lane >= off ? y : 0;
             }
             excl = inc - c;
+            tot = rdl(inc, WAVE - 1);
             // entries taken whole: the first ones whose events fit a batch
-            const unsigned long long cut = bal(on & ((inc > WAVE) | (c >= WAVE)));
+            const unsigned long long cut = bal((inc > WAVE) | (c >= WAVE));
             if (cut) {
                 nc = (int)__builtin_ctzll(cut);
                 if (nc == 0) {
                     // (the first alone fills it: its next WAVE events, and on)
-                    put_skip = skip + WAVE;
+                    part = skip + WAVE;
                     tot = WAVE;
                     c = lane == 0 ? WAVE : 0;
                 } else {
                     tot = rdl(inc, nc - 1);
                     c = lane < nc ? c : 0;
                 }
-            } else {
-                tot = rdl(inc, WAVE - 1);
             }
         }
-        if (tot) {
-            int *q = ring(k + 1);
-            const int tail = rdl(qh, k + 1) + rdl(qn, k + 1) + excl;
-            if (c > 0) {
-                const int s0 = tail & (QCAP - 1);
-                q[s0] = pl.tick();
-                q[QCAP + s0] = apos;
-                if constexpr (POS) q[2 * QCAP + s0] = pl.p();
-            }
+        if (tot == 0) return;
+        tail += excl;
+        if (c > 0) {
+            const int s = tail & (QCAP - 1);
+            q[s] = p;
+            q[QCAP + s] = src;
+        }
+        if (many)
             for (int j = 1; bal(c > j) != 0; ++j) {
                 if (c > j) {
-                    const int s0 = (tail + j) & (QCAP - 1);
-                    q[s0] = ix.et[start + pl.p() + j];
-                    q[QCAP + s0] = apos;
-                    if constexpr (POS) q[2 * QCAP + s0] = pl.p() + j;
+                    const int s = (tail + j) & (QCAP - 1);
+                    q[s] = p + j;
+                    q[QCAP + s] = src;
                 }
             }
+        __builtin_amdgcn_wave_barrier();
+    };
+    // a batch of ring k's entries (flush: no more will come)
+    auto deeper = [&](int k, bool flush) {
+        const int *q = ring(k);
+        const int hk = k == S + 1 ? h1 : rdl(qh, k), ck = k == S + 1 ? n1 : rdl(qn, k);
+        int n = (flush || k == E) ? ck : ck - 1;
+        n = n < WAVE ? n : WAVE;
+        const int i0 = lane < ck ? lane : ck - 1, i1 = lane + 1 < ck ? lane + 1 : ck - 1;
+        const int s0 = (hk + i0) & (QCAP - 1), s1 = (hk + i1) & (QCAP - 1);
+        const int own = q[s0], src = q[QCAP + s0];
+        const int *list = ix.et + rdl(row.start, k);
+        const int t = at(list, own);
+        const bool on = lane < n;
+        int nc = n;
+        if (k == E) {
+            sink(n, on, t, src, own, -1);
+        } else {
+            const Hop h = hop_of(ix, row, k);
+            const int next = q[s1];
+            const int tn = lane + 1 < ck ? at(list, next) : FAR_TICK;
+            const int skip = rdl(sk, k);
+            int p, c, tot, part;
+            events_of<REL, false>(h, on, t, tn, own, next, table_at<REL>(h, t), skip, p, c);
+            put(ring(k + 1), rdl(qh, k + 1) + rdl(qn, k + 1), n, p, c, src, skip, nc, tot, part);
             qn = lane == k + 1 ? qn + tot : qn;
-            __builtin_amdgcn_wave_barrier();
+            sk = lane == k ? part : sk;
         }
-        sk = lane == k ? put_skip : sk;
-        if (k == S) {
-            a += nc;
+        if (k == S + 1) {
+            h1 = (h1 + nc) & (QCAP - 1);
+            n1 -= nc;
         } else {
             qh = lane == k ? (qh + nc) & (QCAP - 1) : qh;
             qn = lane == k ? qn - nc : qn;
         }
-        if (k == S && pa < aend) load_L();
+    };
+    // full batches, the deepest first
+    const int full1 = E == S + 1 ? WAVE : WAVE + 1;
+    auto drain = [&] {
+        for (;;) {
+            const unsigned long long ready = bal(qn >= (lane == E ? WAVE : WAVE + 1));
+            if (ready) deeper(63 - __builtin_clzll(ready), false);
+            else if (n1 >= full1) deeper(S + 1, false);
+            else break;
+        }
+    };
+    {
+        const Hop h = hop_of(ix, row, S);
+        int *q = ring(S + 1);
+        // (the next batch is read while this one is worked on)
+        int t = at(src_t, place(a)), tn = at(src_t, place(a) + 1);
+        int L = table_at<REL>(h, t);
+        for (;;) {
+            const int pos = place(a), n = aend - a < WAVE ? aend - a : WAVE;
+            const int t_now = t, tn_now = tn, a_next = a + WAVE;
+            if (a_next < aend) {
+                const int np = place(a_next);
+                t = at(src_t, np);
+                tn = at(src_t, np + 1);
+            }
+            int p, c, nc, tot, part;
+            events_of<REL, false>(h, lane < n, t_now, tn_now, pos, pos + 1, L, sk0, p, c);
+            put(q, h1 + n1, n, p, c, pos, sk0, nc, tot, part);
+            n1 += tot;
+            sk0 = part;
+            a += nc;
+            if (n1 >= full1) drain();
+            if (a >= aend) break;
+            if (__builtin_expect(a != a_next, 0)) {
+                t = at(src_t, place(a));
+                tn = at(src_t, place(a) + 1);
+            }
+            L = table_at<REL>(h, t);
+        }
+    }
+    // what is left, from the source on (a stage's entries are its last when
+    // every stage before it is done)
+    for (;;) {
+        drain();
+        if (n1 > 0) {
+            deeper(S + 1, true);
+        } else {
+            const unsigned long long some = bal(qn > 0);
+            if (!some) break;
+            deeper((int)__builtin_ctzll(some), true);
+        }
     }
 }
 
