@@ -121,38 +121,56 @@ void launch_chains(const ChainJob *jobs, const int64_t *first, int njobs, int64_
 // *out = the number of v[0..M) that are at least theta.
 void launch_count_ge(const int *v, int M, int theta, int *out, const int *status, hipStream_t s);
 
-// ---- mining: join siblings (the candidates one frequent episode is joined
-// into differ in their last node and hop alone)
+// ---- mining: every candidate is a frequent episode and one more node and
+// hop (a join sibling), and every entry of its last shared node is met with
+// all types at once
 
-// 32-bit words of a mask over T types
-constexpr int mask_words(int T) { return (T + 31) / 32; }
+// 64-bit words of a place's masks: 64 types and a hop each
+constexpr int mask_words(int T, int n_iv) { return (T + 63) / 64 * n_iv; }
 
+// Node 1's entries of every pair (a pair's share: (first type's rank * n_iv +
+// hop) * stride + the second type's place in the lists; see Seeds).
+struct PairLists {
+    int *t, *a, *p;
+    int *n;  // [pairs] entries
+    int64_t stride;
+};
+
+// Level 2: the entries and the counts of every pair of frequent types.
+struct PairJob {
+    ChainIdx ix;
+    const int *F1;  // [nF] frequent types
+    int nF;
+    const int *ivlo, *ivhi;  // the interval set (device)
+    int n_iv;
+    PairLists sd;
+    int *out;          // counts in the level's order, (a * nF + b) * n_iv + k; may be null
+    const int *upper;  // set: -1 for candidates with upper < theta
+    int theta;
+};
+
+// Level m + 1 from its frequent episodes of m >= 2 nodes.
 struct SibJob {
     ChainIdx ix;
     const int *F;                // frequent episodes' keys, sorted, w ints each
     int w, m;                    // m nodes
     const int64_t *first, *off;  // episode a's siblings end like F[first[a] + c]; outputs off[a] + c
-    int *out;                    // exact counts
-    // masks[h][list entry][word]: types with an event in hop h's window
-    const unsigned *mask;
-    int64_t hop;  // words of one hop's masks
-    int words;
+    int *out;                    // counts
+    const int *upper;            // set: -1 for candidates with upper < theta
+    int theta;
+    const uint2 *mask;  // [place][Q]
+    int Q;
     const int *ivlo, *ivhi;  // the interval set (device)
     int n_iv;
-    // node 1's entries of every pair: (first type's rank * n_iv + hop) *
-    // sd_stride + the second type's place in the lists; sd_n: their numbers
-    const int *sd_t, *sd_a, *sd_p, *sd_n;
-    int64_t sd_stride;
+    PairLists sd;
     const int *rank;  // [num_types] rank among the frequent types
     int nF;
 };
 
-void launch_masks(const IndexPlan &p, const int *base, const int *ivlo, const int *ivhi, int n_iv,
-                  unsigned *mask, hipStream_t s);
-void launch_seeds(const ChainIdx &ix, const int *F1, int nF, const int *ivlo, const int *ivhi,
-                  int n_iv, int *sd_t, int *sd_a, int *sd_p, int *sd_n, int64_t stride,
-                  hipStream_t s);
-// cnt episodes, `longest` siblings at most.
-void launch_siblings(const SibJob &j, int64_t cnt, int64_t longest, hipStream_t s);
+void launch_masks(bool rel, const IndexPlan &p, const int *base, const int *ivlo, const int *ivhi,
+                  int n_iv, uint2 *mask, hipStream_t s);
+void launch_pairs(bool rel, const PairJob &j, hipStream_t s);
+// cnt episodes.
+void launch_siblings(bool rel, const SibJob &j, int64_t cnt, hipStream_t s);
 
 }  // namespace fe

@@ -760,75 +760,85 @@ void launch_chains(const ChainJob *jobs, const int64_t *first, int njobs, int64_
 // ------------------------------------------------------------------ siblings
 namespace {
 
-// mask[h][place][word]: bit (type & 31) of word (type >> 5) is set where an
-// event of the type lies in (t + lo_h, t + hi_h], t the tick at the place (an
-// entry of the lists).  One thread per word; its types' lists are searched at
-// ticks that ascend along a wave, so the reads are nearly coalesced.
-__global__ __launch_bounds__(256) void k_masks(ChainIdx ix, const int *__restrict__ et, int places,
-                                               int T, int words, const int *__restrict__ ivlo,
+// mask[place][q], q = (type >> 6) * n_iv + h: bit (type & 63) is set where the
+// type has an event in hop h's range after the event at the place (an entry of
+// the lists): exact, ticks in (t + lo, t + hi]; relaxed, later events up to
+// tick t + hi.  One thread per 32 types of a place and hop; the types' lists
+// are searched at ticks that ascend along a wave, so the reads are nearly
+// coalesced.
+template <bool REL>
+__global__ __launch_bounds__(256) void k_masks(ChainIdx ix, int places, int T, int n_iv,
+                                               const int *__restrict__ ivlo,
                                                const int *__restrict__ ivhi,
-                                               unsigned *__restrict__ mask, int64_t hop)
+                                               unsigned *__restrict__ mask, int Q)
 {
     const int place = blockIdx.x * 256 + threadIdx.x;
-    const int w = blockIdx.y % words, h = blockIdx.y / words;
+    const int h = blockIdx.y % n_iv, w = blockIdx.y / n_iv;  // types 32 w ...
     if (place >= places) return;
-    const int t = et[place];
+    const int t = ix.et[place];
     if (t == FAR_TICK) return;  // a guard
-    const int x = t + ivlo[h] + 1, lim = t + ivhi[h];
+    const int x = REL ? t : t + ivlo[h] + 1, lim = t + ivhi[h];
+    const int i = REL ? ix.ei[place] : 0;
     unsigned bits = 0;
     const int e1 = (w + 1) * 32 < T ? (w + 1) * 32 : T;
     for (int e = w * 32; e < e1; ++e) {
         const TypeIdx ty = ix.ty[e];
         const int b = bucket(x, ty.t0, ty.sh, ty.nb);
-        int lo = ix.tab[ty.boff + b];
-        const int hi = ix.tab[ty.boff + b + 1];
-        int v = ix.et[ty.start + lo];
-        if (v < x) {
-            int a = lo + 1, z = hi;
+        int a = ix.tab[ty.boff + b];
+        const int *et = ix.et + ty.start, *ei = ix.ei + ty.start;
+        auto before = [&](int p) { return REL ? at(ei, p) <= i : at(et, p) < x; };
+        if (before(a)) {
+            int z = ix.tab[ty.boff + b + 1];
+            ++a;
             while (a < z) {
                 const int mid = (a + z) >> 1;
-                const bool before = ix.et[ty.start + mid] < x;
-                a = before ? mid + 1 : a;
-                z = before ? z : mid;
+                const bool l = before(mid);
+                a = l ? mid + 1 : a;
+                z = l ? z : mid;
             }
-            v = ix.et[ty.start + a];
         }
-        bits |= v <= lim ? 1u << (e & 31) : 0u;
+        bits |= at(et, a) <= lim ? 1u << (e & 31) : 0u;
     }
-    mask[h * hop + (int64_t)place * words + w] = bits;
+    mask[((int64_t)place * Q + (w >> 1) * n_iv + h) * 2 + (w & 1)] = bits;
 }
 
-// The entries of node 1 of every pair of frequent types and interval, in
-// the place of the second type's list within the pair's share.
-struct SeedOut {
+// The entries of node 1 of every pair of frequent types and interval, in the
+// place of the second type's list within the pair's share; and the pair's
+// count: each entry is a completion of the chain that starts at its first
+// event (a chain's later ones start no later than the one taken).
+template <bool REL> struct SeedOut {
+    const ChainIdx &ix;
+    const NodeRow &row;
+    Count<REL, false> cnt;
     int *t, *a, *p;
     int64_t base;
     int n = 0;
     static constexpr bool SEARCHES = false;
     __device__ __forceinline__ void operator()(int c, bool on, int tk, int src, int own, int)
     {
+        const int s = on ? at(ix.ei + rdl(row.start, 0), src) : FAR_TICK;
+        const int i = on ? at(ix.ei + rdl(row.start, 1), own) : FAR_TICK;
         if (on) {
-            const int64_t at = base + n + __lane_id();
-            t[at] = tk;
-            a[at] = src;
-            p[at] = own;
+            const int64_t to = base + n + __lane_id();
+            t[to] = tk;
+            a[to] = src;
+            p[to] = own;
         }
+        cnt.choose(bal(on), s, i, cnt.r, cnt.cnt);
         n += c;
     }
 };
 
-__global__ __launch_bounds__(WAVE) void k_seeds(ChainIdx ix, const int *__restrict__ F1, int nF,
-                                                const int *__restrict__ ivlo,
-                                                const int *__restrict__ ivhi, int n_iv, int *sd_t,
-                                                int *sd_a, int *sd_p, int *sd_n, int64_t stride)
+template <bool REL>
+__global__ __launch_bounds__(WAVE) void k_pairs(PairJob j)
 {
     extern __shared__ int lds[];
     const int64_t item = grid_item();
-    if (item >= (int64_t)nF * nF * n_iv) return;
+    if (item >= (int64_t)j.nF * j.nF * j.n_iv) return;
     const int lane = __lane_id();
-    const int b = (int)(item % nF), ak = (int)(item / nF);  // ak = first type's rank * n_iv + k
-    const int k = ak % n_iv;
-    const TypeIdx ty = ix.ty[lane == 1 ? F1[b] : F1[ak / n_iv]];
+    // ak = first type's rank * n_iv + k
+    const int b = (int)(item % j.nF), ak = (int)(item / j.nF), k = ak % j.n_iv, f = ak / j.n_iv;
+    const TypeIdx ty = j.ix.ty[lane == 1 ? j.F1[b] : j.F1[f]];
     NodeRow row;
     row.start = ty.start;
     row.count = ty.count;
@@ -836,162 +846,188 @@ __global__ __launch_bounds__(WAVE) void k_seeds(ChainIdx ix, const int *__restri
     row.nb = ty.nb;
     row.sh = ty.sh;
     row.t0 = __builtin_amdgcn_readfirstlane(ty.t0);
-    row.lo = lane == 0 ? ivlo[k] : 0;
-    row.hi = lane == 0 ? ivhi[k] : 0;
-    SeedOut out{sd_t, sd_a, sd_p, ak * stride + rdl(ty.start, 1)};
-    walk<false, false>(ix, row, 1, 0, rdl(row.count, 0), lds, out);
+    row.lo = lane == 0 ? j.ivlo[k] : 0;
+    row.hi = lane == 0 ? j.ivhi[k] : 0;
+    SeedOut<REL> out{j.ix, row, Count<REL, false>(j.ix, row, 2, 0, nullptr, -1), j.sd.t, j.sd.a,
+                     j.sd.p, (int64_t)ak * j.sd.stride + rdl(ty.start, 1)};
+    walk<REL, false>(j.ix, row, 1, 0, rdl(row.count, 0), lds, out);
     if (lane == 0) {
-        sd_t[out.base + out.n] = FAR_TICK;  // (a list has its guards' room)
-        sd_n[item] = out.n;
+        j.sd.t[out.base + out.n] = FAR_TICK;  // (a list has its guards' room)
+        j.sd.n[item] = out.n;
+        const int64_t c = ((int64_t)f * j.nF + b) * j.n_iv + k;  // in the level's order
+        if (j.out) j.out[c] = j.upper && j.upper[c] < j.theta ? -1 : out.cnt.cnt;
     }
 }
 
-constexpr int SIB = 2;  // siblings a lane counts
+// ---- 64 x 64 bits across a wave
+// Lane i holds row i (bit j of the 64: column j); afterwards lane j holds
+// column j (bit i: row i).  Halves are swapped between lanes 32 apart, then
+// inside each 32-bit word 16-, 8-, 4-, 2- and 1-bit blocks between lanes as far
+// apart.
+struct Flip {
+    unsigned s16, s8, r4, m4, r2, m2, r1, m1;
+    __device__ __forceinline__ Flip()
+    {
+        const unsigned l = __lane_id();
+        s16 = l & 16 ? 0x07060302u : 0x05040100u;
+        s8 = l & 8 ? 0x03070105u : 0x06020400u;
+        r4 = l & 4 ? 4 : 28;
+        m4 = l & 4 ? 0xf0f0f0f0u : 0x0f0f0f0fu;
+        r2 = l & 2 ? 2 : 30;
+        m2 = l & 2 ? 0xccccccccu : 0x33333333u;
+        r1 = l & 1 ? 1 : 31;
+        m1 = l & 1 ? 0xaaaaaaaau : 0x55555555u;
+    }
+    template <int CTRL> static __device__ __forceinline__ unsigned dpp(unsigned v)
+    {
+        return (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xf, 0xf, true);
+    }
+    static __device__ __forceinline__ unsigned mix(unsigned own, unsigned other, unsigned rot,
+                                                   unsigned mask)
+    {
+        return (own & mask) | (__builtin_amdgcn_alignbit(other, other, rot) & ~mask);
+    }
+    __device__ __forceinline__ unsigned word(unsigned w) const
+    {
+        const auto r = __builtin_amdgcn_permlane16_swap(w, w, false, false);
+        w = __builtin_amdgcn_perm(r[1], r[0], s16);
+        w = __builtin_amdgcn_perm(dpp<0x128>(w), w, s8);        // lane ^ 8 (row_ror:8)
+        w = mix(w, dpp<0x1b>(dpp<0x141>(w)), r4, m4);           // lane ^ 4 (mirrors of 8, of 4)
+        w = mix(w, dpp<0x4e>(w), r2, m2);                       // lane ^ 2 (quad_perm)
+        return mix(w, dpp<0xb1>(w), r1, m1);                    // lane ^ 1
+    }
+    __device__ __forceinline__ void operator()(unsigned &lo, unsigned &hi) const
+    {
+        const auto r = __builtin_amdgcn_permlane32_swap(lo, hi, false, false);
+        lo = word(r[0]);
+        hi = word(r[1]);
+    }
+};
 
-// Join siblings: one frequent episode's entries (t, s) against each lane's
-// own last node and hop.  A lane counts an entry when its last type has an
-// event in the window (t + lo, t + hi] (a bit of the masks) and the chain
-// starts after the lane's last completion.  That completion is the first such
-// event of an earlier entry's window: later than its t + lo, at most its
-// t + hi = rb.  So a chain that starts after tick rb is free and one that
-// starts by t + lo = rb - len is not; in between the event is looked up.
-template <int G> struct Siblings {
+constexpr int QW = 4;  // mask words (64 types and a hop each) a wave counts
+
+// Join siblings: one frequent episode's entries against 64 types at a time
+// and a hop.  Of 64 entries, one per lane, the mask words (bit = type) are
+// transposed, so that a lane holds, for its type, which entries have an event
+// of it in range (bit = entry).  All of them are counted, but for those whose
+// chain may start by the lane's last completion: an entry is looked at where
+// its chain starts within the hop's width of the entry before it.  The last
+// completion is the first event in range of the last entry counted (tick tl),
+// so after tl + lo (relaxed: not before tl) and by tl + hi; in between the
+// event is looked up.
+template <bool REL> struct Columns {
     const SibJob &j;
     const ChainIdx &ix;
-    const unsigned *base;  // masks of the last shared node's list
-    int start0;            // node 0's list
-    int type[G], lo[G], hi[G], cnt[G], rb[G];
-    unsigned off[G], bit[G];
-    int hm = 0;           // widest hi
-    int mb = -1;          // no lane's rb is larger
+    int q0, nq;                      // the words of this wave
+    int start0, start_m;             // node 0's and the last shared node's lists
+    const int *seed_a;               // the source's positions in node 0's list
+    Flip flip;
+    int lo[QW], hi[QW];              // the words' hops (wave-uniform)
+    int cnt[QW], tl[QW], ol[QW];     // per type: completions, the last entry counted
+    int t_last = -(1 << 30);
     static constexpr bool SEARCHES = false;
-    const int *seed_a;  // the source's positions in node 0's list
-    __device__ __forceinline__ void operator()(int n, bool, int t, int src, int own, int)
+    __device__ __forceinline__ void operator()(int n, bool on, int t, int src, int own, int)
     {
+        const int lane = __lane_id();
         const int apos = at(seed_a, src);
         const int st = ix.et[start0 + apos];
-        constexpr int U = 8;
-        for (int e0 = 0; e0 < n; e0 += U) {
-            unsigned w[U][G];
+        int tp = __shfl_up(t, 1);
+        tp = lane == 0 ? t_last : tp;
+        t_last = rdl(t, n - 1);
+        const uint2 *row = j.mask + (int64_t)(start_m + own) * j.Q + q0;
+        uint2 w[QW];
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const unsigned *m = base + (int64_t)rdl(own, e0 + u) * j.words;
+        for (int q = 0; q < QW; ++q) w[q] = on && q < nq ? row[q] : make_uint2(0, 0);
 #pragma unroll
-                for (int g = 0; g < G; ++g) w[u][g] = m[off[g]];
+        for (int q = 0; q < QW; ++q) {
+            if (q >= nq) break;
+            unsigned c0 = w[q].x, c1 = w[q].y;
+            flip(c0, c1);
+            unsigned long long near = bal(on & (st <= tp + hi[q]));
+            while (near) {
+                const int e = (int)__builtin_ctzll(near);
+                near &= near - 1;
+                const bool has = ((e < 32 ? c0 : c1) >> (e & 31)) & 1u;
+                if (bal(has) == 0) continue;
+                const unsigned long long lower = (1ull << e) - 1ull;
+                const unsigned b0 = c0 & (unsigned)lower, b1 = c1 & (unsigned)(lower >> 32);
+                const int before = b1 ? 63 - __builtin_clz(b1) : b0 ? 31 - __builtin_clz(b0) : -1;
+                const int tb = __shfl(t, before >= 0 ? before : 0);
+                const int tj = before >= 0 ? tb : tl[q];
+                const int te = rdl(st, e);
+                bool cut = has & (te <= tj + hi[q]);
+                const bool open = cut & (REL ? te >= tj : te > tj + lo[q]);
+                if (bal(open) != 0) {
+                    const int s = ix.ei[start0 + rdl(apos, e)];
+                    const int ob = __shfl(own, before >= 0 ? before : 0);
+                    const int oj = before >= 0 ? ob : ol[q];
+                    if (open) cut = s <= completed(q, tj, oj);
+                }
+                const unsigned bit = cut ? 1u << (e & 31) : 0u;
+                if (e < 32) c0 &= ~bit;
+                else c1 &= ~bit;
             }
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                if (e0 + u >= n) break;
-                const int te = rdl(t, e0 + u), se = rdl(st, e0 + u);
-                bool take[G];
-#pragma unroll
-                for (int g = 0; g < G; ++g) take[g] = (w[u][g] & bit[g]) != 0;
-                if (se <= mb) {
-#pragma unroll
-                    for (int g = 0; g < G; ++g) {
-                        bool fr = se > rb[g];
-                        const bool open = take[g] & !fr & (se > rb[g] - (hi[g] - lo[g]));
-                        if (bal(open) != 0) {
-                            const int s = ix.ei[start0 + rdl(apos, e0 + u)];
-                            if (open) fr = s > completed(g);
-                        }
-                        take[g] &= fr;
-                    }
-                }
-                bool any = false;
-#pragma unroll
-                for (int g = 0; g < G; ++g) {
-                    cnt[g] += take[g] ? 1 : 0;
-                    rb[g] = take[g] ? te + hi[g] : rb[g];
-                    any |= take[g];
-                }
-                if (bal(any) != 0) mb = te + hm;
+            cnt[q] += __builtin_popcount(c0) + __builtin_popcount(c1);
+            const int last = c1 ? 63 - __builtin_clz(c1) : c0 ? 31 - __builtin_clz(c0) : -1;
+            const int tv = __shfl(t, last >= 0 ? last : 0);
+            tl[q] = last >= 0 ? tv : tl[q];
+            if constexpr (REL) {
+                const int ov = __shfl(own, last >= 0 ? last : 0);
+                ol[q] = last >= 0 ? ov : ol[q];
             }
         }
     }
-    // index of the lane's last completion: the first event of its last type
-    // after tick rb - (hi - lo)
-    __device__ __forceinline__ int completed(int g) const
+    // index of the completion of the entry at tick tj (relaxed: at place oj)
+    // by the lane's type of word q: its first event in range
+    __device__ __forceinline__ int completed(int q, int tj, int oj) const
     {
-        const TypeIdx ty = ix.ty[type[g]];
-        const int x = rb[g] - (hi[g] - lo[g]) + 1;
+        const TypeIdx ty = ix.ty[(q0 + q) / j.n_iv * 64 + __lane_id()];
+        const int x = REL ? tj : tj + lo[q] + 1;
+        const int i = REL ? ix.ei[start_m + oj] : 0;
+        const int *et = ix.et + ty.start, *ei = ix.ei + ty.start;
         const int b = bucket(x, ty.t0, ty.sh, ty.nb);
         int a = ix.tab[ty.boff + b], z = ix.tab[ty.boff + b + 1];
         while (a < z) {
             const int mid = (a + z) >> 1;
-            const bool before = ix.et[ty.start + mid] < x;
+            const bool before = REL ? at(ei, mid) <= i : at(et, mid) < x;
             a = before ? mid + 1 : a;
             z = before ? z : mid;
         }
-        return ix.ei[ty.start + a];
+        return at(ei, a);
     }
 };
 
-template <int G>
-__device__ __forceinline__ void count_siblings(const SibJob &j, int64_t al, int g0, int len,
-                                               const NodeRow &row, int m, int *lds)
-{
-    const int lane = __lane_id();
-    const int start_m = rdl(row.start, m - 1);
-    Siblings<G> sink{j, j.ix, j.mask + (int64_t)start_m * j.words, rdl(row.start, 0)};
-    const int *key = j.F + al * j.w;
-#pragma unroll
-    for (int g = 0; g < G; ++g) {
-        const int c = g0 + g * WAVE + lane;
-        const bool on = c < len;
-        const int *last = j.F + (j.first[al] + (on ? c : 0)) * j.w + (j.w - 3);
-        sink.lo[g] = last[0];
-        sink.hi[g] = last[1];
-        sink.type[g] = last[2];
-        int h = 0;
-        for (int k = 1; k < j.n_iv; ++k)
-            h = (j.ivlo[k] == sink.lo[g] && j.ivhi[k] == sink.hi[g]) ? k : h;
-        sink.off[g] = (unsigned)(h * j.hop + (sink.type[g] >> 5));
-        sink.bit[g] = on ? 1u << (sink.type[g] & 31) : 0u;
-        sink.cnt[g] = 0;
-        sink.rb[g] = -1;
-        int hx = sink.hi[g];
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) {
-            const int o = __shfl_xor(hx, off);
-            hx = o > hx ? o : hx;
-        }
-        hx = __builtin_amdgcn_readfirstlane(hx);
-        sink.hm = hx > sink.hm ? hx : sink.hm;
-    }
-    // the pair (node 0, hop 0, node 1)'s entries
-    int k0 = 0;
-    for (int k = 1; k < j.n_iv; ++k) k0 = (j.ivlo[k] == key[1] && j.ivhi[k] == key[2]) ? k : k0;
-    const int64_t ak = (int64_t)j.rank[key[0]] * j.n_iv + k0;
-    const int64_t sd = ak * j.sd_stride + rdl(row.start, 1);
-    const int c1 = j.sd_n[ak * j.nF + j.rank[key[3]]];
-    const Seeds seed{j.sd_t + sd, j.sd_a + sd, j.sd_p + sd};
-    sink.seed_a = seed.a;
-    walk<false, true>(j.ix, row, m - 1, 0, c1, lds, sink, seed);
-#pragma unroll
-    for (int g = 0; g < G; ++g) {
-        const int c = g0 + g * WAVE + lane;
-        if (c < len) j.out[j.off[al] + c] = sink.cnt[g];
-    }
-}
-
-// One wave per frequent episode and SIB*64 of its siblings.
-//   Bound by instruction issue: an entry costs about 16 instructions for 64
-// siblings (24 for 128), where the scan of the whole stream it replaces costs
-// about 60 for each 64 events; an episode of 3 nodes has a few hundred
-// entries in 1.06e6 events.  Mining 13 minutes of 64 neurons, levels 2-6:
-// level 4 (2.1e7 candidates) 315 -> 12.5 ms, level 3 33 -> 3.2 ms.  Two
-// siblings a lane, as a frequent episode has 69 on average there and each
-// wave walks to the entries itself.
+// One wave per frequent episode and QW mask words (grid z).
+//   Bound by instruction issue: 64 entries cost about 50 instructions for 64
+// types and a hop, where the scan of the whole stream it replaces costs about
+// 60 for each 64 events and 64 siblings; an episode of 3 nodes has a few
+// hundred entries in 1.06e6 events.
+template <bool REL>
 __global__ __launch_bounds__(WAVE) void k_siblings(SibJob j, int64_t cnt)
 {
     extern __shared__ int lds[];
     const int64_t al = grid_item();
     if (al >= cnt) return;
-    const int g0 = (int)blockIdx.z * SIB * WAVE;
-    const int64_t len64 = j.off[al + 1] - j.off[al];
-    if (g0 >= len64) return;
-    const int len = (int)len64;
+    const int lane = __lane_id();
+    const int q0 = (int)blockIdx.z * QW;
+    const int nq = j.Q - q0 < QW ? j.Q - q0 : QW;
+    const int64_t out0 = j.off[al];
+    const int len = (int)(j.off[al + 1] - out0);
+    const int *sib = j.F + j.first[al] * j.w + (j.w - 3);  // (lo, hi, type) of a sibling
+    // the sibling's mask word
+    auto word_of = [&](int c) {
+        const int *s = sib + (int64_t)c * j.w;
+        int h = 0;
+        for (int k = 1; k < j.n_iv; ++k) h = (j.ivlo[k] == s[0] && j.ivhi[k] == s[1]) ? k : h;
+        return (s[2] >> 6) * j.n_iv + h;
+    };
+    if (len == 0) return;
+    if (j.Q > QW) {
+        // (none of this wave's words may have a sibling)
+        bool any = false;
+        for (int c = lane; c < len; c += WAVE) any |= (unsigned)(word_of(c) - q0) < (unsigned)nq;
+        if (bal(any) == 0) return;
+    }
     NodeRow row;
     Rows rows{};
     rows.ty = j.F;
@@ -1001,37 +1037,70 @@ __global__ __launch_bounds__(WAVE) void k_siblings(SibJob j, int64_t cnt)
     rows.tk = rows.hk = 3;
     rows.N = j.m;
     const int m = load_row(j.ix, rows, al, row);
-    if (len - g0 > WAVE) count_siblings<SIB>(j, al, g0, len, row, m, lds);
-    else count_siblings<1>(j, al, g0, len, row, m, lds);
+    // the entries of its first pair (node 0, hop 0, node 1)
+    const int *key = j.F + al * j.w;
+    int k0 = 0;
+    for (int k = 1; k < j.n_iv; ++k) k0 = (j.ivlo[k] == key[1] && j.ivhi[k] == key[2]) ? k : k0;
+    const int64_t ak = (int64_t)j.rank[key[0]] * j.n_iv + k0;
+    const int64_t sd = ak * j.sd.stride + rdl(row.start, 1);
+    const Seeds seed{j.sd.t + sd, j.sd.a + sd, j.sd.p + sd};
+    Columns<REL> sink{j, j.ix, q0, nq, rdl(row.start, 0), rdl(row.start, m - 1), seed.a};
+#pragma unroll
+    for (int q = 0; q < QW; ++q) {
+        const int h = (q0 + (q < nq ? q : 0)) % j.n_iv;
+        sink.lo[q] = j.ivlo[h];
+        sink.hi[q] = j.ivhi[h];
+        sink.cnt[q] = 0;
+        sink.tl[q] = -(1 << 30);
+        sink.ol[q] = 0;
+    }
+    walk<REL, true>(j.ix, row, m - 1, 0, j.sd.n[ak * j.nF + j.rank[key[3]]], lds, sink, seed);
+    // counts by type to the siblings
+    int *tot = lds;
+#pragma unroll
+    for (int q = 0; q < QW; ++q) tot[q * WAVE + lane] = sink.cnt[q];
+    __builtin_amdgcn_wave_barrier();
+    for (int c = lane; c < len; c += WAVE) {
+        const unsigned q = (unsigned)(word_of(c) - q0);
+        if (q >= (unsigned)nq) continue;
+        const int v = tot[q * WAVE + (sib[(int64_t)c * j.w + 2] & 63)];
+        j.out[out0 + c] = j.upper && j.upper[out0 + c] < j.theta ? -1 : v;
+    }
 }
 
 }  // namespace
 
-void launch_masks(const IndexPlan &p, const int *base, const int *ivlo, const int *ivhi, int n_iv,
-                  unsigned *mask, hipStream_t s)
+void launch_masks(bool rel, const IndexPlan &p, const int *base, const int *ivlo, const int *ivhi,
+                  int n_iv, uint2 *mask, hipStream_t s)
 {
     const ChainIdx ix = index_view(p, const_cast<int *>(base));
-    const int places = p.n + LIST_PAD * p.T, words = mask_words(p.T);
-    hipLaunchKernelGGL(k_masks, dim3((unsigned)((places + 255) / 256), (unsigned)(words * n_iv)),
-                       dim3(256), 0, s, ix, ix.et, places, p.T, words, ivlo, ivhi, mask,
-                       (int64_t)places * words);
+    const int places = p.n + LIST_PAD * p.T, Q = mask_words(p.T, n_iv);
+    const dim3 grid((unsigned)((places + 255) / 256), (unsigned)((p.T + 63) / 64 * 2 * n_iv));
+    if (rel)
+        hipLaunchKernelGGL(k_masks<true>, grid, dim3(256), 0, s, ix, places, p.T, n_iv, ivlo, ivhi,
+                           (unsigned *)mask, Q);
+    else
+        hipLaunchKernelGGL(k_masks<false>, grid, dim3(256), 0, s, ix, places, p.T, n_iv, ivlo,
+                           ivhi, (unsigned *)mask, Q);
 }
 
-void launch_seeds(const ChainIdx &ix, const int *F1, int nF, const int *ivlo, const int *ivhi,
-                  int n_iv, int *sd_t, int *sd_a, int *sd_p, int *sd_n, int64_t stride,
-                  hipStream_t s)
+void launch_pairs(bool rel, const PairJob &j, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_seeds, grid_of((int64_t)nF * nF * n_iv), dim3(WAVE),
-                       (size_t)RING_INTS * sizeof(int), s, ix, F1, nF, ivlo, ivhi, n_iv,
-                       sd_t, sd_a, sd_p, sd_n, stride);
+    const dim3 grid = grid_of((int64_t)j.nF * j.nF * j.n_iv);
+    const size_t lds = RING_INTS * sizeof(int);
+    if (rel) hipLaunchKernelGGL(k_pairs<true>, grid, dim3(WAVE), lds, s, j);
+    else hipLaunchKernelGGL(k_pairs<false>, grid, dim3(WAVE), lds, s, j);
 }
 
-void launch_siblings(const SibJob &j, int64_t cnt, int64_t longest, hipStream_t s)
+void launch_siblings(bool rel, const SibJob &j, int64_t cnt, hipStream_t s)
 {
-    if (cnt <= 0 || longest <= 0) return;
-    hipLaunchKernelGGL(k_siblings, grid_of(cnt, (longest + SIB * WAVE - 1) / (SIB * WAVE)),
-                       dim3(WAVE), (size_t)(j.m > 2 ? j.m - 2 : 1) * RING_INTS * sizeof(int),
-                       s, j, cnt);
+    if (cnt <= 0) return;
+    const dim3 grid = grid_of(cnt, (j.Q + QW - 1) / QW);
+    // (rings of the stages between node 1 and the last; the counts at the end)
+    const int rings = (j.m > 2 ? j.m - 2 : 0) * RING_INTS;
+    const size_t lds = (size_t)(rings > QW * WAVE ? rings : QW * WAVE) * sizeof(int);
+    if (rel) hipLaunchKernelGGL(k_siblings<true>, grid, dim3(WAVE), lds, s, j, cnt);
+    else hipLaunchKernelGGL(k_siblings<false>, grid, dim3(WAVE), lds, s, j, cnt);
 }
 
 }  // namespace fe

@@ -117,7 +117,7 @@ struct fe_ctx {
     Buf keys, hist, wmax, pk, orig, tileW, lam, tbl, flags, sel, nsel, status, small, cmask;
     Buf mtypes, mlen, mlo, mhi, mup, mex, msel, mn, mkey, tscr, tinfo, mfk, mfo, mfsel, pbc;
     Buf deep;  // window rings of the deep-class exact launches
-    Buf smask, sseed, sivl;    // miner: window masks, pairs' entries, intervals and ranks
+    Buf smask[2], sseed[2], sivl;  // miner: masks and pairs' entries (exact, relaxed), intervals
     Buf cidx, cseg;           // stream index and segment results of chain counting
     hipEvent_t checked = nullptr;  // the input checks of the call have run
     Buf skey, sup;  // keys and relaxed counts of a level's elimination sample
@@ -931,7 +931,7 @@ extern "C" int fe_destroy(fe_ctx *c)
                    &c->mtypes, &c->mlen, &c->mlo, &c->mhi, &c->mup, &c->mex, &c->msel, &c->mn,
                    &c->mkey, &c->tscr, &c->tinfo, &c->mfk, &c->mfo, &c->mfsel, &c->pbc,
                    &c->deep, &c->skey, &c->sup, &c->cidx, &c->cseg,
-                   &c->smask, &c->sseed, &c->sivl};
+                   &c->smask[0], &c->smask[1], &c->sseed[0], &c->sseed[1], &c->sivl};
     for (Buf *b : bufs)
         if (b->p) (void)hipFree(b->p);
     if (c->checked) (void)hipEventDestroy(c->checked);
@@ -1371,9 +1371,15 @@ struct MineChains {
     IndexPlan ip;
     ChainIdx ix;
     bool on = false;
+    // siblings (exact, relaxed): pairs' entries from level 2 on, masks when
+    // first used
+    bool fits = false;
+    bool pairs[2] = {false, false}, masks[2] = {false, false};
+    int64_t n_pairs = 0, sd_ints = 0;
+    size_t mask_bytes = 0;
     int n_iv = 0, nF = 0;
-    int tried = 0;    // siblings: 0 not set up yet, 1 ready, -1 not possible
-    SibJob sib{};
+    const int *ivlo = nullptr, *ivhi = nullptr, *rank = nullptr, *F1 = nullptr;
+    PairLists sd[2] = {};
 };
 
 bool chains_on(const MineChains &mc) { return mc.on; }
@@ -1404,22 +1410,19 @@ int mine_index(fe_ctx *c, const int *ids, const int *ticks, int64_t n, int num_t
     return FE_OK;
 }
 
-// The masks and the pairs' entries that sibling counting reads, made once a
-// run, when a level first takes one exact pass; they take at most 2 and 16 GiB.
-int sibling_setup(fe_ctx *c, MineChains &mc, const std::vector<int> &F1, const std::vector<int> &ilo,
-                  const std::vector<int> &ihi, int num_types)
+// Whether the miner may keep pairs' entries and masks (16 GiB of lists and
+// 2 GiB of masks a counter at most), and the interval set and ranks they need.
+int mine_pairs_setup(fe_ctx *c, MineChains &mc, const std::vector<int> &F1,
+                     const std::vector<int> &ilo, const std::vector<int> &ihi, int num_types)
 {
-    hipStream_t s = c->stream;
-    mc.tried = -1;
     const int64_t places = mc.ip.n + (int64_t)LIST_PAD * num_types;
-    const int words = mask_words(num_types), n_iv = (int)ilo.size(), nF = (int)F1.size();
-    const int64_t mask_ints = places * words * n_iv;
-    const int64_t pairs = (int64_t)nF * nF * n_iv, sd = (int64_t)nF * n_iv * places;
-    if (mask_ints > ((int64_t)1 << 29) || (int64_t)words * n_iv > 65535 ||
-        sd > ((int64_t)1 << 32) / 3 || pairs >= ((int64_t)1 << 31))
-        return FE_OK;
-    if (ensure(c, c->smask, (size_t)mask_ints * sizeof(int)) ||
-        ensure(c, c->sseed, (size_t)(3 * sd + pairs) * sizeof(int)) ||
+    const int n_iv = (int)ilo.size(), nF = (int)F1.size();
+    const int64_t Q = mask_words(num_types, n_iv);
+    mc.n_pairs = (int64_t)nF * nF * n_iv;
+    mc.sd_ints = (int64_t)nF * n_iv * places;
+    mc.mask_bytes = (size_t)(places * Q) * sizeof(uint2);
+    if (places * Q > ((int64_t)1 << 28) || 2 * Q > 65535 ||
+        mc.sd_ints > ((int64_t)1 << 32) / 3 || mc.n_pairs >= ((int64_t)1 << 31) ||
         ensure(c, c->sivl, (size_t)(2 * n_iv + num_types + nF) * sizeof(int)))
         return FE_OK;
     std::vector<int> h(2 * n_iv + num_types + nF, 0);
@@ -1429,30 +1432,88 @@ int sibling_setup(fe_ctx *c, MineChains &mc, const std::vector<int> &F1, const s
         h[2 * n_iv + F1[k]] = k;
         h[2 * n_iv + num_types + k] = F1[k];
     }
-    HIPCHK(c, hipMemcpyAsync(c->sivl.p, h.data(), h.size() * sizeof(int), hipMemcpyHostToDevice, s));
-    SibJob &j = mc.sib;
+    // (pageable: staged when the call returns)
+    HIPCHK(c, hipMemcpyAsync(c->sivl.p, h.data(), h.size() * sizeof(int), hipMemcpyHostToDevice,
+                             c->stream));
+    mc.n_iv = n_iv;
+    mc.nF = nF;
+    mc.ivlo = P<int>(c->sivl);
+    mc.ivhi = mc.ivlo + n_iv;
+    mc.rank = mc.ivlo + 2 * n_iv;
+    mc.F1 = mc.rank + num_types;
+    mc.fits = true;
+    return FE_OK;
+}
+
+// One counter's pairs' entries, which the later levels start from, with
+// level 2's counts in out (may be null); mc.pairs[rel] stays false when there
+// is no memory for them.
+int mine_pairs(fe_ctx *c, MineChains &mc, bool rel, int theta, const int *upper, int *out)
+{
+    if (!mc.fits || ensure(c, c->smask[rel], mc.mask_bytes) ||
+        ensure(c, c->sseed[rel], (size_t)(3 * mc.sd_ints + mc.n_pairs) * sizeof(int)))
+        return FE_OK;
+    int *t = P<int>(c->sseed[rel]);
+    mc.sd[rel] = PairLists{t, t + mc.sd_ints, t + 2 * mc.sd_ints, t + 3 * mc.sd_ints,
+                           mc.ip.n + (int64_t)LIST_PAD * mc.ip.T};
+    PairJob j{};
     j.ix = mc.ix;
-    j.mask = (const unsigned *)c->smask.p;
-    j.hop = places * words;
-    j.words = words;
-    j.ivlo = P<int>(c->sivl);
-    j.ivhi = j.ivlo + n_iv;
-    j.n_iv = n_iv;
-    j.rank = j.ivlo + 2 * n_iv;
-    j.nF = nF;
-    int *t = P<int>(c->sseed);
-    j.sd_t = t;
-    j.sd_a = t + sd;
-    j.sd_p = t + 2 * sd;
-    j.sd_n = t + 3 * sd;
-    j.sd_stride = places;
-    KTimer kt(c, "sibling_setup", 0);
-    launch_masks(mc.ip, P<int>(c->cidx), j.ivlo, j.ivhi, n_iv, (unsigned *)c->smask.p, s);
-    launch_seeds(mc.ix, j.rank + num_types, nF, j.ivlo, j.ivhi, n_iv, t, t + sd, t + 2 * sd,
-                 t + 3 * sd, places, s);
-    // (h is pageable: its copy has been staged when the call returns)
+    j.F1 = mc.F1;
+    j.nF = mc.nF;
+    j.ivlo = mc.ivlo;
+    j.ivhi = mc.ivhi;
+    j.n_iv = mc.n_iv;
+    j.sd = mc.sd[rel];
+    j.out = out;
+    j.upper = upper;
+    j.theta = theta;
+    KTimer kt(c, rel ? "map_relaxed_pairs" : "map_exact_pairs",
+              (double)mc.n_pairs * (double)mc.ip.n);
+    launch_pairs(rel, j, c->stream);
     HIPCHK(c, hipGetLastError());
-    mc.tried = 1;
+    c->stats.map_launches++;
+    c->stats.segments_max = std::max<int64_t>(c->stats.segments_max, 1);
+    mc.pairs[rel] = true;
+    return FE_OK;
+}
+
+// One counter over a joined level: F's episodes on the device with the
+// join's ranges.
+int mine_siblings(fe_ctx *c, MineChains &mc, bool rel, int level, const int *F,
+                  const int64_t *first, int64_t cnt, int64_t M, int num_types, int theta,
+                  const int *upper, int *out)
+{
+    hipStream_t s = c->stream;
+    SibJob j{};
+    j.ix = mc.ix;
+    j.F = F;
+    j.m = level - 1;
+    j.w = 3 * j.m - 2;
+    j.first = first;
+    j.off = first + cnt + 1;
+    j.out = out;
+    j.upper = upper;
+    j.theta = theta;
+    j.mask = (const uint2 *)c->smask[rel].p;
+    j.Q = mask_words(num_types, mc.n_iv);
+    j.ivlo = mc.ivlo;
+    j.ivhi = mc.ivhi;
+    j.n_iv = mc.n_iv;
+    j.sd = mc.sd[rel];
+    j.rank = mc.rank;
+    j.nF = mc.nF;
+    if (!mc.masks[rel]) {
+        KTimer kt(c, "masks", 0);
+        launch_masks(rel, mc.ip, P<int>(c->cidx), mc.ivlo, mc.ivhi, mc.n_iv,
+                     (uint2 *)c->smask[rel].p, s);
+        mc.masks[rel] = true;
+    }
+    c->stats.map_launches++;
+    char kname[40];
+    snprintf(kname, sizeof kname, "map_%s_siblings_n%d", rel ? "relaxed" : "exact", level);
+    KTimer kt(c, kname, (double)M * (double)mc.ip.n);
+    launch_siblings(rel, j, cnt, s);
+    HIPCHK(c, hipGetLastError());
     return FE_OK;
 }
 
@@ -1505,7 +1566,6 @@ extern "C" int fe_mine(fe_ctx *c, const int32_t *ids, const int32_t *ticks, int6
     c->stats = fe_stats{};
     hipStream_t s = c->stream;
     MineChains mc;
-    mc.n_iv = n_iv;
     if (chain_takes(c, n, num_types) && c->param[FE_PARAM_HOST_TILING] == 0)
         if ((rc = mine_index(c, ids, ticks, n, num_types, mc))) return rc;
     StreamInfo si{};
@@ -1582,20 +1642,18 @@ extern "C" int fe_mine(fe_ctx *c, const int32_t *ids, const int32_t *ticks, int6
         const int64_t emode = c->param[FE_PARAM_ELIMINATION];
         const double r1 = (double)c->param[FE_PARAM_PASS1_COST] / 1000.0;
         const bool large = emode == 2 && !htile && (int64_t)M >= c->param[FE_PARAM_SAMPLE_MIN];
-        // one exact pass over a joined level, siblings together: the
-        // candidates' keys are only written out when something asks for them
-        bool sib = mc.on && djoin && (emode == 0 || (large && r1 >= 1.0));
-        if (sib && !mc.tried &&
-            (rc = sibling_setup(c, mc, levels[0].types, ilo, ihi, num_types)))
+        // the siblings of a joined level are counted together, straight from
+        // the frequent set: the candidates' keys are only written out when
+        // something asks for them (samples: the relaxed pass over a sample)
+        const bool sample = large && r1 < 1.0;
+        const bool relaxed = emode != 0 && (!large || sample);  // (may run)
+        if (mc.on && djoin && relaxed && mc.pairs[0] && !mc.pairs[1] &&
+            (rc = mine_pairs(c, mc, true, theta, nullptr, nullptr)))
             return rc;
-        sib = sib && mc.tried > 0;
-        const bool keys_on = !sib || c->param[FE_PARAM_KEEP_CANDIDATES] != 0;
+        const bool sib = djoin && mc.pairs[0] && (!relaxed || mc.pairs[1]);
+        const bool keys_on = !sib || sample || c->param[FE_PARAM_KEEP_CANDIDATES] != 0;
         if (keys_on && (rc = ensure(c, c->mkey, std::max<size_t>(M * wk, 1) * sizeof(int))))
             return rc;
-        int64_t longest = 0;  // most siblings of one episode
-        if (sib)
-            for (size_t a = 0; a + 1 < joff.size(); ++a)
-                longest = std::max(longest, joff[a + 1] - joff[a]);
         if (djoin) {
             const int64_t cnt = (int64_t)F.count();
             const size_t fb = F.key.size() * sizeof(int), ob = (size_t)(cnt + 1) * sizeof(int64_t);
@@ -1638,26 +1696,31 @@ extern "C" int fe_mine(fe_ctx *c, const int32_t *ids, const int32_t *ticks, int6
         int64_t kept = 0;  // candidates of the exact pass (device tiling)
         int *nkept_d = P<int>(c->mn) + 1;  // the same, still on the device (chains)
         if (mc.on) {
+            bool done = false;
             if (sib) {
-                SibJob j = mc.sib;
-                j.F = P<int>(c->mfk);
-                j.m = F.m;
-                j.w = 3 * F.m - 2;
                 const int64_t cnt = (int64_t)F.count();
-                j.first = (const int64_t *)c->mfo.p;
-                j.off = j.first + cnt + 1;
-                j.out = ex;
-                c->stats.map_launches++;
-                char kname[40];
-                snprintf(kname, sizeof kname, "map_exact_siblings_n%d", level);
-                KTimer kt(c, kname, (double)M * (double)n);
-                launch_siblings(j, cnt, longest, s);
-                HIPCHK(c, hipGetLastError());
-            } else if ((rc = chain_rows(c, mc, key_rows(P<int>(c->mkey), level, (int64_t)M),
-                                        num_types, elim ? CHAIN_TWO_PASS : CHAIN_EXACT, theta, up,
-                                        ex, elim ? "map_two_pass_chain" : "map_exact_chain"))) {
-                return rc;
+                const int64_t *first = (const int64_t *)c->mfo.p;
+                if (elim && (rc = mine_siblings(c, mc, true, level, P<int>(c->mfk), first, cnt,
+                                                (int64_t)M, num_types, theta, nullptr, up)))
+                    return rc;
+                if ((rc = mine_siblings(c, mc, false, level, P<int>(c->mfk), first, cnt,
+                                        (int64_t)M, num_types, theta, elim ? up : nullptr, ex)))
+                    return rc;
+                done = true;
+            } else if (level == 2) {
+                if ((rc = mine_pairs_setup(c, mc, levels[0].types, ilo, ihi, num_types)))
+                    return rc;
+                if (elim && (rc = mine_pairs(c, mc, true, theta, nullptr, up))) return rc;
+                if ((!elim || mc.pairs[1]) &&
+                    (rc = mine_pairs(c, mc, false, theta, elim ? up : nullptr, ex)))
+                    return rc;
+                done = mc.pairs[0];
             }
+            if (!done && (rc = chain_rows(c, mc, key_rows(P<int>(c->mkey), level, (int64_t)M),
+                                          num_types, elim ? CHAIN_TWO_PASS : CHAIN_EXACT, theta,
+                                          up, ex, elim ? "map_two_pass_chain"
+                                                       : "map_exact_chain")))
+                return rc;
             if (elim) launch_count_ge(up, (int)M, theta, nkept_d, P<int>(c->status), s);
             else if (c->param[FE_PARAM_KEEP_CANDIDATES]) launch_fill(up, -1, (int64_t)M, s);
         } else if (!htile) {

@@ -234,7 +234,6 @@ template <bool REL, bool SEED, class Sink>
 __device__ __forceinline__ void walk(const ChainIdx &ix, const NodeRow &row, int E, int a,
                                      int aend, int *lds, Sink &sink, const Seeds &seed = Seeds())
 {
-    static_assert(!SEED || !REL, "pairs' entries are kept for the exact counter");
     constexpr int S = SEED ? 1 : 0;  // the source's node
     if (a >= aend) return;
     const int lane = __lane_id();
@@ -304,6 +303,7 @@ __device__ __forceinline__ void walk(const ChainIdx &ix, const NodeRow &row, int
             }
         }
         if (tot == 0) return;
+        tot = __builtin_amdgcn_readfirstlane(tot);
         tail += excl;
         if (c > 0) {
             const int s = tail & (QCAP - 1);
@@ -378,8 +378,13 @@ __device__ __forceinline__ void walk(const ChainIdx &ix, const NodeRow &row, int
                 t = at(src_t, np);
                 tn = at(src_t, np + 1);
             }
+            int own = pos, next = pos + 1;
+            if constexpr (SEED && REL) {
+                own = at(seed.p, pos);
+                next = at(seed.p, pos + 1);  // (behind the last: not used)
+            }
             int p, c, nc, tot, part;
-            events_of<REL, false>(h, lane < n, t_now, tn_now, pos, pos + 1, L, sk0, p, c);
+            events_of<REL, false>(h, lane < n, t_now, tn_now, own, next, L, sk0, p, c);
             put(q, h1 + n1, n, p, c, pos, sk0, nc, tot, part);
             n1 += tot;
             sk0 = part;

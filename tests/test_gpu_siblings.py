@@ -1,9 +1,9 @@
-"""Mining with join siblings counted together (one exact pass per level)
-against the oracle's miner, bit for bit, where the masks, the pairs' entries
-and the sibling groups can go wrong: type counts around a mask word, runs of
-siblings around 64 and 128, dense streams (chains that start inside an earlier
-completion's window), ties, intervals given twice, unsorted, narrow or wide;
-and every candidate's count against the event-by-event kernels."""
+"""Mining with join siblings counted together against the oracle's miner, bit
+for bit, where the masks, the pairs' entries and the columns can go wrong:
+type counts around a mask word, more words than a wave takes, dense streams
+(chains that start inside an earlier completion's range), ties, intervals
+given twice, unsorted, narrow or wide; and both counters of every candidate
+against the event-by-event kernels."""
 import numpy as np
 import pytest
 
@@ -60,15 +60,17 @@ def _check_oracle(got, want, theta):
 
 
 def _same_as_events(ctx, fe, ids_h, ticks_h, T, ivs, theta, max_level):
-    base = {fe.PARAM_ELIMINATION: 0, fe.PARAM_KEEP_CANDIDATES: 1}
-    a = _mine(ctx, fe, ids_h, ticks_h, T, ivs, theta, max_level, base)
-    b = _mine(ctx, fe, ids_h, ticks_h, T, ivs, theta, max_level,
-              {**base, fe.PARAM_TYPE_DISPATCH: 0})
-    assert [x["level"] for x in a] == [x["level"] for x in b]
-    for x, y in zip(a, b):
-        for k in ("types", "lo", "hi", "exact", "upper", "all_types", "all_lo", "all_hi",
-                  "all_exact", "all_upper"):
-            assert np.array_equal(np.asarray(x[k]), np.asarray(y[k])), (x["level"], k)
+    for elim in (1, 0):  # both counters; the exact one alone
+        base = {fe.PARAM_ELIMINATION: elim, fe.PARAM_KEEP_CANDIDATES: 1}
+        a = _mine(ctx, fe, ids_h, ticks_h, T, ivs, theta, max_level, base)
+        b = _mine(ctx, fe, ids_h, ticks_h, T, ivs, theta, max_level,
+                  {**base, fe.PARAM_TYPE_DISPATCH: 0})
+        assert [x["level"] for x in a] == [x["level"] for x in b]
+        for x, y in zip(a, b):
+            assert x["n_survivors"] == y["n_survivors"], x["level"]
+            for k in ("types", "lo", "hi", "exact", "upper", "all_types", "all_lo", "all_hi",
+                      "all_exact", "all_upper"):
+                assert np.array_equal(np.asarray(x[k]), np.asarray(y[k])), (elim, x["level"], k)
     return a
 
 
