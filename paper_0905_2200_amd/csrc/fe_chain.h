@@ -154,6 +154,7 @@ struct SibJob {
     ChainIdx ix;
     const int *F;                // frequent episodes' keys, sorted, w ints each
     int w, m;                    // m nodes
+    const int *order;            // the order to take them in (launch_order)
     const int64_t *first, *off;  // episode a's siblings end like F[first[a] + c]; outputs off[a] + c
     int *out;                    // counts
     const int *upper;            // set: -1 for candidates with upper < theta
@@ -170,6 +171,9 @@ struct SibJob {
 void launch_masks(bool rel, const IndexPlan &p, const int *base, const int *ivlo, const int *ivhi,
                   int n_iv, uint2 *mask, hipStream_t s);
 void launch_pairs(bool rel, const PairJob &j, hipStream_t s);
+// The cnt episodes ordered by their last type (order: order_ints ints).
+int64_t order_ints(int64_t cnt, int T);
+void launch_order(const int *F, int w, int64_t cnt, int T, int *order, hipStream_t s);
 // cnt episodes.
 void launch_siblings(bool rel, const SibJob &j, int64_t cnt, hipStream_t s);
 

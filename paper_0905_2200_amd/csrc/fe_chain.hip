@@ -462,12 +462,15 @@ template <bool REL, bool DUAL> struct Count {
         if (fn) drain(fn);
     }
     static constexpr bool SEARCHES = true;
-    __device__ __forceinline__ void operator()(int, bool on, int t, int src, int own, int L)
+    __device__ __forceinline__ void operator()(int, bool on, int t, int src, int own, int L, v4i v)
     {
         const Hop h = hop_of(ix, row, N - 2);
-        if (L < 0 || N > 2) L = table_at<REL>(h, t);
+        if (N > 2) {
+            L = table_at<REL>(h, t);
+            v = at4(h.et, L);
+        }
         int p, c;
-        events_of<REL, true>(h, on, t, FAR_TICK, own, 0, L, 0, p, c);
+        events_of<REL, true>(h, on, t, FAR_TICK, own, 0, L, v, 0, p, c);
         const bool pass = (c != 0) & (src < a1);
         const unsigned long long m = bal(pass);
         if (m == 0) return;
@@ -814,7 +817,7 @@ template <bool REL> struct SeedOut {
     int64_t base;
     int n = 0;
     static constexpr bool SEARCHES = false;
-    __device__ __forceinline__ void operator()(int c, bool on, int tk, int src, int own, int)
+    __device__ __forceinline__ void operator()(int c, bool on, int tk, int src, int own, int, v4i)
     {
         const int s = on ? at(ix.ei + rdl(row.start, 0), src) : FAR_TICK;
         const int i = on ? at(ix.ei + rdl(row.start, 1), own) : FAR_TICK;
@@ -926,7 +929,7 @@ template <bool REL> struct Columns {
     int cnt[QW], tl[QW], ol[QW];     // per type: completions, the last entry counted
     int t_last = -(1 << 30);
     static constexpr bool SEARCHES = false;
-    __device__ __forceinline__ void operator()(int n, bool on, int t, int src, int own, int)
+    __device__ __forceinline__ void operator()(int n, bool on, int t, int src, int own, int, v4i)
     {
         const int lane = __lane_id();
         const int apos = at(seed_a, src);
@@ -997,7 +1000,24 @@ template <bool REL> struct Columns {
     }
 };
 
-// One wave per frequent episode and QW mask words (grid z).
+// Episodes by their last type: k_order_count, a scan, k_order_place.
+__global__ __launch_bounds__(256) void k_order_count(const int *__restrict__ F, int w, int cnt,
+                                                     int *__restrict__ hist)
+{
+    const int a = blockIdx.x * 256 + threadIdx.x;
+    if (a < cnt) atomicAdd(&hist[F[(int64_t)a * w + w - 1]], 1);
+}
+__global__ __launch_bounds__(256) void k_order_place(const int *__restrict__ F, int w, int cnt,
+                                                     int *__restrict__ next, int *__restrict__ order)
+{
+    const int a = blockIdx.x * 256 + threadIdx.x;
+    if (a < cnt) order[atomicAdd(&next[F[(int64_t)a * w + w - 1]], 1)] = a;
+}
+
+// One wave per frequent episode and QW mask words (grid z), by the episodes'
+// last types: what a wave reads at random -- the last stage's list and the
+// masks of its entries -- is then the same few lists for all waves at a time,
+// and stays in every XCD's L2.
 //   Bound by instruction issue: 64 entries cost about 50 instructions for 64
 // types and a hop, where the scan of the whole stream it replaces costs about
 // 60 for each 64 events and 64 siblings; an episode of 3 nodes has a few
@@ -1006,8 +1026,9 @@ template <bool REL>
 __global__ __launch_bounds__(WAVE) void k_siblings(SibJob j, int64_t cnt)
 {
     extern __shared__ int lds[];
-    const int64_t al = grid_item();
-    if (al >= cnt) return;
+    const int64_t item = grid_item();
+    if (item >= cnt) return;
+    const int64_t al = j.order[item];
     const int lane = __lane_id();
     const int q0 = (int)blockIdx.z * QW;
     const int nq = j.Q - q0 < QW ? j.Q - q0 : QW;
@@ -1090,6 +1111,19 @@ void launch_pairs(bool rel, const PairJob &j, hipStream_t s)
     const size_t lds = RING_INTS * sizeof(int);
     if (rel) hipLaunchKernelGGL(k_pairs<true>, grid, dim3(WAVE), lds, s, j);
     else hipLaunchKernelGGL(k_pairs<false>, grid, dim3(WAVE), lds, s, j);
+}
+
+int64_t order_ints(int64_t cnt, int T) { return cnt + 2 * (int64_t)T + scan_scratch_ints(T); }
+
+void launch_order(const int *F, int w, int64_t cnt, int T, int *order, hipStream_t s)
+{
+    if (cnt <= 0) return;
+    int *hist = order + cnt, *next = hist + T;
+    launch_fill(hist, 0, T, s);
+    const dim3 grid((unsigned)((cnt + 255) / 256));
+    hipLaunchKernelGGL(k_order_count, grid, dim3(256), 0, s, F, w, (int)cnt, hist);
+    launch_scan_excl(hist, T, next, next + T, s);
+    hipLaunchKernelGGL(k_order_place, grid, dim3(256), 0, s, F, w, (int)cnt, next, order);
 }
 
 void launch_siblings(bool rel, const SibJob &j, int64_t cnt, hipStream_t s)

@@ -117,7 +117,7 @@ struct fe_ctx {
     Buf keys, hist, wmax, pk, orig, tileW, lam, tbl, flags, sel, nsel, status, small, cmask;
     Buf mtypes, mlen, mlo, mhi, mup, mex, msel, mn, mkey, tscr, tinfo, mfk, mfo, mfsel, pbc;
     Buf deep;  // window rings of the deep-class exact launches
-    Buf smask[2], sseed[2], sivl;  // miner: masks and pairs' entries (exact, relaxed), intervals
+    Buf smask[2], sseed[2], sivl, sord;  // miner: masks and pairs' entries (exact, relaxed), intervals
     Buf cidx, cseg;           // stream index and segment results of chain counting
     hipEvent_t checked = nullptr;  // the input checks of the call have run
     Buf skey, sup;  // keys and relaxed counts of a level's elimination sample
@@ -931,7 +931,8 @@ extern "C" int fe_destroy(fe_ctx *c)
                    &c->mtypes, &c->mlen, &c->mlo, &c->mhi, &c->mup, &c->mex, &c->msel, &c->mn,
                    &c->mkey, &c->tscr, &c->tinfo, &c->mfk, &c->mfo, &c->mfsel, &c->pbc,
                    &c->deep, &c->skey, &c->sup, &c->cidx, &c->cseg,
-                   &c->smask[0], &c->smask[1], &c->sseed[0], &c->sseed[1], &c->sivl};
+                   &c->smask[0], &c->smask[1], &c->sseed[0], &c->sseed[1], &c->sivl,
+                   &c->sord};
     for (Buf *b : bufs)
         if (b->p) (void)hipFree(b->p);
     if (c->checked) (void)hipEventDestroy(c->checked);
@@ -1481,7 +1482,7 @@ int mine_pairs(fe_ctx *c, MineChains &mc, bool rel, int theta, const int *upper,
 // join's ranges.
 int mine_siblings(fe_ctx *c, MineChains &mc, bool rel, int level, const int *F,
                   const int64_t *first, int64_t cnt, int64_t M, int num_types, int theta,
-                  const int *upper, int *out)
+                  const int *upper, int *out, const int *order)
 {
     hipStream_t s = c->stream;
     SibJob j{};
@@ -1491,6 +1492,7 @@ int mine_siblings(fe_ctx *c, MineChains &mc, bool rel, int level, const int *F,
     j.w = 3 * j.m - 2;
     j.first = first;
     j.off = first + cnt + 1;
+    j.order = order;
     j.out = out;
     j.upper = upper;
     j.theta = theta;
@@ -1700,11 +1702,16 @@ extern "C" int fe_mine(fe_ctx *c, const int32_t *ids, const int32_t *ticks, int6
             if (sib) {
                 const int64_t cnt = (int64_t)F.count();
                 const int64_t *first = (const int64_t *)c->mfo.p;
+                if ((rc = ensure(c, c->sord, (size_t)order_ints(cnt, num_types) * sizeof(int))))
+                    return rc;
+                launch_order(P<int>(c->mfk), 3 * F.m - 2, cnt, num_types, P<int>(c->sord), s);
                 if (elim && (rc = mine_siblings(c, mc, true, level, P<int>(c->mfk), first, cnt,
-                                                (int64_t)M, num_types, theta, nullptr, up)))
+                                                (int64_t)M, num_types, theta, nullptr, up,
+                                                P<int>(c->sord))))
                     return rc;
                 if ((rc = mine_siblings(c, mc, false, level, P<int>(c->mfk), first, cnt,
-                                        (int64_t)M, num_types, theta, elim ? up : nullptr, ex)))
+                                        (int64_t)M, num_types, theta, elim ? up : nullptr, ex,
+                                        P<int>(c->sord))))
                     return rc;
                 done = true;
             } else if (level == 2) {

@@ -126,14 +126,13 @@ template <bool REL> __device__ __forceinline__ int table_at(const Hop &h, int t)
 // entry's (own: its position), up to tick t + hi and up to the next entry's
 // event (tick tn, position next).  FIRST: the next entry is left out of it and
 // c only tells whether there is an event.  L: the table at the first tick's
-// bucket.
-//   Four entries from L on are read at once (L <= count, and LIST_PAD guards
-// of INT_MAX, which stop every search, follow a list); relaxed, indices are
-// only read where ticks are equal.  skip: events of lane 0's entry that have
-// been put out already.
+// bucket; v: four entries from there on (L <= count, and LIST_PAD guards of
+// INT_MAX, which stop every search, follow a list); relaxed, indices are only
+// read where ticks are equal.  skip: events of lane 0's entry that have been
+// put out already.
 template <bool REL, bool FIRST>
 __device__ __forceinline__ void events_of(const Hop &h, bool on, int t, int tn, int own, int next,
-                                          int L, int skip, int &p, int &c)
+                                          int L, v4i v, int skip, int &p, int &c)
 {
     const int x = from_tick<REL>(h, t);
     int lim = t + h.hi;
@@ -141,7 +140,6 @@ __device__ __forceinline__ void events_of(const Hop &h, bool on, int t, int tn, 
         const int tl = REL ? tn : __builtin_elementwise_add_sat(tn, h.lo);
         lim = tl < lim ? tl : lim;
     }
-    const v4i v = at4(h.et, L);
     const int k = (v[0] < x) + (v[1] < x) + (v[2] < x) + (v[3] < x);
     const int m = (v[0] <= lim) + (v[1] <= lim) + (v[2] <= lim) + (v[3] <= lim);
     p = L + k;
@@ -226,10 +224,11 @@ struct Seeds {
 // Entries of node E, in order, from the source [a, aend): node 0's events of
 // the row's first list (aend is either the list's end or past every tick that
 // an entry wanted from [a, ...) can reach), or, SEED, all of a pair's entries
-// of node 1.  sink(n, on, t, src, own, L): the next n <= 64 entries, one per
+// of node 1.  sink(n, on, t, src, own, L, v): the next n <= 64 entries, one per
 // lane (on; the other lanes' values are in range too): tick, position of the
-// chain's first event in the source, own position; L: straight from the
-// source, the sink's list's table at their buckets, else -1.
+// chain's first event in the source, own position; L, v: straight from the
+// source to a sink that SEARCHES node E + 1's list, that list's table at their
+// buckets and four entries from there on, else L = -1.
 template <bool REL, bool SEED, class Sink>
 __device__ __forceinline__ void walk(const ChainIdx &ix, const NodeRow &row, int E, int a,
                                      int aend, int *lds, Sink &sink, const Seeds &seed = Seeds())
@@ -239,17 +238,48 @@ __device__ __forceinline__ void walk(const ChainIdx &ix, const NodeRow &row, int
     const int lane = __lane_id();
     const int *src_t = SEED ? seed.t : ix.et + rdl(row.start, 0);
     auto place = [&](int from) { return from + lane < aend ? from + lane : aend - 1; };
+    // (the source's batches in flight, each a read behind the one before:
+    // while one is worked on, the next one's four entries, the table of the
+    // one after it and the ticks of the third are read)
+    const Hop h = hop_of(ix, row, S);
+    int t0 = 0, tn0 = 0, t1 = 0, tn1 = 0, t2 = 0, tn2 = 0, L0 = -1, L1 = -1;
+    v4i v0 = {0, 0, 0, 0};
+    auto ticks = [&](int from, int &t, int &tn) {
+        const int np = place(from < aend ? from : aend - 1);
+        t = at(src_t, np);
+        tn = at(src_t, np + 1);
+    };
+    auto fill = [&](bool look) {
+        ticks(a, t0, tn0);
+        ticks(a + WAVE, t1, tn1);
+        ticks(a + 2 * WAVE, t2, tn2);
+        if (!look) return;
+        L0 = table_at<REL>(h, t0);
+        L1 = table_at<REL>(h, t1);
+        v0 = at4(h.et, L0);
+    };
+    auto next_batch = [&](bool look) {
+        if (look) {
+            v0 = at4(h.et, L1);
+            L0 = L1;
+            L1 = table_at<REL>(h, t2);
+        }
+        t0 = t1;
+        tn0 = tn1;
+        t1 = t2;
+        tn1 = tn2;
+        ticks(a + 3 * WAVE, t2, tn2);
+    };
     if (E == S) {
-        const Hop h = hop_of(ix, row, S);
-        int t = at(src_t, place(a)), L = Sink::SEARCHES ? table_at<REL>(h, t) : 0;
+        fill(Sink::SEARCHES);
         for (;;) {
             const int pos = place(a), n = aend - a < WAVE ? aend - a : WAVE;
-            const int t_now = t, L_now = L;
-            if (a + WAVE < aend) t = at(src_t, place(a + WAVE));
-            sink(n, lane < n, t_now, pos, SEED ? at(seed.p, pos) : pos, L_now);
+            const int t = t0, L = L0;
+            const v4i v = v0;
+            next_batch(Sink::SEARCHES);
+            sink(n, lane < n, t, pos, SEED ? at(seed.p, pos) : pos, L, v);
             a += WAVE;
             if (a >= aend) return;
-            if (Sink::SEARCHES) L = table_at<REL>(h, t);
         }
     }
     // lane q: ring q's first slot, its entries, and how many events of its
@@ -334,14 +364,15 @@ __device__ __forceinline__ void walk(const ChainIdx &ix, const NodeRow &row, int
         const bool on = lane < n;
         int nc = n;
         if (k == E) {
-            sink(n, on, t, src, own, -1);
+            sink(n, on, t, src, own, -1, v4i{0, 0, 0, 0});
         } else {
             const Hop h = hop_of(ix, row, k);
             const int next = q[s1];
             const int tn = lane + 1 < ck ? at(list, next) : FAR_TICK;
             const int skip = rdl(sk, k);
+            const int L = table_at<REL>(h, t);
             int p, c, tot, part;
-            events_of<REL, false>(h, on, t, tn, own, next, table_at<REL>(h, t), skip, p, c);
+            events_of<REL, false>(h, on, t, tn, own, next, L, at4(h.et, L), skip, p, c);
             put(ring(k + 1), rdl(qh, k + 1) + rdl(qn, k + 1), n, p, c, src, skip, nc, tot, part);
             qn = lane == k + 1 ? qn + tot : qn;
             sk = lane == k ? part : sk;
@@ -365,37 +396,27 @@ __device__ __forceinline__ void walk(const ChainIdx &ix, const NodeRow &row, int
         }
     };
     {
-        const Hop h = hop_of(ix, row, S);
         int *q = ring(S + 1);
-        // (the next batch is read while this one is worked on)
-        int t = at(src_t, place(a)), tn = at(src_t, place(a) + 1);
-        int L = table_at<REL>(h, t);
+        fill(true);
         for (;;) {
             const int pos = place(a), n = aend - a < WAVE ? aend - a : WAVE;
-            const int t_now = t, tn_now = tn, a_next = a + WAVE;
-            if (a_next < aend) {
-                const int np = place(a_next);
-                t = at(src_t, np);
-                tn = at(src_t, np + 1);
-            }
+            const int a_next = a + WAVE, L_now = L0, t_now = t0, tn_now = tn0;
+            const v4i v_now = v0;
+            next_batch(true);
             int own = pos, next = pos + 1;
             if constexpr (SEED && REL) {
                 own = at(seed.p, pos);
                 next = at(seed.p, pos + 1);  // (behind the last: not used)
             }
             int p, c, nc, tot, part;
-            events_of<REL, false>(h, lane < n, t_now, tn_now, own, next, L, sk0, p, c);
+            events_of<REL, false>(h, lane < n, t_now, tn_now, own, next, L_now, v_now, sk0, p, c);
             put(q, h1 + n1, n, p, c, pos, sk0, nc, tot, part);
             n1 += tot;
             sk0 = part;
             a += nc;
             if (n1 >= full1) drain();
             if (a >= aend) break;
-            if (__builtin_expect(a != a_next, 0)) {
-                t = at(src_t, place(a));
-                tn = at(src_t, place(a) + 1);
-            }
-            L = table_at<REL>(h, t);
+            if (__builtin_expect(a != a_next, 0)) fill(true);
         }
     }
     // what is left, from the source on (a stage's entries are its last when
