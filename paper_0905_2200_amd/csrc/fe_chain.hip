@@ -422,14 +422,17 @@ template <bool REL, bool DUAL> struct Count {
     }
 
     // the greedy choice among 64 completions in order (valid: their lanes),
-    // after one at rr: an entry whose chain starts after its predecessor's
-    // completion is always taken; the others depend on the last one taken
+    // after one at rr: of a chain's completions only the first can be taken;
+    // one whose chain starts after its predecessor's completion always is; the
+    // others depend on the last one taken
     __device__ __forceinline__ void choose(unsigned long long valid, int s, int i, int &rr,
                                            int &c) const
     {
         const int lane = __lane_id();
         int ip = __shfl_up(i, 1);
         ip = lane == 0 ? rr : ip;
+        const int sp = __shfl_up(s, 1);
+        valid &= bal((lane == 0) | (s != sp));
         unsigned long long conf = bal(s <= ip) & valid;
         unsigned long long sel = valid & ~conf;
         while (conf) {
@@ -912,12 +915,16 @@ constexpr int QW = 4;  // mask words (64 types and a hop each) a wave counts
 // Join siblings: one frequent episode's entries against 64 types at a time
 // and a hop.  Of 64 entries, one per lane, the mask words (bit = type) are
 // transposed, so that a lane holds, for its type, which entries have an event
-// of it in range (bit = entry).  All of them are counted, but for those whose
-// chain may start by the lane's last completion: an entry is looked at where
-// its chain starts within the hop's width of the entry before it.  The last
-// completion is the first event in range of the last entry counted (tick tl),
-// so after tl + lo (relaxed: not before tl) and by tl + hi; in between the
-// event is looked up.
+// of it in range (bit = entry).  Of the entries of one chain only the first
+// such can complete it, and if that one may not, none may: the lowest bit of
+// each chain's stretch of bits is kept, all stretches at once (subtracting
+// their first bits from the word with their last bits set borrows inside
+// each stretch alone).  What is left counts, but for entries whose chain may
+// start by the lane's last completion, and those are looked at one by one:
+// where a chain starts within the hop's width of the last entry before it.
+// The last completion is the first event in range of the last entry counted
+// (tick tl), so after tl + lo (relaxed: not before tl) and by tl + hi; in
+// between the event is looked up.
 template <bool REL> struct Columns {
     const SibJob &j;
     const ChainIdx &ix;
@@ -934,8 +941,15 @@ template <bool REL> struct Columns {
         const int lane = __lane_id();
         const int apos = at(seed_a, src);
         const int st = ix.et[start0 + apos];
-        int tp = __shfl_up(t, 1);
-        tp = lane == 0 ? t_last : tp;
+        // chains' stretches: first and last bits, and the tick of the last
+        // entry before the lane's own (a stretch that goes on from the batch
+        // before has it among its own, and so within the width)
+        const int ap = __shfl_up(apos, 1);
+        const unsigned long long first = bal((lane == 0) | (apos != ap));
+        const unsigned long long last = (first >> 1) | (1ull << 63);
+        const int g = 63 - __builtin_clzll(first & ((2ull << lane) - 1ull));
+        const int tb = __shfl(t, g > 0 ? g - 1 : 0);
+        const int tp = g > 0 ? tb : t_last;
         t_last = rdl(t, n - 1);
         const uint2 *row = j.mask + (int64_t)(start_m + own) * j.Q + q0;
         uint2 w[QW];
@@ -946,6 +960,12 @@ template <bool REL> struct Columns {
             if (q >= nq) break;
             unsigned c0 = w[q].x, c1 = w[q].y;
             flip(c0, c1);
+            {
+                const unsigned long long c = c0 | (unsigned long long)c1 << 32, x = c | last;
+                const unsigned long long low = c & ~(x - first);
+                c0 = (unsigned)low;
+                c1 = (unsigned)(low >> 32);
+            }
             unsigned long long near = bal(on & (st <= tp + hi[q]));
             while (near) {
                 const int e = (int)__builtin_ctzll(near);
@@ -971,12 +991,12 @@ template <bool REL> struct Columns {
                 else c1 &= ~bit;
             }
             cnt[q] += __builtin_popcount(c0) + __builtin_popcount(c1);
-            const int last = c1 ? 63 - __builtin_clz(c1) : c0 ? 31 - __builtin_clz(c0) : -1;
-            const int tv = __shfl(t, last >= 0 ? last : 0);
-            tl[q] = last >= 0 ? tv : tl[q];
+            const int top = c1 ? 63 - __builtin_clz(c1) : c0 ? 31 - __builtin_clz(c0) : -1;
+            const int tv = __shfl(t, top >= 0 ? top : 0);
+            tl[q] = top >= 0 ? tv : tl[q];
             if constexpr (REL) {
-                const int ov = __shfl(own, last >= 0 ? last : 0);
-                ol[q] = last >= 0 ? ov : ol[q];
+                const int ov = __shfl(own, top >= 0 ? top : 0);
+                ol[q] = top >= 0 ? ov : ol[q];
             }
         }
     }
