@@ -117,7 +117,7 @@ struct fe_ctx {
     Buf keys, hist, wmax, pk, orig, tileW, lam, tbl, flags, sel, nsel, status, small, cmask;
     Buf mtypes, mlen, mlo, mhi, mup, mex, msel, mn, mkey, tscr, tinfo, mfk, mfo, mfsel, pbc;
     Buf deep;  // window rings of the deep-class exact launches
-    Buf smask[2], sseed[2], sivl, sord;  // miner: masks and pairs' entries (exact, relaxed), intervals
+    Buf smask[2], sseed[2], sivl, sord, msplit;  // miner: masks and pairs' entries (exact, relaxed), intervals
     Buf cidx, cseg;           // stream index and segment results of chain counting
     hipEvent_t checked = nullptr;  // the input checks of the call have run
     Buf skey, sup;  // keys and relaxed counts of a level's elimination sample
@@ -128,6 +128,8 @@ struct fe_ctx {
     size_t arena_cap = 0, arena_used = 0;
     // host arrays of the mining driver, kept for reuse (large ones are pinned)
     ivec keypool, lanepool, uphpool, orderpool;
+    int *pin = nullptr;   // pinned: a level's frequent set on its way back
+    size_t pin_cap = 0;
     int *host = nullptr;  // pinned host staging for small readbacks
     size_t host_cap = 0;
     // kernel timing
@@ -220,6 +222,25 @@ int ensure_host(fe_ctx *c, size_t ints)
         return fail(c, FE_ENOMEM, "pinned host allocation failed");
     }
     c->host_cap = ints;
+    return FE_OK;
+}
+
+int ensure_pin(fe_ctx *c, size_t ints)
+{
+    if (c->pin_cap >= ints) return FE_OK;
+    if (c->pin) {
+        HIPCHK(c, hipStreamSynchronize(c->stream));
+        HIPCHK(c, hipHostFree(c->pin));
+        c->pin = nullptr;
+        c->pin_cap = 0;
+    }
+    ints += ints / 4;
+    if (hipHostMalloc((void **)&c->pin, ints * sizeof(int)) != hipSuccess) {
+        (void)hipGetLastError();
+        c->pin = nullptr;
+        return fail(c, FE_ENOMEM, "pinned host allocation failed");
+    }
+    c->pin_cap = ints;
     return FE_OK;
 }
 
@@ -932,7 +953,7 @@ extern "C" int fe_destroy(fe_ctx *c)
                    &c->mkey, &c->tscr, &c->tinfo, &c->mfk, &c->mfo, &c->mfsel, &c->pbc,
                    &c->deep, &c->skey, &c->sup, &c->cidx, &c->cseg,
                    &c->smask[0], &c->smask[1], &c->sseed[0], &c->sseed[1], &c->sivl,
-                   &c->sord};
+                   &c->sord, &c->msplit};
     for (Buf *b : bufs)
         if (b->p) (void)hipFree(b->p);
     if (c->checked) (void)hipEventDestroy(c->checked);
@@ -942,6 +963,7 @@ extern "C" int fe_destroy(fe_ctx *c)
     }
     for (hipEvent_t e : c->event_pool) (void)hipEventDestroy(e);
     if (c->host) (void)hipHostFree(c->host);
+    if (c->pin) (void)hipHostFree(c->pin);
     if (c->own_stream) (void)hipStreamDestroy(c->stream);
     delete c;
     return FE_OK;
@@ -1207,14 +1229,46 @@ struct HTimer {
 };
 
 struct LevelOut {
-    int level;
-    int64_t ncand, nsurv, nfreq;
+    int level = 0;
+    int64_t ncand = 0, nsurv = 0, nfreq = 0;
     std::vector<int> types, lo, hi, upper, exact;
-    double gen_ms, count_ms;
+    double gen_ms = 0, count_ms = 0;
     int passes = 2;
     int64_t sample_n = 0, sample_kept = 0;
     // every candidate (FE_PARAM_KEEP_CANDIDATES)
     std::vector<int> all_types, all_lo, all_hi, all_upper, all_exact;
+    // types, lo, hi, upper, exact as allocated arrays in place of the vectors
+    int *raw[5] = {nullptr, nullptr, nullptr, nullptr, nullptr};
+    LevelOut() = default;
+    LevelOut(LevelOut &&o) { *this = std::move(o); }
+    LevelOut &operator=(LevelOut &&o)
+    {
+        level = o.level;
+        ncand = o.ncand;
+        nsurv = o.nsurv;
+        nfreq = o.nfreq;
+        types.swap(o.types);
+        lo.swap(o.lo);
+        hi.swap(o.hi);
+        upper.swap(o.upper);
+        exact.swap(o.exact);
+        gen_ms = o.gen_ms;
+        count_ms = o.count_ms;
+        passes = o.passes;
+        sample_n = o.sample_n;
+        sample_kept = o.sample_kept;
+        all_types.swap(o.all_types);
+        all_lo.swap(o.all_lo);
+        all_hi.swap(o.all_hi);
+        all_upper.swap(o.all_upper);
+        all_exact.swap(o.all_exact);
+        std::swap(raw, o.raw);
+        return *this;
+    }
+    ~LevelOut()
+    {
+        for (int *p : raw) std::free(p);
+    }
 };
 
 // keys (E1, lo1, hi1, E2, ...) of m-node episodes to types / lo / hi rows
@@ -1324,14 +1378,8 @@ int dev_pack(fe_ctx *c, const int *key_d, int m, int64_t M, const int *up, int t
 // relaxed pass over a sample of the level's candidates (every 64th block of
 // 64 consecutive ones, so join siblings stay together); ns sampled, nk of
 // them with upper >= theta.
-struct MineChains;
-int chain_rows(fe_ctx *c, const MineChains &mc, const Rows &rows, int num_types, ChainMode mode,
-               int theta, int *up, int *ex, const char *name);
-bool chains_on(const MineChains &mc);
-
-int sample_survival(fe_ctx *c, const int *ids, const int *ticks, const StreamInfo &si,
-                    const MineChains &mc, int num_types, int level, int64_t M, int wbound,
-                    int bbound, int theta, int64_t &ns, int64_t &nk)
+int sample_survival(fe_ctx *c, const int *ids, const int *ticks, const StreamInfo &si, int level,
+                    int64_t M, int wbound, int bbound, int theta, int64_t &ns, int64_t &nk)
 {
     int rc;
     hipStream_t s = c->stream;
@@ -1342,16 +1390,6 @@ int sample_survival(fe_ctx *c, const int *ids, const int *ticks, const StreamInf
     if ((rc = ensure(c, c->skey, (size_t)ns * wk * sizeof(int)))) return rc;
     if ((rc = ensure(c, c->sup, (size_t)ns * sizeof(int)))) return rc;
     launch_sample_keys(P<int>(c->mkey), wk, M, P<int>(c->skey), s);
-    if (chains_on(mc)) {
-        if ((rc = chain_rows(c, mc, key_rows(P<int>(c->skey), level, ns), num_types, CHAIN_RELAXED,
-                             theta, P<int>(c->sup), P<int>(c->sup), "sample_relaxed_chain")))
-            return rc;
-        launch_count_ge(P<int>(c->sup), (int)ns, theta, P<int>(c->mn), P<int>(c->status), s);
-        HIPCHK(c, hipMemcpyAsync(c->host, P<int>(c->mn), sizeof(int), hipMemcpyDeviceToHost, s));
-        HIPCHK(c, hipStreamSynchronize(s));
-        nk = c->host[0];
-        return FE_OK;
-    }
     std::vector<GroupDesc> groups;
     int64_t kept = 0;
     if ((rc = dev_pack(c, P<int>(c->skey), level, ns, nullptr, 0, false, wbound, bbound, groups,
@@ -1379,21 +1417,23 @@ struct MineChains {
     int64_t n_pairs = 0, sd_ints = 0;
     size_t mask_bytes = 0;
     int n_iv = 0, nF = 0;
-    const int *ivlo = nullptr, *ivhi = nullptr, *rank = nullptr, *F1 = nullptr;
+    const int *ivlo = nullptr, *ivhi = nullptr, *ord = nullptr,
+              *rank = nullptr, *F1 = nullptr;
     PairLists sd[2] = {};
 };
 
-bool chains_on(const MineChains &mc) { return mc.on; }
-
-// Index of the stream, with its checks (synchronises).
+// Index of the stream, with its checks (synchronises), and every type's events
+// in hist.
 int mine_index(fe_ctx *c, const int *ids, const int *ticks, int64_t n, int num_types,
-               MineChains &mc)
+               MineChains &mc, std::vector<int> &hist)
 {
     hipStream_t s = c->stream;
     int rc;
     mc.ip = index_plan(n, num_types, true);
     if (ensure(c, c->cidx, (size_t)mc.ip.ints * sizeof(int))) return FE_OK;
     if ((rc = ensure_host(c, 4))) return rc;
+    const size_t tyb = (size_t)num_types * sizeof(TypeIdx);
+    if ((rc = ensure_pin(c, tyb / sizeof(int)))) return rc;
     if (!c->checked) HIPCHK(c, hipEventCreateWithFlags(&c->checked, hipEventDisableTiming));
     int *base = P<int>(c->cidx);
     const int *st = P<int>(c->status);
@@ -1402,36 +1442,53 @@ int mine_index(fe_ctx *c, const int *ids, const int *ticks, int64_t n, int num_t
         const IndexSet x = index_set(mc.ip, index_job(mc.ip, ids, ticks, base, 0), base);
         launch_index_check(x, Rows{}, 1, num_types, P<int>(c->status), nullptr, s);
         launch_index_types(x, st, c->host, s);
+        HIPCHK(c, hipMemcpyAsync(c->pin, base + mc.ip.o_ty, tyb, hipMemcpyDeviceToHost, s));
         HIPCHK(c, hipEventRecord(c->checked, s));
         launch_index_lists(x, st, s);
     }
     if ((rc = wait_checks(c))) return rc;
+    hist.resize(num_types);
+    for (int e = 0; e < num_types; ++e) hist[e] = ((const TypeIdx *)c->pin)[e].count;
     mc.ix = index_view(mc.ip, base);
     mc.on = true;
     return FE_OK;
 }
 
-// Whether the miner may keep pairs' entries and masks (16 GiB of lists and
-// 2 GiB of masks a counter at most), and the interval set and ranks they need.
-int mine_pairs_setup(fe_ctx *c, MineChains &mc, const std::vector<int> &F1,
-                     const std::vector<int> &ilo, const std::vector<int> &ihi, int num_types)
+// The interval set (also sorted) and the frequent types' ranks on the device,
+// and whether the miner may keep pairs' entries and masks (16 GiB of lists and
+// 2 GiB of masks a counter at most).
+int mine_setup(fe_ctx *c, MineChains &mc, const std::vector<int> &F1, const std::vector<int> &ilo,
+               const std::vector<int> &ihi, int num_types)
 {
+    int rc;
     const int64_t places = mc.ip.n + (int64_t)LIST_PAD * num_types;
     const int n_iv = (int)ilo.size(), nF = (int)F1.size();
     const int64_t Q = mask_words(num_types, n_iv);
     mc.n_pairs = (int64_t)nF * nF * n_iv;
     mc.sd_ints = (int64_t)nF * n_iv * places;
     mc.mask_bytes = (size_t)(places * Q) * sizeof(uint2);
-    if (places * Q > ((int64_t)1 << 28) || 2 * Q > 65535 ||
-        mc.sd_ints > ((int64_t)1 << 32) / 3 || mc.n_pairs >= ((int64_t)1 << 31) ||
-        ensure(c, c->sivl, (size_t)(2 * n_iv + num_types + nF) * sizeof(int)))
-        return FE_OK;
-    std::vector<int> h(2 * n_iv + num_types + nF, 0);
+    mc.fits = places * Q <= ((int64_t)1 << 28) && 2 * Q <= 65535 &&
+              mc.sd_ints <= ((int64_t)1 << 32) / 3 && mc.n_pairs < ((int64_t)1 << 31);
+    std::vector<int> h(5 * n_iv + num_types + nF, 0);
+    if ((rc = ensure(c, c->sivl, h.size() * sizeof(int)))) return rc;
     std::copy(ilo.begin(), ilo.end(), h.begin());
     std::copy(ihi.begin(), ihi.end(), h.begin() + n_iv);
+    int *ord = h.data() + 2 * n_iv;
+    for (int k = 0; k < n_iv; ++k) ord[k] = k;
+    std::sort(ord, ord + n_iv, [&](int a, int b) {
+        return ilo[a] != ilo[b] ? ilo[a] < ilo[b] : ihi[a] != ihi[b] ? ihi[a] < ihi[b] : a < b;
+    });
+    // (sorted places of equal intervals: the first, and how many)
+    int *grp = ord + n_iv, *same = ord + 2 * n_iv;
+    for (int k = 0; k < n_iv; ++k) {
+        const bool eq = k && ilo[ord[k]] == ilo[ord[k - 1]] && ihi[ord[k]] == ihi[ord[k - 1]];
+        grp[k] = eq ? grp[k - 1] : k;
+        ++same[grp[k]];
+    }
+    for (int k = 0; k < n_iv; ++k) same[k] = same[grp[k]];
     for (int k = 0; k < nF; ++k) {
-        h[2 * n_iv + F1[k]] = k;
-        h[2 * n_iv + num_types + k] = F1[k];
+        h[5 * n_iv + F1[k]] = k;
+        h[5 * n_iv + num_types + k] = F1[k];
     }
     // (pageable: staged when the call returns)
     HIPCHK(c, hipMemcpyAsync(c->sivl.p, h.data(), h.size() * sizeof(int), hipMemcpyHostToDevice,
@@ -1440,9 +1497,9 @@ int mine_pairs_setup(fe_ctx *c, MineChains &mc, const std::vector<int> &F1,
     mc.nF = nF;
     mc.ivlo = P<int>(c->sivl);
     mc.ivhi = mc.ivlo + n_iv;
-    mc.rank = mc.ivlo + 2 * n_iv;
+    mc.ord = mc.ivlo + 2 * n_iv;
+    mc.rank = mc.ivlo + 5 * n_iv;
     mc.F1 = mc.rank + num_types;
-    mc.fits = true;
     return FE_OK;
 }
 
@@ -1478,11 +1535,11 @@ int mine_pairs(fe_ctx *c, MineChains &mc, bool rel, int theta, const int *upper,
     return FE_OK;
 }
 
-// One counter over a joined level: F's episodes on the device with the
-// join's ranges.
+// One counter over a joined level: F's episodes on the device with the join's
+// ranges.
 int mine_siblings(fe_ctx *c, MineChains &mc, bool rel, int level, const int *F,
-                  const int64_t *first, int64_t cnt, int64_t M, int num_types, int theta,
-                  const int *upper, int *out, const int *order)
+                  const int64_t *first, const int64_t *off, int64_t cnt, int64_t M, int num_types,
+                  int theta, const int *upper, int *out, const int *order)
 {
     hipStream_t s = c->stream;
     SibJob j{};
@@ -1491,7 +1548,7 @@ int mine_siblings(fe_ctx *c, MineChains &mc, bool rel, int level, const int *F,
     j.m = level - 1;
     j.w = 3 * j.m - 2;
     j.first = first;
-    j.off = first + cnt + 1;
+    j.off = off;
     j.order = order;
     j.out = out;
     j.upper = upper;
@@ -1542,69 +1599,38 @@ int chain_rows(fe_ctx *c, const MineChains &mc, const Rows &rows, int num_types,
     return FE_OK;
 }
 
-}  // namespace
-
-extern "C" int fe_mine(fe_ctx *c, const int32_t *ids, const int32_t *ticks, int64_t n,
-                       int32_t num_types, const int32_t *iv_lo, const int32_t *iv_hi, int32_t n_iv,
-                       int32_t theta, int32_t max_level, fe_result **out)
+// sample_survival by chains.
+int sample_chains(fe_ctx *c, const MineChains &mc, int num_types, int level, int64_t M, int theta,
+                  int64_t &ns, int64_t &nk)
 {
     int rc;
-    const double t_call = now_ms();
-    if (!out) return fail(c, FE_EINVAL, "null result pointer");
-    *out = nullptr;
-    if ((rc = check_common(c, ids, ticks, n, num_types))) return rc;
-    if (max_level < 1 || max_level > NMAX) return fail(c, FE_EINVAL, "max_level outside [1,8]");
-    if (n_iv < 0 || (n_iv > 0 && (!iv_lo || !iv_hi)))
-        return fail(c, FE_EINVAL, "bad interval set");
-    std::vector<int> ilo(iv_lo, iv_lo + n_iv), ihi(iv_hi, iv_hi + n_iv);
-    for (int k = 0; k < n_iv; ++k) {
-        const int l = ilo[k], h = ihi[k];
-        if (l < 0 || l >= h || h >= TICK_LIMIT)
-            return fail(c, FE_EINVAL, "interval %d = (%d,%d] invalid", k, l, h);
-        if ((int64_t)h * max_level >= TICK_LIMIT)
-            return fail(c, FE_EINVAL, "interval %d too wide for max_level", k);
-    }
-    HIPCHK(c, hipSetDevice(c->device));
-    c->stats = fe_stats{};
     hipStream_t s = c->stream;
-    MineChains mc;
-    if (chain_takes(c, n, num_types) && c->param[FE_PARAM_HOST_TILING] == 0)
-        if ((rc = mine_index(c, ids, ticks, n, num_types, mc))) return rc;
-    StreamInfo si{};
-    if (!mc.on && (rc = stream_info(c, ids, ticks, (int)n, num_types, si))) return rc;
-
-    std::vector<LevelOut> levels;
-    // level 1: a one-node episode occurs at every event of its type
-    double t0 = now_ms();
-    if ((rc = ensure(c, c->mn, (size_t)num_types * sizeof(int)))) return rc;
-    launch_fill(P<int>(c->mn), 0, num_types, s);
-    launch_histogram(ids, (int)n, num_types, P<int>(c->mn), s);
-    std::vector<int> hist(num_types);
-    HIPCHK(c, hipMemcpyAsync(hist.data(), P<int>(c->mn), num_types * sizeof(int),
-                             hipMemcpyDeviceToHost, s));
+    const int wk = 3 * level - 2;
+    ns = sample_count(M);
+    nk = 0;
+    if (ns <= 0) return FE_OK;
+    if ((rc = ensure(c, c->skey, (size_t)ns * wk * sizeof(int)))) return rc;
+    if ((rc = ensure(c, c->sup, (size_t)ns * sizeof(int)))) return rc;
+    launch_sample_keys(P<int>(c->mkey), wk, M, P<int>(c->skey), s);
+    if ((rc = chain_rows(c, mc, key_rows(P<int>(c->skey), level, ns), num_types, CHAIN_RELAXED,
+                         theta, P<int>(c->sup), P<int>(c->sup), "sample_relaxed_chain")))
+        return rc;
+    launch_count_ge(P<int>(c->sup), (int)ns, theta, P<int>(c->mn), P<int>(c->status), s);
+    HIPCHK(c, hipMemcpyAsync(c->host, P<int>(c->mn), sizeof(int), hipMemcpyDeviceToHost, s));
     HIPCHK(c, hipStreamSynchronize(s));
-    {
-        LevelOut L1;
-        L1.level = 1;
-        L1.ncand = num_types;
-        L1.nsurv = num_types;
-        for (int e = 0; e < num_types; ++e)
-            if (hist[e] >= theta) {
-                L1.types.push_back(e);
-                L1.upper.push_back(hist[e]);
-                L1.exact.push_back(hist[e]);
-            }
-        L1.nfreq = (int64_t)L1.types.size();
-        L1.passes = 1;
-        if (c->param[FE_PARAM_KEEP_CANDIDATES]) {
-            for (int e = 0; e < num_types; ++e) L1.all_types.push_back(e);
-            L1.all_upper = hist;
-            L1.all_exact = hist;
-        }
-        L1.gen_ms = 0;
-        L1.count_ms = now_ms() - t0;
-        levels.push_back(std::move(L1));
-    }
+    nk = c->host[0];
+    return FE_OK;
+}
+
+// Levels 2 and up counted event by event (the Map kernels), after level 1.
+int mine_events(fe_ctx *c, const int *ids, const int *ticks, const StreamInfo &si, int theta,
+                int max_level, const std::vector<int> &ilo, const std::vector<int> &ihi,
+                std::vector<LevelOut> &levels)
+{
+    int rc;
+    double t0;
+    hipStream_t s = c->stream;
+    const int n_iv = (int)ilo.size();
     Episodes F;
     F.m = 1;
     for (int e : levels[0].types) F.key.push_back(e);
@@ -1641,21 +1667,7 @@ extern "C" int fe_mine(fe_ctx *c, const int32_t *ids, const int32_t *ticks, int6
         int bbound = 1;  // largest window bound of the interval set
         for (int k = 0; k < n_iv; ++k) bbound = std::max(bbound, window_bound(ilo[k], ihi[k]));
         const int wk = 3 * level - 2;  // ints per key
-        const int64_t emode = c->param[FE_PARAM_ELIMINATION];
-        const double r1 = (double)c->param[FE_PARAM_PASS1_COST] / 1000.0;
-        const bool large = emode == 2 && !htile && (int64_t)M >= c->param[FE_PARAM_SAMPLE_MIN];
-        // the siblings of a joined level are counted together, straight from
-        // the frequent set: the candidates' keys are only written out when
-        // something asks for them (samples: the relaxed pass over a sample)
-        const bool sample = large && r1 < 1.0;
-        const bool relaxed = emode != 0 && (!large || sample);  // (may run)
-        if (mc.on && djoin && relaxed && mc.pairs[0] && !mc.pairs[1] &&
-            (rc = mine_pairs(c, mc, true, theta, nullptr, nullptr)))
-            return rc;
-        const bool sib = djoin && mc.pairs[0] && (!relaxed || mc.pairs[1]);
-        const bool keys_on = !sib || sample || c->param[FE_PARAM_KEEP_CANDIDATES] != 0;
-        if (keys_on && (rc = ensure(c, c->mkey, std::max<size_t>(M * wk, 1) * sizeof(int))))
-            return rc;
+        if ((rc = ensure(c, c->mkey, std::max<size_t>(M * wk, 1) * sizeof(int)))) return rc;
         if (djoin) {
             const int64_t cnt = (int64_t)F.count();
             const size_t fb = F.key.size() * sizeof(int), ob = (size_t)(cnt + 1) * sizeof(int64_t);
@@ -1667,10 +1679,9 @@ extern "C" int fe_mine(fe_ctx *c, const int32_t *ids, const int32_t *ticks, int6
                                      hipMemcpyHostToDevice, s));
             HIPCHK(c, hipMemcpyAsync((char *)c->mfo.p + ob, joff.data(), ob,
                                      hipMemcpyHostToDevice, s));
-            if (keys_on)
-                launch_join(P<int>(c->mfk), 3 * F.m - 2, (const int64_t *)c->mfo.p,
-                            (const int64_t *)((char *)c->mfo.p + ob), cnt, (int64_t)M,
-                            P<int>(c->mkey), s);
+            launch_join(P<int>(c->mfk), 3 * F.m - 2, (const int64_t *)c->mfo.p,
+                        (const int64_t *)((char *)c->mfo.p + ob), cnt, (int64_t)M,
+                        P<int>(c->mkey), s);
             HIPCHK(c, hipGetLastError());
             // (F, jfirst and joff outlive the stream synchronisation below)
         } else {
@@ -1681,56 +1692,24 @@ extern "C" int fe_mine(fe_ctx *c, const int32_t *ids, const int32_t *ticks, int6
         }
         HostPack hp;
         ivec order;
+        const int64_t emode = c->param[FE_PARAM_ELIMINATION];
         bool elim = emode != 0;
         int64_t smp_n = 0, smp_kept = 0;
-        if (large) {
+        if (emode == 2 && !htile && (int64_t)M >= c->param[FE_PARAM_SAMPLE_MIN]) {
             // two passes pay when the relaxed pass (cost r per candidate,
             // relative to the exact one) prunes more than r of the level;
             // with r >= 1 nothing can, and no sample is taken
+            const double r = (double)c->param[FE_PARAM_PASS1_COST] / 1000.0;
             elim = false;
-            if (r1 < 1.0) {
-                if ((rc = sample_survival(c, ids, ticks, si, mc, num_types, level, (int64_t)M,
-                                          wbound, bbound, theta, smp_n, smp_kept)))
+            if (r < 1.0) {
+                if ((rc = sample_survival(c, ids, ticks, si, level, (int64_t)M, wbound, bbound,
+                                          theta, smp_n, smp_kept)))
                     return rc;
-                elim = (double)smp_kept < (1.0 - r1) * (double)smp_n;
+                elim = (double)smp_kept < (1.0 - r) * (double)smp_n;
             }
         }
         int64_t kept = 0;  // candidates of the exact pass (device tiling)
-        int *nkept_d = P<int>(c->mn) + 1;  // the same, still on the device (chains)
-        if (mc.on) {
-            bool done = false;
-            if (sib) {
-                const int64_t cnt = (int64_t)F.count();
-                const int64_t *first = (const int64_t *)c->mfo.p;
-                if ((rc = ensure(c, c->sord, (size_t)order_ints(cnt, num_types) * sizeof(int))))
-                    return rc;
-                launch_order(P<int>(c->mfk), 3 * F.m - 2, cnt, num_types, P<int>(c->sord), s);
-                if (elim && (rc = mine_siblings(c, mc, true, level, P<int>(c->mfk), first, cnt,
-                                                (int64_t)M, num_types, theta, nullptr, up,
-                                                P<int>(c->sord))))
-                    return rc;
-                if ((rc = mine_siblings(c, mc, false, level, P<int>(c->mfk), first, cnt,
-                                        (int64_t)M, num_types, theta, elim ? up : nullptr, ex,
-                                        P<int>(c->sord))))
-                    return rc;
-                done = true;
-            } else if (level == 2) {
-                if ((rc = mine_pairs_setup(c, mc, levels[0].types, ilo, ihi, num_types)))
-                    return rc;
-                if (elim && (rc = mine_pairs(c, mc, true, theta, nullptr, up))) return rc;
-                if ((!elim || mc.pairs[1]) &&
-                    (rc = mine_pairs(c, mc, false, theta, elim ? up : nullptr, ex)))
-                    return rc;
-                done = mc.pairs[0];
-            }
-            if (!done && (rc = chain_rows(c, mc, key_rows(P<int>(c->mkey), level, (int64_t)M),
-                                          num_types, elim ? CHAIN_TWO_PASS : CHAIN_EXACT, theta,
-                                          up, ex, elim ? "map_two_pass_chain"
-                                                       : "map_exact_chain")))
-                return rc;
-            if (elim) launch_count_ge(up, (int)M, theta, nkept_d, P<int>(c->status), s);
-            else if (c->param[FE_PARAM_KEEP_CANDIDATES]) launch_fill(up, -1, (int64_t)M, s);
-        } else if (!htile) {
+        if (!htile) {
             // prune and tile on the device: pass 1 (Algorithm 3) over every
             // candidate, then pass 2 (Algorithm 1) over those with
             // upper >= theta (Algorithm 4), or over all in one-pass mode
@@ -1778,7 +1757,7 @@ extern "C" int fe_mine(fe_ctx *c, const int32_t *ids, const int32_t *ticks, int6
             // one pass: Algorithm 1 over every candidate, no relaxed count
             launch_fill(up, -1, (int64_t)M, s);
         }
-        int64_t nsurv = !htile ? kept : elim ? (int64_t)order.size() : (int64_t)M;
+        const int64_t nsurv = !htile ? kept : elim ? (int64_t)order.size() : (int64_t)M;
         // pass 2 (Algorithm 1) over the survivors; the others keep -1
         if (htile) launch_fill(ex, -1, (int64_t)M, s);
         if (htile && nsurv > 0) {
@@ -1794,31 +1773,20 @@ extern "C" int fe_mine(fe_ctx *c, const int32_t *ids, const int32_t *ticks, int6
             if ((rc = launch_groups(c, ids, ticks, si, hp.groups, true, ex))) return rc;
         }
         // frequent = exact >= theta
-        if (mc.on) {
-            // (in candidate order, which is key order)
-            if ((rc = ensure(c, c->tscr, (size_t)pick_scratch_ints((int64_t)M) * sizeof(int))))
-                return rc;
-            launch_pick(up, ex, (int64_t)M, theta, P<int>(c->tscr), P<int>(c->mn),
-                        P<int>(c->msel), elim ? up + M : nullptr, ex + M, s);
-        } else {
-            launch_fill(P<int>(c->mn), 0, 1, s);
-            launch_compact(ex, (int)M, theta, nullptr, P<int>(c->msel), P<int>(c->mn), s);
-            launch_gather2(up, ex, P<int>(c->msel), P<int>(c->mn), (int)M, up + M, ex + M, s);
-        }
+        launch_fill(P<int>(c->mn), 0, 1, s);
+        launch_compact(ex, (int)M, theta, nullptr, P<int>(c->msel), P<int>(c->mn), s);
+        launch_gather2(up, ex, P<int>(c->msel), P<int>(c->mn), (int)M, up + M, ex + M, s);
         int cnts[2];
-        HIPCHK(c, hipMemcpyAsync(cnts, P<int>(c->mn), 2 * sizeof(int), hipMemcpyDeviceToHost, s));
+        HIPCHK(c, hipMemcpyAsync(cnts, P<int>(c->mn), sizeof(int), hipMemcpyDeviceToHost, s));
         HIPCHK(c, hipStreamSynchronize(s));
-        if (mc.on) nsurv = elim ? cnts[1] : (int64_t)M;
         cnts[1] = (int)nsurv;
         const int nf = cnts[0];
-        std::vector<int> fsel(nf), fup(nf, -1), fex(nf);
+        std::vector<int> fsel(nf), fup(nf), fex(nf);
         if (nf > 0) {
-            if (!djoin || !mc.on)
-                HIPCHK(c, hipMemcpyAsync(fsel.data(), P<int>(c->msel), nf * sizeof(int),
-                                         hipMemcpyDeviceToHost, s));
-            if (elim || !mc.on)
-                HIPCHK(c, hipMemcpyAsync(fup.data(), up + M, nf * sizeof(int),
-                                         hipMemcpyDeviceToHost, s));
+            HIPCHK(c, hipMemcpyAsync(fsel.data(), P<int>(c->msel), nf * sizeof(int),
+                                     hipMemcpyDeviceToHost, s));
+            HIPCHK(c, hipMemcpyAsync(fup.data(), up + M, nf * sizeof(int), hipMemcpyDeviceToHost,
+                                     s));
             HIPCHK(c, hipMemcpyAsync(fex.data(), ex + M, nf * sizeof(int), hipMemcpyDeviceToHost,
                                      s));
             HIPCHK(c, hipStreamSynchronize(s));
@@ -1852,13 +1820,7 @@ extern "C" int fe_mine(fe_ctx *c, const int32_t *ids, const int32_t *ticks, int6
             // the frequent keys come back from the device
             if (nf > 0) {
                 if ((rc = ensure(c, c->mfsel, (size_t)nf * wk * sizeof(int)))) return rc;
-                if (keys_on)
-                    launch_gather_keys(P<int>(c->mkey), wk, P<int>(c->msel), nf, P<int>(c->mfsel),
-                                       s);
-                else
-                    launch_join_sel(P<int>(c->mfk), 3 * F.m - 2, (const int64_t *)c->mfo.p,
-                                    (const int64_t *)c->mfo.p + F.count() + 1,
-                                    (int64_t)F.count(), P<int>(c->msel), nf, P<int>(c->mfsel), s);
+                launch_gather_keys(P<int>(c->mkey), wk, P<int>(c->msel), nf, P<int>(c->mfsel), s);
                 HIPCHK(c, hipMemcpyAsync(NF.key.data(), c->mfsel.p, (size_t)nf * wk * sizeof(int),
                                          hipMemcpyDeviceToHost, s));
                 HIPCHK(c, hipStreamSynchronize(s));
@@ -1867,7 +1829,7 @@ extern "C" int fe_mine(fe_ctx *c, const int32_t *ids, const int32_t *ticks, int6
             for (int i = 0; i < nf; ++i)
                 std::memcpy(NF.key.data() + (size_t)i * wk, C.at(fsel[i]), wk * sizeof(int));
         }
-        if (!mc.on || !djoin) {
+        {
             HTimer ht(c, "host_sort");
             // (the join writes candidates in key order; the compaction that
             // found the frequent ones does not keep it)
@@ -1901,6 +1863,279 @@ extern "C" int fe_mine(fe_ctx *c, const int32_t *ids, const int32_t *ticks, int6
         if (hp.orig.capacity() > c->lanepool.capacity()) c->lanepool.swap(hp.orig);
         c->orderpool.swap(order);
     }
+    return FE_OK;
+}
+
+// The same by chains: candidates, counts and frequent sets stay on the device;
+// the host learns each level's sizes and copies its frequent set while the
+// next level is counted.
+int mine_levels(fe_ctx *c, MineChains &mc, int64_t n, int num_types, int theta, int max_level,
+                const std::vector<int> &ilo, const std::vector<int> &ihi,
+                std::vector<LevelOut> &levels)
+{
+    int rc;
+    hipStream_t s = c->stream;
+    const int n_iv = (int)ilo.size();
+    const std::vector<int> F1 = levels[0].types;
+    const int64_t nF = (int64_t)F1.size();
+    if (max_level < 2 || nF == 0 || n_iv == 0) return FE_OK;
+    if ((rc = mine_setup(c, mc, F1, ilo, ihi, num_types))) return rc;
+    const int64_t emode = c->param[FE_PARAM_ELIMINATION];
+    const double r1 = (double)c->param[FE_PARAM_PASS1_COST] / 1000.0;
+    const bool keep = c->param[FE_PARAM_KEEP_CANDIDATES] != 0;
+    const int *st = P<int>(c->status);
+    if ((rc = ensure_host(c, 8))) return rc;
+    volatile int *host = c->host;
+    // the level whose frequent set is on its way to pinned memory
+    int64_t late_n = 0;
+    bool late_up = false, late = false;
+    auto finish = [&]() -> int {
+        if (!late) return FE_OK;
+        late = false;
+        LevelOut &L = levels.back();
+        const size_t m = L.level, f = (size_t)late_n;
+        const size_t len[5] = {f * m, f * (m - 1), f * (m - 1), f, f};
+        const int *src = c->pin;
+        for (int k = 0; k < 5; ++k) {
+            // (types, lo, hi, exact, then upper if there is one)
+            const int q = k == 3 ? 4 : k == 4 ? 3 : k;
+            int *d = (int *)std::malloc(std::max<size_t>(len[k], 1) * sizeof(int));
+            if (!d) return fail(c, FE_ENOMEM, "host allocation failed");
+            L.raw[q] = d;
+            if (k == 4 && !late_up) {
+                std::fill(d, d + f, -1);
+            } else if (len[k]) {
+                std::memcpy(d, src, len[k] * sizeof(int));
+                src += len[k];
+            }
+        }
+        return FE_OK;
+    };
+    int64_t cnt = 0;  // frequent episodes of the level before, their keys in mfk
+    for (int level = 2; level <= max_level; ++level) {
+        const double t_gen = now_ms();
+        const int wk = 3 * level - 2, wf = wk - 3;  // ints per key, here and one level up
+        int64_t M = nF * nF * n_iv;
+        int64_t *first = nullptr, *off = nullptr;
+        if (level > 2) {
+            if ((rc = ensure(c, c->mfo, (size_t)(2 * (cnt + 1) + 1) * sizeof(int64_t))) ||
+                (rc = ensure(c, c->tscr, (size_t)join_plan_ints(cnt) * sizeof(int))))
+                return rc;
+            first = (int64_t *)c->mfo.p;
+            off = first + cnt + 1;
+            unsigned long long *tot = (unsigned long long *)(off + cnt + 1);
+            launch_join_plan(P<int>(c->mfk), wf, cnt, first, off, tot, P<int>(c->tscr), s);
+            HIPCHK(c, hipMemcpyAsync((void *)(c->host + 4), tot, sizeof *tot,
+                                     hipMemcpyDeviceToHost, s));
+            HIPCHK(c, hipStreamSynchronize(s));
+            M = (int64_t)(unsigned)host[4] | (int64_t)host[5] << 32;
+        }
+        if (M == 0) break;
+        if (M >= (int64_t)1 << 31 || M * level >= (int64_t)1 << 31)
+            return fail(c, FE_ENOMEM, "level %d has too many candidates (%zu)", level, (size_t)M);
+        const double t0 = now_ms();
+        if ((rc = ensure(c, c->mup, 2 * M * sizeof(int))) ||
+            (rc = ensure(c, c->mex, 2 * M * sizeof(int))) ||
+            (rc = ensure(c, c->msel, M * sizeof(int))) ||
+            (rc = ensure(c, c->mn, 4 * sizeof(int))) ||
+            (rc = ensure(c, c->tscr, (size_t)pick_scratch_ints(M) * sizeof(int))))
+            return rc;
+        int *up = P<int>(c->mup), *ex = P<int>(c->mex);
+        const bool large = emode == 2 && M >= c->param[FE_PARAM_SAMPLE_MIN];
+        // two passes pay when the relaxed pass (cost r per candidate, relative
+        // to the exact one) prunes more than r of the level; with r >= 1
+        // nothing can, and no sample is taken
+        const bool sample = large && r1 < 1.0;
+        const bool relaxed = emode != 0 && (!large || sample);  // (may run)
+        if (level > 2 && relaxed && mc.pairs[0] && !mc.pairs[1] &&
+            (rc = mine_pairs(c, mc, true, theta, nullptr, nullptr)))
+            return rc;
+        const bool sib = level > 2 && mc.pairs[0] && (!relaxed || mc.pairs[1]);
+        // keys are written out only when something asks for them
+        auto write_keys = [&]() -> int {
+            int rc;
+            if ((rc = ensure(c, c->mkey, (size_t)M * wk * sizeof(int)))) return rc;
+            if (level == 2)
+                launch_pair_keys(mc.F1, (int)nF, mc.ivlo, mc.ivhi, n_iv, nullptr, M,
+                                 P<int>(c->mkey), s);
+            else
+                launch_join(P<int>(c->mfk), wf, first, off, cnt, M, P<int>(c->mkey), s);
+            return FE_OK;
+        };
+        bool keys = keep || sample || (level > 2 && !sib);
+        if (keys && (rc = write_keys())) return rc;
+        LevelOut Lv;
+        Lv.level = level;
+        Lv.ncand = M;
+        bool elim = emode != 0 && !large;
+        if (sample) {
+            if ((rc = sample_chains(c, mc, num_types, level, M, theta, Lv.sample_n,
+                                    Lv.sample_kept)))
+                return rc;
+            elim = (double)Lv.sample_kept < (1.0 - r1) * (double)Lv.sample_n;
+        }
+        bool done = false;
+        if (sib) {
+            if ((rc = ensure(c, c->sord, (size_t)order_ints(cnt, num_types) * sizeof(int))))
+                return rc;
+            launch_order(P<int>(c->mfk), wf, cnt, num_types, P<int>(c->sord), s);
+            if (elim && (rc = mine_siblings(c, mc, true, level, P<int>(c->mfk), first, off, cnt, M,
+                                            num_types, theta, nullptr, up, P<int>(c->sord))))
+                return rc;
+            if ((rc = mine_siblings(c, mc, false, level, P<int>(c->mfk), first, off, cnt, M,
+                                    num_types, theta, elim ? up : nullptr, ex, P<int>(c->sord))))
+                return rc;
+            done = true;
+        } else if (level == 2) {
+            if (elim && (rc = mine_pairs(c, mc, true, theta, nullptr, up))) return rc;
+            if ((!elim || mc.pairs[1]) &&
+                (rc = mine_pairs(c, mc, false, theta, elim ? up : nullptr, ex)))
+                return rc;
+            done = mc.pairs[0];
+            if (!done && !keys && (rc = write_keys())) return rc;
+        }
+        if (!done &&
+            (rc = chain_rows(c, mc, key_rows(P<int>(c->mkey), level, M), num_types,
+                             elim ? CHAIN_TWO_PASS : CHAIN_EXACT, theta, up, ex,
+                             elim ? "map_two_pass_chain" : "map_exact_chain")))
+            return rc;
+        int *mn = P<int>(c->mn);
+        if (elim) launch_count_ge(up, (int)M, theta, mn + 1, st, s);
+        else if (keep) launch_fill(up, -1, M, s);
+        // frequent: exact >= theta, in key order
+        int *fup = elim ? up + M : nullptr, *fex = ex + M;
+        if (level == 2)
+            launch_pick_pairs(up, ex, (int)nF, n_iv, mc.ord, theta, P<int>(c->tscr), mn,
+                              P<int>(c->msel), fup, fex, s);
+        else
+            launch_pick(up, ex, M, theta, P<int>(c->tscr), mn, P<int>(c->msel), fup, fex, s);
+        HIPCHK(c, hipGetLastError());
+        HIPCHK(c, hipMemcpyAsync((void *)c->host, mn, 2 * sizeof(int), hipMemcpyDeviceToHost, s));
+        // (the host copies the level before meanwhile)
+        if ((rc = finish())) return rc;
+        HIPCHK(c, hipStreamSynchronize(s));
+        const int64_t nf = host[0];
+        Lv.nsurv = elim ? (int64_t)host[1] : M;
+        Lv.nfreq = nf;
+        Lv.passes = elim ? 2 : 1;
+        if (keep) {
+            Lv.all_upper.resize(M);
+            Lv.all_exact.resize(M);
+            std::vector<int> kv((size_t)M * wk);
+            HIPCHK(c, hipMemcpyAsync(Lv.all_upper.data(), up, M * sizeof(int),
+                                     hipMemcpyDeviceToHost, s));
+            HIPCHK(c, hipMemcpyAsync(Lv.all_exact.data(), ex, M * sizeof(int),
+                                     hipMemcpyDeviceToHost, s));
+            HIPCHK(c, hipMemcpyAsync(kv.data(), P<int>(c->mkey), kv.size() * sizeof(int),
+                                     hipMemcpyDeviceToHost, s));
+            HIPCHK(c, hipStreamSynchronize(s));
+            split_keys(kv.data(), (size_t)M, level, Lv.all_types, Lv.all_lo, Lv.all_hi);
+        }
+        // the frequent keys for the next level, and the set split for the host
+        const size_t ints = (size_t)nf * (3 * level - 2), all = ints + (size_t)nf * (elim ? 2 : 1);
+        if (nf > 0) {
+            if ((rc = ensure(c, c->mfsel, ints * sizeof(int))) ||
+                (rc = ensure(c, c->msplit, ints * sizeof(int))) || (rc = ensure_pin(c, all)))
+                return rc;
+            if (level == 2)
+                launch_pair_keys(mc.F1, (int)nF, mc.ivlo, mc.ivhi, n_iv, P<int>(c->msel), nf,
+                                 P<int>(c->mfsel), s);
+            else
+                launch_join_sel(P<int>(c->mfk), wf, first, off, cnt, P<int>(c->msel), (int)nf,
+                                P<int>(c->mfsel), s);
+            launch_split_keys(P<int>(c->mfsel), level, nf, P<int>(c->msplit), s);
+            HIPCHK(c, hipGetLastError());
+            HIPCHK(c, hipMemcpyAsync(c->pin, c->msplit.p, ints * sizeof(int),
+                                     hipMemcpyDeviceToHost, s));
+            HIPCHK(c, hipMemcpyAsync(c->pin + ints, fex, nf * sizeof(int), hipMemcpyDeviceToHost,
+                                     s));
+            if (elim)
+                HIPCHK(c, hipMemcpyAsync(c->pin + ints + nf, fup, nf * sizeof(int),
+                                         hipMemcpyDeviceToHost, s));
+            std::swap(c->mfk, c->mfsel);
+        }
+        Lv.gen_ms = t0 - t_gen;
+        Lv.count_ms = now_ms() - t0;
+        levels.push_back(std::move(Lv));
+        late_n = nf;
+        late_up = elim;
+        late = true;
+        cnt = nf;
+        if (nf == 0) break;
+    }
+    HIPCHK(c, hipStreamSynchronize(s));
+    return finish();
+}
+
+}  // namespace
+
+extern "C" int fe_mine(fe_ctx *c, const int32_t *ids, const int32_t *ticks, int64_t n,
+                       int32_t num_types, const int32_t *iv_lo, const int32_t *iv_hi, int32_t n_iv,
+                       int32_t theta, int32_t max_level, fe_result **out)
+{
+    int rc;
+    const double t_call = now_ms();
+    if (!out) return fail(c, FE_EINVAL, "null result pointer");
+    *out = nullptr;
+    if ((rc = check_common(c, ids, ticks, n, num_types))) return rc;
+    if (max_level < 1 || max_level > NMAX) return fail(c, FE_EINVAL, "max_level outside [1,8]");
+    if (n_iv < 0 || (n_iv > 0 && (!iv_lo || !iv_hi)))
+        return fail(c, FE_EINVAL, "bad interval set");
+    std::vector<int> ilo(iv_lo, iv_lo + n_iv), ihi(iv_hi, iv_hi + n_iv);
+    for (int k = 0; k < n_iv; ++k) {
+        const int l = ilo[k], h = ihi[k];
+        if (l < 0 || l >= h || h >= TICK_LIMIT)
+            return fail(c, FE_EINVAL, "interval %d = (%d,%d] invalid", k, l, h);
+        if ((int64_t)h * max_level >= TICK_LIMIT)
+            return fail(c, FE_EINVAL, "interval %d too wide for max_level", k);
+    }
+    HIPCHK(c, hipSetDevice(c->device));
+    c->stats = fe_stats{};
+    hipStream_t s = c->stream;
+    MineChains mc;
+    std::vector<int> hist;
+    if (chain_takes(c, n, num_types) && c->param[FE_PARAM_HOST_TILING] == 0)
+        if ((rc = mine_index(c, ids, ticks, n, num_types, mc, hist))) return rc;
+    StreamInfo si{};
+    if (!mc.on && (rc = stream_info(c, ids, ticks, (int)n, num_types, si))) return rc;
+
+    std::vector<LevelOut> levels;
+    // level 1: a one-node episode occurs at every event of its type
+    const double t0 = now_ms();
+    if (!mc.on) {
+        if ((rc = ensure(c, c->mn, (size_t)num_types * sizeof(int)))) return rc;
+        launch_fill(P<int>(c->mn), 0, num_types, s);
+        launch_histogram(ids, (int)n, num_types, P<int>(c->mn), s);
+        hist.resize(num_types);
+        HIPCHK(c, hipMemcpyAsync(hist.data(), P<int>(c->mn), num_types * sizeof(int),
+                                 hipMemcpyDeviceToHost, s));
+        HIPCHK(c, hipStreamSynchronize(s));
+    }
+    {
+        LevelOut L1;
+        L1.level = 1;
+        L1.ncand = num_types;
+        L1.nsurv = num_types;
+        for (int e = 0; e < num_types; ++e)
+            if (hist[e] >= theta) {
+                L1.types.push_back(e);
+                L1.upper.push_back(hist[e]);
+                L1.exact.push_back(hist[e]);
+            }
+        L1.nfreq = (int64_t)L1.types.size();
+        L1.passes = 1;
+        if (c->param[FE_PARAM_KEEP_CANDIDATES]) {
+            for (int e = 0; e < num_types; ++e) L1.all_types.push_back(e);
+            L1.all_upper = hist;
+            L1.all_exact = hist;
+        }
+        L1.gen_ms = 0;
+        L1.count_ms = now_ms() - t0;
+        levels.push_back(std::move(L1));
+    }
+    rc = mc.on ? mine_levels(c, mc, n, num_types, theta, max_level, ilo, ihi, levels)
+               : mine_events(c, ids, ticks, si, theta, max_level, ilo, ihi, levels);
+    if (rc) return rc;
 
     fe_result *r = (fe_result *)std::calloc(1, sizeof(fe_result));
     if (!r) return fail(c, FE_ENOMEM, "host allocation failed");
@@ -1910,6 +2145,11 @@ extern "C" int fe_mine(fe_ctx *c, const int32_t *ids, const int32_t *ticks, int6
         std::free(r);
         return fail(c, FE_ENOMEM, "host allocation failed");
     }
+    auto raw = [](int *&p) {
+        int *q = p;
+        p = nullptr;
+        return q;
+    };
     auto dup = [](const std::vector<int> &v) {
         int *p = (int *)std::malloc(std::max<size_t>(v.size(), 1) * sizeof(int));
         if (p && !v.empty()) std::memcpy(p, v.data(), v.size() * sizeof(int));
@@ -1917,16 +2157,16 @@ extern "C" int fe_mine(fe_ctx *c, const int32_t *ids, const int32_t *ticks, int6
     };
     for (size_t i = 0; i < levels.size(); ++i) {
         fe_level &d = r->levels[i];
-        const LevelOut &L = levels[i];
+        LevelOut &L = levels[i];
         d.level = L.level;
         d.n_candidates = L.ncand;
         d.n_survivors = L.nsurv;
         d.n_frequent = L.nfreq;
-        d.types = dup(L.types);
-        d.lo = dup(L.lo);
-        d.hi = dup(L.hi);
-        d.upper = dup(L.upper);
-        d.exact = dup(L.exact);
+        d.types = L.raw[0] ? raw(L.raw[0]) : dup(L.types);
+        d.lo = L.raw[1] ? raw(L.raw[1]) : dup(L.lo);
+        d.hi = L.raw[2] ? raw(L.raw[2]) : dup(L.hi);
+        d.upper = L.raw[3] ? raw(L.raw[3]) : dup(L.upper);
+        d.exact = L.raw[4] ? raw(L.raw[4]) : dup(L.exact);
         d.gen_ms = L.gen_ms;
         d.count_ms = L.count_ms;
         d.passes = L.passes;

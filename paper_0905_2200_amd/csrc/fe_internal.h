@@ -138,6 +138,22 @@ void launch_join_sel(const int *F, int w, const int64_t *first, const int64_t *o
 int64_t pick_scratch_ints(int64_t M);
 void launch_pick(const int *up, const int *ex, int64_t M, int theta, int *scratch, int *total,
                  int *sel, int *out_up, int *out_ex, hipStream_t s);
+// The join's ranges found on the device (scratch: join_plan_ints ints):
+// first[a], off[0..cnt], *total the number of candidates.
+int64_t join_plan_ints(int64_t cnt);
+void launch_join_plan(const int *F, int w, int64_t cnt, int64_t *first, int64_t *off,
+                      unsigned long long *total, int *scratch, hipStream_t s);
+// Level 2 (every ordered pair of nF types times n_iv intervals, in that
+// order): the candidates with ex >= theta in key order (ord: see PairAt), and
+// the keys of candidates sel[0..n) (null: all).
+void launch_pick_pairs(const int *up, const int *ex, int nF, int n_iv, const int *ord, int theta,
+                       int *scratch, int *total, int *sel, int *out_up, int *out_ex,
+                       hipStream_t s);
+void launch_pair_keys(const int *F1, int nF, const int *ivlo, const int *ivhi, int n_iv,
+                      const int *sel, int64_t n, int *out, hipStream_t s);
+// n keys of m nodes as types [n][m], lo [n][m-1] and hi [n][m-1], one after
+// the other.
+void launch_split_keys(const int *key, int m, int64_t n, int *out, hipStream_t s);
 void launch_gather_keys(const int *key, int w, const int *sel, int nsel, int *out, hipStream_t s);
 // Sample of a level for the elimination decision: every SAMPLE_STRIDE-th
 // block of 64 consecutive candidates; sample_count(M) candidates.

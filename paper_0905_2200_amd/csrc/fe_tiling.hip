@@ -424,6 +424,122 @@ __global__ void k_pick(const int *__restrict__ up, const int *__restrict__ ex, i
     if (out_up) out_up[at] = up[i];
 }
 
+// Join plan: the range of beta for each alpha of the sorted F (the first
+// m - 1 nodes and hops of beta equal alpha's last m - 1), its length in num;
+// *total += all lengths.
+__global__ void k_join_plan(const int *__restrict__ F, int w, int cnt,
+                            int64_t *__restrict__ first, int *__restrict__ num,
+                            unsigned long long *__restrict__ total)
+{
+    const int a = blockIdx.x * TB + threadIdx.x;
+    const int ov = w - 3;
+    int n = 0;
+    if (a < cnt) {
+        const int *suf = F + (int64_t)a * w + 3;
+        // F[b]'s prefix against the suffix: -1, 0, 1
+        auto cmp = [&](int b) {
+            const int *p = F + (int64_t)b * w;
+            for (int k = 0; k < ov; ++k)
+                if (p[k] != suf[k]) return p[k] < suf[k] ? -1 : 1;
+            return 0;
+        };
+        int lo = 0, hi = cnt;
+        while (lo < hi) {
+            const int mid = (lo + hi) >> 1;
+            if (cmp(mid) < 0) lo = mid + 1;
+            else hi = mid;
+        }
+        int lo2 = lo, hi2 = cnt;
+        while (lo2 < hi2) {
+            const int mid = (lo2 + hi2) >> 1;
+            if (cmp(mid) <= 0) lo2 = mid + 1;
+            else hi2 = mid;
+        }
+        n = lo2 - lo;
+        first[a] = lo;
+        num[a] = n;
+    }
+    unsigned long long s = n;
+    for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off);
+    if ((threadIdx.x & (WAVE - 1)) == 0 && s) atomicAdd(total, s);
+}
+
+__global__ void k_widen(const int *__restrict__ a, const int *__restrict__ total, int cnt,
+                        int64_t *__restrict__ out)
+{
+    const int i = blockIdx.x * TB + threadIdx.x;
+    if (i < cnt) out[i] = a[i];
+    if (i == cnt) out[i] = *total;
+}
+
+// Level 2 by position: candidate (a, b, k) of the frequent types' ranks and
+// interval k is number (a * nF + b) * n_iv + k.  In key order a's candidates
+// go by interval, b and then equal intervals: ord holds the intervals sorted,
+// then for each sorted place the first place with the same interval and their
+// number.
+struct PairAt {
+    int nF, n_iv;
+    const int *ord;
+    __device__ int64_t operator()(int64_t i) const
+    {
+        const int64_t per = (int64_t)nF * n_iv, a = i / per, r = i - a * per;
+        const int at = (int)(r / nF), g = ord[n_iv + at], same = ord[2 * n_iv + at];
+        const int64_t q = r - (int64_t)g * nF, b = q / same;
+        return (a * nF + b) * n_iv + ord[g + (int)(q - b * same)];
+    }
+};
+struct PairAtLeast {
+    const int *a;
+    int theta;
+    PairAt at;
+    __device__ int operator()(int64_t i) const { return a[at(i)] >= theta ? 1 : 0; }
+};
+__global__ void k_pick_pairs(const int *__restrict__ up, const int *__restrict__ ex, int64_t M,
+                             int theta, PairAt at, const int *__restrict__ pos,
+                             int *__restrict__ sel, int *__restrict__ out_up,
+                             int *__restrict__ out_ex)
+{
+    const int64_t i = blockIdx.x * (int64_t)TB + threadIdx.x;
+    if (i >= M) return;
+    const int64_t c = at(i);
+    const int x = ex[c];
+    if (x < theta) return;
+    const int to = pos[i];
+    sel[to] = (int)c;
+    out_ex[to] = x;
+    if (out_up) out_up[to] = up[c];
+}
+
+// keys of level 2's candidates sel[0..n) (all of them in order: sel null)
+__global__ void k_pair_keys(const int *__restrict__ F1, int nF, const int *__restrict__ ivlo,
+                            const int *__restrict__ ivhi, int n_iv, const int *__restrict__ sel,
+                            int64_t n, int *__restrict__ out)
+{
+    const int64_t i = blockIdx.x * (int64_t)TB + threadIdx.x;
+    if (i >= n) return;
+    const int64_t c = sel ? sel[i] : i;
+    const int k = (int)(c % n_iv);
+    const int64_t ab = c / n_iv;
+    int *o = out + i * 4;
+    o[0] = F1[ab / nF];
+    o[1] = ivlo[k];
+    o[2] = ivhi[k];
+    o[3] = F1[ab % nF];
+}
+
+// n keys of m nodes to rows of types, lo and hi (in that order in out)
+__global__ void k_split_keys(const int *__restrict__ key, int m, int64_t n, int *__restrict__ out)
+{
+    const int w = 3 * m - 2;
+    const int64_t t = blockIdx.x * (int64_t)TB + threadIdx.x;
+    if (t >= n * w) return;
+    const int64_t i = t / w;
+    const int q = (int)(t - i * w), k = q / 3, r = q % 3;
+    const int v = key[t];
+    if (r == 0) out[i * m + k] = v;
+    else out[n * m + (r - 1) * n * (m - 1) + i * (m - 1) + k] = v;
+}
+
 __global__ void k_gather_keys(const int *__restrict__ key, int w, const int *__restrict__ sel,
                               int nsel, int *__restrict__ out)
 {
@@ -478,6 +594,49 @@ void launch_pick(const int *up, const int *ex, int64_t M, int theta, int *scratc
     if (M > 0)
         hipLaunchKernelGGL(k_pick, dim3((unsigned)((M + TB - 1) / TB)), dim3(TB), 0, s, up, ex, M,
                            theta, scratch, sel, out_up, out_ex);
+}
+
+int64_t join_plan_ints(int64_t cnt) { return 2 * cnt + 2 + scan_scratch_ints(cnt); }
+
+void launch_join_plan(const int *F, int w, int64_t cnt, int64_t *first, int64_t *off,
+                      unsigned long long *total, int *scratch, hipStream_t s)
+{
+    launch_fill((int *)total, 0, 2, s);
+    if (cnt <= 0) return;
+    int *num = scratch, *pos = num + cnt, *sc = pos + cnt;
+    hipLaunchKernelGGL(k_join_plan, dim3((unsigned)((cnt + TB - 1) / TB)), dim3(TB), 0, s, F, w,
+                       (int)cnt, first, num, total);
+    launch_scan_excl(num, cnt, pos, sc, s);
+    hipLaunchKernelGGL(k_widen, dim3((unsigned)((cnt + TB) / TB)), dim3(TB), 0, s, pos, sc,
+                       (int)cnt, off);
+}
+
+void launch_pick_pairs(const int *up, const int *ex, int nF, int n_iv, const int *ord, int theta,
+                       int *scratch, int *total, int *sel, int *out_up, int *out_ex,
+                       hipStream_t s)
+{
+    const int64_t M = (int64_t)nF * nF * n_iv;
+    const PairAt at{nF, n_iv, ord};
+    scan(PairAtLeast{ex, theta, at}, nullptr, M, scratch, scratch + M, total, s);
+    if (M > 0)
+        hipLaunchKernelGGL(k_pick_pairs, dim3((unsigned)((M + TB - 1) / TB)), dim3(TB), 0, s, up,
+                           ex, M, theta, at, scratch, sel, out_up, out_ex);
+}
+
+void launch_pair_keys(const int *F1, int nF, const int *ivlo, const int *ivhi, int n_iv,
+                      const int *sel, int64_t n, int *out, hipStream_t s)
+{
+    if (n <= 0) return;
+    hipLaunchKernelGGL(k_pair_keys, dim3((unsigned)((n + TB - 1) / TB)), dim3(TB), 0, s, F1, nF,
+                       ivlo, ivhi, n_iv, sel, n, out);
+}
+
+void launch_split_keys(const int *key, int m, int64_t n, int *out, hipStream_t s)
+{
+    const int64_t t = n * (3 * m - 2);
+    if (t <= 0) return;
+    hipLaunchKernelGGL(k_split_keys, dim3((unsigned)((t + TB - 1) / TB)), dim3(TB), 0, s, key, m,
+                       n, out);
 }
 
 void launch_join_sel(const int *F, int w, const int64_t *first, const int64_t *off, int64_t cnt,
