@@ -6,6 +6,13 @@
 
 namespace fe {
 
+// A pointer read from memory as one to global memory (the compiler would
+// otherwise go through flat accesses).
+template <class T> __device__ __forceinline__ T *global_ptr(T *p)
+{
+    return (T *)(__attribute__((address_space(1))) T *)(unsigned long long)p;
+}
+
 // ------------------------------------------------------------------ index
 // A stable counting sort by type: one wave per chunk of consecutive events
 // counts its types, the counts are scanned type by type, and the wave then
@@ -100,19 +107,32 @@ ChainIdx index_view(const IndexPlan &p, int *base)
 
 namespace {
 
+__device__ __forceinline__ IndexJob global_job(IndexJob j)
+{
+    j.ids = global_ptr(j.ids);
+    j.ticks = global_ptr(j.ticks);
+    j.et = global_ptr(j.et);
+    j.ei = global_ptr(j.ei);
+    j.tab = global_ptr(j.tab);
+    j.hist = global_ptr(j.hist);
+    j.off = global_ptr(j.off);
+    j.ty = global_ptr(j.ty);
+    return j;
+}
+
 // The job of a block, by its number among all jobs' chunks or types (FIRST
 // reads a job's first).
 template <class First>
 __device__ __forceinline__ IndexJob job_of(const IndexSet &x, int block, First first)
 {
-    if (!x.jobs) return x.one;
+    if (!x.jobs) return global_job(x.one);
     int lo = 0, hi = x.njobs;  // the last job that starts by block
     while (hi - lo > 1) {
         const int mid = (lo + hi) >> 1;
         if (first(x.jobs[mid]) <= block) lo = mid;
         else hi = mid;
     }
-    return x.jobs[lo];
+    return global_job(x.jobs[lo]);
 }
 
 // Blocks [0, chunks): stream checks (ticks non-decreasing and in range, ids
@@ -206,7 +226,7 @@ __global__ __launch_bounds__(TYB) void k_ix_types(IndexSet x, int scan_here, con
     const int st = *status;
     if (threadIdx.x == 0 && blockIdx.x == 0 && hstat) *hstat = st;
     if (st) return;
-    const IndexJob j = x.jobs ? x.jobs[blockIdx.x] : x.one;
+    const IndexJob j = global_job(x.jobs ? x.jobs[blockIdx.x] : x.one);
     const int n = j.n, T = j.T, nch = j.nch;
     const int *hist = j.hist;
     int *off = j.off, *et = j.et, *ei = j.ei;
@@ -569,22 +589,17 @@ __device__ __forceinline__ void chain_item(const ChainJob &j, int64_t item, int 
     const int M = j.rows.M;
     const int p = (int)((unsigned)item / (unsigned)M), m = (int)((unsigned)item - (unsigned)p * (unsigned)M);
     const int lane = __lane_id();
+    // (P > 1: MODE is EXACT or RELAXED; with upper set, survivors only)
+    if (MODE == CHAIN_EXACT && j.P > 1 && j.upper && j.upper[m] < j.theta) return;
     NodeRow row;
-    int dr = -1, dc = 0, s1 = FAR_TICK;
-    if (j.P > 1) {
-        // (MODE is EXACT or RELAXED; theta > 0 with upper set: survivors only)
-        constexpr bool REL = MODE == CHAIN_RELAXED;
-        if (!REL && j.upper && j.upper[m] < j.theta) return;
-        const int N = load_row(j.ix, j.rows, m, row);
-        const int c = rdl(row.count, 0);
-        const int a0 = seg_at(c, p, j.P), a1 = seg_at(c, p + 1, j.P);
-        int r = -1, cnt = 0;
-        count_range<REL, false>(j.ix, row, N, a0, a1, lds, r, cnt, dr, dc, s1);
-        if (lane == 0) j.seg[(int64_t)p * M + m] = make_int4(cnt, r, s1, 0);
-        return;
-    }
     const int N = load_row(j.ix, j.rows, m, row);
-    if (j.count_io) {
+    const int c = rdl(row.count, 0);
+    int dr = -1, dc = 0, s1 = FAR_TICK;
+    int a0 = 0, a1 = c, r = -1;
+    if (MODE != CHAIN_TWO_PASS && j.P > 1) {
+        a0 = seg_at(c, p, j.P);
+        a1 = seg_at(c, p + 1, j.P);
+    } else if (MODE != CHAIN_TWO_PASS && j.count_io) {
         // chains that start after the last completion, and no more than the
         // episode's width before the first new event: the others have been
         // counted or can complete at no new event
@@ -592,34 +607,35 @@ __device__ __forceinline__ void chain_item(const ChainJob &j, int64_t item, int 
         last = last < j.from ? last : j.from - 1;
         const int start = rdl(row.start, 0);
         const int x = j.t_from[0] - row_width(row, N);
-        int lo = 0, hi = rdl(row.count, 0);
-        const int c = hi;
-        while (lo < hi) {
-            const int mid = (lo + hi) >> 1;
+        int hi = c;
+        while (a0 < hi) {
+            const int mid = (a0 + hi) >> 1;
             const bool before = (j.ix.ei[start + mid] <= last) | (j.ix.et[start + mid] < x);
-            if (bal(before) != 0) lo = mid + 1;
+            if (bal(before) != 0) a0 = mid + 1;
             else hi = mid;
         }
-        int r = last, cnt = 0;
-        count_range<MODE == CHAIN_RELAXED, false>(j.ix, row, N, lo, c, lds, r, cnt, dr, dc, s1);
-        if (lane == 0 && cnt) {
+        r = last;
+    }
+    bool take = true;
+    if (MODE == CHAIN_TWO_PASS) {
+        int cnt = 0;
+        count_range<true, false>(j.ix, row, N, a0, a1, lds, r, cnt, dr, dc, s1);
+        if (lane == 0) j.upper[m] = cnt;
+        take = cnt >= j.theta;
+        r = -1;
+    }
+    int cnt = 0;
+    if (take) count_range<MODE == CHAIN_RELAXED, false>(j.ix, row, N, a0, a1, lds, r, cnt, dr, dc, s1);
+    if (lane != 0) return;
+    if (MODE != CHAIN_TWO_PASS && j.P > 1) {
+        j.seg[(int64_t)p * M + m] = make_int4(cnt, r, s1, 0);
+    } else if (MODE != CHAIN_TWO_PASS && j.count_io) {
+        if (cnt) {
             j.count_io[m] += cnt;
             j.last_io[m] = r;
         }
-        return;
-    }
-    const int c = rdl(row.count, 0);
-    bool take = true;
-    if (MODE != CHAIN_EXACT) {
-        int r = -1, cnt = 0;
-        count_range<true, false>(j.ix, row, N, 0, c, lds, r, cnt, dr, dc, s1);
-        if (lane == 0) j.upper[m] = cnt;
-        take = cnt >= j.theta;
-    }
-    if (MODE != CHAIN_RELAXED) {
-        int r = -1, cnt = 0;
-        if (take) count_range<false, false>(j.ix, row, N, 0, c, lds, r, cnt, dr, dc, s1);
-        if (lane == 0) j.exact[m] = take ? cnt : -1;
+    } else {
+        (MODE == CHAIN_RELAXED ? j.upper : j.exact)[m] = take ? cnt : -1;
     }
 }
 
@@ -646,7 +662,20 @@ __global__ __launch_bounds__(WAVE) void k_chains(const ChainJob *jobs, const int
         if (first[mid] <= item) lo = mid;
         else hi = mid;
     }
-    const ChainJob j = jobs[lo];
+    ChainJob j = jobs[lo];
+    j.ix.et = global_ptr(j.ix.et);
+    j.ix.ei = global_ptr(j.ix.ei);
+    j.ix.tab = global_ptr(j.ix.tab);
+    j.ix.ty = global_ptr(j.ix.ty);
+    j.rows.ty = global_ptr(j.rows.ty);
+    j.rows.lo = global_ptr(j.rows.lo);
+    j.rows.hi = global_ptr(j.rows.hi);
+    j.rows.len = global_ptr(j.rows.len);
+    j.upper = global_ptr(j.upper);
+    j.exact = global_ptr(j.exact);
+    j.seg = nullptr;  // (P = 1, not incremental)
+    j.count_io = nullptr;
+    j.P = 1;
     chain_item<MODE>(j, item - first[lo], lds);
 }
 
@@ -769,9 +798,11 @@ namespace {
 // mask[place][q], q = (type >> 6) * n_iv + h: bit (type & 63) is set where the
 // type has an event in hop h's range after the event at the place (an entry of
 // the lists): exact, ticks in (t + lo, t + hi]; relaxed, later events up to
-// tick t + hi.  One thread per 32 types of a place and hop; the types' lists
-// are searched at ticks that ascend along a wave, so the reads are nearly
-// coalesced.
+// tick t + hi.  One thread per 32 types of a place and up to four hops: each
+// type's list is searched once, at the ticks' narrowest start, and four entries
+// from there on settle nearly every hop; the ticks ascend along a wave, so the
+// reads are nearly coalesced.
+constexpr int MH = 4;  // hops a thread takes
 template <bool REL>
 __global__ __launch_bounds__(256) void k_masks(ChainIdx ix, int places, int T, int n_iv,
                                                const int *__restrict__ ivlo,
@@ -779,33 +810,57 @@ __global__ __launch_bounds__(256) void k_masks(ChainIdx ix, int places, int T, i
                                                unsigned *__restrict__ mask, int Q)
 {
     const int place = blockIdx.x * 256 + threadIdx.x;
-    const int h = blockIdx.y % n_iv, w = blockIdx.y / n_iv;  // types 32 w ...
+    const int hg = (n_iv + MH - 1) / MH;
+    const int h0 = blockIdx.y % hg * MH, w = blockIdx.y / hg;  // hops h0 .., types 32 w ..
+    const int nh = n_iv - h0 < MH ? n_iv - h0 : MH;
     if (place >= places) return;
     const int t = ix.et[place];
     if (t == FAR_TICK) return;  // a guard
-    const int x = REL ? t : t + ivlo[h] + 1, lim = t + ivhi[h];
+    int lo[MH], lim[MH], least = FAR_TICK;
+#pragma unroll
+    for (int h = 0; h < MH; ++h) {
+        const int k = h0 + (h < nh ? h : 0);
+        lo[h] = REL ? t : t + ivlo[k] + 1;
+        lim[h] = t + ivhi[k];
+        least = lo[h] < least ? lo[h] : least;
+    }
     const int i = REL ? ix.ei[place] : 0;
-    unsigned bits = 0;
+    unsigned bits[MH] = {0, 0, 0, 0};
     const int e1 = (w + 1) * 32 < T ? (w + 1) * 32 : T;
     for (int e = w * 32; e < e1; ++e) {
         const TypeIdx ty = ix.ty[e];
-        const int b = bucket(x, ty.t0, ty.sh, ty.nb);
-        int a = ix.tab[ty.boff + b];
         const int *et = ix.et + ty.start, *ei = ix.ei + ty.start;
-        auto before = [&](int p) { return REL ? at(ei, p) <= i : at(et, p) < x; };
-        if (before(a)) {
-            int z = ix.tab[ty.boff + b + 1];
-            ++a;
-            while (a < z) {
-                const int mid = (a + z) >> 1;
-                const bool l = before(mid);
-                a = l ? mid + 1 : a;
-                z = l ? z : mid;
+        const int *tab = ix.tab + ty.boff;
+        const int a = at(tab, bucket(least, ty.t0, ty.sh, ty.nb));
+        const v4i v = at4(et, a);
+        // relaxed: entries of tick t count from the first with a later index
+        int tie = 0;
+        if constexpr (REL) tie = (v[0] == t) | (v[1] == t) | (v[2] == t) | (v[3] == t);
+        const unsigned bit = 1u << (e & 31);
+#pragma unroll
+        for (int h = 0; h < MH; ++h) {
+            if (h >= nh) break;
+            bool in = false;
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                in |= (unsigned)(v[q] - lo[h]) <= (unsigned)(lim[h] - lo[h]);
+            // (before the range still after four entries, or ties to settle)
+            if ((!in & (v[3] < lo[h])) | (REL & (tie != 0))) {
+                const int b = bucket(lo[h], ty.t0, ty.sh, ty.nb);
+                int p = at(tab, b), z = at(tab, b + 1);
+                while (p < z) {
+                    const int mid = (p + z) >> 1;
+                    const bool l = REL ? at(ei, mid) <= i : at(et, mid) < lo[h];
+                    p = l ? mid + 1 : p;
+                    z = l ? z : mid;
+                }
+                in = at(et, p) <= lim[h];
             }
+            bits[h] |= in ? bit : 0u;
         }
-        bits |= at(et, a) <= lim ? 1u << (e & 31) : 0u;
     }
-    mask[((int64_t)place * Q + (w >> 1) * n_iv + h) * 2 + (w & 1)] = bits;
+    for (int h = 0; h < nh; ++h)
+        mask[((int64_t)place * Q + (w >> 1) * n_iv + h0 + h) * 2 + (w & 1)] = bits[h];
 }
 
 // The entries of node 1 of every pair of frequent types and interval, in the
@@ -1020,18 +1075,26 @@ template <bool REL> struct Columns {
     }
 };
 
-// Episodes by their last type: k_order_count, a scan, k_order_place.
-__global__ __launch_bounds__(256) void k_order_count(const int *__restrict__ F, int w, int cnt,
-                                                     int *__restrict__ hist)
+// Episodes by their last type: counts by block (in LDS, then one atomic a
+// block and type), a scan, places.
+constexpr int ORDER_PER = 4096;  // episodes a block takes
+template <bool PLACE>
+__global__ __launch_bounds__(256) void k_order(const int *__restrict__ F, int w, int cnt, int T,
+                                               int *__restrict__ next, int *__restrict__ order)
 {
-    const int a = blockIdx.x * 256 + threadIdx.x;
-    if (a < cnt) atomicAdd(&hist[F[(int64_t)a * w + w - 1]], 1);
-}
-__global__ __launch_bounds__(256) void k_order_place(const int *__restrict__ F, int w, int cnt,
-                                                     int *__restrict__ next, int *__restrict__ order)
-{
-    const int a = blockIdx.x * 256 + threadIdx.x;
-    if (a < cnt) order[atomicAdd(&next[F[(int64_t)a * w + w - 1]], 1)] = a;
+    extern __shared__ int sh[];
+    for (int e = threadIdx.x; e < T; e += 256) sh[e] = 0;
+    __syncthreads();
+    const int a0 = blockIdx.x * ORDER_PER;
+    const int a1 = a0 + ORDER_PER < cnt ? a0 + ORDER_PER : cnt;
+    for (int a = a0 + threadIdx.x; a < a1; a += 256) atomicAdd(&sh[F[(int64_t)a * w + w - 1]], 1);
+    __syncthreads();
+    for (int e = threadIdx.x; e < T; e += 256)
+        if (sh[e]) sh[e] = atomicAdd(&next[e], sh[e]);
+    if (!PLACE) return;
+    __syncthreads();
+    for (int a = a0 + threadIdx.x; a < a1; a += 256)
+        order[atomicAdd(&sh[F[(int64_t)a * w + w - 1]], 1)] = a;
 }
 
 // One wave per frequent episode and QW mask words (grid z), by the episodes'
@@ -1116,7 +1179,7 @@ void launch_masks(bool rel, const IndexPlan &p, const int *base, const int *ivlo
 {
     const ChainIdx ix = index_view(p, const_cast<int *>(base));
     const int places = p.n + LIST_PAD * p.T, Q = mask_words(p.T, n_iv);
-    const dim3 grid((unsigned)((places + 255) / 256), (unsigned)((p.T + 63) / 64 * 2 * n_iv));
+    const dim3 grid((unsigned)((places + 255) / 256), (unsigned)((p.T + 63) / 64 * 2 * ((n_iv + MH - 1) / MH)));
     if (rel)
         hipLaunchKernelGGL(k_masks<true>, grid, dim3(256), 0, s, ix, places, p.T, n_iv, ivlo, ivhi,
                            (unsigned *)mask, Q);
@@ -1140,10 +1203,11 @@ void launch_order(const int *F, int w, int64_t cnt, int T, int *order, hipStream
     if (cnt <= 0) return;
     int *hist = order + cnt, *next = hist + T;
     launch_fill(hist, 0, T, s);
-    const dim3 grid((unsigned)((cnt + 255) / 256));
-    hipLaunchKernelGGL(k_order_count, grid, dim3(256), 0, s, F, w, (int)cnt, hist);
+    const dim3 grid((unsigned)((cnt + ORDER_PER - 1) / ORDER_PER));
+    const size_t lds = (size_t)T * sizeof(int);
+    hipLaunchKernelGGL(k_order<false>, grid, dim3(256), lds, s, F, w, (int)cnt, T, hist, order);
     launch_scan_excl(hist, T, next, next + T, s);
-    hipLaunchKernelGGL(k_order_place, grid, dim3(256), 0, s, F, w, (int)cnt, next, order);
+    hipLaunchKernelGGL(k_order<true>, grid, dim3(256), lds, s, F, w, (int)cnt, T, next, order);
 }
 
 void launch_siblings(bool rel, const SibJob &j, int64_t cnt, hipStream_t s)

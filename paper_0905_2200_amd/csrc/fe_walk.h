@@ -350,7 +350,8 @@ __device__ __forceinline__ void walk(const ChainIdx &ix, const NodeRow &row, int
             }
         __builtin_amdgcn_wave_barrier();
     };
-    // a batch of ring k's entries (flush: no more will come)
+    // a batch of ring k's entries (flush: no more will come; k == S + 1 is the
+    // ring whose counters are scalars)
     auto deeper = [&](int k, bool flush) {
         const int *q = ring(k);
         const int hk = k == S + 1 ? h1 : rdl(qh, k), ck = k == S + 1 ? n1 : rdl(qn, k);
@@ -385,20 +386,14 @@ __device__ __forceinline__ void walk(const ChainIdx &ix, const NodeRow &row, int
             qn = lane == k ? qn - nc : qn;
         }
     };
-    // full batches, the deepest first
     const int full1 = E == S + 1 ? WAVE : WAVE + 1;
-    auto drain = [&] {
-        for (;;) {
-            const unsigned long long ready = bal(qn >= (lane == E ? WAVE : WAVE + 1));
-            if (ready) deeper(63 - __builtin_clzll(ready), false);
-            else if (n1 >= full1) deeper(S + 1, false);
-            else break;
-        }
-    };
-    {
-        int *q = ring(S + 1);
-        fill(true);
-        for (;;) {
+    fill(true);
+    // (each stage's code once: the source, then every full batch, the deepest
+    // first, and after the source's end what is left, from the source on -- a
+    // stage's entries are its last when every stage before it is done)
+    for (;;) {
+        const bool more = a < aend;
+        if (more) {
             const int pos = place(a), n = aend - a < WAVE ? aend - a : WAVE;
             const int a_next = a + WAVE, L_now = L0, t_now = t0, tn_now = tn0;
             const v4i v_now = v0;
@@ -410,25 +405,34 @@ __device__ __forceinline__ void walk(const ChainIdx &ix, const NodeRow &row, int
             }
             int p, c, nc, tot, part;
             events_of<REL, false>(h, lane < n, t_now, tn_now, own, next, L_now, v_now, sk0, p, c);
-            put(q, h1 + n1, n, p, c, pos, sk0, nc, tot, part);
+            put(ring(S + 1), h1 + n1, n, p, c, pos, sk0, nc, tot, part);
             n1 += tot;
             sk0 = part;
             a += nc;
-            if (n1 >= full1) drain();
-            if (a >= aend) break;
-            if (__builtin_expect(a != a_next, 0)) fill(true);
+            if (__builtin_expect((a != a_next) & (a < aend), 0)) fill(true);
+            if (n1 < full1 && a < aend) continue;
         }
-    }
-    // what is left, from the source on (a stage's entries are its last when
-    // every stage before it is done)
-    for (;;) {
-        drain();
-        if (n1 > 0) {
-            deeper(S + 1, true);
-        } else {
-            const unsigned long long some = bal(qn > 0);
-            if (!some) break;
-            deeper((int)__builtin_ctzll(some), true);
+        for (;;) {
+            const bool end = a >= aend;
+            const unsigned long long ready = bal(qn >= (lane == E ? WAVE : WAVE + 1));
+            int k;
+            bool flush = false;
+            if (ready) {
+                k = 63 - __builtin_clzll(ready);
+            } else if (n1 >= full1) {
+                k = S + 1;
+            } else if (!end) {
+                break;
+            } else if (n1 > 0) {
+                k = S + 1;
+                flush = true;
+            } else {
+                const unsigned long long some = bal(qn > 0);
+                if (!some) return;
+                k = (int)__builtin_ctzll(some);
+                flush = true;
+            }
+            deeper(k, flush);
         }
     }
 }
