@@ -12,8 +12,10 @@ namespace fe {
 // Types an index may hold: the sort keeps three words of LDS per type in
 // each wave (48 KiB at this limit).  Streams with more take the Map kernels.
 constexpr int CHAIN_TYPES = 4096;
-// Guard entries behind every type's list: a search reads four entries at once.
+// Guard entries around every type's list, as a search reads four entries at
+// once: one of INT_MIN before it, four of INT_MAX behind it.
 constexpr int LIST_PAD = 4;
+constexpr int LIST_EXTRA = LIST_PAD + 1;
 
 // One type's events in the index.
 struct TypeIdx {
@@ -29,7 +31,7 @@ struct TypeIdx {
 // Per-type event lists of a stream (in stream order) and, per type, the
 // position of the first event of each power-of-two stretch of ticks.
 struct ChainIdx {
-    const int *et;       // ticks, LIST_PAD guards of INT_MAX after each list
+    const int *et;       // ticks, with guards around each list
     const int *ei;       // stream indices, same layout
     const int *tab;      // bucket tables
     const TypeIdx *ty;   // [num_types]
@@ -87,6 +89,7 @@ struct ChainJob {
     int *upper;  // relaxed counts
     int *exact;  // exact counts
     int P;       // segments per candidate
+    unsigned share;  // (set by the launcher: 2^32 / P, less)
     int4 *seg;   // [P][M] segment results (P > 1): completions, last one's index
     // incremental form (count_io set): the events before `from`, whose tick
     // is *t_from, are counted; adds the rest to the carry

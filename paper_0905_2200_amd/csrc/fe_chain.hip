@@ -47,8 +47,8 @@ IndexPlan index_plan(int64_t n, int T, bool alone)
         return at;
     };
     const int64_t H = (int64_t)T * p.nch;
-    p.o_et = take(n + (int64_t)LIST_PAD * T);
-    p.o_ei = take(n + (int64_t)LIST_PAD * T);
+    p.o_et = take(n + (int64_t)LIST_EXTRA * T);
+    p.o_ei = take(n + (int64_t)LIST_EXTRA * T);
     p.o_tab = take(tab_room(n, T));
     p.o_ty = take((int64_t)T * (sizeof(TypeIdx) / sizeof(int)));
     p.o_hist = take(H);
@@ -254,12 +254,13 @@ __global__ __launch_bounds__(TYB) void k_ix_types(IndexSet x, int scan_here, con
         if (e < T) {
             const int a = n ? off[(int64_t)e * nch] : 0;
             const int b = n && e + 1 < T ? off[(int64_t)(e + 1) * nch] : n;
-            x.start = a + LIST_PAD * e;
+            x.start = a + LIST_EXTRA * e + 1;
             x.count = b - a;
             x.t0 = t0;
             const int64_t most = 2 * (int64_t)x.count;
             while (((int64_t)span >> x.sh) + 1 > (most > 1 ? most : 1)) ++x.sh;
             x.nb = (span >> x.sh) + 1;
+            et[x.start - 1] = ei[x.start - 1] = BEFORE;
             for (int j = 0; j < LIST_PAD; ++j) {
                 et[x.start + x.count + j] = FAR_TICK;
                 ei[x.start + x.count + j] = FAR_TICK;
@@ -288,7 +289,7 @@ __global__ __launch_bounds__(WAVE) void k_ix_lists(IndexSet x, const int *status
     const int lane = threadIdx.x, c = (int)blockIdx.x - j.first_chunk;
     for (int e = lane; e < T; e += WAVE) {
         mask[e] = 0;
-        cur[e] = j.off[(int64_t)e * nch + c] + LIST_PAD * e;
+        cur[e] = j.off[(int64_t)e * nch + c] + LIST_EXTRA * e + 1;
     }
     __syncthreads();
     const int b = c * chunk, e = b + chunk < n ? b + chunk : n;
@@ -418,17 +419,20 @@ __device__ __forceinline__ int64_t grid_item()
     return (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
 }
 
+constexpr int XCDS = 8;
 constexpr int FCAP = 2 * WAVE;  // completions waiting (64 and one batch's)
 
 // Takes node N-2's entries, finds each one's first event of the last type
 // and counts the completions (s, i) greedily.  Only the first event matters:
 // a later one of the same entry has the same s and comes after it.
+//   PULL: the source is node 1's list; node 0's events are found at the end.
 //   DUAL: the same also from rf, the state the segment's own run began in;
 // both runs are the same from their first common completion on.
-template <bool REL, bool DUAL> struct Count {
+template <bool REL, bool DUAL, bool PULL> struct Count {
     const ChainIdx &ix;
     const NodeRow &row;
-    int N, a1;       // completions of chains from [.., a1) of node 0's list count
+    int N, a1;       // completions of chains from [.., a1) of the source count
+    const Hop h;     // the last hop
     int *fq;         // FCAP (chain start, completing event) positions
     int fh = 0, fn = 0;
     int r, cnt = 0;
@@ -437,42 +441,60 @@ template <bool REL, bool DUAL> struct Count {
 
     __device__ __forceinline__ Count(const ChainIdx &x, const NodeRow &w, int N_, int a1_, int *q,
                                      int r0)
-        : ix(x), row(w), N(N_), a1(a1_), fq(q), r(r0)
+        : ix(x), row(w), N(N_), a1(a1_), h(x, w, N_ - 2), fq(q), r(r0)
     {
     }
 
-    // the greedy choice among 64 completions in order (valid: their lanes),
-    // after one at rr: of a chain's completions only the first can be taken;
-    // one whose chain starts after its predecessor's completion always is; the
-    // others depend on the last one taken
+    // The greedy choice among 64 completions in order (valid: their lanes),
+    // after one at rr: one is taken if its chain starts after the last one
+    // taken.  If that is after its neighbour's completion it always is; its
+    // neighbour taken, it is not, and two lanes on the same with the one
+    // before; what is left goes one stretch at a time.  (A later completion of
+    // a chain is not taken by the same rules.)
     __device__ __forceinline__ void choose(unsigned long long valid, int s, int i, int &rr,
                                            int &c) const
     {
-        const int lane = __lane_id();
-        int ip = __shfl_up(i, 1);
-        ip = lane == 0 ? rr : ip;
-        const int sp = __shfl_up(s, 1);
-        valid &= bal((lane == 0) | (s != sp));
-        unsigned long long conf = bal(s <= ip) & valid;
-        unsigned long long sel = valid & ~conf;
-        while (conf) {
-            const int j = (int)__builtin_ctzll(conf);
-            conf &= conf - 1;
-            const unsigned long long lower = sel & ((1ull << j) - 1ull);
-            const int last = lower ? rdl(i, 63 - __builtin_clzll(lower)) : rr;
-            if (rdl(s, j) > last) sel |= 1ull << j;
+        const int i1 = before(i, rr);
+        unsigned long long sel = bal(s > i1) & valid;
+        unsigned long long rem = valid & ~sel, no = rem & (sel << 1 | 1ull);
+        rem &= ~no;
+        if (rem) {
+            const unsigned long long free2 = bal(s > before(i1, rr));
+            for (;;) {
+                const unsigned long long next = rem & (no << 1), yes = next & free2;
+                rem &= ~next;
+                if (yes == 0) break;
+                sel |= yes;
+                no = rem & (yes << 1);
+                rem &= ~no;
+            }
+            while (rem) {
+                const unsigned long long from = rem & -rem, lower = sel & (from - 1ull);
+                const int last = lower ? rdl(i, 63 - __builtin_clzll(lower)) : rr;
+                const unsigned long long free = bal(s > last) & valid & ~(from - 1ull);
+                const unsigned long long take = free & -free;
+                sel |= take;
+                rem &= take ? ~(take | (take - 1ull)) : 0;
+            }
         }
         c += __builtin_popcountll(sel);
         if (sel) rr = rdl(i, 63 - __builtin_clzll(sel));
+    }
+    // the lane's before, lane 0's: first
+    static __device__ __forceinline__ int before(int v, int first)
+    {
+        return __builtin_amdgcn_update_dpp(first, v, 0x138, 0xf, 0xf, false);  // wave_shr:1
     }
     __device__ __forceinline__ void drain(int n)
     {
         const int lane = __lane_id();
         const bool on = lane < n;
-        const int q = (fh + lane) & (FCAP - 1);
-        const int ap = on ? fq[q] : 0, dp = on ? fq[FCAP + q] : 0;
-        const int s = on ? ix.ei[rdl(row.start, 0) + ap] : FAR_TICK;
-        const int i = on ? ix.ei[rdl(row.start, N - 1) + dp] : FAR_TICK;
+        const int q = (fh + (on ? lane : 0)) & (FCAP - 1);
+        int ap = fq[q];
+        const int dp = fq[FCAP + q];
+        if (PULL && N > 3) ap = first_of<REL>(ix, row, on, ap);
+        const int s = at(ix.ei + rdl(row.start, 0), ap);
+        const int i = at(ix.ei + rdl(row.start, N - 1), dp);
         const unsigned long long valid = bal(on);
         if (s1 == FAR_TICK) s1 = rdl(s, 0);
         choose(valid, s, i, r, cnt);
@@ -484,18 +506,27 @@ template <bool REL, bool DUAL> struct Count {
     {
         if (fn) drain(fn);
     }
-    static constexpr bool SEARCHES = true;
+    static constexpr bool SEARCHES = true, FIRSTS = false;
     __device__ __forceinline__ void operator()(int, bool on, int t, int src, int own, int L, v4i v)
     {
-        const Hop h = hop_of(ix, row, N - 2);
         if (N > 2) {
             L = table_at<REL>(h, t);
             v = at4(h.et, L);
         }
-        int p, c;
-        events_of<REL, true>(h, on, t, FAR_TICK, own, 0, L, v, 0, p, c);
-        const bool pass = (c != 0) & (src < a1);
-        const unsigned long long m = bal(pass);
+        search(on, t, src, own, L, v);
+    }
+    __device__ __forceinline__ void search(bool on, int t, int src, int own, int L, v4i v)
+    {
+        int p;
+        const int f = first_after<REL>(h, on, t, own, L, v, p);
+        const int from = PULL && N == 3 ? own : src;
+        const bool reached = f <= t + h.hi, counts = from < a1;
+        take(on & reached & counts, bal(on) & bal(reached) & bal(counts), src, p);
+    }
+    // completions at positions p of the last list, of chains from src on
+    // (m: the lanes that pass)
+    __device__ __forceinline__ void take(bool pass, unsigned long long m, int src, int p)
+    {
         if (m == 0) return;
         if (pass) {
             const int q = (fh + fn + below(m)) & (FCAP - 1);
@@ -505,6 +536,11 @@ template <bool REL, bool DUAL> struct Count {
         __builtin_amdgcn_wave_barrier();
         fn += __builtin_popcountll(m);
         if (fn >= WAVE) drain(WAVE);
+    }
+    // (two nodes, pulled: the source's own events complete; it ends at a1)
+    __device__ __forceinline__ void direct(bool pass, unsigned long long m, int pos, int first)
+    {
+        take(pass, m, first, pos);
     }
 };
 
@@ -516,25 +552,44 @@ __device__ __forceinline__ int row_width(const NodeRow &row, int N)
     return W;
 }
 
-// Where the walk over chains from [.., a1) of node 0's list may end: past
-// every event within W ticks of the last one (their entries bound those of
-// the chains counted); a bucket's end, so possibly a few more.
-__device__ __forceinline__ int look_ahead(const ChainIdx &ix, const NodeRow &row, int N, int a1)
+// Where the walk over chains from [.., a1) of the source (node sn's list) may
+// end: past every event within W ticks of the last one (their entries bound
+// those of the chains counted); a bucket's end, so possibly a few more.
+__device__ __forceinline__ int look_ahead(const ChainIdx &ix, const NodeRow &row, int N, int sn,
+                                          int a1)
 {
-    const int start = rdl(row.start, 0), count = rdl(row.count, 0);
-    if (N <= 2 || a1 >= count || a1 <= 0) return a1;
+    const int start = rdl(row.start, sn), count = rdl(row.count, sn);
+    if (N - sn <= 2 || a1 >= count || a1 <= 0) return a1;
     const int x = ix.et[start + a1 - 1] + row_width(row, N);
-    const int b = bucket(x, row.t0, rdl(row.sh, 0), rdl(row.nb, 0));
-    const int e = __builtin_amdgcn_readfirstlane(ix.tab[rdl(row.boff, 0) + b + 1]);
+    const int b = bucket(x, row.t0, rdl(row.sh, sn), rdl(row.nb, sn));
+    const int e = __builtin_amdgcn_readfirstlane(ix.tab[rdl(row.boff, sn) + b + 1]);
     return e > a1 ? e : a1;
 }
 
-// Counts the chains from [a0, a1) of node 0's list after a completion at
-// index r (DUAL: and, into rf/cntf, after none).  s1: the first event of the
+// Counts the chains from [a0, a1) of the source after a completion at index r
+// (DUAL: and, into rf/cntf, after none).  s1: the first event of the
 // first chain that completes (unless N = 1, where none can be cut off).
-template <bool REL, bool DUAL>
-__device__ __forceinline__ void count_range(const ChainIdx &ix, const NodeRow &row, int N, int a0,
-                                            int a1, int *lds, int &r, int &cnt, int &rf,
+template <bool REL, bool DUAL, Source SRC, int EMAX>
+__device__ __forceinline__ void count_from(const ChainIdx &ix, const NodeRow &row, int N, int a0,
+                                           int a1, int *lds, int &r, int &cnt, int &rf, int &cntf,
+                                           int &s1)
+{
+    constexpr int sn = SRC == FROM_SECOND ? 1 : 0;
+    Count<REL, DUAL, SRC == FROM_SECOND> sink(ix, row, N, a1, lds, r);
+    if (DUAL) sink.rf = rf;
+    walk<REL, SRC, EMAX>(ix, row, N - 2, a0, look_ahead(ix, row, N, sn, a1), lds + 2 * FCAP, sink);
+    sink.finish();
+    s1 = sink.s1;
+    r = sink.r;
+    cnt += sink.cnt;
+    if (DUAL) {
+        rf = sink.rf;
+        cntf += sink.cntf;
+    }
+}
+template <bool REL, bool DUAL, int EMAX>
+__device__ __forceinline__ void count_range(const ChainIdx &ix, const NodeRow &row, int N, bool pull,
+                                            int a0, int a1, int *lds, int &r, int &cnt, int &rf,
                                             int &cntf, int &s1)
 {
     if (a0 >= a1) return;
@@ -550,55 +605,56 @@ __device__ __forceinline__ void count_range(const ChainIdx &ix, const NodeRow &r
         }
         return;
     }
-    Count<REL, DUAL> sink(ix, row, N, a1, lds, r);
-    if (DUAL) sink.rf = rf;
-    walk<REL, false>(ix, row, N - 2, a0, look_ahead(ix, row, N, a1), lds + 2 * FCAP, sink);
-    sink.finish();
-    s1 = sink.s1;
-    r = sink.r;
-    cnt += sink.cnt;
-    if (DUAL) {
-        rf = sink.rf;
-        cntf += sink.cntf;
-    }
+    if (pull) count_from<REL, DUAL, FROM_SECOND, EMAX>(ix, row, N, a0, a1, lds, r, cnt, rf, cntf, s1);
+    else count_from<REL, DUAL, FROM_FIRST, EMAX>(ix, row, N, a0, a1, lds, r, cnt, rf, cntf, s1);
 }
 
 __host__ __device__ constexpr int chain_lds(int nmax)
 {
-    return 2 * FCAP + (nmax > 2 ? nmax - 2 : 0) * RING_INTS;
+    return 2 * FCAP + (nmax > 3 ? (nmax - 2) * RING_INTS : nmax == 3 ? 3 * QCAP : 0);
 }
 
-// Segment p of P of a list of c events.
-__device__ __forceinline__ int seg_at(int c, int p, int P) { return (int)((int64_t)p * c / P); }
+// Where segment p of a list of c events starts (j.share: 2^32 / P, less).
+__device__ __forceinline__ int seg_at(const ChainJob &j, int c, int p)
+{
+    return p < j.P ? (int)__umulhi(j.share * (unsigned)p, (unsigned)c) : c;
+}
+
+// Waves a SIMD is given registers for.  Tables of up to three nodes (EMAX = 1)
+// need 2.5 KB of LDS a wave, so their walks keep to eight waves' scalar
+// registers, the rest of them in vector lanes: 14.5 -> 12.3 ms for the 1e5
+// rows above (5.7 -> 7.6 waves resident).  Longer tables have LDS for five
+// waves only, and 2% more time with fewer registers.
+constexpr int chain_waves(int emax) { return emax == 1 ? 8 : 1; }
 
 // One wave per (segment, candidate).  P = 1 writes the counts; P > 1 the
 // segment's own count (after no completion), its last completion's index
 // and the first event of its first completed chain.
-//   A batch of 64 node-0 events is one coalesced read of their ticks and two
-// of the next list (its bucket, four entries), so the kernel is bound by the
-// latency of those reads at few waves and by the lists' bytes at many.  Why
-// not the Map kernels' scan: a wave there reads every event of the stream
-// for 64 candidates, here only its candidate's first list and the few
-// entries that pass.  20011 episodes of 1-8 nodes over 3.0e5 events of 200
-// types: 22.6 -> 0.25 ms a call; 5000 relaxed of 5-8 nodes over 1.06e6 events
-// of 128 types: 13.2 -> 0.58 ms; 1e5 of 3 nodes over 9.7e6 events, both
-// passes: 81 -> 42 ms; 3000 with 9 to 19 live windows a list: 26 -> 0.08 ms.
-template <int MODE>
-__device__ __forceinline__ void chain_item(const ChainJob &j, int64_t item, int *lds)
+//   A batch of 64 source events is one coalesced read of their ticks and two
+// of the other list (its bucket, four entries), so the kernel is bound by the
+// latency of those reads at few waves and by its instructions at many (1e5
+// rows of 3 nodes: 0.73 of the vector issue rate).  Why not the Map kernels'
+// scan: a wave there reads every event of the stream for 64 candidates, here
+// only its candidate's shorter list of the first two and the few entries that
+// pass.  20011 episodes of 1-8 nodes over 3.0e5 events of 200 types: 22.6 ->
+// 0.17 ms a call; 5000 relaxed of 5-8 nodes over 1.06e6 events of 128 types:
+// 13.2 -> 0.30 ms; 1e5 of 3 nodes over 9.7e6 events, both passes: 81 -> 10.4
+// ms (16.1 from node 0's list; 12.3 with the survivors' exact pass launched
+// for every row); 3000 with 9 to 19 live windows a list: 26 -> 0.08 ms.
+template <int MODE, int EMAX>
+__device__ __forceinline__ void chain_item(const ChainJob &j, int m, int p, int *lds)
 {
-    const int M = j.rows.M;
-    const int p = (int)((unsigned)item / (unsigned)M), m = (int)((unsigned)item - (unsigned)p * (unsigned)M);
     const int lane = __lane_id();
-    // (P > 1: MODE is EXACT or RELAXED; with upper set, survivors only)
-    if (MODE == CHAIN_EXACT && j.P > 1 && j.upper && j.upper[m] < j.theta) return;
     NodeRow row;
     const int N = load_row(j.ix, j.rows, m, row);
-    const int c = rdl(row.count, 0);
+    // (the incremental form starts at an event of node 0)
+    const bool pull = (MODE == CHAIN_TWO_PASS || !j.count_io) && pulls(row, N);
+    const int c = rdl(row.count, pull ? 1 : 0);
     int dr = -1, dc = 0, s1 = FAR_TICK;
     int a0 = 0, a1 = c, r = -1;
     if (MODE != CHAIN_TWO_PASS && j.P > 1) {
-        a0 = seg_at(c, p, j.P);
-        a1 = seg_at(c, p + 1, j.P);
+        a0 = seg_at(j, c, p);
+        a1 = seg_at(j, c, p + 1);
     } else if (MODE != CHAIN_TWO_PASS && j.count_io) {
         // chains that start after the last completion, and no more than the
         // episode's width before the first new event: the others have been
@@ -619,16 +675,17 @@ __device__ __forceinline__ void chain_item(const ChainJob &j, int64_t item, int 
     bool take = true;
     if (MODE == CHAIN_TWO_PASS) {
         int cnt = 0;
-        count_range<true, false>(j.ix, row, N, a0, a1, lds, r, cnt, dr, dc, s1);
+        count_range<true, false, EMAX>(j.ix, row, N, pull, a0, a1, lds, r, cnt, dr, dc, s1);
         if (lane == 0) j.upper[m] = cnt;
         take = cnt >= j.theta;
         r = -1;
     }
     int cnt = 0;
-    if (take) count_range<MODE == CHAIN_RELAXED, false>(j.ix, row, N, a0, a1, lds, r, cnt, dr, dc, s1);
+    if (take)
+        count_range<MODE == CHAIN_RELAXED, false, EMAX>(j.ix, row, N, pull, a0, a1, lds, r, cnt, dr, dc, s1);
     if (lane != 0) return;
     if (MODE != CHAIN_TWO_PASS && j.P > 1) {
-        j.seg[(int64_t)p * M + m] = make_int4(cnt, r, s1, 0);
+        j.seg[(int64_t)p * j.rows.M + m] = make_int4(cnt, r, s1, 0);
     } else if (MODE != CHAIN_TWO_PASS && j.count_io) {
         if (cnt) {
             j.count_io[m] += cnt;
@@ -639,17 +696,34 @@ __device__ __forceinline__ void chain_item(const ChainJob &j, int64_t item, int 
     }
 }
 
-template <int MODE> __global__ __launch_bounds__(WAVE) void k_chain(ChainJob j, const int *status)
+template <int MODE, int EMAX>
+__global__ __launch_bounds__(WAVE, chain_waves(EMAX)) void k_chain(ChainJob j, const int *status,
+                                                                   int log2_rows)
 {
     extern __shared__ int lds[];
     if (*status) return;
-    const int64_t item = grid_item();
-    if (item < (int64_t)j.P * j.rows.M) chain_item<MODE>(j, item, lds);
+    const int M = j.rows.M, b = (int)grid_item(), per_wave = 1 << log2_rows;
+    const int blocks = (M + per_wave - 1) >> log2_rows;
+    if (b >= blocks) return;
+    // (blocks go round the XCDs: each XCD takes a stretch of the rows, whose
+    // lines then come into one L2)
+    const int per = blocks / XCDS;
+    const int m = (b < per * XCDS ? b % XCDS * per + b / XCDS : b) << log2_rows;
+    unsigned long long todo = 1;
+    if (MODE == CHAIN_EXACT && j.P > 1 && j.upper) {
+        // survivors only
+        const int at = m + __lane_id();
+        todo = bal((int)__lane_id() < per_wave && at < M && j.upper[at < M ? at : 0] >= j.theta);
+    }
+    for (; todo; todo &= todo - 1) {
+        chain_item<MODE, EMAX>(j, m + (int)__builtin_ctzll(todo), (int)blockIdx.z, lds);
+        if (MODE != CHAIN_EXACT) break;
+    }
 }
 
 // The same for the rows of several jobs.
-template <int MODE>
-__global__ __launch_bounds__(WAVE) void k_chains(const ChainJob *jobs, const int64_t *first,
+template <int MODE, int EMAX>
+__global__ __launch_bounds__(WAVE, chain_waves(EMAX)) void k_chains(const ChainJob *jobs, const int64_t *first,
                                                  int njobs, int64_t total, const int *status)
 {
     extern __shared__ int lds[];
@@ -676,7 +750,7 @@ __global__ __launch_bounds__(WAVE) void k_chains(const ChainJob *jobs, const int
     j.seg = nullptr;  // (P = 1, not incremental)
     j.count_io = nullptr;
     j.P = 1;
-    chain_item<MODE>(j, item - first[lo], lds);
+    chain_item<MODE, EMAX>(j, (int)(item - first[lo]), 0, lds);
 }
 
 // One wave per 64 candidates: their segments' results in order.  A
@@ -710,13 +784,14 @@ template <bool REL> __global__ __launch_bounds__(WAVE) void k_stitch(ChainJob j,
             const int mq = (int)blockIdx.x * WAVE + q;
             NodeRow row;
             const int N = load_row(j.ix, j.rows, mq, row);
-            const int c = rdl(row.count, 0);
-            const int a1 = seg_at(c, p + 1, j.P);
-            int b = seg_at(c, p, j.P), len = WAVE;
+            const bool pull = pulls(row, N);
+            const int c = rdl(row.count, pull ? 1 : 0);
+            const int a1 = seg_at(j, c, p + 1);
+            int b = seg_at(j, c, p), len = WAVE;
             int rr = rdl(r, q), cnt = 0, rf = -1, cntf = 0, s1 = 0;
             while (b < a1 && (rf != rr)) {
                 const int e = a1 - b < len ? a1 : b + len;
-                count_range<REL, true>(j.ix, row, N, b, e, lds, rr, cnt, rf, cntf, s1);
+                count_range<REL, true, NMAX - 2>(j.ix, row, N, pull, b, e, lds, rr, cnt, rf, cntf, s1);
                 b = e;
                 len *= 2;
             }
@@ -735,11 +810,20 @@ template <bool REL> __global__ __launch_bounds__(WAVE) void k_stitch(ChainJob j,
     if (on) out[m] = tot;
 }
 
-template <int MODE> void chain_mode(const ChainJob &j, int nmax, const int *status, hipStream_t s)
+template <int MODE> void chain_mode(ChainJob j, int nmax, const int *status, hipStream_t s)
 {
+    j.share = 0xffffffffu / (unsigned)j.P;
     const size_t lds = (size_t)chain_lds(nmax) * sizeof(int);
-    hipLaunchKernelGGL((k_chain<MODE>), grid_of((int64_t)j.P * j.rows.M), dim3(WAVE), lds, s, j,
-                       status);
+    // (survivors of a first pass: a wave looks for them among several rows
+    // where that leaves eight waves' worth for every place on the chip)
+    int rows = 0;
+    if (MODE == CHAIN_EXACT && j.P > 1 && j.upper)
+        while (rows < 4 && (int64_t)j.P * j.rows.M >> (rows + 1) >= 65536) ++rows;
+    const dim3 grid = grid_of((j.rows.M + (1 << rows) - 1) >> rows, j.P);
+    if (nmax <= 3)
+        hipLaunchKernelGGL((k_chain<MODE, 1>), grid, dim3(WAVE), lds, s, j, status, rows);
+    else
+        hipLaunchKernelGGL((k_chain<MODE, NMAX - 2>), grid, dim3(WAVE), lds, s, j, status, rows);
     if (j.P > 1)
         hipLaunchKernelGGL((k_stitch<MODE == CHAIN_RELAXED>),
                            dim3((unsigned)((j.rows.M + WAVE - 1) / WAVE)), dim3(WAVE), lds, s, j,
@@ -787,9 +871,13 @@ void launch_chains(const ChainJob *jobs, const int64_t *first, int njobs, int64_
                    const int *status, hipStream_t s)
 {
     if (total <= 0) return;
-    hipLaunchKernelGGL((k_chains<CHAIN_TWO_PASS>), grid_of(total), dim3(WAVE),
-                       (size_t)chain_lds(nmax) * sizeof(int), s, jobs, first, njobs, total,
-                       status);
+    const size_t lds = (size_t)chain_lds(nmax) * sizeof(int);
+    if (nmax <= 3)
+        hipLaunchKernelGGL((k_chains<CHAIN_TWO_PASS, 1>), grid_of(total), dim3(WAVE), lds, s, jobs,
+                           first, njobs, total, status);
+    else
+        hipLaunchKernelGGL((k_chains<CHAIN_TWO_PASS, NMAX - 2>), grid_of(total), dim3(WAVE), lds, s,
+                           jobs, first, njobs, total, status);
 }
 
 // ------------------------------------------------------------------ siblings
@@ -815,7 +903,7 @@ __global__ __launch_bounds__(256) void k_masks(ChainIdx ix, int places, int T, i
     const int nh = n_iv - h0 < MH ? n_iv - h0 : MH;
     if (place >= places) return;
     const int t = ix.et[place];
-    if (t == FAR_TICK) return;  // a guard
+    if (t == FAR_TICK || t == BEFORE) return;  // a guard
     int lo[MH], lim[MH], least = FAR_TICK;
 #pragma unroll
     for (int h = 0; h < MH; ++h) {
@@ -870,11 +958,12 @@ __global__ __launch_bounds__(256) void k_masks(ChainIdx ix, int places, int T, i
 template <bool REL> struct SeedOut {
     const ChainIdx &ix;
     const NodeRow &row;
-    Count<REL, false> cnt;
+    Count<REL, false, false> cnt;
     int *t, *a, *p;
     int64_t base;
     int n = 0;
-    static constexpr bool SEARCHES = false;
+    static constexpr bool SEARCHES = false, FIRSTS = true;
+    __device__ __forceinline__ void direct(bool, unsigned long long, int, int) {}
     __device__ __forceinline__ void operator()(int c, bool on, int tk, int src, int own, int, v4i)
     {
         const int s = on ? at(ix.ei + rdl(row.start, 0), src) : FAR_TICK;
@@ -890,8 +979,25 @@ template <bool REL> struct SeedOut {
     }
 };
 
+template <bool REL, Source SRC>
+__device__ __forceinline__ void pair_entries(const PairJob &j, const NodeRow &row, int64_t item,
+                                             int ak, int *lds)
+{
+    SeedOut<REL> out{j.ix, row, Count<REL, false, false>(j.ix, row, 2, 0, nullptr, -1), j.sd.t,
+                     j.sd.a, j.sd.p, (int64_t)ak * j.sd.stride + rdl(row.start, 1)};
+    walk<REL, SRC, 1>(j.ix, row, 1, 0, rdl(row.count, SRC == FROM_SECOND ? 1 : 0), lds, out);
+    if (__lane_id() != 0) return;
+    j.sd.t[out.base + out.n] = FAR_TICK;  // (a list has its guards' room)
+    j.sd.n[item] = out.n;
+    if (!j.out) return;
+    // in the level's order
+    const int k = ak % j.n_iv, f = ak / j.n_iv, b = (int)(item % j.nF);
+    const int64_t c = ((int64_t)f * j.nF + b) * j.n_iv + k;
+    j.out[c] = j.upper && j.upper[c] < j.theta ? -1 : out.cnt.cnt;
+}
+
 template <bool REL>
-__global__ __launch_bounds__(WAVE) void k_pairs(PairJob j)
+__global__ __launch_bounds__(WAVE, 8) void k_pairs(PairJob j)
 {
     extern __shared__ int lds[];
     const int64_t item = grid_item();
@@ -909,15 +1015,8 @@ __global__ __launch_bounds__(WAVE) void k_pairs(PairJob j)
     row.t0 = __builtin_amdgcn_readfirstlane(ty.t0);
     row.lo = lane == 0 ? j.ivlo[k] : 0;
     row.hi = lane == 0 ? j.ivhi[k] : 0;
-    SeedOut<REL> out{j.ix, row, Count<REL, false>(j.ix, row, 2, 0, nullptr, -1), j.sd.t, j.sd.a,
-                     j.sd.p, (int64_t)ak * j.sd.stride + rdl(ty.start, 1)};
-    walk<REL, false>(j.ix, row, 1, 0, rdl(row.count, 0), lds, out);
-    if (lane == 0) {
-        j.sd.t[out.base + out.n] = FAR_TICK;  // (a list has its guards' room)
-        j.sd.n[item] = out.n;
-        const int64_t c = ((int64_t)f * j.nF + b) * j.n_iv + k;  // in the level's order
-        if (j.out) j.out[c] = j.upper && j.upper[c] < j.theta ? -1 : out.cnt.cnt;
-    }
+    if (pulls(row, 3)) pair_entries<REL, FROM_SECOND>(j, row, item, ak, lds);
+    else pair_entries<REL, FROM_FIRST>(j, row, item, ak, lds);
 }
 
 // ---- 64 x 64 bits across a wave
@@ -990,7 +1089,8 @@ template <bool REL> struct Columns {
     int lo[QW], hi[QW];              // the words' hops (wave-uniform)
     int cnt[QW], tl[QW], ol[QW];     // per type: completions, the last entry counted
     int t_last = -(1 << 30);
-    static constexpr bool SEARCHES = false;
+    static constexpr bool SEARCHES = false, FIRSTS = true;
+    __device__ __forceinline__ void direct(bool, unsigned long long, int, int) {}
     __device__ __forceinline__ void operator()(int n, bool on, int t, int src, int own, int, v4i)
     {
         const int lane = __lane_id();
@@ -1158,7 +1258,7 @@ __global__ __launch_bounds__(WAVE) void k_siblings(SibJob j, int64_t cnt)
         sink.tl[q] = -(1 << 30);
         sink.ol[q] = 0;
     }
-    walk<REL, true>(j.ix, row, m - 1, 0, j.sd.n[ak * j.nF + j.rank[key[3]]], lds, sink, seed);
+    walk<REL, FROM_PAIR, NMAX - 2>(j.ix, row, m - 1, 0, j.sd.n[ak * j.nF + j.rank[key[3]]], lds, sink, seed);
     // counts by type to the siblings
     int *tot = lds;
 #pragma unroll
@@ -1178,7 +1278,7 @@ void launch_masks(bool rel, const IndexPlan &p, const int *base, const int *ivlo
                   int n_iv, uint2 *mask, hipStream_t s)
 {
     const ChainIdx ix = index_view(p, const_cast<int *>(base));
-    const int places = p.n + LIST_PAD * p.T, Q = mask_words(p.T, n_iv);
+    const int places = p.n + LIST_EXTRA * p.T, Q = mask_words(p.T, n_iv);
     const dim3 grid((unsigned)((places + 255) / 256), (unsigned)((p.T + 63) / 64 * 2 * ((n_iv + MH - 1) / MH)));
     if (rel)
         hipLaunchKernelGGL(k_masks<true>, grid, dim3(256), 0, s, ix, places, p.T, n_iv, ivlo, ivhi,

@@ -1461,7 +1461,7 @@ int mine_setup(fe_ctx *c, MineChains &mc, const std::vector<int> &F1, const std:
                const std::vector<int> &ihi, int num_types)
 {
     int rc;
-    const int64_t places = mc.ip.n + (int64_t)LIST_PAD * num_types;
+    const int64_t places = mc.ip.n + (int64_t)LIST_EXTRA * num_types;
     const int n_iv = (int)ilo.size(), nF = (int)F1.size();
     const int64_t Q = mask_words(num_types, n_iv);
     mc.n_pairs = (int64_t)nF * nF * n_iv;
@@ -1513,7 +1513,7 @@ int mine_pairs(fe_ctx *c, MineChains &mc, bool rel, int theta, const int *upper,
         return FE_OK;
     int *t = P<int>(c->sseed[rel]);
     mc.sd[rel] = PairLists{t, t + mc.sd_ints, t + 2 * mc.sd_ints, t + 3 * mc.sd_ints,
-                           mc.ip.n + (int64_t)LIST_PAD * mc.ip.T};
+                           mc.ip.n + (int64_t)LIST_EXTRA * mc.ip.T};
     PairJob j{};
     j.ix = mc.ix;
     j.F1 = mc.F1;

@@ -33,6 +33,7 @@ namespace fe {
 
 constexpr int QCAP = 128;  // entries a ring holds: 64 waiting and one batch's output
 constexpr int FAR_TICK = 0x7fffffff;
+constexpr int BEFORE = -0x7fffffff - 1;
 
 typedef int v4i __attribute__((ext_vector_type(4), aligned(4)));
 
@@ -43,6 +44,10 @@ __device__ __forceinline__ int below(unsigned long long m)
     return __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32),
                                      __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
 }
+
+// A value read in a rarely taken branch has to be there when the branch ends:
+// where the paths join, the wait for it would be one for every read in flight.
+__device__ __forceinline__ void arrived(int &v) { asm volatile("" : "+v"(v)); }
 
 // Lane k: node k's list and hop k.
 struct NodeRow {
@@ -71,11 +76,11 @@ __device__ __forceinline__ int load_row(const ChainIdx &ix, const Rows &rows, in
     return N;
 }
 
-// bucket of tick x >= t0 in a list's table
+// bucket of tick x in a list's table
 __device__ __forceinline__ int bucket(int x, int t0, int sh, int nb)
 {
     const int b = (x - t0) >> sh;
-    return b < nb ? b : nb;
+    return b < 0 ? 0 : b < nb ? b : nb;
 }
 
 // list[i] at a 32-bit byte offset (lists hold fewer than 2^30 entries)
@@ -88,29 +93,27 @@ __device__ __forceinline__ v4i at4(const int *list, int i)
     return *(const v4i *)((const char *)list + (size_t)((unsigned)i << 2));
 }
 
-// A hop (wave-uniform): from node k's list to the next node's.
+// A hop (wave-uniform): from node k's list to the next node's.  What only
+// ties and crowded buckets need is made where it is used, as a walk has more
+// uniform values than eight waves a SIMD leave it registers for.
 struct Hop {
-    const int *et, *ei;    // the next list
-    const int *tab;        // its bucket table
-    const int *own;        // stream indices of node k's list
-    int lo, hi, count, nb, sh, t0;
+    const ChainIdx &ix;
+    const NodeRow &row;
+    int k;
+    const int *et, *tab;  // the next list and its bucket table
+    int lo, hi, nb, sh, t0;
+
+    __device__ __forceinline__ Hop(const ChainIdx &x, const NodeRow &w, int k_)
+        : ix(x), row(w), k(k_), et(x.et + rdl(w.start, k_ + 1)),
+          tab(x.tab + rdl(w.boff, k_ + 1)), lo(rdl(w.lo, k_)), hi(rdl(w.hi, k_)),
+          nb(rdl(w.nb, k_ + 1)), sh(rdl(w.sh, k_ + 1)), t0(w.t0)
+    {
+    }
+    // stream indices of the next list and of node k's, the former's length
+    __device__ __forceinline__ const int *ei() const { return ix.ei + rdl(row.start, k + 1); }
+    __device__ __forceinline__ const int *own() const { return ix.ei + rdl(row.start, k); }
+    __device__ __forceinline__ int count() const { return rdl(row.count, k + 1); }
 };
-__device__ __forceinline__ Hop hop_of(const ChainIdx &ix, const NodeRow &row, int k)
-{
-    Hop h;
-    const int start = rdl(row.start, k + 1);
-    h.et = ix.et + start;
-    h.ei = ix.ei + start;
-    h.tab = ix.tab + rdl(row.boff, k + 1);
-    h.own = ix.ei + rdl(row.start, k);
-    h.lo = rdl(row.lo, k);
-    h.hi = rdl(row.hi, k);
-    h.count = rdl(row.count, k + 1);
-    h.nb = rdl(row.nb, k + 1);
-    h.sh = rdl(row.sh, k + 1);
-    h.t0 = row.t0;
-    return h;
-}
 // the tick a hop's events start at, and its place in the table
 template <bool REL> __device__ __forceinline__ int from_tick(const Hop &h, int t)
 {
@@ -121,94 +124,205 @@ template <bool REL> __device__ __forceinline__ int table_at(const Hop &h, int t)
     return at(h.tab, bucket(from_tick<REL>(h, t), h.t0, h.sh, h.nb));
 }
 
+// The first event after an entry by search: from tick x on (the entry's own
+// tick, relaxed: then after it by index), in x's bucket or first behind it;
+// p: where it is if v's four entries reach tick x.
+template <bool REL>
+__device__ __forceinline__ int start_in_bucket(const Hop &h, int t, int x, int own, v4i v, int p)
+{
+    const int end = at(h.tab, bucket(x, h.t0, h.sh, h.nb) + 1);  // the bucket's end
+    int q = p;
+    if (v[3] < x) {
+        int z = end;
+        while (q < z) {
+            const int mid = (q + z) >> 1;
+            const bool before = at(h.et, mid) < x;
+            q = before ? mid + 1 : q;
+            z = before ? z : mid;
+        }
+    }
+    if constexpr (REL) {
+        if (at(h.et, q) == t) {
+            // (the entries of tick t end by the bucket's end)
+            const int i = at(h.own(), own);
+            int z = end;
+            while (q < z) {
+                const int mid = (q + z) >> 1;
+                const bool before = at(h.ei(), mid) <= i;
+                q = before ? mid + 1 : q;
+                z = before ? z : mid;
+            }
+        }
+    }
+    return q;
+}
+
 // The events of the next list chained to an entry: positions [p, p + c).
 // Exact: ticks in (t + lo, min(t + hi, tn + lo)]; relaxed: events after the
 // entry's (own: its position), up to tick t + hi and up to the next entry's
-// event (tick tn, position next).  FIRST: the next entry is left out of it and
-// c only tells whether there is an event.  L: the table at the first tick's
-// bucket; v: four entries from there on (L <= count, and LIST_PAD guards of
-// INT_MAX, which stop every search, follow a list); relaxed, indices are only
-// read where ticks are equal.  skip: events of lane 0's entry that have been
-// put out already.
-template <bool REL, bool FIRST>
+// event (tick tn, position next).  L: the table at the first tick's bucket; v:
+// four entries from there on (L <= count, and LIST_PAD guards of INT_MAX,
+// which stop every search, follow a list); relaxed, indices are only read
+// where ticks are equal.  skip: events of lane 0's entry that have been put
+// out already.
+template <bool REL>
 __device__ __forceinline__ void events_of(const Hop &h, bool on, int t, int tn, int own, int next,
                                           int L, v4i v, int skip, int &p, int &c)
 {
     const int x = from_tick<REL>(h, t);
-    int lim = t + h.hi;
-    if constexpr (!FIRST) {
-        const int tl = REL ? tn : __builtin_elementwise_add_sat(tn, h.lo);
-        lim = tl < lim ? tl : lim;
-    }
+    const int tl = REL ? tn : __builtin_elementwise_add_sat(tn, h.lo);
+    const int lim = tl < t + h.hi ? tl : t + h.hi;
     const int k = (v[0] < x) + (v[1] < x) + (v[2] < x) + (v[3] < x);
     const int m = (v[0] <= lim) + (v[1] <= lim) + (v[2] <= lim) + (v[3] <= lim);
     p = L + k;
     c = m > k ? m - k : 0;
-    bool odd = v[3] < x;
-    if constexpr (!FIRST) odd |= v[3] <= lim;
+    bool odd = (v[3] < x) | (v[3] <= lim);
     if constexpr (REL) {
         odd |= (v[0] == t) | (v[1] == t) | (v[2] == t) | (v[3] == t);
-        if constexpr (!FIRST) odd |= (v[0] == tn) | (v[1] == tn) | (v[2] == tn) | (v[3] == tn);
+        odd |= (v[0] == tn) | (v[1] == tn) | (v[2] == tn) | (v[3] == tn);
     }
     c = on ? c : 0;
     odd &= on;
     if (skip) odd |= __lane_id() == 0;
     if (__builtin_expect(bal(odd) != 0, 0)) {
         if (odd) {
-            const int end = at(h.tab, bucket(x, h.t0, h.sh, h.nb) + 1);  // the bucket's end
-            int q = p;
-            if (v[3] < x) {
-                int z = end;
-                while (q < z) {
-                    const int mid = (q + z) >> 1;
-                    const bool before = at(h.et, mid) < x;
-                    q = before ? mid + 1 : q;
-                    z = before ? z : mid;
-                }
+            int q = start_in_bucket<REL>(h, t, x, own, v, p);
+            // (those entries were in range: the place exists)
+            p = q = q + (__lane_id() == 0 ? skip : 0);
+            const int in = REL && tn != FAR_TICK ? at(h.own(), next) : FAR_TICK;
+            auto in_range = [&](int e) {
+                const int te = at(h.et, e);
+                if constexpr (REL) return (te <= lim) & ((te != tn) || at(h.ei(), e) <= in);
+                else return te <= lim;
+            };
+            // (a guard ends every range; at most a batch is put out at once)
+            int step = 4;  // entries before q are in range
+            while (q + step <= h.count() && q < p + WAVE && in_range(q + step - 1)) {
+                q += step;
+                step *= 2;
             }
-            if constexpr (REL) {
-                if (at(h.et, q) == t) {
-                    // (the entries of tick t end by the bucket's end)
-                    const int i = at(h.own, own);
-                    int z = end;
-                    while (q < z) {
-                        const int mid = (q + z) >> 1;
-                        const bool before = at(h.ei, mid) <= i;
-                        q = before ? mid + 1 : q;
-                        z = before ? z : mid;
-                    }
-                }
+            int z = q + step <= h.count() ? q + step - 1 : h.count();  // z is not (or the end)
+            if (q >= p + WAVE) z = q;
+            while (q < z) {
+                const int mid = (q + z) >> 1;
+                const bool r = in_range(mid);
+                q = r ? mid + 1 : q;
+                z = r ? z : mid;
             }
-            if constexpr (FIRST) {
-                p = q;
-                c = at(h.et, q) <= lim ? 1 : 0;
-            } else {
-                // (those entries were in range: the place exists)
-                p = q = q + (__lane_id() == 0 ? skip : 0);
-                const int in = REL && tn != FAR_TICK ? at(h.own, next) : FAR_TICK;
-                auto in_range = [&](int e) {
-                    const int te = at(h.et, e);
-                    if constexpr (REL) return (te <= lim) & ((te != tn) || at(h.ei, e) <= in);
-                    else return te <= lim;
-                };
-                // (a guard ends every range; at most a batch is put out at once)
-                int step = 4;  // entries before q are in range
-                while (q + step <= h.count && q < p + WAVE && in_range(q + step - 1)) {
-                    q += step;
-                    step *= 2;
-                }
-                int z = q + step <= h.count ? q + step - 1 : h.count;  // z is not (or the end)
-                if (q >= p + WAVE) z = q;
-                while (q < z) {
-                    const int mid = (q + z) >> 1;
-                    const bool r = in_range(mid);
-                    q = r ? mid + 1 : q;
-                    z = r ? z : mid;
-                }
-                c = q - p < WAVE ? q - p : WAVE;
-            }
+            c = q - p < WAVE ? q - p : WAVE;
         }
     }
+}
+
+// The first event after an entry (of the same arguments): its position p and
+// tick (FAR_TICK if there is none).
+template <bool REL>
+__device__ __forceinline__ int first_after(const Hop &h, bool on, int t, int own, int L, v4i v,
+                                           int &p)
+{
+    const int x = from_tick<REL>(h, t);
+    const bool b0 = v[0] < x, b1 = v[1] < x, b2 = v[2] < x;
+    int f = b0 ? v[1] : v[0];
+    f = b1 ? v[2] : f;
+    f = b2 ? v[3] : f;
+    p = L + b0 + b1 + b2;
+    bool odd = f < x;
+    if constexpr (REL) odd |= f == t;
+    odd &= on;
+    if (__builtin_expect(bal(odd) != 0, 0)) {
+        if (odd) {
+            p = start_in_bucket<REL>(h, t, x, own, v, p);
+            f = at(h.et, p);
+            arrived(f);
+        }
+    }
+    return f;
+}
+
+// The first hop the other way round: the newest event of node 0's list for an
+// event of node 1's (tick t, position own) -- exact, the last one by tick
+// t - lo - 1; relaxed, the last one before it.  A node 1 event has one
+// predecessor at most, so this way there are no ranges to lay out.
+struct Back {
+    const ChainIdx &ix;
+    const NodeRow &row;
+    const int *et, *tab;  // node 0's list (from the guard before it)
+    int lo, hi, nb, sh, t0;
+
+    __device__ __forceinline__ Back(const ChainIdx &x, const NodeRow &w)
+        : ix(x), row(w), et(x.et + rdl(w.start, 0) - 1), tab(x.tab + rdl(w.boff, 0)),
+          lo(rdl(w.lo, 0)), hi(rdl(w.hi, 0)), nb(rdl(w.nb, 0)), sh(rdl(w.sh, 0)), t0(w.t0)
+    {
+    }
+    // stream indices of node 0's list and of node 1's
+    __device__ __forceinline__ const int *ei() const { return ix.ei + rdl(row.start, 0); }
+    __device__ __forceinline__ const int *own() const { return ix.ei + rdl(row.start, 1); }
+};
+template <bool REL> __device__ __forceinline__ int to_tick(const Back &h, int t)
+{
+    return REL ? t : t - h.lo - 1;
+}
+template <bool REL> __device__ __forceinline__ int table_at(const Back &h, int t)
+{
+    return at(h.tab, bucket(to_tick<REL>(h, t), h.t0, h.sh, h.nb));
+}
+// Its tick (the guard's, BEFORE, if there is none), from L, the table at the
+// last tick's bucket, and v, four of et from L on (the entry before the
+// bucket first); POS: and its position p.
+template <bool REL, bool POS>
+__device__ __forceinline__ int newest_before(const Back &h, bool on, int t, int own, int L, v4i v,
+                                             int &p)
+{
+    const int y = to_tick<REL>(h, t);
+    const bool b1 = v[1] <= y, b2 = v[2] <= y, b3 = v[3] <= y;
+    int f = b1 ? v[1] : v[0];
+    f = b2 ? v[2] : f;
+    f = b3 ? v[3] : f;
+    if (POS) p = L - 1 + b1 + b2 + b3;
+    // (a crowded bucket, or events of the same tick)
+    bool odd = b3;
+    if constexpr (REL) odd |= f == t;
+    odd &= on;
+    if (__builtin_expect(bal(odd) != 0, 0)) {
+        if (odd) {
+            const int i = REL ? at(h.own(), own) : 0;
+            // (every event before the bucket is older)
+            int q = L, z = at(h.tab, bucket(y, h.t0, h.sh, h.nb) + 1);
+            while (q < z) {
+                const int mid = (q + z) >> 1;
+                const bool older = REL ? at(h.ei(), mid) < i : at(h.et, mid + 1) <= y;
+                q = older ? mid + 1 : q;
+                z = older ? z : mid;
+            }
+            f = at(h.et, q);
+            arrived(f);
+            if (POS) p = q - 1;
+        }
+    }
+    return f;
+}
+// The position of that event for an event in range of it (lanes on; the
+// others' own is a position too).
+template <bool REL>
+__device__ __forceinline__ int first_of(const ChainIdx &ix, const NodeRow &row, bool on, int own)
+{
+    const Back h(ix, row);
+    const int t = at(ix.et + rdl(row.start, 1), own);
+    const int L = table_at<REL>(h, t);
+    int p;
+    newest_before<REL, true>(h, on, t, own, L, at4(h.et, L), p);
+    return p;
+}
+
+// Whether a row's walk starts at node 1's list, pulling.  2048 rows over lists
+// of about 2e5, ms a call from node 0's / pulling, by the lists' ratio.
+// Relaxed, two nodes: 2.4 / 0.7 at 1/4, 3.0 / 2.9 at 1, 1.4 / 2.9 at 2 (both
+// hops are one search; the shorter list wins).  Three nodes: 2.6 / 1.4 at 1/4,
+// 8.8 / 7.0 at 1, 4.7 / 2.7 at 8, 2.6 / 1.4 at 24; four: 4.5 / 3.5 at 24 (from
+// node 0's the same entries of node 1 are laid out and read again).
+__device__ __forceinline__ bool pulls(const NodeRow &row, int N)
+{
+    return N >= 2 && rdl(row.count, 1) / (N == 2 ? 1 : 32) <= rdl(row.count, 0);
 }
 
 // One wave's rings in LDS: ring q's entries as their positions in node q's
@@ -221,54 +335,75 @@ struct Seeds {
     const int *t, *a, *p;
 };
 
-// Entries of node E, in order, from the source [a, aend): node 0's events of
-// the row's first list (aend is either the list's end or past every tick that
-// an entry wanted from [a, ...) can reach), or, SEED, all of a pair's entries
-// of node 1.  sink(n, on, t, src, own, L, v): the next n <= 64 entries, one per
+// The source of a walk: events of node 0's list, of node 1's, pulled, or a
+// pair's entries of node 1.
+enum Source { FROM_FIRST, FROM_SECOND, FROM_PAIR };
+
+// Entries of node E, in order, from the source [a, aend) (aend is either the
+// source's end or past every tick that an entry wanted from [a, ...) can
+// reach).  sink(n, on, t, src, own, L, v): the next n <= 64 entries, one per
 // lane (on; the other lanes' values are in range too): tick, position of the
 // chain's first event in the source, own position; L, v: straight from the
 // source to a sink that SEARCHES node E + 1's list, that list's table at their
-// buckets and four entries from there on, else L = -1.
-template <bool REL, bool SEED, class Sink>
+// buckets and four entries from there on, else L = -1.  FROM_SECOND with
+// E = 0: sink.direct(pass, its lanes, position, its node 0 event's) for every event of
+// the source instead; a sink with FIRSTS gets E = 1's with src that position,
+// as does sink.search(on, t, src, own, L, v), which takes E = 1's entries of
+// one that SEARCHES.  E <= EMAX.
+template <bool REL, Source SRC, int EMAX, class Sink>
 __device__ __forceinline__ void walk(const ChainIdx &ix, const NodeRow &row, int E, int a,
                                      int aend, int *lds, Sink &sink, const Seeds &seed = Seeds())
 {
-    constexpr int S = SEED ? 1 : 0;  // the source's node
+    constexpr int S = SRC == FROM_PAIR ? 1 : 0;  // the source's node (pulled: one less)
+    constexpr bool PULL = SRC == FROM_SECOND;
     if (a >= aend) return;
     const int lane = __lane_id();
-    const int *src_t = SEED ? seed.t : ix.et + rdl(row.start, 0);
+    const int *src_t = SRC == FROM_PAIR ? seed.t : ix.et + rdl(row.start, PULL ? 1 : 0);
     auto place = [&](int from) { return from + lane < aend ? from + lane : aend - 1; };
     // (the source's batches in flight, each a read behind the one before:
     // while one is worked on, the next one's four entries, the table of the
     // one after it and the ticks of the third are read)
-    const Hop h = hop_of(ix, row, S);
+    const Hop h(ix, row, S);
+    const Back bk(ix, row);
     int t0 = 0, tn0 = 0, t1 = 0, tn1 = 0, t2 = 0, tn2 = 0, L0 = -1, L1 = -1;
     v4i v0 = {0, 0, 0, 0};
     auto ticks = [&](int from, int &t, int &tn) {
         const int np = place(from < aend ? from : aend - 1);
         t = at(src_t, np);
-        tn = at(src_t, np + 1);
+        if (!PULL) tn = at(src_t, np + 1);
     };
-    auto fill = [&](bool look) {
+    auto look = [&](int t) {
+        if constexpr (PULL) return table_at<REL>(bk, t);
+        else return table_at<REL>(h, t);
+    };
+    const int *to_et = PULL ? bk.et : h.et;
+    auto fill = [&](bool search) {
         ticks(a, t0, tn0);
         ticks(a + WAVE, t1, tn1);
         ticks(a + 2 * WAVE, t2, tn2);
-        if (!look) return;
-        L0 = table_at<REL>(h, t0);
-        L1 = table_at<REL>(h, t1);
-        v0 = at4(h.et, L0);
+        if (!search) return;
+        L0 = look(t0);
+        L1 = look(t1);
+        v0 = at4(to_et, L0);
     };
-    auto next_batch = [&](bool look) {
-        if (look) {
-            v0 = at4(h.et, L1);
+    auto next_batch = [&](bool search) {
+        if (search) {
+            v0 = at4(to_et, L1);
             L0 = L1;
-            L1 = table_at<REL>(h, t2);
+            L1 = look(t2);
         }
         t0 = t1;
         tn0 = tn1;
         t1 = t2;
         tn1 = tn2;
         ticks(a + 3 * WAVE, t2, tn2);
+    };
+    // whether a pulled event has a predecessor in range
+    // (m: the lanes')
+    auto has_first = [&](bool on, int t, int pos, int L, v4i v, int &p, unsigned long long &m) {
+        const int f = newest_before<REL, true>(bk, on, t, pos, L, v, p);
+        m = bal(f >= t - bk.hi) & bal(on);
+        return on & (f >= t - bk.hi);
     };
     if (E == S) {
         fill(Sink::SEARCHES);
@@ -277,9 +412,71 @@ __device__ __forceinline__ void walk(const ChainIdx &ix, const NodeRow &row, int
             const int t = t0, L = L0;
             const v4i v = v0;
             next_batch(Sink::SEARCHES);
-            sink(n, lane < n, t, pos, SEED ? at(seed.p, pos) : pos, L, v);
+            if constexpr (PULL) {
+                int first;
+                unsigned long long m;
+                const bool pass = has_first(lane < n, t, pos, L, v, first, m);
+                sink.direct(pass, m, pos, first);
+            } else
+                sink(n, lane < n, t, pos, S ? at(seed.p, pos) : pos, L, v);
             a += WAVE;
             if (a >= aend) return;
+        }
+    }
+    if constexpr (PULL && Sink::SEARCHES) {
+        // (three nodes: the second hop's reads are in flight too, a step of
+        // one of its batches beside each of the source's; its entries keep
+        // their ticks and first events' positions)
+        if (E == S + 1) {
+            const Hop hn(ix, row, S + 1);
+            int *own_q = lds, *t_q = lds + QCAP, *first_q = lds + 2 * QCAP;
+            int head = 0, n1 = 0;
+            int np = 0, own = 0, t = 0, first = 0, L = 0;  // the batch in flight
+            bool read = false;                             // its four entries too
+            v4i v = {0, 0, 0, 0};
+            fill(true);
+            for (;;) {
+                if (a < aend && n1 <= QCAP - WAVE) {
+                    const int pos = place(a), n = aend - a < WAVE ? aend - a : WAVE;
+                    const int tk = t0, Lk = L0;
+                    const v4i vk = v0;
+                    next_batch(true);
+                    int f;
+                    unsigned long long m;
+                    const bool pass = has_first(lane < n, tk, pos, Lk, vk, f, m);
+                    if (pass) {
+                        const int to = (head + n1 + below(m)) & (QCAP - 1);
+                        own_q[to] = pos;
+                        t_q[to] = tk;
+                        first_q[to] = f;
+                    }
+                    __builtin_amdgcn_wave_barrier();
+                    n1 += __builtin_popcountll(m);
+                    a += WAVE;
+                }
+                if (np) {
+                    if (!read) {
+                        v = at4(hn.et, L);
+                        read = true;
+                        continue;
+                    }
+                    sink.search(lane < np, t, first, own, L, v);
+                    np = 0;
+                }
+                if (n1 >= WAVE || (a >= aend && n1 > 0)) {
+                    np = n1 < WAVE ? n1 : WAVE;
+                    read = false;
+                    const int q = (head + (lane < np ? lane : np - 1)) & (QCAP - 1);
+                    own = own_q[q];
+                    t = t_q[q];
+                    first = first_q[q];
+                    L = table_at<REL>(hn, t);
+                    head = (head + np) & (QCAP - 1);
+                    n1 -= np;
+                } else if (a >= aend) {
+                    return;
+                }
+            }
         }
     }
     // lane q: ring q's first slot, its entries, and how many events of its
@@ -359,21 +556,24 @@ __device__ __forceinline__ void walk(const ChainIdx &ix, const NodeRow &row, int
         n = n < WAVE ? n : WAVE;
         const int i0 = lane < ck ? lane : ck - 1, i1 = lane + 1 < ck ? lane + 1 : ck - 1;
         const int s0 = (hk + i0) & (QCAP - 1), s1 = (hk + i1) & (QCAP - 1);
-        const int own = q[s0], src = q[QCAP + s0];
+        // (a pulled source's entries keep their ticks, if not their firsts)
+        const bool kept = PULL && !Sink::FIRSTS && k == S + 1;
+        const int own = q[s0], q0 = q[QCAP + s0];
         const int *list = ix.et + rdl(row.start, k);
-        const int t = at(list, own);
+        const int src = kept ? own : q0;
+        const int t = kept ? q0 : at(list, own);
         const bool on = lane < n;
         int nc = n;
-        if (k == E) {
+        if (EMAX == S + 1 || k == E) {
             sink(n, on, t, src, own, -1, v4i{0, 0, 0, 0});
         } else {
-            const Hop h = hop_of(ix, row, k);
+            const Hop h(ix, row, k);
             const int next = q[s1];
-            const int tn = lane + 1 < ck ? at(list, next) : FAR_TICK;
+            const int tn = lane + 1 >= ck ? FAR_TICK : kept ? q[QCAP + s1] : at(list, next);
             const int skip = rdl(sk, k);
             const int L = table_at<REL>(h, t);
             int p, c, tot, part;
-            events_of<REL, false>(h, on, t, tn, own, next, L, at4(h.et, L), skip, p, c);
+            events_of<REL>(h, on, t, tn, own, next, L, at4(h.et, L), skip, p, c);
             put(ring(k + 1), rdl(qh, k + 1) + rdl(qn, k + 1), n, p, c, src, skip, nc, tot, part);
             qn = lane == k + 1 ? qn + tot : qn;
             sk = lane == k ? part : sk;
@@ -398,14 +598,32 @@ __device__ __forceinline__ void walk(const ChainIdx &ix, const NodeRow &row, int
             const int a_next = a + WAVE, L_now = L0, t_now = t0, tn_now = tn0;
             const v4i v_now = v0;
             next_batch(true);
-            int own = pos, next = pos + 1;
-            if constexpr (SEED && REL) {
-                own = at(seed.p, pos);
-                next = at(seed.p, pos + 1);  // (behind the last: not used)
+            int nc, tot, part;
+            if constexpr (PULL) {
+                int first;
+                unsigned long long m;
+                const bool pass = has_first(lane < n, t_now, pos, L_now, v_now, first, m);
+                if (pass) {
+                    int *q = ring(S + 1);
+                    const int to = (h1 + n1 + below(m)) & (QCAP - 1);
+                    q[to] = pos;
+                    q[QCAP + to] = Sink::FIRSTS ? first : t_now;
+                }
+                __builtin_amdgcn_wave_barrier();
+                nc = n;
+                tot = __builtin_popcountll(m);
+                part = 0;
+            } else {
+                int own = pos, next = pos + 1;
+                if constexpr (S && REL) {
+                    own = at(seed.p, pos);
+                    next = at(seed.p, pos + 1);  // (behind the last: not used)
+                }
+                int p, c;
+                events_of<REL>(h, lane < n, t_now, tn_now, own, next, L_now, v_now, sk0, p,
+                                      c);
+                put(ring(S + 1), h1 + n1, n, p, c, pos, sk0, nc, tot, part);
             }
-            int p, c, nc, tot, part;
-            events_of<REL, false>(h, lane < n, t_now, tn_now, own, next, L_now, v_now, sk0, p, c);
-            put(ring(S + 1), h1 + n1, n, p, c, pos, sk0, nc, tot, part);
             n1 += tot;
             sk0 = part;
             a += nc;
@@ -414,7 +632,8 @@ __device__ __forceinline__ void walk(const ChainIdx &ix, const NodeRow &row, int
         }
         for (;;) {
             const bool end = a >= aend;
-            const unsigned long long ready = bal(qn >= (lane == E ? WAVE : WAVE + 1));
+            const unsigned long long ready =
+                EMAX == S + 1 ? 0 : bal(qn >= (lane == E ? WAVE : WAVE + 1));
             int k;
             bool flush = false;
             if (ready) {
@@ -427,7 +646,7 @@ __device__ __forceinline__ void walk(const ChainIdx &ix, const NodeRow &row, int
                 k = S + 1;
                 flush = true;
             } else {
-                const unsigned long long some = bal(qn > 0);
+                const unsigned long long some = EMAX == S + 1 ? 0 : bal(qn > 0);
                 if (!some) return;
                 k = (int)__builtin_ctzll(some);
                 flush = true;

@@ -112,6 +112,62 @@ def test_dense_segments(ctx, fe, T, mean_gap):
             ctx.set_param(p, v)
 
 
+@pytest.mark.parametrize("ratio", [0.1, 0.95, 1.05, 7.0, 30.0, 34.0])
+@pytest.mark.parametrize("gap", [0, 1, 9])
+def test_either_list_first(ctx, ratio, gap):
+    # the second nodes' lists are `ratio` times the first nodes' length: walked
+    # from the shorter side on, up to the lines between, with ties (gap 0, 1)
+    rng = np.random.default_rng(int(10 * ratio) + gap)
+    n = 12_000
+    first = rng.random(n) < 1.0 / (1.0 + ratio)
+    ids_h = (rng.integers(0, 2, n) + np.where(first, 0, 2)).astype(np.int32)
+    ticks_h = np.cumsum(rng.integers(0, 2 * gap + 1, n) * (rng.random(n) < 0.7)).astype(np.int32)
+    ivs = [(0, 1), (0, 6), (2, 40), (30, 33), (0, 500)]
+    eps = []
+    for _ in range(300):
+        k = int(rng.integers(2, 6))
+        ty = (int(rng.integers(0, 2)),) + tuple(int(x) for x in rng.integers(2, 4, k - 1))
+        iv = [ivs[int(x)] for x in rng.integers(0, len(ivs), k - 1)]
+        eps.append((ty, tuple(l for l, _ in iv), tuple(h for _, h in iv)))
+    for nmax in (2, 3, 5):  # (tables of two, three and more nodes)
+        cand = synth.pack([e for e in eps if len(e[0]) <= nmax])
+        banner("lists 1:%g gap %d nmax %d" % (ratio, gap, nmax))
+        _check(ctx, ids_h, ticks_h, 4, cand, "ratio=%g gap=%d nmax=%d" % (ratio, gap, nmax))
+
+
+@pytest.mark.parametrize("M", [6800, 14001, 70001, 140007])
+def test_survivors_in_segments(ctx, fe, M):
+    # the exact pass over the segments of survivors alone, looked for among 1
+    # to 16 rows a wave
+    rng = np.random.default_rng(M)
+    n = 20_000
+    ids_h = rng.integers(0, 2, n).astype(np.int32)
+    ticks_h = np.cumsum(rng.integers(0, 9, n)).astype(np.int32)
+    eps = synth.random_episodes(rng, 211, 2, 3, IVS, n_min=1)
+    cand = synth.pack(eps)
+    many = synth.pack([eps[i % len(eps)] for i in range(M)])
+    up = oracle_counts(ids_h, ticks_h, 2, cand, RELAXED)
+    ids, ticks = ctx.stream_tensors(ids_h, ticks_h)
+    keys = (fe.PARAM_CROSSOVER_B, fe.PARAM_CROSSOVER_B_RELAXED, fe.PARAM_TARGET_WAVES)
+    saved = [ctx.get_param(p) for p in keys]
+    try:
+        for p in keys:
+            ctx.set_param(p, 1 << 22)
+        for theta in (1, int(np.median(up)), int(up.max()) + 1):
+            banner("survivors in segments: M=%d theta=%d" % (M, theta))
+            wu, we = oracle.two_pass(ids_h, ticks_h, 2, cand["types"], cand["len"], cand["lo"],
+                                     cand["hi"], theta, projection=True)
+            gu, ge, ns = ctx.count_two_pass(ids, ticks, 2, many, theta)
+            at = np.arange(M) % len(eps)
+            assert np.array_equal(gu.cpu().numpy(), wu[at])
+            assert np.array_equal(ge.cpu().numpy(), we[at])
+            assert int(ns.item()) == int((wu[at] >= theta).sum())
+            assert ctx.stats()["segments_max"] >= 2
+    finally:
+        for p, v in zip(keys, saved):
+            ctx.set_param(p, v)
+
+
 @pytest.mark.parametrize("T", [1000, 1025, 4096, 4097, 9000])
 def test_many_types(ctx, T):
     # (beyond 4096 types the Map kernels count)
