@@ -966,8 +966,8 @@ template <bool REL> struct SeedOut {
     __device__ __forceinline__ void direct(bool, unsigned long long, int, int) {}
     __device__ __forceinline__ void operator()(int c, bool on, int tk, int src, int own, int, v4i)
     {
-        const int s = on ? at(ix.ei + rdl(row.start, 0), src) : FAR_TICK;
-        const int i = on ? at(ix.ei + rdl(row.start, 1), own) : FAR_TICK;
+        const int s = at(ix.ei + rdl(row.start, 0), src);
+        const int i = at(ix.ei + rdl(row.start, 1), own);
         if (on) {
             const int64_t to = base + n + __lane_id();
             t[to] = tk;

@@ -37,6 +37,8 @@ constexpr int BEFORE = -0x7fffffff - 1;
 
 typedef int v4i __attribute__((ext_vector_type(4), aligned(4)));
 
+// (only where all lanes are on: in a branch that some lanes skip, the register
+// may have been filled for the others alone)
 __device__ __forceinline__ int rdl(int v, int k) { return __builtin_amdgcn_readlane(v, k); }
 __device__ __forceinline__ unsigned long long bal(bool p) { return __builtin_amdgcn_ballot_w64(p); }
 __device__ __forceinline__ int below(unsigned long long m)
@@ -93,9 +95,16 @@ __device__ __forceinline__ v4i at4(const int *list, int i)
     return *(const v4i *)((const char *)list + (size_t)((unsigned)i << 2));
 }
 
-// A hop (wave-uniform): from node k's list to the next node's.  What only
-// ties and crowded buckets need is made where it is used, as a walk has more
-// uniform values than eight waves a SIMD leave it registers for.
+// What only ties and crowded buckets need: stream indices of the list looked
+// into and of the entries' own, the former's length.  It is made where a wave
+// needs it, as a walk has more uniform values than eight waves a SIMD leave it
+// registers for, and by all lanes.
+struct Spare {
+    const int *ei, *own;
+    int count;
+};
+
+// A hop (wave-uniform): from node k's list to the next node's.
 struct Hop {
     const ChainIdx &ix;
     const NodeRow &row;
@@ -109,10 +118,11 @@ struct Hop {
           nb(rdl(w.nb, k_ + 1)), sh(rdl(w.sh, k_ + 1)), t0(w.t0)
     {
     }
-    // stream indices of the next list and of node k's, the former's length
-    __device__ __forceinline__ const int *ei() const { return ix.ei + rdl(row.start, k + 1); }
-    __device__ __forceinline__ const int *own() const { return ix.ei + rdl(row.start, k); }
-    __device__ __forceinline__ int count() const { return rdl(row.count, k + 1); }
+    __device__ __forceinline__ Spare spare() const
+    {
+        return Spare{ix.ei + rdl(row.start, k + 1), ix.ei + rdl(row.start, k),
+                     rdl(row.count, k + 1)};
+    }
 };
 // the tick a hop's events start at, and its place in the table
 template <bool REL> __device__ __forceinline__ int from_tick(const Hop &h, int t)
@@ -128,7 +138,8 @@ template <bool REL> __device__ __forceinline__ int table_at(const Hop &h, int t)
 // tick, relaxed: then after it by index), in x's bucket or first behind it;
 // p: where it is if v's four entries reach tick x.
 template <bool REL>
-__device__ __forceinline__ int start_in_bucket(const Hop &h, int t, int x, int own, v4i v, int p)
+__device__ __forceinline__ int start_in_bucket(const Hop &h, const Spare &sp, int t, int x, int own,
+                                               v4i v, int p)
 {
     const int end = at(h.tab, bucket(x, h.t0, h.sh, h.nb) + 1);  // the bucket's end
     int q = p;
@@ -144,11 +155,11 @@ __device__ __forceinline__ int start_in_bucket(const Hop &h, int t, int x, int o
     if constexpr (REL) {
         if (at(h.et, q) == t) {
             // (the entries of tick t end by the bucket's end)
-            const int i = at(h.own(), own);
+            const int i = at(sp.own, own);
             int z = end;
             while (q < z) {
                 const int mid = (q + z) >> 1;
-                const bool before = at(h.ei(), mid) <= i;
+                const bool before = at(sp.ei, mid) <= i;
                 q = before ? mid + 1 : q;
                 z = before ? z : mid;
             }
@@ -185,23 +196,24 @@ __device__ __forceinline__ void events_of(const Hop &h, bool on, int t, int tn, 
     odd &= on;
     if (skip) odd |= __lane_id() == 0;
     if (__builtin_expect(bal(odd) != 0, 0)) {
+        const Spare sp = h.spare();
         if (odd) {
-            int q = start_in_bucket<REL>(h, t, x, own, v, p);
+            int q = start_in_bucket<REL>(h, sp, t, x, own, v, p);
             // (those entries were in range: the place exists)
             p = q = q + (__lane_id() == 0 ? skip : 0);
-            const int in = REL && tn != FAR_TICK ? at(h.own(), next) : FAR_TICK;
+            const int in = REL && tn != FAR_TICK ? at(sp.own, next) : FAR_TICK;
             auto in_range = [&](int e) {
                 const int te = at(h.et, e);
-                if constexpr (REL) return (te <= lim) & ((te != tn) || at(h.ei(), e) <= in);
+                if constexpr (REL) return (te <= lim) & ((te != tn) || at(sp.ei, e) <= in);
                 else return te <= lim;
             };
             // (a guard ends every range; at most a batch is put out at once)
             int step = 4;  // entries before q are in range
-            while (q + step <= h.count() && q < p + WAVE && in_range(q + step - 1)) {
+            while (q + step <= sp.count && q < p + WAVE && in_range(q + step - 1)) {
                 q += step;
                 step *= 2;
             }
-            int z = q + step <= h.count() ? q + step - 1 : h.count();  // z is not (or the end)
+            int z = q + step <= sp.count ? q + step - 1 : sp.count;  // z is not (or the end)
             if (q >= p + WAVE) z = q;
             while (q < z) {
                 const int mid = (q + z) >> 1;
@@ -230,8 +242,9 @@ __device__ __forceinline__ int first_after(const Hop &h, bool on, int t, int own
     if constexpr (REL) odd |= f == t;
     odd &= on;
     if (__builtin_expect(bal(odd) != 0, 0)) {
+        const Spare sp = h.spare();
         if (odd) {
-            p = start_in_bucket<REL>(h, t, x, own, v, p);
+            p = start_in_bucket<REL>(h, sp, t, x, own, v, p);
             f = at(h.et, p);
             arrived(f);
         }
@@ -254,9 +267,10 @@ struct Back {
           lo(rdl(w.lo, 0)), hi(rdl(w.hi, 0)), nb(rdl(w.nb, 0)), sh(rdl(w.sh, 0)), t0(w.t0)
     {
     }
-    // stream indices of node 0's list and of node 1's
-    __device__ __forceinline__ const int *ei() const { return ix.ei + rdl(row.start, 0); }
-    __device__ __forceinline__ const int *own() const { return ix.ei + rdl(row.start, 1); }
+    __device__ __forceinline__ Spare spare() const
+    {
+        return Spare{ix.ei + rdl(row.start, 0), ix.ei + rdl(row.start, 1), rdl(row.count, 0)};
+    }
 };
 template <bool REL> __device__ __forceinline__ int to_tick(const Back &h, int t)
 {
@@ -284,13 +298,14 @@ __device__ __forceinline__ int newest_before(const Back &h, bool on, int t, int 
     if constexpr (REL) odd |= f == t;
     odd &= on;
     if (__builtin_expect(bal(odd) != 0, 0)) {
+        const Spare sp = h.spare();
         if (odd) {
-            const int i = REL ? at(h.own(), own) : 0;
+            const int i = REL ? at(sp.own, own) : 0;
             // (every event before the bucket is older)
             int q = L, z = at(h.tab, bucket(y, h.t0, h.sh, h.nb) + 1);
             while (q < z) {
                 const int mid = (q + z) >> 1;
-                const bool older = REL ? at(h.ei(), mid) < i : at(h.et, mid + 1) <= y;
+                const bool older = REL ? at(sp.ei, mid) < i : at(h.et, mid + 1) <= y;
                 q = older ? mid + 1 : q;
                 z = older ? z : mid;
             }
