@@ -954,7 +954,9 @@ __global__ __launch_bounds__(256) void k_masks(ChainIdx ix, int places, int T, i
 // The entries of node 1 of every pair of frequent types and interval, in the
 // place of the second type's list within the pair's share; and the pair's
 // count: each entry is a completion of the chain that starts at its first
-// event (a chain's later ones start no later than the one taken).
+// event (a chain's later ones start no later than the one taken).  An entry
+// names its chain's first event by its position or, exact, where no two chains
+// start at one tick, by its tick, which is then at hand where it is needed.
 template <bool REL> struct SeedOut {
     const ChainIdx &ix;
     const NodeRow &row;
@@ -968,10 +970,11 @@ template <bool REL> struct SeedOut {
     {
         const int s = at(ix.ei + rdl(row.start, 0), src);
         const int i = at(ix.ei + rdl(row.start, 1), own);
+        const int first = REL ? src : at(ix.et + rdl(row.start, 0), src);
         if (on) {
             const int64_t to = base + n + __lane_id();
             t[to] = tk;
-            a[to] = src;
+            a[to] = first;
             p[to] = own;
         }
         cnt.choose(bal(on), s, i, cnt.r, cnt.cnt);
@@ -1084,36 +1087,54 @@ template <bool REL> struct Columns {
     const ChainIdx &ix;
     int q0, nq;                      // the words of this wave
     int start0, start_m;             // node 0's and the last shared node's lists
-    const int *seed_a;               // the source's positions in node 0's list
+    int boff0, nb0, sh0, t0;         // node 0's table
+    const int *seed_a;               // the source's chains' first events
     Flip flip;
     int lo[QW], hi[QW];              // the words' hops (wave-uniform)
     int cnt[QW], tl[QW], ol[QW];     // per type: completions, the last entry counted
     int t_last = -(1 << 30);
     static constexpr bool SEARCHES = false, FIRSTS = true;
     __device__ __forceinline__ void direct(bool, unsigned long long, int, int) {}
+    // What a batch needs: its entries' ticks, places, chains' first events (as
+    // a pair's entries name them) and mask words.
+    struct In {
+        int t, own, first;
+        uint2 w[QW];
+    };
+    __device__ __forceinline__ void read(bool on, int src, int own, In &in) const
+    {
+        in.own = own;
+        in.first = at(seed_a, src);
+        const uint2 *row = j.mask + (int64_t)(start_m + own) * j.Q + q0;
+#pragma unroll
+        for (int q = 0; q < QW; ++q) in.w[q] = on && q < nq ? row[q] : make_uint2(0, 0);
+    }
     __device__ __forceinline__ void operator()(int n, bool on, int t, int src, int own, int, v4i)
     {
+        In in;
+        in.t = t;
+        read(on, src, own, in);
+        take(n, on, in);
+    }
+    __device__ __forceinline__ void take(int n, bool on, const In &in)
+    {
         const int lane = __lane_id();
-        const int apos = at(seed_a, src);
-        const int st = ix.et[start0 + apos];
+        const int t = in.t, own = in.own;
+        const int st = REL ? ix.et[start0 + in.first] : in.first;
         // chains' stretches: first and last bits, and the tick of the last
         // entry before the lane's own (a stretch that goes on from the batch
         // before has it among its own, and so within the width)
-        const int ap = __shfl_up(apos, 1);
-        const unsigned long long first = bal((lane == 0) | (apos != ap));
+        const int before_first = __shfl_up(in.first, 1);
+        const unsigned long long first = bal(in.first != before_first) | 1ull;
         const unsigned long long last = (first >> 1) | (1ull << 63);
         const int g = 63 - __builtin_clzll(first & ((2ull << lane) - 1ull));
         const int tb = __shfl(t, g > 0 ? g - 1 : 0);
         const int tp = g > 0 ? tb : t_last;
         t_last = rdl(t, n - 1);
-        const uint2 *row = j.mask + (int64_t)(start_m + own) * j.Q + q0;
-        uint2 w[QW];
-#pragma unroll
-        for (int q = 0; q < QW; ++q) w[q] = on && q < nq ? row[q] : make_uint2(0, 0);
 #pragma unroll
         for (int q = 0; q < QW; ++q) {
             if (q >= nq) break;
-            unsigned c0 = w[q].x, c1 = w[q].y;
+            unsigned c0 = in.w[q].x, c1 = in.w[q].y;
             flip(c0, c1);
             {
                 const unsigned long long c = c0 | (unsigned long long)c1 << 32, x = c | last;
@@ -1136,7 +1157,7 @@ template <bool REL> struct Columns {
                 bool cut = has & (te <= tj + hi[q]);
                 const bool open = cut & (REL ? te >= tj : te > tj + lo[q]);
                 if (bal(open) != 0) {
-                    const int s = ix.ei[start0 + rdl(apos, e)];
+                    const int s = chain_start(rdl(in.first, e));
                     const int ob = __shfl(own, before >= 0 ? before : 0);
                     const int oj = before >= 0 ? ob : ol[q];
                     if (open) cut = s <= completed(q, tj, oj);
@@ -1154,6 +1175,20 @@ template <bool REL> struct Columns {
                 ol[q] = top >= 0 ? ov : ol[q];
             }
         }
+    }
+    // stream index of a chain's first event (exact: the last at its tick)
+    __device__ __forceinline__ int chain_start(int first) const
+    {
+        if (REL) return ix.ei[start0 + first];
+        const int b = bucket(first, t0, sh0, nb0);
+        int a = ix.tab[boff0 + b], z = ix.tab[boff0 + b + 1];
+        while (a < z) {
+            const int mid = (a + z) >> 1;
+            const bool past = bal(ix.et[start0 + mid] > first) != 0;
+            a = past ? a : mid + 1;
+            z = past ? mid : z;
+        }
+        return ix.ei[start0 + a - 1];
     }
     // index of the completion of the entry at tick tj (relaxed: at place oj)
     // by the lane's type of word q: its first event in range
@@ -1201,12 +1236,20 @@ __global__ __launch_bounds__(256) void k_order(const int *__restrict__ F, int w,
 // last types: what a wave reads at random -- the last stage's list and the
 // masks of its entries -- is then the same few lists for all waves at a time,
 // and stays in every XCD's L2.
-//   Bound by instruction issue: 64 entries cost about 50 instructions for 64
-// types and a hop, where the scan of the whole stream it replaces costs about
-// 60 for each 64 events and 64 siblings; an episode of 3 nodes has a few
-// hundred entries in 1.06e6 events.
-template <bool REL>
-__global__ __launch_bounds__(WAVE) void k_siblings(SibJob j, int64_t cnt)
+//   64 entries cost about 55 vector instructions for 64 types and a hop, where
+// the scan of the whole stream it replaces costs about 60 for each 64 events
+// and 64 siblings; an episode of 3 nodes has a few hundred entries in 1.06e6
+// events.  It is bound by issue (0.6 of its rate) and by the masks' latency
+// at the waves its registers leave, so the lengths have kernels of their own:
+// two and three shared nodes take the mask words of a batch while the one
+// before is counted, 7 and 6 waves a SIMD instead of 4 and 5 -- 64 types and 3
+// hops over 780 s, four-node level 4.94 -> 4.2 ms; 200 types, three-node
+// level 1.04 -> 0.87 ms.
+// Waves a SIMD is given registers for, by length (2, 3, more shared nodes).
+constexpr int sib_waves(bool rel, int emax) { return emax == 1 ? 7 : emax == 2 && !rel ? 6 : 5; }
+
+template <bool REL, int EMAX>
+__global__ __launch_bounds__(WAVE, sib_waves(REL, EMAX)) void k_siblings(SibJob j, int64_t cnt)
 {
     extern __shared__ int lds[];
     const int64_t item = grid_item();
@@ -1240,7 +1283,8 @@ __global__ __launch_bounds__(WAVE) void k_siblings(SibJob j, int64_t cnt)
     rows.ts = rows.hs = j.w;
     rows.tk = rows.hk = 3;
     rows.N = j.m;
-    const int m = load_row(j.ix, rows, al, row);
+    load_row(j.ix, rows, al, row);
+    const int m = EMAX < NMAX - 2 ? EMAX + 1 : j.m;
     // the entries of its first pair (node 0, hop 0, node 1)
     const int *key = j.F + al * j.w;
     int k0 = 0;
@@ -1248,7 +1292,17 @@ __global__ __launch_bounds__(WAVE) void k_siblings(SibJob j, int64_t cnt)
     const int64_t ak = (int64_t)j.rank[key[0]] * j.n_iv + k0;
     const int64_t sd = ak * j.sd.stride + rdl(row.start, 1);
     const Seeds seed{j.sd.t + sd, j.sd.a + sd, j.sd.p + sd};
-    Columns<REL> sink{j, j.ix, q0, nq, rdl(row.start, 0), rdl(row.start, m - 1), seed.a};
+    Columns<REL> sink{j,
+                      j.ix,
+                      q0,
+                      nq,
+                      rdl(row.start, 0),
+                      rdl(row.start, m - 1),
+                      rdl(row.boff, 0),
+                      rdl(row.nb, 0),
+                      rdl(row.sh, 0),
+                      row.t0,
+                      seed.a};
 #pragma unroll
     for (int q = 0; q < QW; ++q) {
         const int h = (q0 + (q < nq ? q : 0)) % j.n_iv;
@@ -1258,7 +1312,7 @@ __global__ __launch_bounds__(WAVE) void k_siblings(SibJob j, int64_t cnt)
         sink.tl[q] = -(1 << 30);
         sink.ol[q] = 0;
     }
-    walk<REL, FROM_PAIR, NMAX - 2>(j.ix, row, m - 1, 0, j.sd.n[ak * j.nF + j.rank[key[3]]], lds, sink, seed);
+    walk<REL, FROM_PAIR, EMAX>(j.ix, row, m - 1, 0, j.sd.n[ak * j.nF + j.rank[key[3]]], lds, sink, seed);
     // counts by type to the siblings
     int *tot = lds;
 #pragma unroll
@@ -1310,6 +1364,19 @@ void launch_order(const int *F, int w, int64_t cnt, int T, int *order, hipStream
     hipLaunchKernelGGL(k_order<true>, grid, dim3(256), lds, s, F, w, (int)cnt, T, next, order);
 }
 
+namespace {
+template <bool REL>
+void siblings_by_length(const SibJob &j, int64_t cnt, dim3 grid, size_t lds, hipStream_t s)
+{
+    if (j.m == 2)
+        hipLaunchKernelGGL((k_siblings<REL, 1>), grid, dim3(WAVE), lds, s, j, cnt);
+    else if (j.m == 3)
+        hipLaunchKernelGGL((k_siblings<REL, 2>), grid, dim3(WAVE), lds, s, j, cnt);
+    else
+        hipLaunchKernelGGL((k_siblings<REL, NMAX - 2>), grid, dim3(WAVE), lds, s, j, cnt);
+}
+}  // namespace
+
 void launch_siblings(bool rel, const SibJob &j, int64_t cnt, hipStream_t s)
 {
     if (cnt <= 0) return;
@@ -1317,8 +1384,8 @@ void launch_siblings(bool rel, const SibJob &j, int64_t cnt, hipStream_t s)
     // (rings of the stages between node 1 and the last; the counts at the end)
     const int rings = (j.m > 2 ? j.m - 2 : 0) * RING_INTS;
     const size_t lds = (size_t)(rings > QW * WAVE ? rings : QW * WAVE) * sizeof(int);
-    if (rel) hipLaunchKernelGGL(k_siblings<true>, grid, dim3(WAVE), lds, s, j, cnt);
-    else hipLaunchKernelGGL(k_siblings<false>, grid, dim3(WAVE), lds, s, j, cnt);
+    if (rel) siblings_by_length<true>(j, cnt, grid, lds, s);
+    else siblings_by_length<false>(j, cnt, grid, lds, s);
 }
 
 }  // namespace fe

@@ -175,10 +175,12 @@ __device__ __forceinline__ int start_in_bucket(const Hop &h, const Spare &sp, in
 // four entries from there on (L <= count, and LIST_PAD guards of INT_MAX,
 // which stop every search, follow a list); relaxed, indices are only read
 // where ticks are equal.  skip: events of lane 0's entry that have been put
-// out already.
+// out already.  via: own and next are places in a pair's share, and their
+// positions there.
 template <bool REL>
 __device__ __forceinline__ void events_of(const Hop &h, bool on, int t, int tn, int own, int next,
-                                          int L, v4i v, int skip, int &p, int &c)
+                                          int L, v4i v, int skip, int &p, int &c,
+                                          const int *via = nullptr)
 {
     const int x = from_tick<REL>(h, t);
     const int tl = REL ? tn : __builtin_elementwise_add_sat(tn, h.lo);
@@ -198,10 +200,12 @@ __device__ __forceinline__ void events_of(const Hop &h, bool on, int t, int tn, 
     if (__builtin_expect(bal(odd) != 0, 0)) {
         const Spare sp = h.spare();
         if (odd) {
+            if (REL && via) own = at(via, own);
             int q = start_in_bucket<REL>(h, sp, t, x, own, v, p);
             // (those entries were in range: the place exists)
             p = q = q + (__lane_id() == 0 ? skip : 0);
-            const int in = REL && tn != FAR_TICK ? at(sp.own, next) : FAR_TICK;
+            const int in =
+                REL && tn != FAR_TICK ? at(sp.own, via ? at(via, next) : next) : FAR_TICK;
             auto in_range = [&](int e) {
                 const int te = at(h.et, e);
                 if constexpr (REL) return (te <= lim) & ((te != tn) || at(sp.ei, e) <= in);
@@ -364,7 +368,9 @@ enum Source { FROM_FIRST, FROM_SECOND, FROM_PAIR };
 // E = 0: sink.direct(pass, its lanes, position, its node 0 event's) for every event of
 // the source instead; a sink with FIRSTS gets E = 1's with src that position,
 // as does sink.search(on, t, src, own, L, v), which takes E = 1's entries of
-// one that SEARCHES.  E <= EMAX.
+// one that SEARCHES.  E <= EMAX; FROM_PAIR, E = EMAX where that is 1 or 2, with
+// sink.read(on, src, own, in) and sink.take(n, on, in) for a batch whose ticks
+// are in.t, and E > 2 else.
 template <bool REL, Source SRC, int EMAX, class Sink>
 __device__ __forceinline__ void walk(const ChainIdx &ix, const NodeRow &row, int E, int a,
                                      int aend, int *lds, Sink &sink, const Seeds &seed = Seeds())
@@ -380,12 +386,14 @@ __device__ __forceinline__ void walk(const ChainIdx &ix, const NodeRow &row, int
     // one after it and the ticks of the third are read)
     const Hop h(ix, row, S);
     const Back bk(ix, row);
-    int t0 = 0, tn0 = 0, t1 = 0, tn1 = 0, t2 = 0, tn2 = 0, L0 = -1, L1 = -1;
+    int t0 = 0, t1 = 0, t2 = 0, L0 = -1, L1 = -1;
     v4i v0 = {0, 0, 0, 0};
-    auto ticks = [&](int from, int &t, int &tn) {
-        const int np = place(from < aend ? from : aend - 1);
-        t = at(src_t, np);
-        if (!PULL) tn = at(src_t, np + 1);
+    auto ticks = [&](int from) { return at(src_t, place(from < aend ? from : aend - 1)); };
+    const int t_end = PULL ? 0 : at(src_t, aend);
+    // the next source event's tick: the next lane's, or the next batch's first
+    auto next_tick = [&](int from, int t, int t_after) {
+        const int tn = __builtin_amdgcn_update_dpp(rdl(t_after, 0), t, 0x130, 0xf, 0xf, false);
+        return from + lane == aend - 1 ? t_end : tn;  // (wave_shl:1)
     };
     auto look = [&](int t) {
         if constexpr (PULL) return table_at<REL>(bk, t);
@@ -393,9 +401,9 @@ __device__ __forceinline__ void walk(const ChainIdx &ix, const NodeRow &row, int
     };
     const int *to_et = PULL ? bk.et : h.et;
     auto fill = [&](bool search) {
-        ticks(a, t0, tn0);
-        ticks(a + WAVE, t1, tn1);
-        ticks(a + 2 * WAVE, t2, tn2);
+        t0 = ticks(a);
+        t1 = ticks(a + WAVE);
+        t2 = ticks(a + 2 * WAVE);
         if (!search) return;
         L0 = look(t0);
         L1 = look(t1);
@@ -408,10 +416,8 @@ __device__ __forceinline__ void walk(const ChainIdx &ix, const NodeRow &row, int
             L1 = look(t2);
         }
         t0 = t1;
-        tn0 = tn1;
         t1 = t2;
-        tn1 = tn2;
-        ticks(a + 3 * WAVE, t2, tn2);
+        t2 = ticks(a + 3 * WAVE);
     };
     // whether a pulled event has a predecessor in range
     // (m: the lanes')
@@ -420,7 +426,28 @@ __device__ __forceinline__ void walk(const ChainIdx &ix, const NodeRow &row, int
         m = bal(f >= t - bk.hi) & bal(on);
         return on & (f >= t - bk.hi);
     };
-    if (E == S) {
+    if constexpr (SRC == FROM_PAIR && EMAX == S) {
+        // (what the sink reads for a batch is in flight while it takes the
+        // one before, its places a batch earlier)
+        typename Sink::In now, next;
+        auto on_at = [&](int from) { return from + lane < aend; };
+        int own = at(seed.p, place(a));
+        now.t = at(src_t, place(a));
+        sink.read(on_at(a), place(a), own, now);
+        own = at(seed.p, place(a + WAVE < aend ? a + WAVE : aend - 1));
+        for (;;) {
+            const int an = a + WAVE < aend ? a + WAVE : aend - 1;
+            const int a2 = a + 2 * WAVE < aend ? a + 2 * WAVE : aend - 1;
+            next.t = at(src_t, place(an));
+            sink.read(on_at(an), place(an), own, next);
+            own = at(seed.p, place(a2));
+            sink.take(aend - a < WAVE ? aend - a : WAVE, on_at(a), now);
+            a += WAVE;
+            if (a >= aend) return;
+            now = next;
+        }
+    }
+    if (SRC != FROM_PAIR && E == S) {
         fill(Sink::SEARCHES);
         for (;;) {
             const int pos = place(a), n = aend - a < WAVE ? aend - a : WAVE;
@@ -432,12 +459,14 @@ __device__ __forceinline__ void walk(const ChainIdx &ix, const NodeRow &row, int
                 unsigned long long m;
                 const bool pass = has_first(lane < n, t, pos, L, v, first, m);
                 sink.direct(pass, m, pos, first);
-            } else
-                sink(n, lane < n, t, pos, S ? at(seed.p, pos) : pos, L, v);
+            } else {
+                sink(n, lane < n, t, pos, pos, L, v);
+            }
             a += WAVE;
             if (a >= aend) return;
         }
     }
+    if constexpr (EMAX == S) return;
     if constexpr (PULL && Sink::SEARCHES) {
         // (three nodes: the second hop's reads are in flight too, a step of
         // one of its batches beside each of the source's; its entries keep
@@ -494,12 +523,6 @@ __device__ __forceinline__ void walk(const ChainIdx &ix, const NodeRow &row, int
             }
         }
     }
-    // lane q: ring q's first slot, its entries, and how many events of its
-    // first entry's range have been put out already (an entry with more than
-    // a batch's worth is put out in parts); ring S+1's in scalars
-    int qh = 0, qn = 0, sk = 0;
-    int h1 = 0, n1 = 0, sk0 = 0;
-    auto ring = [&](int q) { return lds + (q - 1 - S) * RING_INTS; };
     // c events from p on of each lane's entry to the ring at slot `tail`, in
     // entry order; n: entries given, nc: taken whole, tot: events put out,
     // part: events of the next entry put out in total
@@ -562,6 +585,49 @@ __device__ __forceinline__ void walk(const ChainIdx &ix, const NodeRow &row, int
             }
         __builtin_amdgcn_wave_barrier();
     };
+    if constexpr (SRC == FROM_PAIR && EMAX == S + 1) {
+        // (the same for the next node's entries, beside the source's batches)
+        const int *list = ix.et + rdl(row.start, S + 1);
+        int *own_q = lds, *src_q = lds + QCAP;
+        int head = 0, n1 = 0, np = 0, skip = 0;
+        typename Sink::In in;
+        fill(true);
+        for (;;) {
+            if (a < aend && n1 <= QCAP - WAVE) {
+                const int pos = place(a), n = aend - a < WAVE ? aend - a : WAVE;
+                const int a_next = a + WAVE, Lk = L0, tk = t0, tnk = next_tick(a, t0, t1);
+                const v4i vk = v0;
+                next_batch(true);
+                int p, c, nc, tot;
+                events_of<REL>(h, lane < n, tk, tnk, pos, pos + 1, Lk, vk, skip, p, c, seed.p);
+                put(own_q, head + n1, n, p, c, pos, skip, nc, tot, skip);
+                n1 += tot;
+                a += nc;
+                if (__builtin_expect((a != a_next) & (a < aend), 0)) fill(true);
+            }
+            if (np) {
+                sink.take(np, lane < np, in);
+                np = 0;
+            }
+            if (n1 >= WAVE || (a >= aend && n1 > 0)) {
+                np = n1 < WAVE ? n1 : WAVE;
+                const int q = (head + (lane < np ? lane : np - 1)) & (QCAP - 1);
+                const int own = own_q[q];
+                in.t = at(list, own);
+                sink.read(lane < np, src_q[q], own, in);
+                head = (head + np) & (QCAP - 1);
+                n1 -= np;
+            } else if (a >= aend) {
+                return;
+            }
+        }
+    }
+    // lane q: ring q's first slot, its entries, and how many events of its
+    // first entry's range have been put out already (an entry with more than
+    // a batch's worth is put out in parts); ring S+1's in scalars
+    int qh = 0, qn = 0, sk = 0;
+    int h1 = 0, n1 = 0, sk0 = 0;
+    auto ring = [&](int q) { return lds + (q - 1 - S) * RING_INTS; };
     // a batch of ring k's entries (flush: no more will come; k == S + 1 is the
     // ring whose counters are scalars)
     auto deeper = [&](int k, bool flush) {
@@ -610,7 +676,8 @@ __device__ __forceinline__ void walk(const ChainIdx &ix, const NodeRow &row, int
         const bool more = a < aend;
         if (more) {
             const int pos = place(a), n = aend - a < WAVE ? aend - a : WAVE;
-            const int a_next = a + WAVE, L_now = L0, t_now = t0, tn_now = tn0;
+            const int a_next = a + WAVE, L_now = L0, t_now = t0;
+            const int tn_now = PULL ? 0 : next_tick(a, t0, t1);
             const v4i v_now = v0;
             next_batch(true);
             int nc, tot, part;
@@ -629,14 +696,9 @@ __device__ __forceinline__ void walk(const ChainIdx &ix, const NodeRow &row, int
                 tot = __builtin_popcountll(m);
                 part = 0;
             } else {
-                int own = pos, next = pos + 1;
-                if constexpr (S && REL) {
-                    own = at(seed.p, pos);
-                    next = at(seed.p, pos + 1);  // (behind the last: not used)
-                }
                 int p, c;
-                events_of<REL>(h, lane < n, t_now, tn_now, own, next, L_now, v_now, sk0, p,
-                                      c);
+                events_of<REL>(h, lane < n, t_now, tn_now, pos, pos + 1, L_now, v_now, sk0, p, c,
+                               seed.p);
                 put(ring(S + 1), h1 + n1, n, p, c, pos, sk0, nc, tot, part);
             }
             n1 += tot;
