@@ -192,6 +192,7 @@ __global__ __launch_bounds__(WAVE) void k_ix_check(IndexSet x, Rows rows, int nm
 }
 
 constexpr int TYB = 1024;  // threads of the type kernel
+constexpr int TYS = 16;    // counts a thread scans at a time
 
 // exclusive prefix of v over the block, and the block's total
 __device__ __forceinline__ int64_t block_prefix(int64_t v, int64_t *sh, int64_t &tot)
@@ -218,7 +219,8 @@ __device__ __forceinline__ int64_t block_prefix(int64_t v, int64_t *sh, int64_t 
 // One block a stream.  Scans the counts (hist to off) unless many blocks
 // have.  Then, per type: its list's place, the buckets of its table (a power
 // of two of ticks wide, so many that a bucket holds half an event to one on
-// average) and the list's guards.
+// average) and the list's guards.  Bound by the latency of the scan's reads:
+// for 32 streams of up to 32768 counts, 61 -> 14 us with 16 in one go.
 __global__ __launch_bounds__(TYB) void k_ix_types(IndexSet x, int scan_here, const int *status,
                                                   int *hstat)
 {
@@ -234,14 +236,27 @@ __global__ __launch_bounds__(TYB) void k_ix_types(IndexSet x, int scan_here, con
     const int64_t H = (int64_t)T * nch;
     int64_t tot;
     if (scan_here) {
-        const int64_t per = (H + TYB - 1) / TYB;
-        const int64_t b = threadIdx.x * per, e = b + per < H ? b + per : H;
-        int64_t s = 0;
-        for (int64_t i = b; i < e; ++i) s += hist[i];
-        int64_t run = block_prefix(s, sh, tot);
-        for (int64_t i = b; i < e; ++i) {
-            off[i] = (int)run;
-            run += hist[i];
+        // (TYS counts a thread at a time, all read at once; the room behind
+        // the counts is a multiple of four)
+        int64_t base = 0;
+        for (int64_t b0 = 0; b0 < H; b0 += TYB * TYS) {
+            const int64_t b = b0 + threadIdx.x * TYS;
+            v4i v[TYS / 4];
+            int s = 0;
+#pragma unroll
+            for (int q = 0; q < TYS / 4; ++q)
+                v[q] = b + 4 * q < H ? *(const v4i *)(hist + b + 4 * q) : v4i{0, 0, 0, 0};
+#pragma unroll
+            for (int q = 0; q < TYS; ++q) {
+                const int c = b + q < H ? v[q / 4][q % 4] : 0;
+                v[q / 4][q % 4] = s;
+                s += c;
+            }
+            const int run = (int)(base + block_prefix(s, sh, tot));
+            base += tot;
+#pragma unroll
+            for (int q = 0; q < TYS / 4; ++q)
+                if (b + 4 * q < H) *(v4i *)(off + b + 4 * q) = v[q] + run;
         }
         __syncthreads();
     }
@@ -833,25 +848,32 @@ template <int MODE> void chain_mode(ChainJob j, int nmax, const int *status, hip
 }  // namespace
 
 namespace {
-__global__ __launch_bounds__(256) void k_count_ge(const int *v, int M, int theta, int *out,
+constexpr int GEB = 1024;
+__global__ __launch_bounds__(GEB) void k_count_ge(const int *v, int M, int theta, int *out,
                                                   const int *status)
 {
-    if (*status) return;
+    __shared__ int part[GEB / WAVE];
     int c = 0;
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < M; i += gridDim.x * blockDim.x)
-        c += v[i] >= theta ? 1 : 0;
+    if (*status == 0)
+        for (int i = blockIdx.x * GEB + threadIdx.x; i < M; i += gridDim.x * GEB)
+            c += v[i] >= theta ? 1 : 0;
     for (int off = 32; off >= 1; off >>= 1) c += __shfl_xor(c, off);
-    if (__lane_id() == 0 && c) atomicAdd(out, c);
+    if (__lane_id() == 0) part[threadIdx.x >> 6] = c;
+    __syncthreads();
+    if (threadIdx.x) return;
+    c = 0;
+    for (int w = 0; w < GEB / WAVE; ++w) c += part[w];
+    if (gridDim.x == 1) *out = c;
+    else if (c) atomicAdd(out, c);
 }
 }  // namespace
 
 void launch_count_ge(const int *v, int M, int theta, int *out, const int *status, hipStream_t s)
 {
-    launch_fill(out, 0, 1, s);
-    if (M <= 0) return;
-    int blocks = (M + 1023) / 1024;
-    if (blocks > 256) blocks = 256;
-    hipLaunchKernelGGL(k_count_ge, dim3(blocks), dim3(256), 0, s, v, M, theta, out, status);
+    // (one block needs no clearing)
+    const int blocks = M <= 8 * GEB ? 1 : std::min((M + 4 * GEB - 1) / (4 * GEB), 256);
+    if (blocks > 1) launch_fill(out, 0, 1, s);
+    hipLaunchKernelGGL(k_count_ge, dim3(blocks), dim3(GEB), 0, s, v, M, theta, out, status);
 }
 
 void launch_chain(const ChainJob &job, ChainMode mode, int nmax, const int *status, hipStream_t s)
