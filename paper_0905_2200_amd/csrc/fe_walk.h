@@ -131,7 +131,10 @@ template <bool REL> __device__ __forceinline__ int from_tick(const Hop &h, int t
 }
 template <bool REL> __device__ __forceinline__ int table_at(const Hop &h, int t)
 {
-    return at(h.tab, bucket(from_tick<REL>(h, t), h.t0, h.sh, h.nb));
+    // (an event's own tick is in the table; a hop's first may be past it)
+    if (REL) return at(h.tab, (t - h.t0) >> h.sh);
+    const int b = (t + (h.lo + 1 - h.t0)) >> h.sh;
+    return at(h.tab, b < h.nb ? b : h.nb);
 }
 
 // The first event after an entry by search: from tick x on (the entry's own
@@ -282,7 +285,9 @@ template <bool REL> __device__ __forceinline__ int to_tick(const Back &h, int t)
 }
 template <bool REL> __device__ __forceinline__ int table_at(const Back &h, int t)
 {
-    return at(h.tab, bucket(to_tick<REL>(h, t), h.t0, h.sh, h.nb));
+    if (REL) return at(h.tab, (t - h.t0) >> h.sh);
+    const int b = (t - (h.lo + 1 + h.t0)) >> h.sh;  // (may be before it)
+    return at(h.tab, b > 0 ? b : 0);
 }
 // Its tick (the guard's, BEFORE, if there is none), from L, the table at the
 // last tick's bucket, and v, four of et from L on (the entry before the
