@@ -137,7 +137,8 @@ __device__ __forceinline__ IndexJob job_of(const IndexSet &x, int block, First f
 
 // Blocks [0, chunks): stream checks (ticks non-decreasing and in range, ids
 // in range) and the chunk's type counts, hist[type*nch + chunk].  Blocks
-// after them: candidate checks, 64 rows each.
+// after them: candidate checks, 64 rows each.  A read of the stream: 54 us for
+// 9.7e6 events and 1e5 rows (1.5 TB/s, a chunk's 8 to 38 reads in a row).
 __global__ __launch_bounds__(WAVE) void k_ix_check(IndexSet x, Rows rows, int nmax, int num_types,
                                                    int *status, int *wmax)
 {
@@ -292,7 +293,10 @@ __global__ __launch_bounds__(TYB) void k_ix_types(IndexSet x, int scan_here, con
 }
 
 // One wave per chunk: 64 events at a time, each lane's rank among the
-// events of its type from a bit mask per type.
+// events of its type from a bit mask per type.  Bound by the scattered stores
+// (two of 4 bytes an event, each to its own line): 280 us for 9.7e6 events of
+// 256 types, the same with the next events read ahead, without the barriers'
+// waits for the stores, and with neighbouring chunks on one XCD.
 __global__ __launch_bounds__(WAVE) void k_ix_lists(IndexSet x, const int *status)
 {
     extern __shared__ unsigned long long sm[];
@@ -332,7 +336,8 @@ __global__ __launch_bounds__(WAVE) void k_ix_lists(IndexSet x, const int *status
 
 // tab[boff + b] = events of the type before bucket b.  Each position fills
 // the buckets after its predecessor's, up to its own; the end of the list
-// fills the rest.  Long stretches are filled by the whole wave.
+// fills the rest.  Long stretches are filled by the whole wave.  (54 us for
+// 9.7e6 events of 256 types, 78 MB of tables.)
 __global__ __launch_bounds__(256) void k_ix_tab(IndexSet s, const int *status)
 {
     if (*status) return;
@@ -653,9 +658,9 @@ constexpr int chain_waves(int emax) { return emax == 1 ? 8 : 1; }
 // only its candidate's shorter list of the first two and the few entries that
 // pass.  20011 episodes of 1-8 nodes over 3.0e5 events of 200 types: 22.6 ->
 // 0.17 ms a call; 5000 relaxed of 5-8 nodes over 1.06e6 events of 128 types:
-// 13.2 -> 0.30 ms; 1e5 of 3 nodes over 9.7e6 events, both passes: 81 -> 10.4
-// ms (16.1 from node 0's list; 12.3 with the survivors' exact pass launched
-// for every row); 3000 with 9 to 19 live windows a list: 26 -> 0.08 ms.
+// 13.2 -> 0.30 ms; 1e5 of 3 nodes over 9.7e6 events, both passes: 81 -> 11
+// ms (16.1 from node 0's list); 3000 with 9 to 19 live windows a list: 26 ->
+// 0.08 ms.
 template <int MODE, int EMAX>
 __device__ __forceinline__ void chain_item(const ChainJob &j, int m, int p, int *lds)
 {
@@ -770,8 +775,10 @@ __global__ __launch_bounds__(WAVE, chain_waves(EMAX)) void k_chains(const ChainJ
 
 // One wave per 64 candidates: their segments' results in order.  A
 // segment's own run stands when the first chain it completes starts after
-// the last completion before it (the run would take it too); otherwise the wave runs it again from there until
-// it meets its own run (a common completion), a growing stretch at a time.
+// the last completion before it (the run would take it too); otherwise the
+// wave runs it again from there until it meets its own run (a common
+// completion), a growing stretch at a time.  (60 us for 1e5 rows of 39
+// segments, one read of 62 MB.)
 template <bool REL> __global__ __launch_bounds__(WAVE) void k_stitch(ChainJob j, const int *status)
 {
     extern __shared__ int lds[];
@@ -911,7 +918,8 @@ namespace {
 // tick t + hi.  One thread per 32 types of a place and up to four hops: each
 // type's list is searched once, at the ticks' narrowest start, and four entries
 // from there on settle nearly every hop; the ticks ascend along a wave, so the
-// reads are nearly coalesced.
+// reads are nearly coalesced.  Bound by those reads' latency: 0.17 ms exact and
+// 0.22 ms relaxed for 1.06e6 places, 64 types and 3 hops.
 constexpr int MH = 4;  // hops a thread takes
 template <bool REL>
 __global__ __launch_bounds__(256) void k_masks(ChainIdx ix, int places, int T, int n_iv,
@@ -979,6 +987,9 @@ __global__ __launch_bounds__(256) void k_masks(ChainIdx ix, int places, int T, i
 // event (a chain's later ones start no later than the one taken).  An entry
 // names its chain's first event by its position or, exact, where no two chains
 // start at one tick, by its tick, which is then at hand where it is needed.
+//   A wave a pair, bound by its instructions: 12288 pairs over 1.06e6 events of
+// 64 types in 0.50 ms exact and 0.66 relaxed (0.62 and 1.25 from the first
+// type's list); counting them as level 2 alone took the scan 0.95 and 3.9 ms.
 template <bool REL> struct SeedOut {
     const ChainIdx &ix;
     const NodeRow &row;
