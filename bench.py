@@ -6,9 +6,8 @@ firing at 20 Hz for 780 s (about 1.05M events, int32 ids and 0.1 ms int32
 ticks) with eight planted cascades of 3-6 nodes, hop intervals
 {(0,5], (5,10], (10,20]} ms, levels 2-6, threshold 0.5 Hz x 780 s = 390.
 One step = one complete level-wise mining run (Problem 1): each level is
-generated on the host and counted on the GPU (MapConcatenate Map and
-Concatenate kernels; two-pass elimination, Algorithm 4, where the library's
-per-level rule finds that the relaxed pass pays for itself).
+joined and counted on the GPU (two-pass elimination, Algorithm 4, where the
+library's per-level rule finds that the relaxed pass pays for itself).
 
 Metric: candidate-episode x events per second, a step's work being
 sum over levels >= 2 of (candidates x events): every candidate counted
@@ -39,8 +38,8 @@ BYTES_PER_EE = 8  # one int32 id + one int32 tick per event per candidate machin
 # instruction issue: 256 CUs x 4 SIMDs, 2.4 GHz, one wave64 VALU (or SALU)
 # instruction per SIMD every 4 cycles
 ISSUE_PEAK_G = 1024 * 2.4 / 4  # 614.4 G wave-instructions/s
-MAP_SOURCES = ["paper_0905_2200_amd/csrc/fe_map.h"] + [
-    "paper_0905_2200_amd/csrc/fe_map_n%d.hip" % n for n in range(1, 9)]
+MAP_SOURCES = ["paper_0905_2200_amd/csrc/fe_chain.h", "paper_0905_2200_amd/csrc/fe_walk.h",
+               "paper_0905_2200_amd/csrc/fe_chain.hip"]
 COUNTERS = os.path.join(ROOT, "profiles", "map_counters.json")
 
 
@@ -58,7 +57,7 @@ def map_source_hash():
 
 def counters_for(kernel):
     """Per-launch rocprofv3 counters of `kernel` on this workload from the
-    committed summary, if they were taken on the current Map sources."""
+    committed summary, if they were taken on the current kernels' sources."""
     if not os.path.exists(COUNTERS):
         return None
     try:
@@ -167,7 +166,7 @@ def bench_mining(args, fe, synth, torch):
                      "achieved_GBs": round(BYTES_PER_EE * ee_launch / t_launch / 1e9, 1),
                      "peak_GBs": HBM_PEAK_GBS,
                      "frac": round(BYTES_PER_EE * ee_launch / t_launch / 1e9 / HBM_PEAK_GBS, 3),
-                     "note": "8 B per candidate-event as if every machine read every event; "
+                     "note": "8 B per candidate-event as if every candidate read every event; "
                              "not DRAM traffic"}
         if cnt and cnt.get("hbm_bytes_per_launch"):
             gbs = cnt["hbm_bytes_per_launch"] / t_launch / 1e9

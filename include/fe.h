@@ -88,7 +88,9 @@ typedef enum fe_mode {
 
 /* Tunables for fe_set_param. */
 typedef enum fe_param {
-    FE_PARAM_SEGMENTS = 0,   /* MapConcatenate segment count P; 0 = automatic  */
+    FE_PARAM_SEGMENTS = 0,   /* MapConcatenate segment count P of the event-by-
+                                event kernels; 0 = automatic, and per-type
+                                lists where the call takes those              */
     FE_PARAM_TARGET_WAVES = 1, /* waves the automatic P aims for per launch
                                 (default 16384: two generations of 8 waves
                                 per SIMD on 256 CUs)                          */
@@ -112,7 +114,9 @@ typedef enum fe_param {
     FE_PARAM_CROSSOVER_B = 7, /* counter: a group of tiles >= A/N + B tiles of
                                 N-node candidates is counted whole-stream
                                 (P = 1), a smaller one by MapConcatenate with
-                                P >= 2.  Defaults 8472 and 13112 (A may be
+                                P >= 2 (over per-type lists: a call's M
+                                candidates as M/64 tiles of nmax nodes).
+                                Defaults 8472 and 13112 (A may be
                                 negative): the least-squares fit to crossovers
                                 measured on a 256-CU MI355X (python -m
                                 paper_0905_2200_amd.crossover).  Ignored when
@@ -136,9 +140,9 @@ typedef enum fe_param {
     FE_PARAM_HOST_TILING = 9, /* fe_mine: 0 (default) = each level's
                                 candidates are pruned and tiled on the device
                                 (sibling runs whole, by list-depth class);
-                                1 = the same tiling on the host (the relaxed
-                                counts are copied back and the lane assignment
-                                uploaded).  Same tiles, same results.  The
+                                1 = event-by-event counting, tiled on the host
+                                (the relaxed counts are copied back and the
+                                lane assignment uploaded).  Same results.  The
                                 per-level decision of FE_PARAM_ELIMINATION = 2
                                 needs device tiling; with host tiling it takes
                                 two passes.                                    */
@@ -157,7 +161,7 @@ typedef enum fe_param {
                                 FE_PARAM_ELIMINATION = 2                      */
     FE_PARAM_SAMPLE_MIN = 14, /* smallest level sampled by FE_PARAM_ELIMINATION
                                 = 2 (default 131072 candidates)                */
-    FE_PARAM_SHARED_LISTS = 15 /* 1 (default) = exact whole-stream counting of
+    FE_PARAM_SHARED_LISTS = 15 /* 1 (default) = exact event-by-event counting of
                                 a tile whose candidates share every node but
                                 the last and every hop but the last (join
                                 siblings, N >= 3) keeps lists 0..N-3 once per
@@ -194,9 +198,13 @@ int fe_validate(fe_ctx *ctx, const int32_t *ids, const int32_t *ticks,
                 int64_t n, int32_t num_types);
 
 /* Count every candidate over the stream (Algorithm 1 for FE_EXACT,
- * Algorithm 3 for FE_RELAXED), by MapConcatenate over P index segments
- * (Sec. 5.2.2) with exact segment stitching.  counts_out: device int32[M],
- * in candidate order.  Synchronises once (candidate grouping). */
+ * Algorithm 3 for FE_RELAXED): by chains of events over per-type lists of
+ * the stream, built by the call, or (FE_PARAM_TYPE_DISPATCH = 0, segments
+ * asked for, more than 4096 types, more than 2^30 events, or no memory for
+ * the lists) event by event; over P segments (MapConcatenate, Sec. 5.2.2)
+ * with exact stitching where the candidates alone do not fill the device.
+ * counts_out: device int32[M], in candidate order.  Synchronises once (input
+ * checks). */
 int fe_count(fe_ctx *ctx, const int32_t *ids, const int32_t *ticks, int64_t n,
              int32_t num_types, const int32_t *types, const int32_t *len,
              const int32_t *lo, const int32_t *hi, int32_t M, int32_t nmax,
@@ -238,7 +246,7 @@ int fe_count_noalloc(fe_ctx *ctx, const int32_t *ids, const int32_t *ticks, int6
  * (the argument behind the segment stitching of fe_count); only that much
  * is read again before `from`.  Errors: FE_EINVAL for from outside [0, n],
  * null carry arrays or bad candidates (as fe_count); stream errors as
- * fe_validate.  Synchronises once (candidate grouping). */
+ * fe_validate.  Synchronises once (input checks). */
 int fe_count_resume(fe_ctx *ctx, const int32_t *ids, const int32_t *ticks, int64_t n,
                     int32_t num_types, const int32_t *types, const int32_t *len,
                     const int32_t *lo, const int32_t *hi, int32_t M, int32_t nmax,
@@ -248,7 +256,7 @@ int fe_count_resume(fe_ctx *ctx, const int32_t *ids, const int32_t *ticks, int64
  * count; candidates with upper < theta are dropped (exact_out[m] = -1);
  * exact_out[m] = exact count for the others.  *n_survivors_out (device
  * int32) receives the number kept.  All outputs are device pointers.
- * Synchronises (grouping of each pass). */
+ * Synchronises once (input checks; event by event: each pass's grouping). */
 int fe_count_two_pass(fe_ctx *ctx, const int32_t *ids, const int32_t *ticks,
                       int64_t n, int32_t num_types, const int32_t *types,
                       const int32_t *len, const int32_t *lo,
@@ -268,7 +276,7 @@ typedef struct fe_level {
     int32_t *hi;          /* [n_frequent * (level-1)]                       */
     int32_t *upper;       /* [n_frequent] relaxed counts                    */
     int32_t *exact;       /* [n_frequent] exact counts                      */
-    double gen_ms;        /* host candidate generation time                 */
+    double gen_ms;        /* candidate generation time                      */
     double count_ms;      /* device counting time (both passes)             */
     int32_t passes;       /* 2: relaxed pass, elimination, exact pass on the
                              survivors (Algorithm 4); 1: exact pass only
@@ -295,7 +303,8 @@ typedef struct fe_result {
  * ordered pair of frequent types (repeats allowed) times every interval of
  * I; level l >= 3 joins two frequent (l-1)-node episodes whose overlapping
  * l-2 nodes and intervals agree.  Every level is counted with Algorithm 4
- * on the device; generation runs on the host (Sec. 5 intro).  Stops after
+ * on the device; the host drives the levels (Sec. 5 intro) and copies each
+ * level's frequent set while the next is counted.  Stops after
  * max_level or at the first level with no frequent episode.  ids, ticks:
  * device; iv_lo, iv_hi: host int32[n_iv] (the set I, in ticks).
  * *out is allocated by the library; free it with fe_result_free.

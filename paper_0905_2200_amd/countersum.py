@@ -6,10 +6,10 @@
 Each DIR is the output directory of one rocprofv3 run of
 ``bench.py --no-extras`` (a kernel trace with --stats, a FETCH_SIZE pass, a
 WRITE_SIZE pass, and one or more passes of SQ counters).  Writes
-profiles/map_counters.json -- per Map kernel (named as the library's kernel
-timers name them, e.g. map_exact_n4_d2) the average per launch of every
+profiles/map_counters.json -- per counting kernel (named as the library's kernel
+timers name them, e.g. map_exact_siblings_n4) the average per launch of every
 counter, the calibrated beyond-L2 bytes and the average duration -- keyed by
-a hash of the Map sources, which bench.py checks before it uses them; and
+a hash of the kernels' sources, which bench.py checks before it uses them; and
 profiles/mining_counters.md, a readable summary with the commands.
 
 FETCH_SIZE and WRITE_SIZE are scaled by what they read for one device copy
@@ -28,8 +28,8 @@ from collections import defaultdict
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
-MAP_SOURCES = ["paper_0905_2200_amd/csrc/fe_map.h"] + [
-    "paper_0905_2200_amd/csrc/fe_map_n%d.hip" % n for n in range(1, 9)]
+MAP_SOURCES = ["paper_0905_2200_amd/csrc/fe_chain.h", "paper_0905_2200_amd/csrc/fe_walk.h",
+               "paper_0905_2200_amd/csrc/fe_chain.hip"]
 
 
 def map_source_hash():
@@ -41,15 +41,17 @@ def map_source_hash():
 
 
 def lib_name(kernel):
-    """The library's timer name of a Map kernel (None for other kernels)."""
-    m = re.search(r"k_map1?<(\d+), (true|false), (\d+), (true|false)>", kernel)
+    """The library's timer name of a counting kernel (None for others)."""
+    m = re.search(r"k_siblings<(true|false), (\d+)>", kernel)
+    if m:  # (two, three, more shared nodes)
+        return "map_%s_siblings_%s" % ("relaxed" if m.group(1) == "true" else "exact",
+                                       {"1": "n3", "2": "n4"}.get(m.group(2), "n5_and_on"))
+    m = re.search(r"k_pairs<(true|false)>", kernel)
     if m:
-        exact = m.group(2) == "true"
-        return "map_%s_n%s_d%s" % ("exact" if exact else "relaxed", m.group(1),
-                                   m.group(3) if exact else "1")
-    m = re.search(r"k_deep<(\d+)>", kernel)
+        return "map_%s_pairs" % ("relaxed" if m.group(1) == "true" else "exact")
+    m = re.search(r"k_chains?<(\d), (\d+)>", kernel)
     if m:
-        return "map_exact_n%s_deep" % m.group(1)
+        return "map_%s_chain" % ("exact", "relaxed", "two_pass")[int(m.group(1))]
     return None
 
 
@@ -151,7 +153,7 @@ def main():
 
     # readable summary
     L = []
-    L.append("# Map kernels of the mining workload: time, traffic and instruction issue\n")
+    L.append("# Counting kernels of the mining workload: time, traffic and instruction issue\n")
     L.append("Workload: 64 neurons x 20 Hz x 780 s (1 057 255 events), levels 2-6, the "
              "library's default per-level elimination rule.  Commands (repo root, MI355X), one "
              "rocprofv3 run each:\n")
@@ -196,7 +198,7 @@ def main():
             "%.2f" % (conf / lds) if lds and conf is not None else "-",
             "%.3e" % hb if hb else "-", "%.1f" % (hb / t / 1e9) if hb else "-"))
     L.append("\n`map_counters.json` holds these figures for `bench.py`, keyed by the hash %s of "
-             "the Map sources they were taken on." % out["map_source_hash"])
+             "the sources they were taken on." % out["map_source_hash"])
     open(os.path.join(prof, "mining_counters.md"), "w").write("\n".join(L) + "\n")
     print(json.dumps({k: {kk: v[kk] for kk in ("avg_ms", "valu_per_launch", "salu_per_launch",
                                                "hbm_bytes_per_launch") if kk in v}
