@@ -643,9 +643,14 @@ __device__ __forceinline__ int seg_at(const ChainJob &j, int c, int p)
 // Waves a SIMD is given registers for.  Tables of up to three nodes (EMAX = 1)
 // need 2.5 KB of LDS a wave, so their walks keep to eight waves' scalar
 // registers, the rest of them in vector lanes: 14.5 -> 12.3 ms for the 1e5
-// rows above (5.7 -> 7.6 waves resident).  Longer tables have LDS for five
-// waves only, and 2% more time with fewer registers.
-constexpr int chain_waves(int emax) { return emax == 1 ? 8 : 1; }
+// rows above (5.7 -> 7.6 waves resident).  Tables of four and five (EMAX = 3; 3
+// and 4 KB) do so where the launch has the waves: 30 000 rows of 4 nodes over
+// 3e6 events (11 segments) 1.13 -> 1.05 ms exact, 1.30 -> 1.17 relaxed; 8000
+// rows (3 segments) 0.22 -> 0.23 and 3000 rows 0.11 -> 0.12 exact, which take
+// the others' kernel.  Longer tables have LDS for five waves only, and 2% more
+// time with fewer registers.
+constexpr int64_t EIGHT_WAVES = 1 << 17;
+constexpr int chain_waves(int emax) { return emax <= 3 ? 8 : 1; }
 
 // One wave per (segment, candidate).  P = 1 writes the counts; P > 1 the
 // segment's own count (after no completion), its last completion's index
@@ -844,6 +849,8 @@ template <int MODE> void chain_mode(ChainJob j, int nmax, const int *status, hip
     const dim3 grid = grid_of((j.rows.M + (1 << rows) - 1) >> rows, j.P);
     if (nmax <= 3)
         hipLaunchKernelGGL((k_chain<MODE, 1>), grid, dim3(WAVE), lds, s, j, status, rows);
+    else if (nmax <= 5 && (int64_t)j.P * j.rows.M >= EIGHT_WAVES)
+        hipLaunchKernelGGL((k_chain<MODE, 3>), grid, dim3(WAVE), lds, s, j, status, rows);
     else
         hipLaunchKernelGGL((k_chain<MODE, NMAX - 2>), grid, dim3(WAVE), lds, s, j, status, rows);
     if (j.P > 1)

@@ -135,15 +135,17 @@ def test_either_list_first(ctx, ratio, gap):
         _check(ctx, ids_h, ticks_h, 4, cand, "ratio=%g gap=%d nmax=%d" % (ratio, gap, nmax))
 
 
+@pytest.mark.parametrize("nmax", [3, 5])
 @pytest.mark.parametrize("M", [6800, 14001, 70001, 140007])
-def test_survivors_in_segments(ctx, fe, M):
+def test_survivors_in_segments(ctx, fe, M, nmax):
     # the exact pass over the segments of survivors alone, looked for among 1
-    # to 16 rows a wave
+    # to 16 rows a wave; tables of three and of five nodes, from too few waves
+    # to fill the device on
     rng = np.random.default_rng(M)
     n = 20_000
     ids_h = rng.integers(0, 2, n).astype(np.int32)
     ticks_h = np.cumsum(rng.integers(0, 9, n)).astype(np.int32)
-    eps = synth.random_episodes(rng, 211, 2, 3, IVS, n_min=1)
+    eps = synth.random_episodes(rng, 211, 2, nmax, IVS, n_min=1)
     cand = synth.pack(eps)
     many = synth.pack([eps[i % len(eps)] for i in range(M)])
     up = oracle_counts(ids_h, ticks_h, 2, cand, RELAXED)
