@@ -169,6 +169,7 @@ struct SibJob {
     PairLists sd;
     const int *rank;  // [num_types] rank among the frequent types
     int nF;
+    int words;   // (set by the launcher: mask words a wave counts)
 };
 
 void launch_masks(bool rel, const IndexPlan &p, const int *base, const int *ivlo, const int *ivhi,

@@ -1107,7 +1107,8 @@ struct Flip {
     }
 };
 
-constexpr int QW = 4;  // mask words (64 types and a hop each) a wave counts
+constexpr int QW = 4;  // mask words (64 types and a hop each) a wave counts at most
+constexpr int64_t SIB_FILL = 8192;  // waves that fill the device
 
 // Join siblings: one frequent episode's entries against 64 types at a time
 // and a hop.  Of 64 entries, one per lane, the mask words (bit = type) are
@@ -1296,8 +1297,8 @@ __global__ __launch_bounds__(WAVE, sib_waves(REL, EMAX)) void k_siblings(SibJob 
     if (item >= cnt) return;
     const int64_t al = j.order[item];
     const int lane = __lane_id();
-    const int q0 = (int)blockIdx.z * QW;
-    const int nq = j.Q - q0 < QW ? j.Q - q0 : QW;
+    const int q0 = (int)blockIdx.z * j.words;
+    const int nq = j.Q - q0 < j.words ? j.Q - q0 : j.words;
     const int64_t out0 = j.off[al];
     const int len = (int)(j.off[al + 1] - out0);
     const int *sib = j.F + j.first[al] * j.w + (j.w - 3);  // (lo, hi, type) of a sibling
@@ -1417,10 +1418,20 @@ void siblings_by_length(const SibJob &j, int64_t cnt, dim3 grid, size_t lds, hip
 }
 }  // namespace
 
-void launch_siblings(bool rel, const SibJob &j, int64_t cnt, hipStream_t s)
+void launch_siblings(bool rel, const SibJob &job, int64_t cnt, hipStream_t s)
 {
     if (cnt <= 0) return;
-    const dim3 grid = grid_of(cnt, (j.Q + QW - 1) / QW);
+    SibJob j = job;
+    // (few episodes leave the device to the latency of a wave's own steps: then
+    // fewer words a wave, though each wave makes the entries anew.  Three words
+    // in one wave each / in three: 1452 episodes of 2 nodes, relaxed, 2.6e5
+    // events 3.96 / 1.96 ms; 1275 of 4 over 1.06e6 0.72 / 0.56; 158 of 5 0.54 /
+    // 0.41.  From about as many waves as the device holds nothing is gained)
+    auto blocks = [&](int words) { return (j.Q + words - 1) / words; };
+    j.words = QW;
+    while (j.words > 1 && cnt * blocks(j.words) < SIB_FILL && blocks(j.words / 2) < 65536)
+        j.words /= 2;
+    const dim3 grid = grid_of(cnt, blocks(j.words));
     // (rings of the stages between node 1 and the last; the counts at the end)
     const int rings = (j.m > 2 ? j.m - 2 : 0) * RING_INTS;
     const size_t lds = (size_t)(rings > QW * WAVE ? rings : QW * WAVE) * sizeof(int);

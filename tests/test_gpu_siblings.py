@@ -126,3 +126,25 @@ def test_rule_with_samples(ctx, fe):
                     {fe.PARAM_ELIMINATION: 2, fe.PARAM_SAMPLE_MIN: 200, fe.PARAM_PASS1_COST: cost})
         _check_oracle(got, want, theta)
         assert cost == 1000 or any(L["sample_n"] > 0 for L in got)
+
+
+@pytest.mark.parametrize("T,words", [(30, 1), (46, 2), (70, 4)])
+def test_words_a_wave(ctx, fe, T, words):
+    # so many frequent pairs that a wave takes one, two or four mask words
+    # (the last few of them fewer), against the event-by-event kernels
+    rng = np.random.default_rng(T)
+    ids, ticks = _stream(rng, 60 * T, T, 1)
+    ivs, theta = [(0, 50), (50, 100), (100, 200)], 12
+    banner("words a wave: T=%d words=%d n=%d" % (T, words, ids.size))
+    a = _mine(ctx, fe, ids, ticks, T, ivs, theta, 3, {fe.PARAM_ELIMINATION: 1})
+    b = _mine(ctx, fe, ids, ticks, T, ivs, theta, 3,
+              {fe.PARAM_ELIMINATION: 1, fe.PARAM_TYPE_DISPATCH: 0})
+    assert len(a) == len(b) == 3
+    cnt, Q = a[1]["n_frequent"], (T + 63) // 64 * 3
+    assert words == 1 or cnt * -(-Q // words) >= 8192
+    assert words == 4 or cnt * -(-Q // (2 * words)) < 8192
+    for x, y in zip(a, b):
+        for k in ("n_candidates", "n_survivors", "n_frequent"):
+            assert x[k] == y[k], (x["level"], k)
+        for k in ("types", "lo", "hi", "upper", "exact"):
+            assert np.array_equal(x[k], y[k]), (x["level"], k)
