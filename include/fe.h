@@ -50,7 +50,7 @@
  *   per-type event lists of the stream, which each call builds in library
  *   workspace (about 16 B per event), and need no lists of their own; calls
  *   those do not take (FE_PARAM_TYPE_DISPATCH = 0, FE_PARAM_SEGMENTS > 0,
- *   more than 4096 types or 2^30 events, or no memory for them) run the
+ *   more than 4096 types or about 2^29 events, or no memory for them) run the
  *   machines event by event.  There, Algorithm 1's list for hop k matters
  *   only through the ticks that pass its test, a union of windows of which
  *   at most hi_k/(hi_k-lo_k+1)+1 are live at once.  Candidates whose hops
@@ -200,7 +200,7 @@ int fe_validate(fe_ctx *ctx, const int32_t *ids, const int32_t *ticks,
 /* Count every candidate over the stream (Algorithm 1 for FE_EXACT,
  * Algorithm 3 for FE_RELAXED): by chains of events over per-type lists of
  * the stream, built by the call, or (FE_PARAM_TYPE_DISPATCH = 0, segments
- * asked for, more than 4096 types, more than 2^30 events, or no memory for
+ * asked for, more than 4096 types, more than about 2^29 events, or no memory for
  * the lists) event by event; over P segments (MapConcatenate, Sec. 5.2.2)
  * with exact stitching where the candidates alone do not fill the device.
  * counts_out: device int32[M], in candidate order.  Synchronises once (input

@@ -665,12 +665,16 @@ int stream_info(fe_ctx *c, const int32_t *ids, const int32_t *ticks, int n, int 
 // built by each call and every candidate is counted by one wave (or one per
 // segment of its first list).
 
+// Events an index may hold: a bucket table has up to two buckets an event and
+// two more a type, and is read at 32-bit byte offsets.
+constexpr int64_t CHAIN_EVENTS = ((int64_t)1 << 29) - 4 * CHAIN_TYPES;
+
 // The calls it takes: per-type dispatch on, no segment count asked for, and
 // a stream whose lists can be built (the others take the Map kernels).
 bool chain_takes(const fe_ctx *c, int64_t n, int num_types)
 {
     return c->param[FE_PARAM_TYPE_DISPATCH] != 0 && c->param[FE_PARAM_SEGMENTS] == 0 && n > 0 &&
-           n <= ((int64_t)1 << 30) && num_types <= CHAIN_TYPES;
+           n <= CHAIN_EVENTS && num_types <= CHAIN_TYPES;
 }
 
 // Segments per candidate: the hybrid rule's crossover (choose_P) decides
@@ -3552,7 +3556,7 @@ extern "C" int fe_server_submit(fe_server *sv, const fe_request *rq, uint64_t *t
     }
     q->foot = req_arena_bytes(sv, q->b - q->a) + 2 * (int64_t)sv->M * 4;
     if (c->param[FE_PARAM_TYPE_DISPATCH] != 0 && sv->maxtypes <= CHAIN_TYPES &&
-        q->b - q->a <= (1 << 30)) {
+        q->b - q->a <= CHAIN_EVENTS) {
         const int64_t f = req_chain_bytes(sv, q->b - q->a) + 2 * (int64_t)sv->M * 4;
         if (f <= sv->cfg.hbm_budget) {
             q->foot = f;
