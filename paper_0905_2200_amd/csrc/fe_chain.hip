@@ -1273,6 +1273,9 @@ __global__ __launch_bounds__(256) void k_order(const int *__restrict__ F, int w,
         order[atomicAdd(&sh[F[(int64_t)a * w + w - 1]], 1)] = a;
 }
 
+// Waves a SIMD is given registers for, by length (2, 3, more shared nodes).
+constexpr int sib_waves(bool rel, int emax) { return emax == 1 ? 7 : emax == 2 && !rel ? 6 : 5; }
+
 // One wave per frequent episode and QW mask words (grid z), by the episodes'
 // last types: what a wave reads at random -- the last stage's list and the
 // masks of its entries -- is then the same few lists for all waves at a time,
@@ -1280,15 +1283,13 @@ __global__ __launch_bounds__(256) void k_order(const int *__restrict__ F, int w,
 //   64 entries cost about 55 vector instructions for 64 types and a hop, where
 // the scan of the whole stream it replaces costs about 60 for each 64 events
 // and 64 siblings; an episode of 3 nodes has a few hundred entries in 1.06e6
-// events.  It is bound by issue (0.6 of its rate) and by the masks' latency
-// at the waves its registers leave, so the lengths have kernels of their own:
+// events.  It is bound by issue (0.85 of its rate at 3e5 episodes of 3 nodes)
+// and, at fewer episodes, by the masks' latency at the waves its registers
+// leave, so the lengths have kernels of their own:
 // two and three shared nodes take the mask words of a batch while the one
 // before is counted, 7 and 6 waves a SIMD instead of 4 and 5 -- 64 types and 3
 // hops over 780 s, four-node level 4.94 -> 4.2 ms; 200 types, three-node
 // level 1.04 -> 0.87 ms.
-// Waves a SIMD is given registers for, by length (2, 3, more shared nodes).
-constexpr int sib_waves(bool rel, int emax) { return emax == 1 ? 7 : emax == 2 && !rel ? 6 : 5; }
-
 template <bool REL, int EMAX>
 __global__ __launch_bounds__(WAVE, sib_waves(REL, EMAX)) void k_siblings(SibJob j, int64_t cnt)
 {

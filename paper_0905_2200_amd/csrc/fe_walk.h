@@ -369,13 +369,14 @@ enum Source { FROM_FIRST, FROM_SECOND, FROM_PAIR };
 // lane (on; the other lanes' values are in range too): tick, position of the
 // chain's first event in the source, own position; L, v: straight from the
 // source to a sink that SEARCHES node E + 1's list, that list's table at their
-// buckets and four entries from there on, else L = -1.  FROM_SECOND with
-// E = 0: sink.direct(pass, its lanes, position, its node 0 event's) for every event of
-// the source instead; a sink with FIRSTS gets E = 1's with src that position,
-// as does sink.search(on, t, src, own, L, v), which takes E = 1's entries of
-// one that SEARCHES.  E <= EMAX; FROM_PAIR, E = EMAX where that is 1 or 2, with
-// sink.read(on, src, own, in) and sink.take(n, on, in) for a batch whose ticks
-// are in.t, and E > 2 else.
+// buckets and four entries from there on, else L = -1.
+//   FROM_SECOND with E = 0: sink.direct(pass, its lanes, position, its node 0
+// event's) for every event of the source instead.  With E = 1, a sink with
+// FIRSTS gets that position as src, as does sink.search(on, t, src, own, L, v)
+// of one that SEARCHES.
+//   E <= EMAX.  FROM_PAIR: E = EMAX where that is 1 or 2, with sink.read(on,
+// src, own, in) and sink.take(n, on, in) for a batch whose ticks are in.t, and
+// E > 2 else.
 template <bool REL, Source SRC, int EMAX, class Sink>
 __device__ __forceinline__ void walk(const ChainIdx &ix, const NodeRow &row, int E, int a,
                                      int aend, int *lds, Sink &sink, const Seeds &seed = Seeds())
