@@ -677,12 +677,17 @@ bool chain_takes(const fe_ctx *c, int64_t n, int num_types)
            n <= CHAIN_EVENTS && num_types <= CHAIN_TYPES;
 }
 
-// Segments per candidate: the hybrid rule's crossover (choose_P) decides
-// between one and several; several are as many as the target number of waves
-// takes, or as make a segment's share of all lists (12 B an event: tick and
-// bucket table) fit in one XCD's 4 MiB L2 -- the waves of one segment run
-// together, over the same stretch of time of every list -- with at least 512
-// events of a list of average length in each.
+// Segments per candidate: one from the hybrid rule's crossover on (choose_P);
+// below it as many as the target number of waves has room for, or as make a
+// segment's share of all lists (12 B an event: tick and bucket table) fit in
+// one XCD's 4 MiB L2 -- the waves of one segment run together, over the same
+// stretch of time of every list -- with at least 512 events of a list of
+// average length in each.  Milliseconds a call with one / these, exact and
+// relaxed, 3-node rows: 1e6 events of 64 types, 5000 rows 0.32 / 0.29 and 0.45
+// / 0.32, 1e5 rows 3.5 / 3.1 and 4.3 / 3.7; 4e6 of 256 types, 1e5 rows 4.4 /
+// 3.7 and 5.7 / 4.1.  Where the lists fit already and the rows fill the device
+// alone, two only cost: 3e5 of 200 types, 20 000 rows 0.17 / 0.19 and 0.18 /
+// 0.18, 1e5 rows 0.39 / 0.46 and 0.40 / 0.47.
 int chain_P(const fe_ctx *c, int64_t M, int64_t n, int num_types, int nmax, bool exact)
 {
     const int64_t tiles = (M + WAVE - 1) / WAVE;
@@ -690,7 +695,7 @@ int chain_P(const fe_ctx *c, int64_t M, int64_t n, int num_types, int nmax, bool
     const int pb = exact ? FE_PARAM_CROSSOVER_B : FE_PARAM_CROSSOVER_B_RELAXED;
     const double cross = (double)c->param[pa] / std::max(nmax, 1) + (double)c->param[pb];
     if ((double)tiles >= cross) return 1;
-    int64_t P = std::max<int64_t>(2, (c->param[FE_PARAM_TARGET_WAVES] + M - 1) / M);
+    int64_t P = c->param[FE_PARAM_TARGET_WAVES] / M;
     P = std::max<int64_t>(P, 12 * n / ((int64_t)3 << 20));
     P = std::min<int64_t>(P, n / ((int64_t)512 * num_types));
     P = std::min<int64_t>(P, ((int64_t)1 << 30) / M);
