@@ -90,7 +90,8 @@ struct ChainJob {
     int *exact;  // exact counts
     int P;       // segments per candidate
     unsigned share;  // (set by the launcher: 2^32 / P, less)
-    int4 *seg;   // [P][M] segment results (P > 1): completions, last one's index
+    int4 *seg;   // [M][P] segment results (P > 1): completions, last one's index, first
+                 // event of the first chain, count of a second run (-1: none)
     // incremental form (count_io set): the events before `from`, whose tick
     // is *t_from, are counted; adds the rest to the carry
     int *count_io, *last_io;

@@ -710,7 +710,7 @@ __device__ __forceinline__ void chain_item(const ChainJob &j, int m, int p, int 
         count_range<MODE == CHAIN_RELAXED, false, EMAX>(j.ix, row, N, pull, a0, a1, lds, r, cnt, dr, dc, s1);
     if (lane != 0) return;
     if (MODE != CHAIN_TWO_PASS && j.P > 1) {
-        j.seg[(int64_t)p * j.rows.M + m] = make_int4(cnt, r, s1, 0);
+        j.seg[(int64_t)m * j.P + p] = make_int4(cnt, r, s1, -1);
     } else if (MODE != CHAIN_TWO_PASS && j.count_io) {
         if (cnt) {
             j.count_io[m] += cnt;
@@ -778,63 +778,137 @@ __global__ __launch_bounds__(WAVE, chain_waves(EMAX)) void k_chains(const ChainJ
     chain_item<MODE, EMAX>(j, (int)(item - first[lo]), 0, lds);
 }
 
-// One wave per 64 candidates: their segments' results in order.  A
-// segment's own run stands when the first chain it completes starts after
-// the last completion before it (the run would take it too); otherwise the
-// wave runs it again from there until it meets its own run (a common
-// completion), a growing stretch at a time.  (60 us for 1e5 rows of 39
-// segments, one read of 62 MB.)
+// A segment's own run, counted after no completion, stands when the first chain
+// it completes starts after the last completion before it (the run would take
+// it too).  Otherwise it is run again from there, a growing stretch at a time,
+// until both runs take the same completion: from then on they are one.
+// r: the last completion before the segment, and after it; the count returned.
+// (own, own_r: the segment's own count and last completion)
+template <bool REL>
+__device__ __forceinline__ int run_again(const ChainJob &j, const NodeRow &row, int N, int p,
+                                         int own, int own_r, int *lds, int &r)
+{
+    const bool pull = pulls(row, N);
+    const int c = rdl(row.count, pull ? 1 : 0);
+    const int a1 = seg_at(j, c, p + 1);
+    int b = seg_at(j, c, p), len = WAVE;
+    int cnt = 0, rf = -1, cntf = 0, s1 = 0;
+    while (b < a1 && rf != r) {
+        const int e = a1 - b < len ? a1 : b + len;
+        count_range<REL, true, NMAX - 2>(j.ix, row, N, pull, b, e, lds, r, cnt, rf, cntf, s1);
+        b = e;
+        len *= 2;
+    }
+    if (rf != r) return cnt;
+    r = own_r;
+    return cnt + own - cntf;
+}
+
+// Segments' second runs, all at once: each from the last completion of the
+// segments' own runs before it, which is the true one unless a run before it
+// ends without having met its own.  A wave looks at 2^log2_items segments of the
+// rows one after the other.  j.seg[].w: the count of a run that met its own.
+//   Without it k_stitch makes them one after the other for each row, which is
+// as good where the rows alone fill the device, and for few segments saves the
+// launch (5000 rows, 3 segments: 0.302 / 0.299 ms with / without).  Dense
+// streams have a second run at every other segment: 64 rows over 1e6 events,
+// relaxed, 8 types and two nodes, 244 segments 0.15 ms, where one wave that took
+// its 64 rows' second runs in order needed 1.5; 3 types at 1 kHz and five nodes,
+// exact, 256 segments 28 ms against 854.
+constexpr int SECOND_RUNS = 8192;  // waves that fill it
+constexpr int FEW_SEGMENTS = 4;
+template <bool REL>
+__global__ __launch_bounds__(WAVE) void k_again(ChainJob j, const int *status, int log2_items)
+{
+    extern __shared__ int lds[];
+    if (*status) return;
+    const int lane = __lane_id(), items = j.rows.M * j.P;
+    const int i = (int)blockIdx.x << log2_items;
+    const int at = i + lane, m = (int)((unsigned)at / (unsigned)j.P), p = at - m * j.P;
+    bool again = false;
+    int4 g = make_int4(0, -1, FAR_TICK, 0);
+    int r = -1;
+    // (a row of the first pass alone has no segments)
+    if (lane < 1 << log2_items && at < items && (REL || !j.upper || j.upper[m] >= j.theta)) {
+        g = j.seg[at];
+        // (behind a few segments without a completion there is hardly one that
+        // matters; k_stitch takes those that do)
+        for (int q = 1; g.x > 0 && q <= p && q <= FEW_SEGMENTS; ++q) {
+            const int4 before = j.seg[at - q];
+            if (before.x == 0) continue;
+            r = before.y;
+            break;
+        }
+        again = g.x > 0 && r >= g.z;
+    }
+    for (unsigned long long todo = bal(again); todo; todo &= todo - 1) {
+        const int q = (int)__builtin_ctzll(todo);
+        NodeRow row;
+        const int N = load_row(j.ix, j.rows, rdl(m, q), row);
+        const int own_r = rdl(g.y, q);
+        int rr = rdl(r, q);
+        const int cnt = run_again<REL>(j, row, N, rdl(p, q), rdl(g.x, q), own_r, lds, rr);
+        if (lane == 0 && rr == own_r) j.seg[i + q].w = cnt;
+    }
+}
+
+// One wave per candidate: its segments' results in order, 64 at a time.  As
+// long as the state is that of the last own run, the counts of those that
+// stand and of the second runs that met them are only added up; a segment that
+// has neither is run again here (regular gaps, whose runs need never meet: the
+// row's second runs are then as long as its list).
 template <bool REL> __global__ __launch_bounds__(WAVE) void k_stitch(ChainJob j, const int *status)
 {
     extern __shared__ int lds[];
     if (*status) return;
-    const int M = j.rows.M, lane = __lane_id();
-    const int m = (int)blockIdx.x * WAVE + lane;
-    bool on = m < M;
+    const int64_t m = grid_item();
+    if (m >= j.rows.M) return;
+    const int lane = __lane_id();
     int *out = REL ? j.upper : j.exact;
-    if (!REL && j.upper && on && j.upper[m] < j.theta) {
-        out[m] = -1;
-        on = false;
+    if (!REL && j.upper && j.upper[m] < j.theta) {
+        if (lane == 0) out[m] = -1;
+        return;
     }
-    int tot = 0, r = -1;
-    for (int p = 0; p < j.P; ++p) {
-        const int4 g = on ? j.seg[(int64_t)p * M + m] : make_int4(0, -1, FAR_TICK, 0);
-        const bool again = on & (g.x > 0) & (r >= g.z);
-        if (on && !again && g.x > 0) {
-            tot += g.x;
-            r = g.y;
-        }
-        unsigned long long todo = bal(again);
-        while (todo) {
-            const int q = (int)__builtin_ctzll(todo);
-            todo &= todo - 1;
-            const int mq = (int)blockIdx.x * WAVE + q;
-            NodeRow row;
-            const int N = load_row(j.ix, j.rows, mq, row);
-            const bool pull = pulls(row, N);
-            const int c = rdl(row.count, pull ? 1 : 0);
-            const int a1 = seg_at(j, c, p + 1);
-            int b = seg_at(j, c, p), len = WAVE;
-            int rr = rdl(r, q), cnt = 0, rf = -1, cntf = 0, s1 = 0;
-            while (b < a1 && (rf != rr)) {
-                const int e = a1 - b < len ? a1 : b + len;
-                count_range<REL, true, NMAX - 2>(j.ix, row, N, pull, b, e, lds, rr, cnt, rf, cntf, s1);
-                b = e;
-                len *= 2;
-            }
-            const int gx = rdl(g.x, q), gy = rdl(g.y, q);
-            if (lane == q) {
-                if (rf == rr && rf >= 0) {
-                    tot += cnt + (gx - cntf);
-                    r = gy;
-                } else {
-                    tot += cnt;
-                    r = rr;
+    NodeRow row;
+    int N = 0;  // (the row is read when it is needed)
+    int sum = 0, tot = 0, r = -1;
+    bool same = true;  // r is the last own run's
+    for (int p0 = 0; p0 < j.P; p0 += WAVE) {
+        const int4 g = p0 + lane < j.P ? j.seg[m * j.P + p0 + lane] : make_int4(0, -1, FAR_TICK, 0);
+        const unsigned long long some = bal(g.x > 0);
+        for (int from = 0; from < WAVE;) {
+            const unsigned long long on = some & (~0ull << from);
+            if (!on) break;
+            int b;  // the next segment that is run again
+            if (same) {
+                const unsigned long long lower = on & ((1ull << lane) - 1ull);
+                const int before = __shfl(g.y, lower ? 63 - __builtin_clzll(lower) : 0);
+                const bool stands = (lower ? before : r) < g.z;
+                const unsigned long long bad = bal(!stands & (g.w < 0)) & on;
+                b = bad ? (int)__builtin_ctzll(bad) : WAVE;
+                sum += ((on >> lane) & 1) && lane < b ? (stands ? g.x : g.w) : 0;
+                const unsigned long long done = bad ? on & ((1ull << b) - 1ull) : on;
+                if (done) r = rdl(g.y, 63 - __builtin_clzll(done));
+                if (!bad) break;
+            } else {
+                b = (int)__builtin_ctzll(on);
+                if (r < rdl(g.z, b)) {
+                    tot += rdl(g.x, b);
+                    r = rdl(g.y, b);
+                    same = true;
+                    from = b + 1;
+                    continue;
                 }
             }
+            if (N == 0) N = load_row(j.ix, j.rows, m, row);
+            const int own_r = rdl(g.y, b);
+            tot += run_again<REL>(j, row, N, p0 + b, rdl(g.x, b), own_r, lds, r);
+            same = r == own_r;
+            from = b + 1;
         }
     }
-    if (on) out[m] = tot;
+    for (int off = 32; off >= 1; off >>= 1) sum += __shfl_xor(sum, off);
+    if (lane == 0) out[m] = tot + sum;
 }
 
 template <int MODE> void chain_mode(ChainJob j, int nmax, const int *status, hipStream_t s)
@@ -853,10 +927,16 @@ template <int MODE> void chain_mode(ChainJob j, int nmax, const int *status, hip
         hipLaunchKernelGGL((k_chain<MODE, 3>), grid, dim3(WAVE), lds, s, j, status, rows);
     else
         hipLaunchKernelGGL((k_chain<MODE, NMAX - 2>), grid, dim3(WAVE), lds, s, j, status, rows);
-    if (j.P > 1)
-        hipLaunchKernelGGL((k_stitch<MODE == CHAIN_RELAXED>),
-                           dim3((unsigned)((j.rows.M + WAVE - 1) / WAVE)), dim3(WAVE), lds, s, j,
-                           status);
+    if (j.P == 1) return;
+    constexpr bool REL = MODE == CHAIN_RELAXED;
+    if (j.rows.M < SECOND_RUNS && j.P > FEW_SEGMENTS) {
+        const int items = j.rows.M * j.P;
+        int each = 0;
+        while (each < 6 && items >> each > SECOND_RUNS) ++each;
+        hipLaunchKernelGGL((k_again<REL>), dim3((unsigned)((items + (1 << each) - 1) >> each)),
+                           dim3(WAVE), lds, s, j, status, each);
+    }
+    hipLaunchKernelGGL((k_stitch<REL>), grid_of(j.rows.M), dim3(WAVE), lds, s, j, status);
 }
 
 }  // namespace
