@@ -390,7 +390,10 @@ typedef struct fe_server fe_server;
 typedef struct fe_server_config {
     int32_t n_arrays;      /* number of streams                               */
     int64_t capacity;      /* events each array's device buffer holds          */
-    int64_t hbm_budget;    /* bytes of per-request device state in flight      */
+    int64_t hbm_budget;    /* bytes of per-request device state in flight; a
+                              window whose per-type lists are more than a
+                              round's share, hbm_budget / max_inflight, is
+                              counted event by event                           */
     int32_t max_inflight;  /* rounds on the device at once (>= 1)              */
     int32_t max_round;     /* requests per round (>= 1)                        */
     int32_t seg_events;    /* target events per work item (0: 16384)           */

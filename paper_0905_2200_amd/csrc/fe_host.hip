@@ -3472,11 +3472,8 @@ extern "C" int fe_server_create(fe_ctx *c, const fe_server_config *cfg, const in
                                                         g.dcap, (int)cfg->capacity).bytes);
     // lanes: stream, completion event, arena sized to the lane's budget
     const int64_t lane_budget = std::max<int64_t>(1, cfg->hbm_budget / cfg->max_inflight);
-    int64_t max_one = req_arena_bytes(sv, (int)cfg->capacity);
-    // (a window whose index exceeds the budget is counted event by event)
-    if (maxtypes <= CHAIN_TYPES)
-        max_one = std::max(max_one, std::min(cfg->hbm_budget,
-                                             req_chain_bytes(sv, (int)cfg->capacity)));
+    // (a window whose index exceeds a lane's share is counted event by event)
+    const int64_t max_one = req_arena_bytes(sv, (int)cfg->capacity);
     const int64_t arena = std::max<int64_t>(lane_budget, max_one) + (64 << 10);
     sv->lanes.resize(cfg->max_inflight);
     for (auto &L : sv->lanes) {
@@ -3563,7 +3560,8 @@ extern "C" int fe_server_submit(fe_server *sv, const fe_request *rq, uint64_t *t
     if (c->param[FE_PARAM_TYPE_DISPATCH] != 0 && sv->maxtypes <= CHAIN_TYPES &&
         q->b - q->a <= CHAIN_EVENTS) {
         const int64_t f = req_chain_bytes(sv, q->b - q->a) + 2 * (int64_t)sv->M * 4;
-        if (f <= sv->cfg.hbm_budget) {
+        // (its lane's share: every lane may hold such a request)
+        if (f <= sv->cfg.hbm_budget / sv->cfg.max_inflight) {
             q->foot = f;
             q->chain = true;
         }

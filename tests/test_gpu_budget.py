@@ -1,0 +1,74 @@
+"""Device memory: what a server, a count and the miner hold stays within what
+they were given, and calls whose lists do not fit are counted all the same."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_0905_2200_amd import synth
+from tests.gpu_util import banner, have_gpu, oracle_counts
+
+pytestmark = [pytest.mark.gpu, pytest.mark.skipif(not have_gpu(), reason="needs a GPU")]
+
+EXACT, RELAXED = 0, 1
+IVS = [(0, 50), (50, 100), (100, 200)]
+
+
+@pytest.fixture(scope="module")
+def fe():
+    from paper_0905_2200_amd import fe as fe_mod
+    return fe_mod
+
+
+@pytest.fixture(scope="module")
+def ctx(fe):
+    c = fe.Context(0)
+    yield c
+    c.close()
+
+
+def _free(ctx):
+    ctx.torch.cuda.synchronize()
+    return ctx.torch.cuda.mem_get_info()[0]
+
+
+def test_server_lanes_share_the_budget(ctx, fe):
+    # 8 lanes of a 2 GiB budget, buffers for windows whose lists alone are 2 GiB
+    cand = synth.pack([((0, 1), (0,), (50,))])
+    before = _free(ctx)
+    sv = fe.Server(ctx, cand, [2], capacity=130_000_000, hbm_budget=2 << 30, max_inflight=8)
+    held = before - _free(ctx)
+    banner("server of 8 lanes holds %.2f GiB" % (held / 2 ** 30))
+    sv.close()
+    # the array (1 GiB), the lanes' shares, a quarter more of each, 1 GiB for all else
+    assert held < 1.25 * (2 * 4 * 130_000_000 + (2 << 30)) + (1 << 30)
+
+
+@pytest.mark.parametrize("lanes", [1, 4])
+def test_windows_between_a_share_and_the_budget(ctx, fe, lanes):
+    rng = np.random.default_rng(61)
+    T, n = 40, 60_000
+    ids = rng.integers(0, T, n).astype(np.int32)
+    ticks = np.cumsum(rng.integers(0, 9, n)).astype(np.int32)
+    cand = synth.pack(synth.random_episodes(rng, 64, T, 3, IVS, n_min=3))
+    budget = 2 << 20
+    sv = fe.Server(ctx, cand, [T], capacity=n, hbm_budget=budget, max_inflight=lanes, max_round=4)
+    sv.append(0, ids, ticks)
+    cuts = [(0, int(ticks[k])) for k in (500, 5_000, 20_000, 30_000, 45_000, 59_000, 200, 58_000)]
+    tk = [sv.submit(0, a, b, 2) for a, b in cuts]
+    banner("windows between a share and the budget: %d lanes" % lanes)
+    feet = []
+    for (a, b), t in zip(cuts, tk):
+        r = sv.wait(t)
+        k = np.searchsorted(ticks, b, "left")
+        wu, we = oracle.two_pass(ids[:k], ticks[:k], T, cand["types"], cand["len"], cand["lo"],
+                                 cand["hi"], 2, projection=True)
+        assert r["status"] == fe.FE_OK and r["n_events"] == k
+        assert np.array_equal(r["upper"], wu) and np.array_equal(r["exact"], we), k
+        feet.append(r["footprint"])
+    st = sv.stats()
+    sv.close()
+    assert st["completed"] == len(cuts) and st["rejected"] == 0
+    # (the widest window's lists are about 1 MiB: within one lane's share of one,
+    # not of four, where it is counted event by event)
+    assert max(feet) <= budget // lanes
+    assert max(feet) > budget // 4 or lanes == 4
