@@ -358,7 +358,9 @@ typedef struct fe_batch_tuning {
  * candidate tables must stay unchanged and valid while the batch exists. */
 int fe_batch_create(fe_ctx *ctx, int32_t R, const fe_job *jobs, fe_batch **out);
 
-/* Enqueue the batch on the context's stream (asynchronous). */
+/* Enqueue the batch on the context's stream (asynchronous).  Over per-type
+ * lists, a run that finds a recording's events unsorted or out of range (they
+ * were changed after fe_batch_create) leaves -1 in every count. */
 int fe_batch_run(fe_batch *b);
 
 /* Time `reps` runs for each launch shape of a small grid (segment length x

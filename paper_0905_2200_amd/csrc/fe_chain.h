@@ -120,6 +120,7 @@ void launch_chain(const ChainJob &job, ChainMode mode, int nmax, const int *stat
                   hipStream_t s);
 // Both counts of every row of several jobs (device array; P = 1), whose rows
 // are numbered first[0..njobs]: job q has rows first[q] to first[q + 1].
+// (status non-zero: every count is -1)
 void launch_chains(const ChainJob *jobs, const int64_t *first, int njobs, int64_t total, int nmax,
                    const int *status, hipStream_t s);
 // *out = the number of v[0..M) that are at least theta.

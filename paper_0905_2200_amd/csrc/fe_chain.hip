@@ -752,7 +752,6 @@ __global__ __launch_bounds__(WAVE, chain_waves(EMAX)) void k_chains(const ChainJ
                                                  int njobs, int64_t total, const int *status)
 {
     extern __shared__ int lds[];
-    if (*status) return;
     const int64_t item = grid_item();
     if (item >= total) return;
     int lo = 0, hi = njobs;
@@ -760,6 +759,11 @@ __global__ __launch_bounds__(WAVE, chain_waves(EMAX)) void k_chains(const ChainJ
         const int mid = (lo + hi) >> 1;
         if (first[mid] <= item) lo = mid;
         else hi = mid;
+    }
+    if (*status) {
+        // (no caller waits for the checks of a batch's run)
+        if (__lane_id() == 0) jobs[lo].upper[item - first[lo]] = jobs[lo].exact[item - first[lo]] = -1;
+        return;
     }
     ChainJob j = jobs[lo];
     j.ix.et = global_ptr(j.ix.et);

@@ -2240,7 +2240,7 @@ struct fe_batch {
     // counting by chains: an index of every stream (made by each run) and
     // one job per recording
     bool chain = false;
-    Buf ixd, cjobs;
+    Buf ixd, cjobs, cstat;  // (cstat: the checks of a run, which are its own)
     IndexSet set;
     const ChainJob *chain_jobs = nullptr;
     const int64_t *chain_first = nullptr;
@@ -2330,7 +2330,7 @@ int batch_chain_plan(fe_batch *b)
         nmax = std::max(nmax, j.nmax);
     }
     if (ensure(c, b->ixd, (size_t)ints * sizeof(int)) ||
-        ensure(c, b->cjobs, chain_block_bytes(R)))
+        ensure(c, b->cjobs, chain_block_bytes(R)) || ensure(c, b->cstat, sizeof(int)))
         return FE_OK;
     std::vector<IndexJob> ij(R);
     std::vector<ChainJob> cj(R);
@@ -2729,8 +2729,9 @@ extern "C" int fe_batch_run(fe_batch *b)
     fe_ctx *c = b->c;
     HIPCHK(c, hipSetDevice(c->device));
     if (b->chain) {
+        launch_fill(P<int>(b->cstat), 0, 1, c->stream);
         launch_chain_block(b->set, b->chain_jobs, b->chain_first, b->total, b->nmax,
-                           P<int>(c->status), c->stream);
+                           P<int>(b->cstat), c->stream);
         HIPCHK(c, hipGetLastError());
         return FE_OK;
     }
@@ -2819,7 +2820,7 @@ extern "C" int fe_batch_destroy(fe_batch *b)
     batch_free_graphs(b);
     Buf *bufs[] = {&b->pk,    &b->origd, &b->tileWd, &b->tilesd, &b->jobsd,  &b->itemsd,
                    &b->listsd, &b->lamd, &b->tbld,   &b->flagsr, &b->flagsx, &b->qctr,
-                   &b->deepd,  &b->ixd,  &b->cjobs};
+                   &b->deepd,  &b->ixd,  &b->cjobs,  &b->cstat};
     for (Buf *x : bufs)
         if (x->p) (void)hipFree(x->p);
     if (b->cap) (void)hipStreamDestroy(b->cap);

@@ -312,3 +312,47 @@ def test_served_arrays_of_different_types(ctx, fe):
             assert res["status"] == fe.FE_OK and res["n_events"] == y - x
             assert np.array_equal(res["upper"], wu) and np.array_equal(res["exact"], we), (a, t0, t1)
         sv.close()
+
+
+def test_batch_over_a_changed_recording(ctx, fe):
+    # a run over events that have become invalid leaves no old counts, and
+    # nothing behind for other calls of the context
+    rng = np.random.default_rng(31)
+    recs, host = [], []
+    for n, T in ((4_000, 6), (900, 3)):
+        ids_h = rng.integers(0, T, n).astype(np.int32)
+        ticks_h = np.cumsum(rng.integers(0, 12, n)).astype(np.int32)
+        cand = synth.pack(synth.random_episodes(rng, 150, T, 4, IVS, n_min=1))
+        ids, ticks = ctx.stream_tensors(ids_h, ticks_h)
+        host.append((ids_h, ticks_h, T, cand))
+        recs.append({"ids": ids, "ticks": ticks, "num_types": T,
+                     "cand": ctx.cand_tensors(cand), "theta": 2})
+    b = fe.Batch(ctx, recs)
+
+    def right():
+        for r, (i, t, T, c) in enumerate(host):
+            wu, we = oracle.two_pass(i, t, T, c["types"], c["len"], c["lo"], c["hi"], 2,
+                                     projection=True)
+            assert np.array_equal(b.upper[r].cpu().numpy(), wu), r
+            assert np.array_equal(b.exact[r].cpu().numpy(), we), r
+    banner("batch over a changed recording")
+    b.run()
+    ctx.sync()
+    right()
+    for k, at, v in (("ids", 7, 6), ("ids", 3_999, -1), ("ticks", 5, 1 << 30), ("ticks", 3_000, 0)):
+        keep = int(recs[0][k][at].item())
+        recs[0][k][at] = v
+        ctx.torch.cuda.synchronize()
+        b.run()
+        ctx.sync()
+        for r in range(2):
+            assert (b.upper[r] == -1).all().item() and (b.exact[r] == -1).all().item(), (k, r)
+        i, t, T, c = host[1]
+        got = ctx.count(recs[1]["ids"], recs[1]["ticks"], T, recs[1]["cand"], EXACT)
+        assert np.array_equal(got.cpu().numpy(), oracle_counts(i, t, T, c, EXACT)), k
+        recs[0][k][at] = keep
+        ctx.torch.cuda.synchronize()
+        b.run()
+        ctx.sync()
+        right()
+    b.close()
