@@ -123,7 +123,8 @@ void launch_chain(const ChainJob &job, ChainMode mode, int nmax, const int *stat
 // (status non-zero: every count is -1)
 void launch_chains(const ChainJob *jobs, const int64_t *first, int njobs, int64_t total, int nmax,
                    const int *status, hipStream_t s);
-// *out = the number of v[0..M) that are at least theta.
+// *out = the number of v[0..M) that are at least theta (status non-zero: not
+// written).
 void launch_count_ge(const int *v, int M, int theta, int *out, const int *status, hipStream_t s);
 
 // ---- mining: every candidate is a frequent episode and one more node and

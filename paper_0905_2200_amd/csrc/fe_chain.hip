@@ -951,10 +951,10 @@ __global__ __launch_bounds__(GEB) void k_count_ge(const int *v, int M, int theta
                                                   const int *status)
 {
     __shared__ int part[GEB / WAVE];
+    if (*status) return;
     int c = 0;
-    if (*status == 0)
-        for (int i = blockIdx.x * GEB + threadIdx.x; i < M; i += gridDim.x * GEB)
-            c += v[i] >= theta ? 1 : 0;
+    for (int i = blockIdx.x * GEB + threadIdx.x; i < M; i += gridDim.x * GEB)
+        c += v[i] >= theta ? 1 : 0;
     for (int off = 32; off >= 1; off >>= 1) c += __shfl_xor(c, off);
     if (__lane_id() == 0) part[threadIdx.x >> 6] = c;
     __syncthreads();
@@ -964,13 +964,17 @@ __global__ __launch_bounds__(GEB) void k_count_ge(const int *v, int M, int theta
     if (gridDim.x == 1) *out = c;
     else if (c) atomicAdd(out, c);
 }
+__global__ void k_clear(int *out, const int *status)
+{
+    if (*status == 0) *out = 0;
+}
 }  // namespace
 
 void launch_count_ge(const int *v, int M, int theta, int *out, const int *status, hipStream_t s)
 {
     // (one block needs no clearing)
     const int blocks = M <= 8 * GEB ? 1 : std::min((M + 4 * GEB - 1) / (4 * GEB), 256);
-    if (blocks > 1) launch_fill(out, 0, 1, s);
+    if (blocks > 1) hipLaunchKernelGGL(k_clear, dim3(1), dim3(1), 0, s, out, status);
     hipLaunchKernelGGL(k_count_ge, dim3(blocks), dim3(GEB), 0, s, v, M, theta, out, status);
 }
 

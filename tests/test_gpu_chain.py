@@ -356,3 +356,25 @@ def test_batch_over_a_changed_recording(ctx, fe):
         ctx.sync()
         right()
     b.close()
+
+
+@pytest.mark.parametrize("rows", [1, 20_000])
+def test_two_pass_errors_write_nothing(ctx, fe, rows):
+    # (the survivors of small and of large tables are counted by one and by many blocks)
+    t = ctx.torch
+    ok = ctx.stream_tensors([0, 1, 0, 1], [0, 5, 6, 9])
+    bad = ctx.stream_tensors([0, 1, 0, 1], [0, 5, 3, 9])
+    good = ctx.cand_tensors(synth.pack([((0, 1), (0,), (10,))] * rows))
+    wrong = ctx.cand_tensors(synth.pack([((0, 1), (0,), (10,))] * (rows - 1) +
+                                        [((0, 2), (0,), (10,))]))
+    up, ex = (t.full((rows,), -7, dtype=t.int32, device=ctx.device) for _ in range(2))
+    ns = t.full((1,), -7, dtype=t.int32, device=ctx.device)
+    for stream, cand, code in ((bad, good, fe.FE_EUNSORTED), (ok, wrong, fe.FE_EINVAL)):
+        with pytest.raises(fe.FeError) as e:
+            ctx.count_two_pass(stream[0], stream[1], 2, cand, 1, up, ex, ns)
+        assert e.value.code == code
+        t.cuda.synchronize()
+        assert (up == -7).all().item() and (ex == -7).all().item() and ns.item() == -7
+    ctx.count_two_pass(ok[0], ok[1], 2, good, 1, up, ex, ns)
+    t.cuda.synchronize()
+    assert (up == 2).all().item() and (ex == 2).all().item() and ns.item() == rows
