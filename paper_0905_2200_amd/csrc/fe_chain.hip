@@ -953,7 +953,7 @@ __global__ __launch_bounds__(GEB) void k_count_ge(const int *v, int M, int theta
     __shared__ int part[GEB / WAVE];
     if (*status) return;
     int c = 0;
-    for (int i = blockIdx.x * GEB + threadIdx.x; i < M; i += gridDim.x * GEB)
+    for (int64_t i = blockIdx.x * GEB + threadIdx.x; i < M; i += gridDim.x * GEB)
         c += v[i] >= theta ? 1 : 0;
     for (int off = 32; off >= 1; off >>= 1) c += __shfl_xor(c, off);
     if (__lane_id() == 0) part[threadIdx.x >> 6] = c;

@@ -378,3 +378,25 @@ def test_two_pass_errors_write_nothing(ctx, fe, rows):
     ctx.count_two_pass(ok[0], ok[1], 2, good, 1, up, ex, ns)
     t.cuda.synchronize()
     assert (up == 2).all().item() and (ex == 2).all().item() and ns.item() == rows
+
+
+def test_nearly_2_to_31_rows(ctx, fe):
+    # one-node rows, type 1 first and last: places past 2^31 - 2^18
+    t = ctx.torch
+    M = (1 << 31) - 300
+    if t.cuda.mem_get_info()[0] < 48 << 30:
+        pytest.skip("needs 34 GB of device memory")
+    ids, ticks = ctx.stream_tensors([0, 1, 0], [0, 5, 6])
+    types = t.zeros((M, 1), dtype=t.int32, device=ctx.device)
+    types[0] = types[-1] = 1
+    one = t.ones(M, dtype=t.int32, device=ctx.device)
+    hop = t.zeros((1, 1), dtype=t.int32, device=ctx.device)
+    cand = {"types": types, "len": one, "lo": hop, "hi": hop, "nmax": 1, "M": M}
+    banner("%d rows" % M)
+    up, ex, ns = ctx.count_two_pass(ids, ticks, 2, cand, 2)
+    assert ns.item() == M - 2
+    for v, drop in ((up, 1), (ex, -1)):
+        assert v[0].item() == drop and v[-1].item() == drop
+        assert v[1].item() == 2 and v[M // 2].item() == 2 and v[-2].item() == 2
+    del up, ex, types, one, cand
+    t.cuda.empty_cache()
