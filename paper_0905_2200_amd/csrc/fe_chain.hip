@@ -227,9 +227,11 @@ __global__ __launch_bounds__(TYB) void k_ix_types(IndexSet x, int scan_here, con
 {
     __shared__ int64_t sh[TYB / WAVE];
     const int st = *status;
-    if (threadIdx.x == 0 && blockIdx.x == 0 && hstat) *hstat = st;
+    if (threadIdx.x == 0 && blockIdx.x == 0 && blockIdx.y == 0 && hstat) *hstat = st;
     if (st) return;
-    const IndexJob j = global_job(x.jobs ? x.jobs[blockIdx.x] : x.one);
+    const int64_t job = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
+    if (job >= x.njobs) return;
+    const IndexJob j = global_job(x.jobs ? x.jobs[job] : x.one);
     const int n = j.n, T = j.T, nch = j.nch;
     const int *hist = j.hist;
     int *off = j.off, *et = j.et, *ei = j.ei;
@@ -341,8 +343,10 @@ __global__ __launch_bounds__(WAVE) void k_ix_lists(IndexSet x, const int *status
 __global__ __launch_bounds__(256) void k_ix_tab(IndexSet s, const int *status)
 {
     if (*status) return;
-    const IndexJob j = job_of(s, blockIdx.x, [](const IndexJob &q) { return q.first_type; });
-    const TypeIdx x = j.ty[(int)blockIdx.x - j.first_type];
+    const int64_t type = (int64_t)blockIdx.z * gridDim.x + blockIdx.x;
+    if (type >= s.types) return;
+    const IndexJob j = job_of(s, (int)type, [](const IndexJob &q) { return q.first_type; });
+    const TypeIdx x = j.ty[(int)type - j.first_type];
     const int *et = j.et;
     int *tab = j.tab;
     const int lane = __lane_id();
@@ -384,8 +388,9 @@ void launch_index_types(const IndexSet &x, const int *status, int *hstat, hipStr
 {
     const bool here = !x.alone || x.scan <= SMALL_SCAN;
     if (!here) launch_scan_excl(x.one.hist, x.scan, x.one.off, x.scan_scratch, s);
-    hipLaunchKernelGGL(k_ix_types, dim3((unsigned)x.njobs), dim3(TYB), 0, s, x, here ? 1 : 0,
-                       status, hstat);
+    const int jx = std::min(x.njobs, 1 << 20);
+    hipLaunchKernelGGL(k_ix_types, dim3((unsigned)jx, (unsigned)((x.njobs + (int64_t)jx - 1) / jx)),
+                       dim3(TYB), 0, s, x, here ? 1 : 0, status, hstat);
 }
 
 void launch_index_lists(const IndexSet &x, const int *status, hipStream_t s)
@@ -394,8 +399,11 @@ void launch_index_lists(const IndexSet &x, const int *status, hipStream_t s)
         hipLaunchKernelGGL(k_ix_lists, dim3((unsigned)x.chunks), dim3(WAVE),
                            (size_t)x.most_types * (sizeof(unsigned long long) + sizeof(int)), s,
                            x, status);
-    hipLaunchKernelGGL(k_ix_tab, dim3((unsigned)x.types, (unsigned)x.parts), dim3(256), 0, s, x,
-                       status);
+    if (x.types == 0) return;
+    // (a grid's dimension holds fewer than 2^32 threads)
+    const int tx = std::min(x.types, 1 << 20);
+    const dim3 grid((unsigned)tx, (unsigned)x.parts, (unsigned)((x.types + (int64_t)tx - 1) / tx));
+    hipLaunchKernelGGL(k_ix_tab, grid, dim3(256), 0, s, x, status);
 }
 
 namespace {

@@ -400,3 +400,27 @@ def test_nearly_2_to_31_rows(ctx, fe):
         assert v[1].item() == 2 and v[M // 2].item() == 2 and v[-2].item() == 2
     del up, ex, types, one, cand
     t.cuda.empty_cache()
+
+
+def test_batch_of_2_to_24_lists(ctx, fe):
+    # 4200 recordings of 4096 types: more lists than a grid's dimension has blocks of 256
+    rng = np.random.default_rng(37)
+    T, n, R = 4096, 300, 4200
+    ids_h = rng.integers(T - 5, T, n).astype(np.int32)
+    ticks_h = np.cumsum(rng.integers(0, 12, n)).astype(np.int32)
+    cand = synth.pack([((T - 1 - a, T - 1 - b), (0,), (40,)) for a in range(5) for b in range(5)])
+    ids, ticks = ctx.stream_tensors(ids_h, ticks_h)
+    cd = ctx.cand_tensors(cand)
+    wu, we = oracle.two_pass(ids_h, ticks_h, T, cand["types"], cand["len"], cand["lo"],
+                             cand["hi"], 3, projection=True)
+    banner("batch of %d lists" % (R * T))
+    b = fe.Batch(ctx, [{"ids": ids, "ticks": ticks, "num_types": T, "cand": cd, "theta": 3}] * R)
+    b.run()
+    ctx.sync()
+    for r in (0, 1, R // 2, R - 105, R - 104, R - 1):
+        assert np.array_equal(b.upper[r].cpu().numpy(), wu), r
+        assert np.array_equal(b.exact[r].cpu().numpy(), we), r
+    t = ctx.torch
+    assert (t.stack(b.upper) == t.stack(b.upper)[0]).all().item()
+    assert (t.stack(b.exact) == t.stack(b.exact)[0]).all().item()
+    b.close()
