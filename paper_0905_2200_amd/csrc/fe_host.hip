@@ -688,6 +688,7 @@ bool chain_takes(const fe_ctx *c, int64_t n, int num_types)
 // 3.7 and 5.7 / 4.1.  Where the lists fit already and the rows fill the device
 // alone, two only cost: 3e5 of 200 types, 20 000 rows 0.17 / 0.19 and 0.18 /
 // 0.18, 1e5 rows 0.39 / 0.46 and 0.40 / 0.47.
+constexpr int64_t SEG_RESULTS = (int64_t)1 << 26;  // segments' results kept (1 GiB)
 int chain_P(const fe_ctx *c, int64_t M, int64_t n, int num_types, int nmax, bool exact)
 {
     const int64_t tiles = (M + WAVE - 1) / WAVE;
@@ -698,8 +699,16 @@ int chain_P(const fe_ctx *c, int64_t M, int64_t n, int num_types, int nmax, bool
     int64_t P = c->param[FE_PARAM_TARGET_WAVES] / M;
     P = std::max<int64_t>(P, 12 * n / ((int64_t)3 << 20));
     P = std::min<int64_t>(P, n / ((int64_t)512 * num_types));
-    P = std::min<int64_t>(P, ((int64_t)1 << 30) / M);
+    P = std::min<int64_t>(P, SEG_RESULTS / M);
     return (int)std::max<int64_t>(1, std::min<int64_t>(P, 4096));
+}
+
+// Room for the results of P segments of M rows; fewer segments, down to one,
+// where memory is short.
+int seg_room(fe_ctx *c, int64_t M, int P)
+{
+    while (P > 1 && ensure(c, c->cseg, (size_t)(P * M) * sizeof(int4))) P /= 2;
+    return P;
 }
 
 Rows table_rows(const CandIn &cin, int M)
@@ -755,10 +764,8 @@ int chain_call(fe_ctx *c, const int *ids, const int *ticks, int64_t n, int num_t
     int rc;
     taken = false;
     const IndexPlan ip = index_plan(n, num_types, true);
-    const int Pn = chain_P(c, M, n, num_types, cin.nmax, mode == CHAIN_EXACT);
-    if (ensure(c, c->cidx, (size_t)ip.ints * sizeof(int)) ||
-        ensure(c, c->cseg, Pn > 1 ? (size_t)Pn * M * sizeof(int4) : 4))
-        return FE_OK;
+    if (ensure(c, c->cidx, (size_t)ip.ints * sizeof(int))) return FE_OK;
+    const int Pn = seg_room(c, M, chain_P(c, M, n, num_types, cin.nmax, mode == CHAIN_EXACT));
     if ((rc = ensure_host(c, 4))) return rc;
     if (!c->checked)
         HIPCHK(c, hipEventCreateWithFlags(&c->checked, hipEventDisableTiming));
@@ -1589,9 +1596,8 @@ int mine_siblings(fe_ctx *c, MineChains &mc, bool rel, int level, const int *F,
 int chain_rows(fe_ctx *c, const MineChains &mc, const Rows &rows, int num_types, ChainMode mode,
                int theta, int *up, int *ex, const char *name)
 {
-    int rc;
-    const int Pn = chain_P(c, rows.M, mc.ip.n, num_types, rows.N, mode == CHAIN_EXACT);
-    if ((rc = ensure(c, c->cseg, Pn > 1 ? (size_t)Pn * rows.M * sizeof(int4) : 4))) return rc;
+    const int Pn = seg_room(c, rows.M, chain_P(c, rows.M, mc.ip.n, num_types, rows.N,
+                                               mode == CHAIN_EXACT));
     ChainJob j{};
     j.ix = mc.ix;
     j.rows = rows;

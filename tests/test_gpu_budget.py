@@ -72,3 +72,22 @@ def test_windows_between_a_share_and_the_budget(ctx, fe, lanes):
     # not of four, where it is counted event by event)
     assert max(feet) <= budget // lanes
     assert max(feet) > budget // 4 or lanes == 4
+
+
+def test_segments_of_many_rows(ctx, fe):
+    # 262144 rows, as many segments as asked for: their results stay within 1 GiB
+    t = ctx.torch
+    M, n = 1 << 18, 1 << 21
+    ids = t.zeros(n, dtype=t.int32, device=ctx.device)
+    ticks = t.arange(n, dtype=t.int32, device=ctx.device)
+    cand = ctx.cand_tensors({"types": np.zeros((M, 1), np.int32), "len": np.ones(M, np.int32),
+                             "lo": np.zeros((M, 0), np.int32), "hi": np.zeros((M, 0), np.int32)})
+    with fe.Context(0) as own:
+        own.set_param(fe.PARAM_TARGET_WAVES, 1 << 30)
+        before = _free(ctx)
+        got = own.count(ids, ticks, 1, cand, EXACT)
+        assert own.stats()["segments_max"] >= 2
+        assert (got == n).all().item()
+        held = before - _free(ctx)
+        banner("segments of %d rows: %.2f GiB" % (M, held / 2 ** 30))
+    assert held < 2 << 30
