@@ -161,13 +161,22 @@ typedef enum fe_param {
                                 FE_PARAM_ELIMINATION = 2                      */
     FE_PARAM_SAMPLE_MIN = 14, /* smallest level sampled by FE_PARAM_ELIMINATION
                                 = 2 (default 131072 candidates)                */
-    FE_PARAM_SHARED_LISTS = 15 /* 1 (default) = exact event-by-event counting of
+    FE_PARAM_SHARED_LISTS = 15, /* 1 (default) = exact event-by-event counting of
                                 a tile whose candidates share every node but
                                 the last and every hop but the last (join
                                 siblings, N >= 3) keeps lists 0..N-3 once per
                                 tile, each entry with the start index of its
                                 newest chain; 0 = per-candidate lists (same
                                 counts)                                       */
+    FE_PARAM_LIST_BYTES = 16 /* most bytes of device workspace for a call's
+                                per-type lists and what is kept beside them
+                                (default: no limit): the lists, about 16 B an
+                                event and 100 B a type; segments' results, at
+                                most 1 GiB; fe_mine's, see there.  A call whose
+                                lists take more is counted event by event (a
+                                server's window: as set when it is submitted).
+                                Setting it gives back what fe_mine keeps
+                                beyond it                                      */
 } fe_param;
 
 typedef struct fe_ctx fe_ctx;
@@ -305,7 +314,14 @@ typedef struct fe_result {
  * l-2 nodes and intervals agree.  Every level is counted with Algorithm 4
  * on the device; the host drives the levels (Sec. 5 intro) and copies each
  * level's frequent set while the next is counted.  Stops after
- * max_level or at the first level with no frequent episode.  ids, ticks:
+ * max_level or at the first level with no frequent episode.
+ * Workspace: the stream's per-type lists, the level's counts and keys, and per
+ * counter the entries of every pair of frequent types, 12 B for each frequent
+ * type, interval and event (at most 16 GiB; more is not kept, and levels are then
+ * counted candidate by candidate), with 8 B an event for each interval and 64
+ * types (at most 2 GiB).  The context keeps these for its next run; they are given
+ * back to a level or a later call that cannot get memory, and by setting
+ * FE_PARAM_LIST_BYTES below them, which bounds them.  ids, ticks:
  * device; iv_lo, iv_hi: host int32[n_iv] (the set I, in ticks).
  * *out is allocated by the library; free it with fe_result_free.
  * Synchronises. */

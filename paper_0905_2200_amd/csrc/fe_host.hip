@@ -103,7 +103,7 @@ double now_ms()
 
 }  // namespace
 
-constexpr int NPARAM = 16;
+constexpr int NPARAM = 17;
 
 struct fe_ctx {
     int device = 0;
@@ -111,13 +111,14 @@ struct fe_ctx {
     bool own_stream = false;
     std::string err;
     int64_t param[NPARAM] = {0, 16384, 1024, 1, 0, 1, 8472, 13112, 2, 0, 0, 9699, 6165, 1000,
-                             131072, 1};
+                             131072, 1, INT64_MAX};
     fe_stats stats{};
     // workspace
     Buf keys, hist, wmax, pk, orig, tileW, lam, tbl, flags, sel, nsel, status, small, cmask;
     Buf mtypes, mlen, mlo, mhi, mup, mex, msel, mn, mkey, tscr, tinfo, mfk, mfo, mfsel, pbc;
     Buf deep;  // window rings of the deep-class exact launches
     Buf smask[2], sseed[2], sivl, sord, msplit;  // miner: masks and pairs' entries (exact, relaxed), intervals
+    bool mining = false;      // (those are in use)
     Buf cidx, cseg;           // stream index and segment results of chain counting
     hipEvent_t checked = nullptr;  // the input checks of the call have run
     Buf skey, sup;  // keys and relaxed counts of a level's elimination sample
@@ -170,6 +171,28 @@ int fail(fe_ctx *c, int code, const char *fmt, ...)
             return fail((c), FE_EDEVICE, "%s failed: %s", #x, hipGetErrorString(e_));  \
     } while (0)
 
+void give_back(fe_ctx *c, Buf &b)
+{
+    if (!b.p) return;
+    (void)hipStreamSynchronize(c->stream);
+    (void)hipFree(b.p);
+    b.p = nullptr;
+    b.cap = 0;
+}
+
+// The miner's pairs' entries and masks, which a context keeps for its next run.
+size_t lists_held(const fe_ctx *c)
+{
+    return c->smask[0].cap + c->smask[1].cap + c->sseed[0].cap + c->sseed[1].cap;
+}
+void give_lists_back(fe_ctx *c)
+{
+    for (int k = 0; k < 2; ++k) {
+        give_back(c, c->smask[k]);
+        give_back(c, c->sseed[k]);
+    }
+}
+
 int ensure(fe_ctx *c, Buf &b, size_t bytes)
 {
     if (bytes == 0) bytes = 4;
@@ -192,15 +215,22 @@ int ensure(fe_ctx *c, Buf &b, size_t bytes)
         b.p = nullptr;
         b.cap = 0;
     }
-    size_t want = bytes + bytes / 4;
+    // (room for calls that grow)
+    size_t want = bytes + std::min(bytes / 4, (size_t)256 << 20);
     if (hipMalloc(&b.p, want) != hipSuccess) {
         (void)hipGetLastError();
-        if (hipMalloc(&b.p, bytes) != hipSuccess) {
+        want = bytes;
+        bool had = hipMalloc(&b.p, bytes) == hipSuccess;
+        if (!had && !c->mining && lists_held(c)) {
+            (void)hipGetLastError();
+            give_lists_back(c);
+            had = hipMalloc(&b.p, bytes) == hipSuccess;
+        }
+        if (!had) {
             (void)hipGetLastError();
             b.p = nullptr;
             return fail(c, FE_ENOMEM, "device allocation of %zu bytes failed", bytes);
         }
-        want = bytes;
     }
     b.cap = want;
     return FE_OK;
@@ -676,6 +706,11 @@ bool chain_takes(const fe_ctx *c, int64_t n, int num_types)
     return c->param[FE_PARAM_TYPE_DISPATCH] != 0 && c->param[FE_PARAM_SEGMENTS] == 0 && n > 0 &&
            n <= CHAIN_EVENTS && num_types <= CHAIN_TYPES;
 }
+bool list_room(const fe_ctx *c, int64_t bytes) { return bytes <= c->param[FE_PARAM_LIST_BYTES]; }
+bool index_room(const fe_ctx *c, const IndexPlan &p)
+{
+    return list_room(c, p.ints * (int64_t)sizeof(int));
+}
 
 // Segments per candidate: one from the hybrid rule's crossover on (choose_P);
 // below it as many as the target number of waves has room for, or as make a
@@ -703,11 +738,14 @@ int chain_P(const fe_ctx *c, int64_t M, int64_t n, int num_types, int nmax, bool
     return (int)std::max<int64_t>(1, std::min<int64_t>(P, 4096));
 }
 
-// Room for the results of P segments of M rows; fewer segments, down to one,
-// where memory is short.
-int seg_room(fe_ctx *c, int64_t M, int P)
+// Room for the results of P segments of M rows beside an index; fewer segments,
+// down to one, where memory is short.
+int seg_room(fe_ctx *c, const IndexPlan &p, int64_t M, int P)
 {
-    while (P > 1 && ensure(c, c->cseg, (size_t)(P * M) * sizeof(int4))) P /= 2;
+    const int64_t ix = p.ints * (int64_t)sizeof(int);
+    while (P > 1 && (!list_room(c, ix + P * M * (int64_t)sizeof(int4)) ||
+                     ensure(c, c->cseg, (size_t)(P * M) * sizeof(int4))))
+        P /= 2;
     return P;
 }
 
@@ -764,8 +802,8 @@ int chain_call(fe_ctx *c, const int *ids, const int *ticks, int64_t n, int num_t
     int rc;
     taken = false;
     const IndexPlan ip = index_plan(n, num_types, true);
-    if (ensure(c, c->cidx, (size_t)ip.ints * sizeof(int))) return FE_OK;
-    const int Pn = seg_room(c, M, chain_P(c, M, n, num_types, cin.nmax, mode == CHAIN_EXACT));
+    if (!index_room(c, ip) || ensure(c, c->cidx, (size_t)ip.ints * sizeof(int))) return FE_OK;
+    const int Pn = seg_room(c, ip, M, chain_P(c, M, n, num_types, cin.nmax, mode == CHAIN_EXACT));
     if ((rc = ensure_host(c, 4))) return rc;
     if (!c->checked)
         HIPCHK(c, hipEventCreateWithFlags(&c->checked, hipEventDisableTiming));
@@ -832,7 +870,7 @@ int chain_resume(fe_ctx *c, const int *ids, const int *ticks, int64_t n, int num
         return fail(c, status_code(bits), "%s", status_text(bits));
     }
     const IndexPlan ip = index_plan(n - lam, num_types, true);
-    if (ensure(c, c->cidx, (size_t)ip.ints * sizeof(int))) return FE_OK;
+    if (!index_room(c, ip) || ensure(c, c->cidx, (size_t)ip.ints * sizeof(int))) return FE_OK;
     taken = true;
     int *base = P<int>(c->cidx);
     {
@@ -1016,6 +1054,7 @@ extern "C" int fe_set_param(fe_ctx *c, int param, int64_t value)
     if (param == FE_PARAM_ELIMINATION && value > 2) return fail(c, FE_EINVAL, "bad parameter");
     if (param == FE_PARAM_TARGET_WAVES && value == 0) return fail(c, FE_EINVAL, "bad parameter");
     c->param[param] = value;
+    if (param == FE_PARAM_LIST_BYTES && lists_held(c) > (size_t)value) give_lists_back(c);
     return FE_OK;
 }
 
@@ -1446,7 +1485,7 @@ int mine_index(fe_ctx *c, const int *ids, const int *ticks, int64_t n, int num_t
     hipStream_t s = c->stream;
     int rc;
     mc.ip = index_plan(n, num_types, true);
-    if (ensure(c, c->cidx, (size_t)mc.ip.ints * sizeof(int))) return FE_OK;
+    if (!index_room(c, mc.ip) || ensure(c, c->cidx, (size_t)mc.ip.ints * sizeof(int))) return FE_OK;
     if ((rc = ensure_host(c, 4))) return rc;
     const size_t tyb = (size_t)num_types * sizeof(TypeIdx);
     if ((rc = ensure_pin(c, tyb / sizeof(int)))) return rc;
@@ -1470,6 +1509,29 @@ int mine_index(fe_ctx *c, const int *ids, const int *ticks, int64_t n, int num_t
     return FE_OK;
 }
 
+// Gives the pairs' entries and masks back; the levels left are counted row by
+// row.
+void drop_lists(fe_ctx *c, MineChains &mc)
+{
+    give_lists_back(c);
+    mc.fits = false;
+    for (int k = 0; k < 2; ++k) mc.pairs[k] = mc.masks[k] = false;
+}
+
+// A buffer that a level cannot do without, if need be in the lists' place.
+int level_room(fe_ctx *c, MineChains &mc, Buf &b, size_t bytes)
+{
+    if (mc.fits && !list_room(c, mc.ip.ints * (int64_t)sizeof(int) +
+                                     (int64_t)(bytes + lists_held(c))))
+        drop_lists(c, mc);
+    int rc = ensure(c, b, bytes);
+    if (rc == FE_ENOMEM && mc.fits) {
+        drop_lists(c, mc);
+        rc = ensure(c, b, bytes);
+    }
+    return rc;
+}
+
 // The interval set (also sorted) and the frequent types' ranks on the device,
 // and whether the miner may keep pairs' entries and masks (16 GiB of lists and
 // 2 GiB of masks a counter at most).
@@ -1483,8 +1545,11 @@ int mine_setup(fe_ctx *c, MineChains &mc, const std::vector<int> &F1, const std:
     mc.n_pairs = (int64_t)nF * nF * n_iv;
     mc.sd_ints = (int64_t)nF * n_iv * places;
     mc.mask_bytes = (size_t)(places * Q) * sizeof(uint2);
+    const int64_t lists = 2 * (int64_t)(mc.mask_bytes + (3 * mc.sd_ints + mc.n_pairs) * sizeof(int));
     mc.fits = places * Q <= ((int64_t)1 << 28) && 2 * Q <= 65535 &&
-              mc.sd_ints <= ((int64_t)1 << 32) / 3 && mc.n_pairs < ((int64_t)1 << 31);
+              mc.sd_ints <= ((int64_t)1 << 32) / 3 && mc.n_pairs < ((int64_t)1 << 31) &&
+              list_room(c, mc.ip.ints * (int64_t)sizeof(int) + lists);
+    if (!mc.fits) drop_lists(c, mc);  // (an earlier run's)
     std::vector<int> h(5 * n_iv + num_types + nF, 0);
     if ((rc = ensure(c, c->sivl, h.size() * sizeof(int)))) return rc;
     std::copy(ilo.begin(), ilo.end(), h.begin());
@@ -1596,8 +1661,8 @@ int mine_siblings(fe_ctx *c, MineChains &mc, bool rel, int level, const int *F,
 int chain_rows(fe_ctx *c, const MineChains &mc, const Rows &rows, int num_types, ChainMode mode,
                int theta, int *up, int *ex, const char *name)
 {
-    const int Pn = seg_room(c, rows.M, chain_P(c, rows.M, mc.ip.n, num_types, rows.N,
-                                               mode == CHAIN_EXACT));
+    const int Pn = seg_room(c, mc.ip, rows.M, chain_P(c, rows.M, mc.ip.n, num_types, rows.N,
+                                                      mode == CHAIN_EXACT));
     ChainJob j{};
     j.ix = mc.ix;
     j.rows = rows;
@@ -1615,7 +1680,7 @@ int chain_rows(fe_ctx *c, const MineChains &mc, const Rows &rows, int num_types,
 }
 
 // sample_survival by chains.
-int sample_chains(fe_ctx *c, const MineChains &mc, int num_types, int level, int64_t M, int theta,
+int sample_chains(fe_ctx *c, MineChains &mc, int num_types, int level, int64_t M, int theta,
                   int64_t &ns, int64_t &nk)
 {
     int rc;
@@ -1624,8 +1689,8 @@ int sample_chains(fe_ctx *c, const MineChains &mc, int num_types, int level, int
     ns = sample_count(M);
     nk = 0;
     if (ns <= 0) return FE_OK;
-    if ((rc = ensure(c, c->skey, (size_t)ns * wk * sizeof(int)))) return rc;
-    if ((rc = ensure(c, c->sup, (size_t)ns * sizeof(int)))) return rc;
+    if ((rc = level_room(c, mc, c->skey, (size_t)ns * wk * sizeof(int)))) return rc;
+    if ((rc = level_room(c, mc, c->sup, (size_t)ns * sizeof(int)))) return rc;
     launch_sample_keys(P<int>(c->mkey), wk, M, P<int>(c->skey), s);
     if ((rc = chain_rows(c, mc, key_rows(P<int>(c->skey), level, ns), num_types, CHAIN_RELAXED,
                          theta, P<int>(c->sup), P<int>(c->sup), "sample_relaxed_chain")))
@@ -1895,6 +1960,11 @@ int mine_levels(fe_ctx *c, MineChains &mc, int64_t n, int num_types, int theta, 
     const int64_t nF = (int64_t)F1.size();
     if (max_level < 2 || nF == 0 || n_iv == 0) return FE_OK;
     if ((rc = mine_setup(c, mc, F1, ilo, ihi, num_types))) return rc;
+    struct Using {
+        fe_ctx *c;
+        ~Using() { c->mining = false; }
+    } in_use{c};
+    c->mining = true;
     const int64_t emode = c->param[FE_PARAM_ELIMINATION];
     const double r1 = (double)c->param[FE_PARAM_PASS1_COST] / 1000.0;
     const bool keep = c->param[FE_PARAM_KEEP_CANDIDATES] != 0;
@@ -1926,6 +1996,7 @@ int mine_levels(fe_ctx *c, MineChains &mc, int64_t n, int num_types, int theta, 
         }
         return FE_OK;
     };
+    auto room = [&](Buf &b, size_t bytes) { return level_room(c, mc, b, bytes); };
     int64_t cnt = 0;  // frequent episodes of the level before, their keys in mfk
     for (int level = 2; level <= max_level; ++level) {
         const double t_gen = now_ms();
@@ -1933,8 +2004,8 @@ int mine_levels(fe_ctx *c, MineChains &mc, int64_t n, int num_types, int theta, 
         int64_t M = nF * nF * n_iv;
         int64_t *first = nullptr, *off = nullptr;
         if (level > 2) {
-            if ((rc = ensure(c, c->mfo, (size_t)(2 * (cnt + 1) + 1) * sizeof(int64_t))) ||
-                (rc = ensure(c, c->tscr, (size_t)join_plan_ints(cnt) * sizeof(int))))
+            if ((rc = room(c->mfo, (size_t)(2 * (cnt + 1) + 1) * sizeof(int64_t))) ||
+                (rc = room(c->tscr, (size_t)join_plan_ints(cnt) * sizeof(int))))
                 return rc;
             first = (int64_t *)c->mfo.p;
             off = first + cnt + 1;
@@ -1949,11 +2020,12 @@ int mine_levels(fe_ctx *c, MineChains &mc, int64_t n, int num_types, int theta, 
         if (M >= (int64_t)1 << 31 || M * level >= (int64_t)1 << 31)
             return fail(c, FE_ENOMEM, "level %d has too many candidates (%zu)", level, (size_t)M);
         const double t0 = now_ms();
-        if ((rc = ensure(c, c->mup, 2 * M * sizeof(int))) ||
-            (rc = ensure(c, c->mex, 2 * M * sizeof(int))) ||
-            (rc = ensure(c, c->msel, M * sizeof(int))) ||
-            (rc = ensure(c, c->mn, 4 * sizeof(int))) ||
-            (rc = ensure(c, c->tscr, (size_t)pick_scratch_ints(M) * sizeof(int))))
+        if ((rc = room(c->mup, 2 * M * sizeof(int))) || (rc = room(c->mex, 2 * M * sizeof(int))) ||
+            (rc = room(c->msel, M * sizeof(int))) || (rc = room(c->mn, 4 * sizeof(int))) ||
+            (rc = room(c->tscr, (size_t)pick_scratch_ints(M) * sizeof(int))))
+            return rc;
+        if (level > 2 && mc.pairs[0] &&
+            (rc = room(c->sord, (size_t)order_ints(cnt, num_types) * sizeof(int))))
             return rc;
         int *up = P<int>(c->mup), *ex = P<int>(c->mex);
         const bool large = emode == 2 && M >= c->param[FE_PARAM_SAMPLE_MIN];
@@ -1965,11 +2037,11 @@ int mine_levels(fe_ctx *c, MineChains &mc, int64_t n, int num_types, int theta, 
         if (level > 2 && relaxed && mc.pairs[0] && !mc.pairs[1] &&
             (rc = mine_pairs(c, mc, true, theta, nullptr, nullptr)))
             return rc;
-        const bool sib = level > 2 && mc.pairs[0] && (!relaxed || mc.pairs[1]);
+        auto sib = [&]() { return level > 2 && mc.pairs[0] && (!relaxed || mc.pairs[1]); };
         // keys are written out only when something asks for them
         auto write_keys = [&]() -> int {
             int rc;
-            if ((rc = ensure(c, c->mkey, (size_t)M * wk * sizeof(int)))) return rc;
+            if ((rc = room(c->mkey, (size_t)M * wk * sizeof(int)))) return rc;
             if (level == 2)
                 launch_pair_keys(mc.F1, (int)nF, mc.ivlo, mc.ivhi, n_iv, nullptr, M,
                                  P<int>(c->mkey), s);
@@ -1977,7 +2049,8 @@ int mine_levels(fe_ctx *c, MineChains &mc, int64_t n, int num_types, int theta, 
                 launch_join(P<int>(c->mfk), wf, first, off, cnt, M, P<int>(c->mkey), s);
             return FE_OK;
         };
-        bool keys = keep || sample || (level > 2 && !sib);
+        // (room for them may cost the lists, from which a level is counted without)
+        const bool keys = keep || sample || (level > 2 && !sib());
         if (keys && (rc = write_keys())) return rc;
         LevelOut Lv;
         Lv.level = level;
@@ -1990,9 +2063,7 @@ int mine_levels(fe_ctx *c, MineChains &mc, int64_t n, int num_types, int theta, 
             elim = (double)Lv.sample_kept < (1.0 - r1) * (double)Lv.sample_n;
         }
         bool done = false;
-        if (sib) {
-            if ((rc = ensure(c, c->sord, (size_t)order_ints(cnt, num_types) * sizeof(int))))
-                return rc;
+        if (sib()) {
             launch_order(P<int>(c->mfk), wf, cnt, num_types, P<int>(c->sord), s);
             if (elim && (rc = mine_siblings(c, mc, true, level, P<int>(c->mfk), first, off, cnt, M,
                                             num_types, theta, nullptr, up, P<int>(c->sord))))
@@ -2049,8 +2120,8 @@ int mine_levels(fe_ctx *c, MineChains &mc, int64_t n, int num_types, int theta, 
         // the frequent keys for the next level, and the set split for the host
         const size_t ints = (size_t)nf * (3 * level - 2), all = ints + (size_t)nf * (elim ? 2 : 1);
         if (nf > 0) {
-            if ((rc = ensure(c, c->mfsel, ints * sizeof(int))) ||
-                (rc = ensure(c, c->msplit, ints * sizeof(int))) || (rc = ensure_pin(c, all)))
+            if ((rc = room(c->mfsel, ints * sizeof(int))) ||
+                (rc = room(c->msplit, ints * sizeof(int))) || (rc = ensure_pin(c, all)))
                 return rc;
             if (level == 2)
                 launch_pair_keys(mc.F1, (int)nF, mc.ivlo, mc.ivhi, n_iv, P<int>(c->msel), nf,
@@ -2335,7 +2406,8 @@ int batch_chain_plan(fe_batch *b)
         ints += plan[r].ints;
         nmax = std::max(nmax, j.nmax);
     }
-    if (ensure(c, b->ixd, (size_t)ints * sizeof(int)) ||
+    if (!list_room(c, ints * (int64_t)sizeof(int)) ||
+        ensure(c, b->ixd, (size_t)ints * sizeof(int)) ||
         ensure(c, b->cjobs, chain_block_bytes(R)) || ensure(c, b->cstat, sizeof(int)))
         return FE_OK;
     std::vector<IndexJob> ij(R);
@@ -3568,7 +3640,7 @@ extern "C" int fe_server_submit(fe_server *sv, const fe_request *rq, uint64_t *t
         q->b - q->a <= CHAIN_EVENTS) {
         const int64_t f = req_chain_bytes(sv, q->b - q->a) + 2 * (int64_t)sv->M * 4;
         // (its lane's share: every lane may hold such a request)
-        if (f <= sv->cfg.hbm_budget / sv->cfg.max_inflight) {
+        if (f <= sv->cfg.hbm_budget / sv->cfg.max_inflight && list_room(c, f)) {
             q->foot = f;
             q->chain = true;
         }

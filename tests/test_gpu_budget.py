@@ -91,3 +91,54 @@ def test_segments_of_many_rows(ctx, fe):
         held = before - _free(ctx)
         banner("segments of %d rows: %.2f GiB" % (M, held / 2 ** 30))
     assert held < 2 << 30
+
+
+def _levels(ctx, fe, s, ivs, max_level, limit):
+    """(levels, kernels' names, device bytes that limit 0 gives back) under a limit."""
+    ids, ticks = ctx.stream_tensors(s["ids"], s["ticks"])
+    with fe.Context(0) as own:
+        if limit is not None:
+            own.set_param(fe.PARAM_LIST_BYTES, limit)
+        own.set_param(fe.PARAM_TIMING, 1)
+        out = own.mine(ids, ticks, s["num_types"], ivs, s["theta"], max_level)
+        names = set(own.kernel_stats())
+        own.set_param(fe.PARAM_TIMING, 0)
+        before = _free(ctx)
+        own.set_param(fe.PARAM_LIST_BYTES, 0)
+        back = _free(ctx) - before
+        # a second run with the limit lowered, and raised again
+        for lim in (0, 1 << 62):
+            own.set_param(fe.PARAM_LIST_BYTES, lim)
+            again = own.mine(ids, ticks, s["num_types"], ivs, s["theta"], max_level)
+            _same(out, again)
+    return out, names, back
+
+
+def _same(a, b):
+    assert len(a) == len(b)
+    for x, y in zip(a, b):
+        for k in ("level", "n_candidates", "n_survivors", "n_frequent", "types", "lo", "hi",
+                  "upper", "exact"):
+            assert np.array_equal(np.asarray(x[k]), np.asarray(y[k])), (x["level"], k)
+
+
+def test_mining_within_a_limit(ctx, fe):
+    # everything fits; the lists do not beside the largest level, so that they
+    # are given up on the way; only the index fits; nothing does
+    s = synth.config_mining(duration_s=30.0)
+    T, n, n_iv = s["num_types"], s["ids"].size, len(s["intervals"])
+    index = 4 * (4 * n + 40 * T) + 8 * T * (n // 512 + 1)
+    # (12 B of entries a type, interval and event, 8 B of masks an interval and event, twice)
+    lists = 2 * (12 * T + 8) * n_iv * (n + 5 * T) + 8 * T * T * n_iv
+    banner("mining within a limit: index %d lists %d" % (index, lists))
+    free, names, back = _levels(ctx, fe, s, s["intervals"], 4, None)
+    assert any("siblings_n4" in k for k in names) and back > lists // 2
+    want = {"mid": lambda k: any("pairs" in x for x in k) and any("_chain" in x for x in k)
+            and not any("siblings_n4" in x for x in k),
+            "index": lambda k: any("_chain" in x for x in k) and not any("pairs" in x for x in k),
+            "none": lambda k: not any("chain" in x or "pairs" in x or "siblings" in x for x in k)}
+    for key, limit in (("mid", index + lists + 64_000), ("index", 2 * index), ("none", 1)):
+        got, names, back = _levels(ctx, fe, s, s["intervals"], 4, limit)
+        _same(free, got)
+        assert want[key](names), (key, sorted(names))
+        assert back == 0, key
