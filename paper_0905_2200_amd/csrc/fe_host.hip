@@ -2807,6 +2807,7 @@ extern "C" int fe_batch_run(fe_batch *b)
     fe_ctx *c = b->c;
     HIPCHK(c, hipSetDevice(c->device));
     if (b->chain) {
+        KTimer kt(c, "batch_two_pass_chain", 0);
         launch_fill(P<int>(b->cstat), 0, 1, c->stream);
         launch_chain_block(b->set, b->chain_jobs, b->chain_first, b->total, b->nmax,
                            P<int>(b->cstat), c->stream);
