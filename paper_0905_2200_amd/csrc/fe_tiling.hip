@@ -531,7 +531,7 @@ __global__ void k_pair_keys(const int *__restrict__ F1, int nF, const int *__res
 __global__ void k_split_keys(const int *__restrict__ key, int m, int64_t n, int *__restrict__ out)
 {
     const int w = 3 * m - 2;
-    const int64_t t = blockIdx.x * (int64_t)TB + threadIdx.x;
+    const int64_t t = ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * TB + threadIdx.x;
     if (t >= n * w) return;
     const int64_t i = t / w;
     const int q = (int)(t - i * w), k = q / 3, r = q % 3;
@@ -635,8 +635,10 @@ void launch_split_keys(const int *key, int m, int64_t n, int *out, hipStream_t s
 {
     const int64_t t = n * (3 * m - 2);
     if (t <= 0) return;
-    hipLaunchKernelGGL(k_split_keys, dim3((unsigned)((t + TB - 1) / TB)), dim3(TB), 0, s, key, m,
-                       n, out);
+    // (a grid's dimension holds fewer than 2^32 threads)
+    const int64_t blocks = (t + TB - 1) / TB, x = blocks < (1 << 22) ? blocks : 1 << 22;
+    hipLaunchKernelGGL(k_split_keys, dim3((unsigned)x, (unsigned)((blocks + x - 1) / x)), dim3(TB),
+                       0, s, key, m, n, out);
 }
 
 void launch_join_sel(const int *F, int w, const int64_t *first, const int64_t *off, int64_t cnt,
