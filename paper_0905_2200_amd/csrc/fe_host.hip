@@ -255,6 +255,9 @@ int ensure_host(fe_ctx *c, size_t ints)
     return FE_OK;
 }
 
+// Pinned memory a context keeps at most, in ints (a quarter more as room to grow).
+constexpr size_t PIN_INTS = (size_t)64 << 20;
+
 int ensure_pin(fe_ctx *c, size_t ints)
 {
     if (c->pin_cap >= ints) return FE_OK;
@@ -1974,27 +1977,29 @@ int mine_levels(fe_ctx *c, MineChains &mc, int64_t n, int num_types, int theta, 
     // the level whose frequent set is on its way to pinned memory
     int64_t late_n = 0;
     bool late_up = false, late = false;
-    auto finish = [&]() -> int {
-        if (!late) return FE_OK;
-        late = false;
-        LevelOut &L = levels.back();
-        const size_t m = L.level, f = (size_t)late_n;
+    // a level's arrays (types, lo, hi, exact and, if there is one, upper), f
+    // rows each, allocated and given to copy(to, array, ints)
+    auto arrays = [&](LevelOut &L, size_t f, bool has_up, auto copy) -> int {
+        const size_t m = L.level;
         const size_t len[5] = {f * m, f * (m - 1), f * (m - 1), f, f};
-        const int *src = c->pin;
         for (int k = 0; k < 5; ++k) {
-            // (types, lo, hi, exact, then upper if there is one)
             const int q = k == 3 ? 4 : k == 4 ? 3 : k;
             int *d = (int *)std::malloc(std::max<size_t>(len[k], 1) * sizeof(int));
             if (!d) return fail(c, FE_ENOMEM, "host allocation failed");
             L.raw[q] = d;
-            if (k == 4 && !late_up) {
-                std::fill(d, d + f, -1);
-            } else if (len[k]) {
-                std::memcpy(d, src, len[k] * sizeof(int));
-                src += len[k];
-            }
+            if (k == 4 && !has_up) std::fill(d, d + f, -1);
+            else if (len[k]) copy(d, k, len[k]);
         }
         return FE_OK;
+    };
+    auto finish = [&]() -> int {
+        if (!late) return FE_OK;
+        late = false;
+        const int *src = c->pin;
+        return arrays(levels.back(), (size_t)late_n, late_up, [&](int *d, int, size_t len) {
+            std::memcpy(d, src, len * sizeof(int));
+            src += len;
+        });
     };
     auto room = [&](Buf &b, size_t bytes) { return level_room(c, mc, b, bytes); };
     int64_t cnt = 0;  // frequent episodes of the level before, their keys in mfk
@@ -2119,10 +2124,13 @@ int mine_levels(fe_ctx *c, MineChains &mc, int64_t n, int num_types, int theta, 
         }
         // the frequent keys for the next level, and the set split for the host
         const size_t ints = (size_t)nf * (3 * level - 2), all = ints + (size_t)nf * (elim ? 2 : 1);
+        bool staged = true;
         if (nf > 0) {
             if ((rc = room(c->mfsel, ints * sizeof(int))) ||
-                (rc = room(c->msplit, ints * sizeof(int))) || (rc = ensure_pin(c, all)))
+                (rc = room(c->msplit, ints * sizeof(int))))
                 return rc;
+            // (sets beyond the pinned memory that is kept are copied at once)
+            staged = all <= PIN_INTS && ensure_pin(c, all) == FE_OK;
             if (level == 2)
                 launch_pair_keys(mc.F1, (int)nF, mc.ivlo, mc.ivhi, n_iv, P<int>(c->msel), nf,
                                  P<int>(c->mfsel), s);
@@ -2131,13 +2139,28 @@ int mine_levels(fe_ctx *c, MineChains &mc, int64_t n, int num_types, int theta, 
                                 P<int>(c->mfsel), s);
             launch_split_keys(P<int>(c->mfsel), level, nf, P<int>(c->msplit), s);
             HIPCHK(c, hipGetLastError());
-            HIPCHK(c, hipMemcpyAsync(c->pin, c->msplit.p, ints * sizeof(int),
-                                     hipMemcpyDeviceToHost, s));
-            HIPCHK(c, hipMemcpyAsync(c->pin + ints, fex, nf * sizeof(int), hipMemcpyDeviceToHost,
-                                     s));
-            if (elim)
-                HIPCHK(c, hipMemcpyAsync(c->pin + ints + nf, fup, nf * sizeof(int),
+            if (staged) {
+                HIPCHK(c, hipMemcpyAsync(c->pin, c->msplit.p, ints * sizeof(int),
                                          hipMemcpyDeviceToHost, s));
+                HIPCHK(c, hipMemcpyAsync(c->pin + ints, fex, nf * sizeof(int),
+                                         hipMemcpyDeviceToHost, s));
+                if (elim)
+                    HIPCHK(c, hipMemcpyAsync(c->pin + ints + nf, fup, nf * sizeof(int),
+                                             hipMemcpyDeviceToHost, s));
+            } else {
+                const int *src = P<int>(c->msplit);
+                hipError_t err = hipSuccess;
+                rc = arrays(Lv, (size_t)nf, elim, [&](int *d, int k, size_t len) {
+                    const hipError_t e = hipMemcpyAsync(d, k == 3 ? fex : k == 4 ? fup : src,
+                                                        len * sizeof(int), hipMemcpyDeviceToHost, s);
+                    if (k < 3) src += len;
+                    if (err == hipSuccess) err = e;
+                });
+                const hipError_t e = hipStreamSynchronize(s);
+                if (rc) return rc;
+                HIPCHK(c, err);
+                HIPCHK(c, e);
+            }
             std::swap(c->mfk, c->mfsel);
         }
         Lv.gen_ms = t0 - t_gen;
@@ -2145,7 +2168,7 @@ int mine_levels(fe_ctx *c, MineChains &mc, int64_t n, int num_types, int theta, 
         levels.push_back(std::move(Lv));
         late_n = nf;
         late_up = elim;
-        late = true;
+        late = staged;
         cnt = nf;
         if (nf == 0) break;
     }

@@ -142,3 +142,24 @@ def test_mining_within_a_limit(ctx, fe):
         _same(free, got)
         assert want[key](names), (key, sorted(names))
         assert back == 0, key
+
+
+def test_frequent_sets_beyond_the_pinned_memory(ctx, fe):
+    # nearly every pair of 2000 types with three intervals is frequent: 7e7 ints, copied
+    # without the pinned staging; the same set from the event-by-event kernels
+    rng = np.random.default_rng(3)
+    T, n = 2000, 200_000
+    ids, ticks = ctx.stream_tensors(rng.integers(0, T, n).astype(np.int32),
+                                    np.sort(rng.integers(0, n // 5, n)).astype(np.int32))
+    with fe.Context(0) as own:
+        a = own.mine(ids, ticks, T, IVS, 1, 2)
+        own.set_param(fe.PARAM_ELIMINATION, 0)
+        b = own.mine(ids, ticks, T, IVS, 1, 2)
+        own.set_param(fe.PARAM_LIST_BYTES, 0)
+        c = own.mine(ids, ticks, T, IVS, 1, 2)
+    nf = a[1]["n_frequent"]
+    banner("frequent pairs: %d" % nf)
+    assert nf * 6 > 64 << 20
+    for k in ("types", "lo", "hi", "exact"):
+        assert np.array_equal(a[1][k], b[1][k]) and np.array_equal(a[1][k], c[1][k]), k
+    assert (b[1]["upper"] == -1).all()
