@@ -114,10 +114,13 @@ typedef enum fe_param {
     FE_PARAM_CROSSOVER_B = 7, /* counter: a group of tiles >= A/N + B tiles of
                                 N-node candidates is counted whole-stream
                                 (P = 1), a smaller one by MapConcatenate with
-                                P >= 2 (over per-type lists: a call's M
-                                candidates as M/64 tiles of nmax nodes).
+                                P >= 2.  Over per-type lists only values
+                                that were set count, a call's M candidates as
+                                M/64 tiles of nmax nodes: their segments are
+                                by default for the caches, whatever M.
                                 Defaults 8472 and 13112 (A may be
                                 negative): the least-squares fit to crossovers
+                                of the event-by-event kernels
                                 measured on a 256-CU MI355X (python -m
                                 paper_0905_2200_amd.crossover).  Ignored when
                                 FE_PARAM_SEGMENTS > 0.                        */

@@ -104,14 +104,15 @@ double now_ms()
 }  // namespace
 
 constexpr int NPARAM = 17;
+constexpr int64_t DEFAULTS[NPARAM] = {0, 16384, 1024, 1, 0, 1, 8472, 13112, 2, 0, 0, 9699, 6165,
+                                      1000, 131072, 1, INT64_MAX};
 
 struct fe_ctx {
     int device = 0;
     hipStream_t stream = nullptr;
     bool own_stream = false;
     std::string err;
-    int64_t param[NPARAM] = {0, 16384, 1024, 1, 0, 1, 8472, 13112, 2, 0, 0, 9699, 6165, 1000,
-                             131072, 1, INT64_MAX};
+    int64_t param[NPARAM];
     fe_stats stats{};
     // workspace
     Buf keys, hist, wmax, pk, orig, tileW, lam, tbl, flags, sel, nsel, status, small, cmask;
@@ -146,6 +147,7 @@ struct fe_ctx {
     std::vector<Pending> pending;
     std::vector<hipEvent_t> event_pool;
     std::map<std::string, Agg> kstats;
+    fe_ctx() { std::copy(DEFAULTS, DEFAULTS + NPARAM, param); }
 };
 
 namespace {
@@ -715,17 +717,19 @@ bool index_room(const fe_ctx *c, const IndexPlan &p)
     return list_room(c, p.ints * (int64_t)sizeof(int));
 }
 
-// Segments per candidate: one from the hybrid rule's crossover on (choose_P);
-// below it as many as the target number of waves has room for, or as make a
-// segment's share of all lists (12 B an event: tick and bucket table) fit in
-// one XCD's 4 MiB L2 -- the waves of one segment run together, over the same
-// stretch of time of every list -- with at least 512 events of a list of
-// average length in each.  Milliseconds a call with one / these, exact and
-// relaxed, 3-node rows: 1e6 events of 64 types, 5000 rows 0.32 / 0.29 and 0.45
-// / 0.32, 1e5 rows 3.5 / 3.1 and 4.3 / 3.7; 4e6 of 256 types, 1e5 rows 4.4 /
-// 3.7 and 5.7 / 4.1.  Where the lists fit already and the rows fill the device
-// alone, two only cost: 3e5 of 200 types, 20 000 rows 0.17 / 0.19 and 0.18 /
-// 0.18, 1e5 rows 0.39 / 0.46 and 0.40 / 0.47.
+// Segments per candidate: as many as the target number of waves has room for,
+// or as make a segment's share of all lists (12 B an event: tick and bucket
+// table) fit in one XCD's 4 MiB L2 -- the waves of one segment run together,
+// over the same stretch of time of every list -- with at least 512 events of a
+// list of average length in each.  The number of rows does not come into it: ms
+// a call with one / these, exact and relaxed, 1e6 events of 64 types, 3 nodes,
+// 5000 rows 0.32 / 0.29 and 0.45 / 0.32, 1.2e6 rows 49 / 30 and 61 / 38; 8 nodes,
+// 1.2e6 rows 53 / 45 and 78 / 71; 4e6 of 256 types, 3 nodes, 6.2e5 rows 35 / 19
+// and 42 / 22; 1e7 of 256 types, 8 nodes, 1.2e6 rows 151 / 134 and 184 / 164.
+// Where the lists fit already and the rows fill the device alone, two only
+// cost: 3e5 of 200 types, 20 000 rows 0.17 / 0.19 and 0.18 / 0.18, 1e5 rows 0.39 /
+// 0.46 and 0.40 / 0.47.  A crossover that the program has set stands (choose_P);
+// the default is the event-by-event kernels'.
 constexpr int64_t SEG_RESULTS = (int64_t)1 << 26;  // segments' results kept (1 GiB)
 int chain_P(const fe_ctx *c, int64_t M, int64_t n, int num_types, int nmax, bool exact)
 {
@@ -733,7 +737,8 @@ int chain_P(const fe_ctx *c, int64_t M, int64_t n, int num_types, int nmax, bool
     const int pa = exact ? FE_PARAM_CROSSOVER_A : FE_PARAM_CROSSOVER_A_RELAXED;
     const int pb = exact ? FE_PARAM_CROSSOVER_B : FE_PARAM_CROSSOVER_B_RELAXED;
     const double cross = (double)c->param[pa] / std::max(nmax, 1) + (double)c->param[pb];
-    if ((double)tiles >= cross) return 1;
+    const bool set = c->param[pa] != DEFAULTS[pa] || c->param[pb] != DEFAULTS[pb];
+    if (set && (double)tiles >= cross) return 1;
     int64_t P = c->param[FE_PARAM_TARGET_WAVES] / M;
     P = std::max<int64_t>(P, 12 * n / ((int64_t)3 << 20));
     P = std::min<int64_t>(P, n / ((int64_t)512 * num_types));

@@ -424,3 +424,24 @@ def test_batch_of_2_to_24_lists(ctx, fe):
     assert (t.stack(b.upper) == t.stack(b.upper)[0]).all().item()
     assert (t.stack(b.exact) == t.stack(b.exact)[0]).all().item()
     b.close()
+
+
+def test_segments_whatever_the_rows(ctx, fe):
+    # tables beyond the event-by-event kernels' whole-stream line keep their segments
+    rng = np.random.default_rng(43)
+    T, n, M, N = 64, 1_000_000, 1_050_000, 3
+    ids_h = rng.integers(0, T, n).astype(np.int32)
+    ticks_h = np.sort(rng.integers(0, 8 * n, n)).astype(np.int32)
+    iv = rng.integers(0, len(IVS), (M, N - 1))
+    lo, hi = np.array(IVS, np.int32).T
+    cand = {"types": rng.integers(0, T, (M, N)).astype(np.int32), "len": np.full(M, N, np.int32),
+            "lo": lo[iv], "hi": hi[iv]}
+    some = rng.choice(M, 40, replace=False)
+    few = dict({k: v[some] for k, v in cand.items()}, M=40, nmax=N)
+    ids, ticks = ctx.stream_tensors(ids_h, ticks_h)
+    cd = ctx.cand_tensors(cand)
+    banner("segments of %d rows" % M)
+    for mode in (EXACT, RELAXED):
+        got = ctx.count(ids, ticks, T, cd, mode).cpu().numpy()
+        assert ctx.stats()["segments_max"] >= 2, mode
+        assert np.array_equal(got[some], oracle_counts(ids_h, ticks_h, T, few, mode)), mode
