@@ -445,3 +445,53 @@ def test_segments_whatever_the_rows(ctx, fe):
         got = ctx.count(ids, ticks, T, cd, mode).cpu().numpy()
         assert ctx.stats()["segments_max"] >= 2, mode
         assert np.array_equal(got[some], oracle_counts(ids_h, ticks_h, T, few, mode)), mode
+
+
+@pytest.mark.parametrize("T,n", [(4096, 300_000), (1000, 1_000_000), (600, 250_000), (600, 200_000)])
+def test_long_streams_of_many_types_in_a_batch(ctx, fe, T, n):
+    # (the last two on both sides of chunks of 4096 events)
+    rng = np.random.default_rng(T)
+    recs, want = [], []
+    for k in range(2):
+        ids_h = rng.integers(0, T, n + k).astype(np.int32)
+        ticks_h = np.sort(rng.integers(0, n, n + k)).astype(np.int32)
+        cand = synth.pack(synth.random_episodes(rng, 60, T, 3, [(0, 50), (50, 2000)], n_min=1))
+        ids, ticks = ctx.stream_tensors(ids_h, ticks_h)
+        recs.append({"ids": ids, "ticks": ticks, "num_types": T, "cand": ctx.cand_tensors(cand),
+                     "theta": 3})
+        want.append(oracle.two_pass(ids_h, ticks_h, T, cand["types"], cand["len"], cand["lo"],
+                                    cand["hi"], 3, projection=True))
+    banner("long streams of %d types in a batch" % T)
+    b = fe.Batch(ctx, recs)
+    b.run()
+    ctx.sync()
+    for r, (wu, we) in enumerate(want):
+        assert np.array_equal(b.upper[r].cpu().numpy(), wu)
+        assert np.array_equal(b.exact[r].cpu().numpy(), we)
+    b.close()
+
+
+def test_many_types_cost_in_a_batch(ctx, fe):
+    # a batch of one takes no longer than twice the same call alone
+    import time
+    rng = np.random.default_rng(2)
+    T, n = 4096, 1_000_000
+    ids, ticks = ctx.stream_tensors(rng.integers(0, T, n).astype(np.int32),
+                                    np.sort(rng.integers(0, n, n)).astype(np.int32))
+    cand = ctx.cand_tensors(synth.pack(synth.random_episodes(rng, 64, T, 2, [(0, 50)], n_min=2)))
+    b = fe.Batch(ctx, [{"ids": ids, "ticks": ticks, "num_types": T, "cand": cand, "theta": 5}])
+
+    def best(call):
+        t = []
+        for _ in range(6):
+            ctx.torch.cuda.synchronize()
+            a = time.perf_counter()
+            call()
+            ctx.torch.cuda.synchronize()
+            t.append(time.perf_counter() - a)
+        return min(t)
+    lone = best(lambda: ctx.count_two_pass(ids, ticks, T, cand, 5))
+    both = best(b.run)
+    banner("4096 types: alone %.0f us, batch %.0f us" % (lone * 1e6, both * 1e6))
+    b.close()
+    assert both < 2 * lone
