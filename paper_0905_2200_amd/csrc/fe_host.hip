@@ -9,6 +9,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cmath>
 #include <chrono>
 #include <cstdarg>
 #include <cstdio>
@@ -800,6 +801,60 @@ int wait_checks(fe_ctx *c)
     return FE_OK;
 }
 
+// Relaxed counts of many episodes over one to four types: the lists are then
+// the stream itself or nearly, a wave each walks them for every row, and where
+// most events have followers it walks them again for every hop, while the
+// event-by-event kernels read the stream once for 64 rows.  f: the events of a
+// type within a hop of the widest row.  Lists / event by event, ms, 20 000 rows over 2e5
+// events, by type and rate in ticks of 0.1 ms, hops of up to 320 ticks:
+//   1 type     20 Hz, 5 nodes 25 / 4.8;  100 Hz, 2 nodes 16 / 11, 8 nodes 123 / 52;
+//              1 kHz, 2 nodes 39 / 14, 8 nodes 209 / 39
+//   2 types    20 Hz, 5 nodes 10 / 3.3;  100 Hz, 5 nodes 41 / 54, 8 nodes 67 / 62;
+//              300 Hz, 3 nodes 28 / 57, 5 nodes 66 / 39;  1 kHz, 8 nodes 129 / 39
+//   4 types    20 Hz, 5 nodes 4.5 / 3.3;  100 Hz, 8 nodes 34 / 63;  300 Hz, 5 nodes
+//              34 / 39, 8 nodes 64 / 39;  1 kHz, 3 nodes 14 / 15, 8 nodes 69 / 39
+//   8 types    20 Hz, 5 nodes 2.2 / 2.5;  1 kHz, 8 nodes 35 / 39
+// (exact, the lists take a tenth or less of the others' time everywhere.)  At
+// 2000 rows the few rows' segments fill the device: 1 type 20 Hz, 5 nodes 2.9 /
+// 1.0, 100 Hz 8.6 / 27, 1 kHz 51 / 22; 2 types 20 Hz 1.2 / 0.72, 1 kHz 22 / 22.
+constexpr int FEW_TYPES = 4;
+constexpr int FEW_TYPES_ROWS = 1024, MANY_ROWS = 8192;
+bool event_by_event(int T, int M, int nmax, double f)
+{
+    const double hops = nmax - 1;
+    if (M < MANY_ROWS) return (T <= 2 && f < 1.0) || (T == 1 && f >= 16.0 && nmax > 2);
+    return T == 1 || f < 1.0 || f * hops * std::sqrt(hops) >= 18.0 * T;
+}
+
+// Decides that for a call whose stream and table it checks (both synchronise;
+// such calls take milliseconds).  si: the stream's, for the other kernels.
+int few_types_rule(fe_ctx *c, const int *ids, const int *ticks, int n, int num_types,
+                   const CandIn &cin, int M, StreamInfo &si, bool &events)
+{
+    int rc;
+    hipStream_t s = c->stream;
+    events = false;
+    if ((rc = stream_info(c, ids, ticks, n, num_types, si))) return rc;
+    if ((rc = ensure(c, c->small, sizeof(int)))) return rc;
+    IndexSet none;
+    none.njobs = 0;
+    launch_fill(P<int>(c->small), 0, 1, s);
+    launch_index_check(none, table_rows(cin, M), cin.nmax, num_types, P<int>(c->status),
+                       P<int>(c->small), s);
+    HIPCHK(c, hipGetLastError());
+    HIPCHK(c, hipMemcpyAsync(c->host, c->small.p, sizeof(int), hipMemcpyDeviceToHost, s));
+    HIPCHK(c, hipMemcpyAsync(c->host + 1, c->status.p, sizeof(int), hipMemcpyDeviceToHost, s));
+    HIPCHK(c, hipStreamSynchronize(s));
+    const int W = c->host[0], bits = c->host[1];
+    if (bits) {
+        launch_fill(P<int>(c->status), 0, 1, s);
+        return fail(c, status_code(bits), "%s", status_text(bits));
+    }
+    const double hop = (double)W / (cin.nmax - 1);
+    events = event_by_event(num_types, M, cin.nmax, hop * n / ((double)si.span * num_types));
+    return FE_OK;
+}
+
 // One call's counting by chains; taken = false (nothing enqueued) when its
 // workspace cannot be had.
 int chain_call(fe_ctx *c, const int *ids, const int *ticks, int64_t n, int num_types,
@@ -1137,14 +1192,18 @@ extern "C" int fe_count(fe_ctx *c, const int32_t *ids, const int32_t *ticks, int
     HIPCHK(c, hipSetDevice(c->device));
     c->stats = fe_stats{};
     CandIn cin{types, len, lo, hi, nmax};
-    bool taken = false;
-    if (M > 0 && chain_takes(c, n, num_types))
+    bool taken = false, events = M == 0 || !chain_takes(c, n, num_types);
+    StreamInfo si{};
+    if (!events && mode == FE_RELAXED && num_types <= FEW_TYPES && nmax > 1 &&
+        M >= FEW_TYPES_ROWS && n >= 16384 && (int64_t)M * (3 * nmax - 2) < (int64_t)1 << 30 &&
+        (rc = few_types_rule(c, ids, ticks, (int)n, num_types, cin, M, si, events)))
+        return rc;
+    if (!events)
         rc = chain_call(c, ids, ticks, n, num_types, cin, M,
                         mode == FE_EXACT ? CHAIN_EXACT : CHAIN_RELAXED, 0, counts_out, counts_out,
                         nullptr, taken);
     if (!taken) {
-        StreamInfo si;
-        if ((rc = stream_info(c, ids, ticks, (int)n, num_types, si))) return rc;
+        if (si.n == 0 && (rc = stream_info(c, ids, ticks, (int)n, num_types, si))) return rc;
         rc = count_impl(c, ids, ticks, si, num_types, cin, M, mode, counts_out);
     }
     c->stats.last_call_ms = now_ms() - t0;

@@ -495,3 +495,41 @@ def test_many_types_cost_in_a_batch(ctx, fe):
     banner("4096 types: alone %.0f us, batch %.0f us" % (lone * 1e6, both * 1e6))
     b.close()
     assert both < 2 * lone
+
+
+@pytest.mark.parametrize("T", [1, 2, 3, 4, 5])
+@pytest.mark.parametrize("rows", [1023, 1024, 8191, 8192])
+def test_relaxed_rows_over_few_types(ctx, fe, T, rows):
+    # sparse, dense and denser streams of few types on both sides of the rows' line
+    # from which some are counted event by event
+    rng = np.random.default_rng(10 * T + rows)
+    n, seen = 17_000, set()
+    eps = synth.random_episodes(rng, 60, T, 6, [(0, 150), (30, 180), (0, 90)], n_min=2)
+    cand = synth.pack(eps)
+    many = synth.pack([eps[i % len(eps)] for i in range(rows)])
+    at = np.arange(rows) % len(eps)
+    ctx.set_param(fe.PARAM_TIMING, 1)
+    try:
+        for gap in (200, 12, 1):  # mean ticks between events, times T
+            ids_h = rng.integers(0, T, n).astype(np.int32)
+            ticks_h = np.sort(rng.integers(0, max(1, gap * n // T), n)).astype(np.int32)
+            ids, ticks = ctx.stream_tensors(ids_h, ticks_h)
+            banner("relaxed rows over few types: T=%d rows=%d gap=%d" % (T, rows, gap))
+            ctx.reset_kernel_stats()
+            got = ctx.count(ids, ticks, T, many, RELAXED).cpu().numpy()
+            assert np.array_equal(got, oracle_counts(ids_h, ticks_h, T, cand, RELAXED)[at]), gap
+            seen.add("map_relaxed_chain" in ctx.kernel_stats())
+    finally:
+        ctx.set_param(fe.PARAM_TIMING, 0)
+    if T == 5 or rows < 1024:
+        assert seen == {True}
+    if rows == 8192 and T <= 4:
+        assert False in seen
+    bad = dict(many, hi=many["lo"])
+    with pytest.raises(fe.FeError) as e:
+        ctx.count(ids, ticks, T, bad, RELAXED)
+    assert e.value.code == fe.FE_EINVAL
+    with pytest.raises(fe.FeError) as e:
+        ctx.count(ids, ticks.flip(0), T, many, RELAXED)
+    assert e.value.code == fe.FE_EUNSORTED
+    assert np.array_equal(ctx.count(ids, ticks, T, many, RELAXED).cpu().numpy(), got)
