@@ -89,7 +89,7 @@ struct ChainJob {
     int *upper;  // relaxed counts
     int *exact;  // exact counts
     int P;       // segments per candidate
-    unsigned share;  // (set by the launcher: 2^32 / P, less)
+    unsigned share;  // seg_share(P) (launch_chain sets it)
     int4 *seg;   // [M][P] segment results (P > 1): completions, last one's index, first
                  // event of the first chain, count of a second run (-1: none)
     // incremental form (count_io set): the events before `from`, whose tick
@@ -98,6 +98,8 @@ struct ChainJob {
     const int *t_from;
     int from;
 };
+
+inline unsigned seg_share(int P) { return 0xffffffffu / (unsigned)P; }
 
 enum ChainMode { CHAIN_EXACT = 0, CHAIN_RELAXED = 1, CHAIN_TWO_PASS = 2 };
 
@@ -118,11 +120,13 @@ void launch_look_back(const int *ticks, int from, const int *wmax, const int *st
 // Counts every row of one job (status non-zero: nothing is written).
 void launch_chain(const ChainJob &job, ChainMode mode, int nmax, const int *status,
                   hipStream_t s);
-// Both counts of every row of several jobs (device array; P = 1), whose rows
-// are numbered first[0..njobs]: job q has rows first[q] to first[q + 1].
-// (status non-zero: every count is -1)
-void launch_chains(const ChainJob *jobs, const int64_t *first, int njobs, int64_t total, int nmax,
-                   const int *status, hipStream_t s);
+// Both counts of every row of several jobs (device array), whose rows are
+// numbered first_row[0..njobs] and segments first_item[0..njobs]: job q has rows
+// first_row[q] to first_row[q + 1] and P times as many segments.  (items == rows:
+// P = 1 throughout.  status non-zero: every count is -1)
+void launch_chains(const ChainJob *jobs, const int64_t *first_row, const int64_t *first_item,
+                   int njobs, int64_t rows, int64_t items, int nmax, const int *status,
+                   hipStream_t s);
 // *out = the number of v[0..M) that are at least theta (status non-zero: not
 // written).
 void launch_count_ge(const int *v, int M, int theta, int *out, const int *status, hipStream_t s);

@@ -766,25 +766,17 @@ __global__ __launch_bounds__(WAVE, chain_waves(EMAX)) void k_chain(ChainJob j, c
     }
 }
 
-// The same for the rows of several jobs.
-template <int MODE, int EMAX>
-__global__ __launch_bounds__(WAVE, chain_waves(EMAX)) void k_chains(const ChainJob *jobs, const int64_t *first,
-                                                 int njobs, int64_t total, const int *status)
+// Job and item of a wave among several jobs' (numbered first[0..njobs]).
+__device__ __forceinline__ ChainJob job_at(const ChainJob *jobs, const int64_t *first, int njobs,
+                                           int64_t item, int &at)
 {
-    extern __shared__ int lds[];
-    const int64_t item = grid_item();
-    if (item >= total) return;
     int lo = 0, hi = njobs;
     while (hi - lo > 1) {
         const int mid = (lo + hi) >> 1;
         if (first[mid] <= item) lo = mid;
         else hi = mid;
     }
-    if (*status) {
-        // (no caller waits for the checks of a batch's run)
-        if (__lane_id() == 0) jobs[lo].upper[item - first[lo]] = jobs[lo].exact[item - first[lo]] = -1;
-        return;
-    }
+    at = (int)(item - first[lo]);
     ChainJob j = jobs[lo];
     j.ix.et = global_ptr(j.ix.et);
     j.ix.ei = global_ptr(j.ix.ei);
@@ -796,10 +788,50 @@ __global__ __launch_bounds__(WAVE, chain_waves(EMAX)) void k_chains(const ChainJ
     j.rows.len = global_ptr(j.rows.len);
     j.upper = global_ptr(j.upper);
     j.exact = global_ptr(j.exact);
-    j.seg = nullptr;  // (P = 1, not incremental)
-    j.count_io = nullptr;
+    j.seg = global_ptr(j.seg);
+    j.count_io = nullptr;  // (not incremental)
+    return j;
+}
+
+// The same for the rows of several jobs, each a wave.
+template <int MODE, int EMAX>
+__global__ __launch_bounds__(WAVE, chain_waves(EMAX)) void k_chains(const ChainJob *jobs, const int64_t *first,
+                                                 int njobs, int64_t total, const int *status)
+{
+    extern __shared__ int lds[];
+    const int64_t item = grid_item();
+    if (item >= total) return;
+    int m;
+    ChainJob j = job_at(jobs, first, njobs, item, m);
+    if (*status) {
+        // (no caller waits for the checks of a batch's run)
+        if (__lane_id() == 0) j.upper[m] = j.exact[m] = -1;
+        return;
+    }
+    j.seg = nullptr;
     j.P = 1;
-    chain_item<MODE, EMAX>(j, (int)(item - first[lo]), 0, lds);
+    chain_item<MODE, EMAX>(j, m, 0, lds);
+}
+
+// One pass over the rows' segments, a wave each (a job's numbered segment by
+// segment): where the jobs' rows leave the device idle, and one of them is long.
+template <int MODE, int EMAX>
+__global__ __launch_bounds__(WAVE, chain_waves(EMAX)) void k_chains_cut(const ChainJob *jobs,
+                                                                        const int64_t *first, int njobs,
+                                                                        int64_t total, const int *status)
+{
+    extern __shared__ int lds[];
+    const int64_t item = grid_item();
+    if (item >= total) return;
+    int at;
+    const ChainJob j = job_at(jobs, first, njobs, item, at);
+    const int p = (int)((unsigned)at / (unsigned)j.rows.M), m = at - p * j.rows.M;
+    int *out = MODE == CHAIN_RELAXED ? j.upper : j.exact;
+    if (*status || (MODE == CHAIN_EXACT && j.upper[m] < j.theta)) {
+        if (p == 0 && __lane_id() == 0) out[m] = -1;
+        return;
+    }
+    chain_item<MODE, EMAX>(j, m, p, lds);
 }
 
 // A segment's own run, counted after no completion, stands when the first chain
@@ -841,6 +873,32 @@ __device__ __forceinline__ int run_again(const ChainJob &j, const NodeRow &row, 
 // exact, 256 segments 28 ms against 854.
 constexpr int SECOND_RUNS = 8192;  // waves that fill it
 constexpr int FEW_SEGMENTS = 4;
+// The second run that a segment's result (place `at` of j.seg, segment p) asks
+// for; r: where it starts.
+__device__ __forceinline__ bool asks_again(const ChainJob &j, int at, int p, int4 &g, int &r)
+{
+    g = j.seg[at];
+    r = -1;
+    // (behind a few segments without a completion there is hardly one that
+    // matters; k_stitch takes those that do)
+    for (int q = 1; g.x > 0 && q <= p && q <= FEW_SEGMENTS; ++q) {
+        const int4 before = j.seg[at - q];
+        if (before.x == 0) continue;
+        r = before.y;
+        break;
+    }
+    return g.x > 0 && r >= g.z;
+}
+template <bool REL>
+__device__ __forceinline__ void again_item(const ChainJob &j, int m, int p, int x, int own_r, int r,
+                                           int *lds)
+{
+    NodeRow row;
+    const int N = load_row(j.ix, j.rows, m, row);
+    const int cnt = run_again<REL>(j, row, N, p, x, own_r, lds, r);
+    if (__lane_id() == 0 && r == own_r) j.seg[(int64_t)m * j.P + p].w = cnt;
+}
+
 template <bool REL>
 __global__ __launch_bounds__(WAVE) void k_again(ChainJob j, const int *status, int log2_items)
 {
@@ -853,27 +911,29 @@ __global__ __launch_bounds__(WAVE) void k_again(ChainJob j, const int *status, i
     int4 g = make_int4(0, -1, FAR_TICK, 0);
     int r = -1;
     // (a row of the first pass alone has no segments)
-    if (lane < 1 << log2_items && at < items && (REL || !j.upper || j.upper[m] >= j.theta)) {
-        g = j.seg[at];
-        // (behind a few segments without a completion there is hardly one that
-        // matters; k_stitch takes those that do)
-        for (int q = 1; g.x > 0 && q <= p && q <= FEW_SEGMENTS; ++q) {
-            const int4 before = j.seg[at - q];
-            if (before.x == 0) continue;
-            r = before.y;
-            break;
-        }
-        again = g.x > 0 && r >= g.z;
-    }
+    if (lane < 1 << log2_items && at < items && (REL || !j.upper || j.upper[m] >= j.theta))
+        again = asks_again(j, at, p, g, r);
     for (unsigned long long todo = bal(again); todo; todo &= todo - 1) {
         const int q = (int)__builtin_ctzll(todo);
-        NodeRow row;
-        const int N = load_row(j.ix, j.rows, rdl(m, q), row);
-        const int own_r = rdl(g.y, q);
-        int rr = rdl(r, q);
-        const int cnt = run_again<REL>(j, row, N, rdl(p, q), rdl(g.x, q), own_r, lds, rr);
-        if (lane == 0 && rr == own_r) j.seg[i + q].w = cnt;
+        again_item<REL>(j, rdl(m, q), rdl(p, q), rdl(g.x, q), rdl(g.y, q), rdl(r, q), lds);
     }
+}
+// The same for several jobs, a wave a segment.
+template <bool REL>
+__global__ __launch_bounds__(WAVE) void k_agains(const ChainJob *jobs, const int64_t *first,
+                                                 int njobs, int64_t total, const int *status)
+{
+    extern __shared__ int lds[];
+    const int64_t item = grid_item();
+    if (item >= total || *status) return;
+    int at;
+    const ChainJob j = job_at(jobs, first, njobs, item, at);
+    const int m = (int)((unsigned)at / (unsigned)j.P), p = at - m * j.P;
+    if (j.P == 1 || (!REL && j.upper[m] < j.theta)) return;
+    int4 g;
+    int r;
+    if (!asks_again(j, at, p, g, r)) return;
+    again_item<REL>(j, m, p, g.x, g.y, r, lds);
 }
 
 // One wave per candidate: its segments' results in order, 64 at a time.  As
@@ -881,12 +941,8 @@ __global__ __launch_bounds__(WAVE) void k_again(ChainJob j, const int *status, i
 // stand and of the second runs that met them are only added up; a segment that
 // has neither is run again here (regular gaps, whose runs need never meet: the
 // row's second runs are then as long as its list).
-template <bool REL> __global__ __launch_bounds__(WAVE) void k_stitch(ChainJob j, const int *status)
+template <bool REL> __device__ __forceinline__ void stitch_row(const ChainJob &j, int64_t m, int *lds)
 {
-    extern __shared__ int lds[];
-    if (*status) return;
-    const int64_t m = grid_item();
-    if (m >= j.rows.M) return;
     const int lane = __lane_id();
     int *out = REL ? j.upper : j.exact;
     if (!REL && j.upper && j.upper[m] < j.theta) {
@@ -935,9 +991,29 @@ template <bool REL> __global__ __launch_bounds__(WAVE) void k_stitch(ChainJob j,
     if (lane == 0) out[m] = tot + sum;
 }
 
+template <bool REL> __global__ __launch_bounds__(WAVE) void k_stitch(ChainJob j, const int *status)
+{
+    extern __shared__ int lds[];
+    if (*status) return;
+    const int64_t m = grid_item();
+    if (m < j.rows.M) stitch_row<REL>(j, m, lds);
+}
+// (jobs' rows numbered first[0..njobs]; those in one segment are done)
+template <bool REL>
+__global__ __launch_bounds__(WAVE) void k_stitches(const ChainJob *jobs, const int64_t *first,
+                                                   int njobs, int64_t total, const int *status)
+{
+    extern __shared__ int lds[];
+    const int64_t item = grid_item();
+    if (item >= total || *status) return;
+    int m;
+    const ChainJob j = job_at(jobs, first, njobs, item, m);
+    if (j.P > 1) stitch_row<REL>(j, m, lds);
+}
+
 template <int MODE> void chain_mode(ChainJob j, int nmax, const int *status, hipStream_t s)
 {
-    j.share = 0xffffffffu / (unsigned)j.P;
+    j.share = seg_share(j.P);
     const size_t lds = (size_t)chain_lds(nmax) * sizeof(int);
     // (survivors of a first pass: a wave looks for them among several rows
     // where that leaves eight waves' worth for every place on the chip)
@@ -1011,17 +1087,45 @@ void launch_chain(const ChainJob &job, ChainMode mode, int nmax, const int *stat
     }
 }
 
-void launch_chains(const ChainJob *jobs, const int64_t *first, int njobs, int64_t total, int nmax,
-                   const int *status, hipStream_t s)
+namespace {
+template <int MODE>
+void chains_cut(const ChainJob *jobs, const int64_t *first_row, const int64_t *first_item,
+                int njobs, int64_t rows, int64_t items, int nmax, size_t lds, const int *status,
+                hipStream_t s)
 {
-    if (total <= 0) return;
-    const size_t lds = (size_t)chain_lds(nmax) * sizeof(int);
+    constexpr bool REL = MODE == CHAIN_RELAXED;
     if (nmax <= 3)
-        hipLaunchKernelGGL((k_chains<CHAIN_TWO_PASS, 1>), grid_of(total), dim3(WAVE), lds, s, jobs,
-                           first, njobs, total, status);
+        hipLaunchKernelGGL((k_chains_cut<MODE, 1>), grid_of(items), dim3(WAVE), lds, s, jobs,
+                           first_item, njobs, items, status);
     else
-        hipLaunchKernelGGL((k_chains<CHAIN_TWO_PASS, NMAX - 2>), grid_of(total), dim3(WAVE), lds, s,
-                           jobs, first, njobs, total, status);
+        hipLaunchKernelGGL((k_chains_cut<MODE, NMAX - 2>), grid_of(items), dim3(WAVE), lds, s, jobs,
+                           first_item, njobs, items, status);
+    hipLaunchKernelGGL((k_agains<REL>), grid_of(items), dim3(WAVE), lds, s, jobs, first_item, njobs,
+                       items, status);
+    hipLaunchKernelGGL((k_stitches<REL>), grid_of(rows), dim3(WAVE), lds, s, jobs, first_row, njobs,
+                       rows, status);
+}
+}  // namespace
+
+void launch_chains(const ChainJob *jobs, const int64_t *first_row, const int64_t *first_item,
+                   int njobs, int64_t rows, int64_t items, int nmax, const int *status,
+                   hipStream_t s)
+{
+    if (rows <= 0) return;
+    const size_t lds = (size_t)chain_lds(nmax) * sizeof(int);
+    if (items > rows) {
+        chains_cut<CHAIN_RELAXED>(jobs, first_row, first_item, njobs, rows, items, nmax, lds,
+                                  status, s);
+        chains_cut<CHAIN_EXACT>(jobs, first_row, first_item, njobs, rows, items, nmax, lds, status,
+                                s);
+        return;
+    }
+    if (nmax <= 3)
+        hipLaunchKernelGGL((k_chains<CHAIN_TWO_PASS, 1>), grid_of(rows), dim3(WAVE), lds, s, jobs,
+                           first_row, njobs, rows, status);
+    else
+        hipLaunchKernelGGL((k_chains<CHAIN_TWO_PASS, NMAX - 2>), grid_of(rows), dim3(WAVE), lds, s,
+                           jobs, first_row, njobs, rows, status);
 }
 
 // ------------------------------------------------------------------ siblings

@@ -2379,6 +2379,15 @@ extern "C" void fe_result_free(fe_result *r)
 
 // ====================================================================== batching
 
+// Streams indexed and counted by one set of launches (device addresses).
+struct ChainLaunch {
+    IndexSet set;
+    const ChainJob *jobs = nullptr;
+    const int64_t *first_row = nullptr, *first_item = nullptr;
+    int64_t rows = 0, items = 0;
+    int nmax = 1;
+};
+
 struct fe_batch {
     fe_ctx *c = nullptr;
     std::vector<fe_job> jobs;
@@ -2404,28 +2413,66 @@ struct fe_batch {
     // counting by chains: an index of every stream (made by each run) and
     // one job per recording
     bool chain = false;
-    Buf ixd, cjobs, cstat;  // (cstat: the checks of a run, which are its own)
-    IndexSet set;
-    const ChainJob *chain_jobs = nullptr;
-    const int64_t *chain_first = nullptr;
-    int64_t total = 0;
-    int nmax = 1;
+    Buf ixd, cjobs, csegs, cstat;  // (cstat: the checks of a run, which are its own)
+    ChainLaunch chains;
 };
 
 namespace {
 
 // Descriptors of streams indexed and counted together, as host bytes and the
-// offsets of its parts: IndexJob[R], ChainJob[R], int64_t first[R + 1].
+// offsets of its parts: IndexJob[R], ChainJob[R], int64_t first rows[R + 1],
+// first segments[R + 1].
 struct ChainBlock {
     std::vector<char> bytes;
-    size_t o_chain = 0, o_first = 0;
+    size_t o_chain = 0, o_row = 0, o_item = 0;
     IndexSet set;
-    int64_t total = 0;
+    int64_t rows = 0, items = 0;
     int nmax = 1;
+    // the launch, from the block's place on the device
+    ChainLaunch at(char *d) const
+    {
+        ChainLaunch l;
+        l.set = set;
+        l.set.jobs = (const IndexJob *)d;
+        l.jobs = (const ChainJob *)(d + o_chain);
+        l.first_row = (const int64_t *)(d + o_row);
+        l.first_item = (const int64_t *)(d + o_item);
+        l.rows = rows;
+        l.items = items;
+        l.nmax = nmax;
+        return l;
+    }
 };
 constexpr size_t chain_block_bytes(size_t R)
 {
-    return R * (sizeof(IndexJob) + sizeof(ChainJob)) + (R + 1) * sizeof(int64_t) + 16;
+    return R * (sizeof(IndexJob) + sizeof(ChainJob)) + 2 * (R + 1) * sizeof(int64_t) + 16;
+}
+
+// Segments a row of streams counted together (of `work` events a list on
+// average, M rows each): one where the rows fill the device or the lists are
+// short, else so many that each has its share of all rows' events for the target
+// number of waves, and at least 512.  Fewer than CUT are no help against the last
+// waves.  Ms a run in one segment / these / event by event, 4 nodes over streams
+// of 1e7 events of 8 types at 25 Hz: one stream of 16 rows 37 / 0.53 / 13, of 1000 rows 64 / 13 / 20,
+// four of 1000 rows 101 / 56 / 56.  Dense streams' second runs take some of it back:
+// 3e5 events of 3 types at 1 kHz, 64 rows 17 / 21 / 288, four of 1000 26 / 33 / 447.
+constexpr int CUT = 4, CUT_EVENTS = 8192;
+int64_t job_segments(const fe_ctx *c, const std::vector<int64_t> &work,
+                     const std::vector<int64_t> &M, std::vector<int> &P)
+{
+    double all = 0;
+    for (size_t r = 0; r < M.size(); ++r) all += (double)M[r] * (double)work[r];
+    const double waves = (double)std::min(c->param[FE_PARAM_TARGET_WAVES], SEG_RESULTS);
+    const double each = std::max(all / waves, 512.0);
+    P.assign(M.size(), 1);
+    int64_t results = 0;
+    for (size_t r = 0; r < M.size(); ++r) {
+        const double p = (double)work[r] / each;
+        if (M[r] == 0 || p < CUT || work[r] < CUT_EVENTS) continue;
+        P[r] = (int)std::min(p, 4096.0);
+        results += M[r] * P[r];
+    }
+    return results;
 }
 
 // ij: the streams' index jobs (first_chunk and first_type are filled in);
@@ -2434,7 +2481,7 @@ ChainBlock chain_block(std::vector<IndexJob> &ij, const std::vector<ChainJob> &c
 {
     ChainBlock b;
     const size_t R = ij.size();
-    std::vector<int64_t> first(R + 1, 0);
+    std::vector<int64_t> row(R + 1, 0), item(R + 1, 0);
     IndexSet &x = b.set;
     x.alone = false;
     x.njobs = (int)R;
@@ -2445,30 +2492,35 @@ ChainBlock chain_block(std::vector<IndexJob> &ij, const std::vector<ChainJob> &c
         x.types += ij[r].T;
         x.most_types = std::max(x.most_types, ij[r].T);
         x.parts = std::max(x.parts, index_parts(ij[r]));
-        first[r + 1] = first[r] + cj[r].rows.M;
+        row[r + 1] = row[r] + cj[r].rows.M;
+        item[r + 1] = item[r] + (int64_t)cj[r].rows.M * cj[r].P;
     }
-    b.total = first[R];
+    b.rows = row[R];
+    b.items = item[R];
     b.nmax = nmax;
     const auto al = [](size_t v) { return (v + 7) & ~(size_t)7; };
+    const size_t firsts = (R + 1) * sizeof(int64_t);
     b.o_chain = al(R * sizeof(IndexJob));
-    b.o_first = al(b.o_chain + R * sizeof(ChainJob));
-    b.bytes.resize(b.o_first + (R + 1) * sizeof(int64_t));
+    b.o_row = al(b.o_chain + R * sizeof(ChainJob));
+    b.o_item = b.o_row + firsts;
+    b.bytes.resize(b.o_item + firsts);
     if (R) {
         std::memcpy(b.bytes.data(), ij.data(), R * sizeof(IndexJob));
         std::memcpy(b.bytes.data() + b.o_chain, cj.data(), R * sizeof(ChainJob));
     }
-    std::memcpy(b.bytes.data() + b.o_first, first.data(), (R + 1) * sizeof(int64_t));
+    std::memcpy(b.bytes.data() + b.o_row, row.data(), firsts);
+    std::memcpy(b.bytes.data() + b.o_item, item.data(), firsts);
     return b;
 }
 
-void launch_chain_block(const IndexSet &set, const ChainJob *jobs, const int64_t *first,
-                        int64_t total, int nmax, int *status, hipStream_t s)
+void launch_chain_block(const ChainLaunch &l, int *status, hipStream_t s)
 {
-    if (set.njobs == 0) return;
-    launch_index_check(set, Rows{}, 1, 1, status, nullptr, s);
-    launch_index_types(set, status, nullptr, s);
-    launch_index_lists(set, status, s);
-    launch_chains(jobs, first, set.njobs, total, nmax, status, s);
+    if (l.set.njobs == 0) return;
+    launch_index_check(l.set, Rows{}, 1, 1, status, nullptr, s);
+    launch_index_types(l.set, status, nullptr, s);
+    launch_index_lists(l.set, status, s);
+    launch_chains(l.jobs, l.first_row, l.first_item, l.set.njobs, l.rows, l.items, l.nmax, status,
+                  s);
 }
 
 // Plans a batch counted by chains: checks every stream and table (one wait)
@@ -2480,11 +2532,14 @@ int batch_chain_plan(fe_batch *b)
     fe_ctx *c = b->c;
     hipStream_t s = c->stream;
     const size_t R = b->jobs.size();
+    int *status = P<int>(c->status);
     std::vector<size_t> order(R);
     for (size_t r = 0; r < R; ++r) order[r] = r;
     std::stable_sort(order.begin(), order.end(),
                      [&](size_t x, size_t y) { return b->jobs[x].n > b->jobs[y].n; });
     std::vector<IndexPlan> plan(R);
+    std::vector<int64_t> work(R), M(R);
+    std::vector<int> cut;  // segments
     int64_t ints = 0;
     int nmax = 1;
     for (size_t r = 0; r < R; ++r) {
@@ -2492,14 +2547,19 @@ int batch_chain_plan(fe_batch *b)
         plan[r] = index_plan(j.n, j.num_types, false);
         ints += plan[r].ints;
         nmax = std::max(nmax, j.nmax);
+        work[r] = j.n / j.num_types;
+        M[r] = j.M;
     }
-    if (!list_room(c, ints * (int64_t)sizeof(int)) ||
+    const int64_t segs = job_segments(c, work, M, cut);
+    if (!list_room(c, ints * (int64_t)sizeof(int) + segs * (int64_t)sizeof(int4)) ||
         ensure(c, b->ixd, (size_t)ints * sizeof(int)) ||
+        ensure(c, b->csegs, (size_t)segs * sizeof(int4)) ||
         ensure(c, b->cjobs, chain_block_bytes(R)) || ensure(c, b->cstat, sizeof(int)))
         return FE_OK;
     std::vector<IndexJob> ij(R);
     std::vector<ChainJob> cj(R);
     int *at = P<int>(b->ixd);
+    int4 *seg = P<int4>(b->csegs);
     for (size_t r = 0; r < R; ++r) {
         const fe_job &j = b->jobs[order[r]];
         ij[r] = index_job(plan[r], j.ids, j.ticks, at, 0);
@@ -2510,31 +2570,31 @@ int batch_chain_plan(fe_batch *b)
         q.theta = j.theta;
         q.upper = j.upper_out;
         q.exact = j.exact_out;
-        q.P = 1;
+        q.P = cut[r];
+        q.share = seg_share(cut[r]);
+        if (cut[r] > 1) {
+            q.seg = seg;
+            seg += M[r] * cut[r];
+        }
         at += plan[r].ints;
     }
     ChainBlock blk = chain_block(ij, cj, nmax);
     char *d = (char *)b->cjobs.p;
     HIPCHK(c, hipMemcpyAsync(d, blk.bytes.data(), blk.bytes.size(), hipMemcpyHostToDevice, s));
-    b->set = blk.set;
-    b->set.jobs = (const IndexJob *)d;
-    b->chain_jobs = (const ChainJob *)(d + blk.o_chain);
-    b->chain_first = (const int64_t *)(d + blk.o_first);
-    b->total = blk.total;
-    b->nmax = nmax;
-    if (R) launch_index_check(b->set, Rows{}, 1, 1, P<int>(c->status), nullptr, s);
+    b->chains = blk.at(d);
+    if (R) launch_index_check(b->chains.set, Rows{}, 1, 1, status, nullptr, s);
     for (size_t r = 0; r < R; ++r) {
         const fe_job &j = b->jobs[order[r]];
         IndexSet none;
         none.njobs = 0;
-        launch_index_check(none, cj[r].rows, j.nmax, j.num_types, P<int>(c->status), nullptr, s);
+        launch_index_check(none, cj[r].rows, j.nmax, j.num_types, status, nullptr, s);
     }
     HIPCHK(c, hipGetLastError());
     HIPCHK(c, hipMemcpyAsync(c->host, c->status.p, sizeof(int), hipMemcpyDeviceToHost, s));
     HIPCHK(c, hipStreamSynchronize(s));
     const int bits = c->host[0];
     if (bits) {
-        launch_fill(P<int>(c->status), 0, 1, s);
+        launch_fill(status, 0, 1, s);
         return fail(c, status_code(bits), "%s", status_text(bits));
     }
     b->chain = true;
@@ -2896,8 +2956,7 @@ extern "C" int fe_batch_run(fe_batch *b)
     if (b->chain) {
         KTimer kt(c, "batch_two_pass_chain", 0);
         launch_fill(P<int>(b->cstat), 0, 1, c->stream);
-        launch_chain_block(b->set, b->chain_jobs, b->chain_first, b->total, b->nmax,
-                           P<int>(b->cstat), c->stream);
+        launch_chain_block(b->chains, P<int>(b->cstat), c->stream);
         HIPCHK(c, hipGetLastError());
         return FE_OK;
     }
@@ -2986,7 +3045,7 @@ extern "C" int fe_batch_destroy(fe_batch *b)
     batch_free_graphs(b);
     Buf *bufs[] = {&b->pk,    &b->origd, &b->tileWd, &b->tilesd, &b->jobsd,  &b->itemsd,
                    &b->listsd, &b->lamd, &b->tbld,   &b->flagsr, &b->flagsx, &b->qctr,
-                   &b->deepd,  &b->ixd,  &b->cjobs,  &b->cstat};
+                   &b->deepd,  &b->ixd,  &b->cjobs,  &b->csegs,  &b->cstat};
     for (Buf *x : bufs)
         if (x->p) (void)hipFree(x->p);
     if (b->cap) (void)hipStreamDestroy(b->cap);
@@ -3073,6 +3132,7 @@ struct fe_server {
         bool busy = false;
         std::vector<Req *> reqs;
         Buf arena, outd, descd, jobsd;
+        Buf segd;                // segments' results of rounds counted by chains
         Buf statd;               // device status word of the lane's rounds
         Buf deepd;               // window rings of deep-class candidates
         int *hout = nullptr;     // pinned results, then the round's status word
@@ -3116,6 +3176,10 @@ int64_t req_chain_bytes(const fe_server *sv, int n)
     return (p.ints + 64) * (int64_t)sizeof(int) + (int64_t)chain_block_bytes(1);
 }
 
+// segments' results a round has room for (more are not asked for, unless
+// FE_PARAM_TARGET_WAVES is)
+constexpr int64_t ROUND_RESULTS = 1 << 16;
+
 // One round counted by chains: the windows' indexes, then every candidate of
 // every request in one launch.
 int server_launch_chain(fe_server *sv, fe_server::Lane &ln)
@@ -3124,6 +3188,14 @@ int server_launch_chain(fe_server *sv, fe_server::Lane &ln)
     const int R = (int)ln.reqs.size(), M = sv->M;
     std::vector<IndexJob> ij(R);
     std::vector<ChainJob> cj(R);
+    std::vector<int64_t> work(R), rows(R, M);
+    std::vector<int> cut;
+    for (int r = 0; r < R; ++r) {
+        const fe_server::Req *q = ln.reqs[r];
+        work[r] = (q->b - q->a) / sv->arr[q->r.array].num_types;
+    }
+    if (job_segments(c, work, rows, cut) > ROUND_RESULTS) cut.assign(R, 1);
+    int4 *seg = P<int4>(ln.segd);
     char *ar = (char *)ln.arena.p;
     size_t off = align_up(chain_block_bytes(R));
     for (int r = 0; r < R; ++r) {
@@ -3140,7 +3212,12 @@ int server_launch_chain(fe_server *sv, fe_server::Lane &ln)
         cj[r].theta = q->r.theta;
         cj[r].upper = P<int>(ln.outd) + (int64_t)r * 2 * M;
         cj[r].exact = cj[r].upper + M;
-        cj[r].P = 1;
+        cj[r].P = cut[r];
+        cj[r].share = seg_share(cut[r]);
+        if (cut[r] > 1) {
+            cj[r].seg = seg;
+            seg += (int64_t)M * cut[r];
+        }
     }
     const ChainBlock blk = chain_block(ij, cj, sv->nmax);
     if (blk.bytes.size() > ln.stage_cap) {
@@ -3154,11 +3231,7 @@ int server_launch_chain(fe_server *sv, fe_server::Lane &ln)
     if (sv->apending) HIPCHK(c, hipStreamWaitEvent(s, sv->aev, 0));
     HIPCHK(c, hipMemcpyAsync(ar, ln.hstage, blk.bytes.size(), hipMemcpyHostToDevice, s));
     launch_fill(P<int>(ln.statd), 0, 1, s);
-    IndexSet set = blk.set;
-    set.jobs = (const IndexJob *)ar;
-    launch_chain_block(set, (const ChainJob *)(ar + blk.o_chain),
-                       (const int64_t *)(ar + blk.o_first), blk.total, blk.nmax,
-                       P<int>(ln.statd), s);
+    launch_chain_block(blk.at(ar), P<int>(ln.statd), s);
     HIPCHK(c, hipMemcpyAsync(ln.hout, ln.outd.p, (size_t)R * 2 * M * sizeof(int),
                              hipMemcpyDeviceToHost, s));
     HIPCHK(c, hipMemcpyAsync(ln.hout + (size_t)R * 2 * M, ln.statd.p, sizeof(int),
@@ -3651,6 +3724,7 @@ extern "C" int fe_server_create(fe_ctx *c, const fe_server_config *cfg, const in
         if ((rc = ensure(c, L.descd, (size_t)cfg->max_round * sv->ntiles * sizeof(TileDesc))))
             return bail(rc);
         if ((rc = ensure(c, L.jobsd, (size_t)cfg->max_round * sizeof(BJob)))) return bail(rc);
+        if ((rc = ensure(c, L.segd, ROUND_RESULTS * sizeof(int4)))) return bail(rc);
         if ((rc = ensure(c, L.statd, sizeof(int)))) return bail(rc);
         if (deep_bytes > 0 && (rc = ensure(c, L.deepd, (size_t)deep_bytes))) return bail(rc);
         HIPCHK(c, hipHostMalloc((void **)&L.hout,
@@ -3831,7 +3905,7 @@ extern "C" int fe_server_destroy(fe_server *sv)
     (void)hipSetDevice(c->device);
     for (auto &L : sv->lanes) {
         if (L.s) (void)hipStreamSynchronize(L.s);
-        Buf *bs[] = {&L.arena, &L.outd, &L.descd, &L.jobsd, &L.statd, &L.deepd};
+        Buf *bs[] = {&L.arena, &L.outd, &L.descd, &L.jobsd, &L.segd, &L.statd, &L.deepd};
         for (Buf *x : bs)
             if (x->p) (void)hipFree(x->p);
         if (L.hout) (void)hipHostFree(L.hout);

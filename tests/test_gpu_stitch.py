@@ -144,3 +144,113 @@ def test_segments_cost(ctx, fe, kind, rows):
     print("cut", cut, "whole", whole, flush=True)
     for c, w in zip(cut, whole):
         assert c < 5 * w + 5e-4
+
+
+def _mixed_jobs(rng):
+    """(ids, ticks, types, rows): few rows over long lists, which are cut, beside
+    short, empty and rowless ones, which are not."""
+    out = []
+    for n, T, gap, rows in ((30_000, 2, 2, 40), (0, 3, 1, 5), (9_000, 3, 1, 7), (500, 4, 20, 60),
+                            (24_000, 2, 0, 9), (4_000, 1, 3, 3), (700, 5, 9, 0)):
+        if gap:
+            ids = rng.integers(0, T, n).astype(np.int32)
+            ticks = np.cumsum(rng.integers(0, gap + 1, n)).astype(np.int32)
+            eps = synth.random_episodes(rng, rows, T, 6, [(0, 5), (0, 60), (20, 24), (30, 90)],
+                                        n_min=1)
+        else:
+            ids, ticks = _periodic(n, T)
+            eps = _episodes(rng, T, "periodic")[:rows]
+        out.append((ids, ticks, T, synth.pack(eps, nmax=6)))
+    return out
+
+
+@pytest.mark.parametrize("nmax", [3, 6])
+def test_batch_in_segments(ctx, fe, nmax):
+    rng = np.random.default_rng(nmax)
+    jobs = []
+    for ids, ticks, T, cand in _mixed_jobs(rng):
+        keep = cand["len"] <= nmax
+        jobs.append((ids, ticks, T, {"types": cand["types"][keep, :nmax], "len": cand["len"][keep],
+                                     "lo": cand["lo"][keep, :nmax - 1],
+                                     "hi": cand["hi"][keep, :nmax - 1],
+                                     "M": int(keep.sum()), "nmax": nmax}))
+    for theta in (1, 300, 20_000):
+        recs = []
+        for ids, ticks, T, cand in jobs:
+            i, t = ctx.stream_tensors(ids, ticks)
+            recs.append({"ids": i, "ticks": t, "num_types": T, "cand": ctx.cand_tensors(cand),
+                         "theta": theta})
+        banner("batch in segments: nmax=%d theta=%d" % (nmax, theta))
+        b = fe.Batch(ctx, recs)
+        for _ in range(2):
+            b.run()
+            ctx.sync()
+            for r, (ids, ticks, T, c) in enumerate(jobs):
+                if c["M"] == 0:
+                    continue
+                wu, we = oracle.two_pass(ids, ticks, T, c["types"], c["len"], c["lo"], c["hi"],
+                                         theta, projection=True)
+                assert np.array_equal(b.upper[r].cpu().numpy(), wu), r
+                assert np.array_equal(b.exact[r].cpu().numpy(), we), r
+        recs[0]["ids"][5] = 99  # (no longer a valid recording)
+        b.run()
+        ctx.sync()
+        for r in range(len(jobs)):
+            assert (b.upper[r][:jobs[r][3]["M"]] == -1).all().item()
+            assert (b.exact[r][:jobs[r][3]["M"]] == -1).all().item()
+        b.close()
+
+
+@pytest.mark.parametrize("waves", [16384, 1 << 20])
+def test_served_in_segments(ctx, fe, waves):
+    # (more segments than a round has room for: none)
+    rng = np.random.default_rng(8)
+    ids = rng.integers(0, 3, 60_000).astype(np.int32)
+    ticks = np.cumsum(rng.integers(0, 3, 60_000)).astype(np.int32)
+    eps = synth.random_episodes(rng, 900, 3, 4, [(0, 5), (0, 60), (20, 24), (30, 90)], n_min=1)
+    cand = synth.pack(eps)
+    saved = ctx.get_param(fe.PARAM_TARGET_WAVES)
+    ctx.set_param(fe.PARAM_TARGET_WAVES, waves)
+    try:
+        sv = fe.Server(ctx, cand, [3, 3], capacity=60_000, hbm_budget=1 << 28, max_round=4)
+        for a in range(2):
+            sv.append(a, ids, ticks)
+        cuts = [(k % 2, int(ticks[k * 900]), int(ticks[59_999 - 4_000 * k])) for k in range(9)]
+        tk = [sv.submit(a, t0, t1, 40) for a, t0, t1 in cuts]
+        banner("served in segments: %d waves" % waves)
+        for (a, t0, t1), t in zip(cuts, tk):
+            res = sv.wait(t)
+            x, y = np.searchsorted(ticks, t0, "left"), np.searchsorted(ticks, t1, "left")
+            wu, we = oracle.two_pass(ids[x:y], ticks[x:y], 3, cand["types"], cand["len"],
+                                     cand["lo"], cand["hi"], 40, projection=True)
+            assert res["status"] == fe.FE_OK
+            assert np.array_equal(res["upper"], wu) and np.array_equal(res["exact"], we), (t0, t1)
+        sv.close()
+    finally:
+        ctx.set_param(fe.PARAM_TARGET_WAVES, saved)
+
+
+def test_long_batch_cost(ctx, fe):
+    # few rows over one long recording: no more than three times the call alone
+    rng = np.random.default_rng(4)
+    T, n = 8, 4_000_000
+    ids, ticks = ctx.stream_tensors(rng.integers(0, T, n).astype(np.int32),
+                                    np.sort(rng.integers(0, 50 * n, n)).astype(np.int32))
+    cand = ctx.cand_tensors(synth.pack(synth.random_episodes(
+        rng, 16, T, 2, [(0, 50), (50, 100), (100, 200)], n_min=2)))
+    b = fe.Batch(ctx, [{"ids": ids, "ticks": ticks, "num_types": T, "cand": cand, "theta": 30}])
+
+    def best(call):
+        t = []
+        for _ in range(6):
+            ctx.torch.cuda.synchronize()
+            a = time.perf_counter()
+            call()
+            ctx.torch.cuda.synchronize()
+            t.append(time.perf_counter() - a)
+        return min(t)
+    lone = best(lambda: ctx.count_two_pass(ids, ticks, T, cand, 30))
+    both = best(b.run)
+    banner("16 rows over 4e6 events: alone %.0f us, batch %.0f us" % (lone * 1e6, both * 1e6))
+    b.close()
+    assert both < 3 * lone
