@@ -324,7 +324,8 @@ typedef struct fe_result {
  * counted candidate by candidate), with 8 B an event for each interval and 64
  * types (at most 2 GiB).  The context keeps these for its next run; they are given
  * back to a level or a later call that cannot get memory, and by setting
- * FE_PARAM_LIST_BYTES below them, which bounds them.  ids, ticks:
+ * FE_PARAM_LIST_BYTES below them, which bounds them.
+ * ids, ticks:
  * device; iv_lo, iv_hi: host int32[n_iv] (the set I, in ticks).
  * *out is allocated by the library; free it with fe_result_free.
  * Synchronises. */

@@ -1601,7 +1601,7 @@ int level_room(fe_ctx *c, MineChains &mc, Buf &b, size_t bytes)
 
 // The interval set (also sorted) and the frequent types' ranks on the device,
 // and whether the miner may keep pairs' entries and masks (16 GiB of lists and
-// 2 GiB of masks a counter at most).
+// 2 GiB of masks a counter at most; memory comes at about 30 ms a GiB, once).
 int mine_setup(fe_ctx *c, MineChains &mc, const std::vector<int> &F1, const std::vector<int> &ilo,
                const std::vector<int> &ihi, int num_types)
 {
@@ -1656,9 +1656,12 @@ int mine_setup(fe_ctx *c, MineChains &mc, const std::vector<int> &F1, const std:
 // is no memory for them.
 int mine_pairs(fe_ctx *c, MineChains &mc, bool rel, int theta, const int *upper, int *out)
 {
-    if (!mc.fits || ensure(c, c->smask[rel], mc.mask_bytes) ||
-        ensure(c, c->sseed[rel], (size_t)(3 * mc.sd_ints + mc.n_pairs) * sizeof(int)))
+    if (!mc.fits) return FE_OK;
+    if (ensure(c, c->smask[rel], mc.mask_bytes) ||
+        ensure(c, c->sseed[rel], (size_t)(3 * mc.sd_ints + mc.n_pairs) * sizeof(int))) {
+        drop_lists(c, mc);
         return FE_OK;
+    }
     int *t = P<int>(c->sseed[rel]);
     mc.sd[rel] = PairLists{t, t + mc.sd_ints, t + 2 * mc.sd_ints, t + 3 * mc.sd_ints,
                            mc.ip.n + (int64_t)LIST_EXTRA * mc.ip.T};
@@ -2016,6 +2019,17 @@ int mine_events(fe_ctx *c, const int *ids, const int *ticks, const StreamInfo &s
 // The same by chains: candidates, counts and frequent sets stay on the device;
 // the host learns each level's sizes and copies its frequent set while the
 // next level is counted.
+//   The pairs' and the siblings' kernels have a wave for a pair or an episode,
+// however long its lists: about 2.6e-8 s an event of a list for both counters'
+// pairs, 1.6e-7 for relaxed and 2e-8 for exact siblings, where rows in segments
+// (chain_rows) take 4e-12 s a row, event and pass.  So a level of few candidates is
+// counted row by row, unless the lists are too short to matter; level 2 up to
+// fewer, as its entries serve the levels after it (they are made for the first
+// that wants them).  Ms a run to level 4, 25 Hz, theta 2 Hz, by a wave each / by
+// this rule / event by event: 1e6 events of 4 types 33 / 1.1 / 2.5, of 8 types 20 /
+// 2.6 / 3.8; 1e7 of 4 types 350 / 8.1 / 7.8; to level 3, 1e7 of 8 types 210 / 17 /
+// 21, 9.6e6 of 32 types (32768 candidates, over the line) 62 / 62 / 35.
+constexpr int FEW_PAIRS = 1024, FEW_ONCE = 4096, FEW_TWICE = 16384, LONG_LIST = 4096;
 int mine_levels(fe_ctx *c, MineChains &mc, int64_t n, int num_types, int theta, int max_level,
                 const std::vector<int> &ilo, const std::vector<int> &ihi,
                 std::vector<LevelOut> &levels)
@@ -2026,6 +2040,9 @@ int mine_levels(fe_ctx *c, MineChains &mc, int64_t n, int num_types, int theta, 
     const std::vector<int> F1 = levels[0].types;
     const int64_t nF = (int64_t)F1.size();
     if (max_level < 2 || nF == 0 || n_iv == 0) return FE_OK;
+    int64_t list = 0;  // events of a frequent type on average
+    for (int x : levels[0].exact) list += x;
+    list /= nF;
     if ((rc = mine_setup(c, mc, F1, ilo, ihi, num_types))) return rc;
     struct Using {
         fe_ctx *c;
@@ -2093,20 +2110,24 @@ int mine_levels(fe_ctx *c, MineChains &mc, int64_t n, int num_types, int theta, 
             (rc = room(c->msel, M * sizeof(int))) || (rc = room(c->mn, 4 * sizeof(int))) ||
             (rc = room(c->tscr, (size_t)pick_scratch_ints(M) * sizeof(int))))
             return rc;
-        if (level > 2 && mc.pairs[0] &&
-            (rc = room(c->sord, (size_t)order_ints(cnt, num_types) * sizeof(int))))
-            return rc;
-        int *up = P<int>(c->mup), *ex = P<int>(c->mex);
         const bool large = emode == 2 && M >= c->param[FE_PARAM_SAMPLE_MIN];
         // two passes pay when the relaxed pass (cost r per candidate, relative
         // to the exact one) prunes more than r of the level; with r >= 1
         // nothing can, and no sample is taken
         const bool sample = large && r1 < 1.0;
         const bool relaxed = emode != 0 && (!large || sample);  // (may run)
-        if (level > 2 && relaxed && mc.pairs[0] && !mc.pairs[1] &&
-            (rc = mine_pairs(c, mc, true, theta, nullptr, nullptr)))
+        const bool few = list >= LONG_LIST && M < (level == 2 ? FEW_PAIRS : relaxed ? FEW_TWICE : FEW_ONCE);
+        if (level > 2 && !few && mc.fits &&
+            (rc = room(c->sord, (size_t)order_ints(cnt, num_types) * sizeof(int))))
             return rc;
-        auto sib = [&]() { return level > 2 && mc.pairs[0] && (!relaxed || mc.pairs[1]); };
+        int *up = P<int>(c->mup), *ex = P<int>(c->mex);
+        if (level > 2 && !few) {
+            if (!mc.pairs[0] && (rc = mine_pairs(c, mc, false, theta, nullptr, nullptr))) return rc;
+            if (relaxed && mc.pairs[0] && !mc.pairs[1] &&
+                (rc = mine_pairs(c, mc, true, theta, nullptr, nullptr)))
+                return rc;
+        }
+        auto sib = [&]() { return level > 2 && !few && mc.pairs[0] && (!relaxed || mc.pairs[1]); };
         // keys are written out only when something asks for them
         auto write_keys = [&]() -> int {
             int rc;
@@ -2119,7 +2140,7 @@ int mine_levels(fe_ctx *c, MineChains &mc, int64_t n, int num_types, int theta, 
             return FE_OK;
         };
         // (room for them may cost the lists, from which a level is counted without)
-        const bool keys = keep || sample || (level > 2 && !sib());
+        const bool keys = keep || sample || few || (level > 2 && !sib());
         if (keys && (rc = write_keys())) return rc;
         LevelOut Lv;
         Lv.level = level;
@@ -2141,7 +2162,7 @@ int mine_levels(fe_ctx *c, MineChains &mc, int64_t n, int num_types, int theta, 
                                     num_types, theta, elim ? up : nullptr, ex, P<int>(c->sord))))
                 return rc;
             done = true;
-        } else if (level == 2) {
+        } else if (level == 2 && !few) {
             if (elim && (rc = mine_pairs(c, mc, true, theta, nullptr, up))) return rc;
             if ((!elim || mc.pairs[1]) &&
                 (rc = mine_pairs(c, mc, false, theta, elim ? up : nullptr, ex)))

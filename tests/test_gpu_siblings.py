@@ -148,3 +148,62 @@ def test_words_a_wave(ctx, fe, T, words):
             assert x[k] == y[k], (x["level"], k)
         for k in ("types", "lo", "hi", "upper", "exact"):
             assert np.array_equal(x[k], y[k]), (x["level"], k)
+
+
+@pytest.mark.parametrize("T,n,levels", [(3, 18_000, 5), (8, 40_000, 4), (8, 30_000, 4), (19, 90_000, 3)])
+@pytest.mark.parametrize("elim", [0, 1])
+def test_few_candidates_over_long_lists(ctx, fe, T, n, levels, elim):
+    # few candidates row by row (lists of 4096 events and more), from more on by
+    # siblings, whose pairs' entries are made then; the same sets event by event
+    rng = np.random.default_rng(100 * T + n)
+    ids_h, ticks_h = _stream(rng, n, T, 20, ties=0.1)
+    ivs = [(0, 50), (50, 100), (100, 200)]
+    theta = 3 * n // (T * T * 100)
+    got = {}
+    ctx.set_param(fe.PARAM_TIMING, 1)
+    try:
+        for room in (1 << 62, 0):
+            ctx.reset_kernel_stats()
+            got[room] = _mine(ctx, fe, ids_h, ticks_h, T, ivs, theta, levels,
+                              {fe.PARAM_LIST_BYTES: room, fe.PARAM_ELIMINATION: elim})
+            if room:
+                names = set(ctx.kernel_stats())
+    finally:
+        ctx.set_param(fe.PARAM_TIMING, 0)
+    banner("few candidates over long lists: T=%d n=%d %s" % (
+        T, n, [lv["n_candidates"] for lv in got[0]]))
+    a, b = got[1 << 62], got[0]
+    assert len(a) == len(b)
+    for x, y in zip(a, b):
+        for k in ("level", "n_candidates", "n_survivors", "n_frequent", "types", "lo", "hi",
+                  "upper", "exact"):
+            assert np.array_equal(np.asarray(x[k]), np.asarray(y[k])), (x["level"], k)
+    long_list = n // T >= 4096
+    small = [lv["n_candidates"] < (1024 if lv["level"] == 2 else 16384 if elim else 4096)
+             for lv in a if lv["level"] > 1]
+    rows = "map_two_pass_chain" if elim else "map_exact_chain"
+    assert (rows in names) == (long_list and any(small))
+    assert any("pairs" in k for k in names) == (not long_list or not all(small))
+
+
+def test_few_candidates_cost(ctx, fe):
+    # a long recording of few types: no more than two and a half times the
+    # event-by-event kernels, which cut its events into segments
+    import time
+    rng = np.random.default_rng(6)
+    T, n = 4, 1_000_000
+    ids, ticks = ctx.stream_tensors(rng.integers(0, T, n).astype(np.int32),
+                                    np.sort(rng.integers(0, 100 * n, n)).astype(np.int32))
+    best = {}
+    for room in (1 << 62, 0):
+        ctx.set_param(fe.PARAM_LIST_BYTES, room)
+        t = []
+        for _ in range(4):
+            a = time.perf_counter()
+            ctx.mine(ids, ticks, T, [(0, 50), (50, 100), (100, 200)], 20_000, 4)
+            t.append(time.perf_counter() - a)
+        best[room] = min(t)
+    ctx.set_param(fe.PARAM_LIST_BYTES, 1 << 62)
+    banner("mining 1e6 events of 4 types: %.2f ms, event by event %.2f ms" % (
+        best[1 << 62] * 1e3, best[0] * 1e3))
+    assert best[1 << 62] < 2.5 * best[0]
