@@ -109,10 +109,10 @@ enum ChainMode { CHAIN_EXACT = 0, CHAIN_RELAXED = 1, CHAIN_TWO_PASS = 2 };
 // be null).
 void launch_index_check(const IndexSet &x, const Rows &rows, int nmax, int num_types, int *status,
                         int *wmax, hipStream_t s);
-// The rest of the index; the first kernel also copies *status to hstat (a
-// pinned host word, may be null).
+// The rest of the index; the first kernel also copies *status to hstat (may be
+// null), the last one zeroes *clear (not status; may be null).
 void launch_index_types(const IndexSet &x, const int *status, int *hstat, hipStream_t s);
-void launch_index_lists(const IndexSet &x, const int *status, hipStream_t s);
+void launch_index_lists(const IndexSet &x, const int *status, int *clear, hipStream_t s);
 // lam[0] = first index with tick >= ticks[from] - *wmax, lam[1] = *status
 // (lam: pinned host words).
 void launch_look_back(const int *ticks, int from, const int *wmax, const int *status, int *lam,

@@ -23,6 +23,7 @@ namespace {
 
 constexpr int MAX_CHUNKS = 4096;
 constexpr int SMALL_SCAN = 16384;  // counts scanned by one block
+constexpr unsigned FOLD = 1u << 20;  // blocks in one dimension of a grid of lists or jobs
 
 int64_t align64(int64_t x) { return (x + 63) & ~(int64_t)63; }
 
@@ -241,8 +242,8 @@ __global__ __launch_bounds__(TYB) void k_ix_types(IndexSet x, int scan_here, con
     const int st = *status;
     if (threadIdx.x == 0 && blockIdx.x == 0 && blockIdx.y == 0 && hstat) *hstat = st;
     if (st) return;
-    const int64_t job = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
-    if (job >= x.njobs) return;
+    const unsigned job = blockIdx.y * FOLD + blockIdx.x;
+    if (job >= (unsigned)x.njobs) return;
     const IndexJob j = global_job(x.jobs ? x.jobs[job] : x.one);
     const int n = j.n, T = j.T, nch = j.nch;
     const int *hist = j.hist;
@@ -352,11 +353,17 @@ __global__ __launch_bounds__(WAVE) void k_ix_lists(IndexSet x, const int *status
 // the buckets after its predecessor's, up to its own; the end of the list
 // fills the rest.  Long stretches are filled by the whole wave.  (54 us for
 // 9.7e6 events of 256 types, 78 MB of tables.)
-__global__ __launch_bounds__(256) void k_ix_tab(IndexSet s, const int *status)
+// clear (may be null): a word to zero.
+__global__ __launch_bounds__(256) void k_ix_tab(IndexSet s, const int *status, int *clear)
 {
-    if (*status) return;
-    const int64_t type = (int64_t)blockIdx.z * gridDim.x + blockIdx.x;
-    if (type >= s.types) return;
+    // (at the end: a store before them would take the jobs' reads off the scalar cache)
+    const bool clears = clear && blockIdx.x + blockIdx.y + blockIdx.z + threadIdx.x == 0;
+    if (*status) {
+        if (clears) *clear = 0;
+        return;
+    }
+    const unsigned type = blockIdx.z * FOLD + blockIdx.x;
+    if (type >= (unsigned)s.types) return;
     const IndexJob j = job_of(s, (int)type, [](const IndexJob &q) { return q.first_type; });
     const TypeIdx x = j.ty[(int)type - j.first_type];
     const int *et = j.et;
@@ -382,6 +389,7 @@ __global__ __launch_bounds__(256) void k_ix_tab(IndexSet s, const int *status)
             for (int b = c0 + lane; b <= c1; b += WAVE) tab[x.boff + b] = (int)(p0 + q);
         }
     }
+    if (clears) *clear = 0;
 }
 
 }  // namespace
@@ -400,12 +408,12 @@ void launch_index_types(const IndexSet &x, const int *status, int *hstat, hipStr
 {
     const bool here = !x.alone || x.scan <= SMALL_SCAN;
     if (!here) launch_scan_excl(x.one.hist, x.scan, x.one.off, x.scan_scratch, s);
-    const int jx = std::min(x.njobs, 1 << 20);
-    hipLaunchKernelGGL(k_ix_types, dim3((unsigned)jx, (unsigned)((x.njobs + (int64_t)jx - 1) / jx)),
-                       dim3(TYB), 0, s, x, here ? 1 : 0, status, hstat);
+    const unsigned R = (unsigned)x.njobs;
+    hipLaunchKernelGGL(k_ix_types, dim3(std::min(R, FOLD), (R - 1) / FOLD + 1), dim3(TYB), 0, s, x,
+                       here ? 1 : 0, status, hstat);
 }
 
-void launch_index_lists(const IndexSet &x, const int *status, hipStream_t s)
+void launch_index_lists(const IndexSet &x, const int *status, int *clear, hipStream_t s)
 {
     if (x.chunks > 0)
         hipLaunchKernelGGL(k_ix_lists, dim3((unsigned)x.chunks), dim3(WAVE),
@@ -413,9 +421,9 @@ void launch_index_lists(const IndexSet &x, const int *status, hipStream_t s)
                            x, status);
     if (x.types == 0) return;
     // (a grid's dimension holds fewer than 2^32 threads)
-    const int tx = std::min(x.types, 1 << 20);
-    const dim3 grid((unsigned)tx, (unsigned)x.parts, (unsigned)((x.types + (int64_t)tx - 1) / tx));
-    hipLaunchKernelGGL(k_ix_tab, grid, dim3(256), 0, s, x, status);
+    const unsigned T = (unsigned)x.types;
+    const dim3 grid(std::min(T, FOLD), (unsigned)x.parts, (T - 1) / FOLD + 1);
+    hipLaunchKernelGGL(k_ix_tab, grid, dim3(256), 0, s, x, status, clear);
 }
 
 namespace {
@@ -801,9 +809,10 @@ __global__ __launch_bounds__(WAVE, chain_waves(EMAX)) void k_chains(const ChainJ
     extern __shared__ int lds[];
     const int64_t item = grid_item();
     if (item >= total) return;
+    const int st = *status;
     int m;
     ChainJob j = job_at(jobs, first, njobs, item, m);
-    if (*status) {
+    if (__builtin_expect(st != 0, 0)) {
         // (no caller waits for the checks of a batch's run)
         if (__lane_id() == 0) j.upper[m] = j.exact[m] = -1;
         return;

@@ -887,7 +887,7 @@ int chain_call(fe_ctx *c, const int *ids, const int *ticks, int64_t n, int num_t
         launch_index_check(x, j.rows, cin.nmax, num_types, P<int>(c->status), nullptr, s);
         launch_index_types(x, st, c->host, s);
         HIPCHK(c, hipEventRecord(c->checked, s));
-        launch_index_lists(x, st, s);
+        launch_index_lists(x, st, nullptr, s);
     }
     c->stats.map_launches += mode == CHAIN_TWO_PASS ? 2 : 1;
     c->stats.segments_max = std::max<int64_t>(c->stats.segments_max, Pn);
@@ -941,7 +941,7 @@ int chain_resume(fe_ctx *c, const int *ids, const int *ticks, int64_t n, int num
         x = index_set(ip, index_job(ip, ids + lam, ticks + lam, base, lam), base);
         launch_index_check(x, Rows{}, 1, num_types, P<int>(c->status), nullptr, s);
         launch_index_types(x, st, nullptr, s);
-        launch_index_lists(x, st, s);
+        launch_index_lists(x, st, nullptr, s);
     }
     ChainJob j{};
     j.ix = index_view(ip, base);
@@ -1566,7 +1566,7 @@ int mine_index(fe_ctx *c, const int *ids, const int *ticks, int64_t n, int num_t
         launch_index_types(x, st, c->host, s);
         HIPCHK(c, hipMemcpyAsync(c->pin, base + mc.ip.o_ty, tyb, hipMemcpyDeviceToHost, s));
         HIPCHK(c, hipEventRecord(c->checked, s));
-        launch_index_lists(x, st, s);
+        launch_index_lists(x, st, nullptr, s);
     }
     if ((rc = wait_checks(c))) return rc;
     hist.resize(num_types);
@@ -2534,14 +2534,16 @@ ChainBlock chain_block(std::vector<IndexJob> &ij, const std::vector<ChainJob> &c
     return b;
 }
 
+// status: two words.  The checks go to the first, which is 0 before and after;
+// the second holds their result from then on.
 void launch_chain_block(const ChainLaunch &l, int *status, hipStream_t s)
 {
     if (l.set.njobs == 0) return;
     launch_index_check(l.set, Rows{}, 1, 1, status, nullptr, s);
-    launch_index_types(l.set, status, nullptr, s);
-    launch_index_lists(l.set, status, s);
-    launch_chains(l.jobs, l.first_row, l.first_item, l.set.njobs, l.rows, l.items, l.nmax, status,
-                  s);
+    launch_index_types(l.set, status, status + 1, s);
+    launch_index_lists(l.set, status + 1, status, s);
+    launch_chains(l.jobs, l.first_row, l.first_item, l.set.njobs, l.rows, l.items, l.nmax,
+                  status + 1, s);
 }
 
 // Plans a batch counted by chains: checks every stream and table (one wait)
@@ -2575,8 +2577,9 @@ int batch_chain_plan(fe_batch *b)
     if (!list_room(c, ints * (int64_t)sizeof(int) + segs * (int64_t)sizeof(int4)) ||
         ensure(c, b->ixd, (size_t)ints * sizeof(int)) ||
         ensure(c, b->csegs, (size_t)segs * sizeof(int4)) ||
-        ensure(c, b->cjobs, chain_block_bytes(R)) || ensure(c, b->cstat, sizeof(int)))
+        ensure(c, b->cjobs, chain_block_bytes(R)) || ensure(c, b->cstat, 2 * sizeof(int)))
         return FE_OK;
+    launch_fill(P<int>(b->cstat), 0, 2, s);
     std::vector<IndexJob> ij(R);
     std::vector<ChainJob> cj(R);
     int *at = P<int>(b->ixd);
@@ -2976,7 +2979,6 @@ extern "C" int fe_batch_run(fe_batch *b)
     HIPCHK(c, hipSetDevice(c->device));
     if (b->chain) {
         KTimer kt(c, "batch_two_pass_chain", 0);
-        launch_fill(P<int>(b->cstat), 0, 1, c->stream);
         launch_chain_block(b->chains, P<int>(b->cstat), c->stream);
         HIPCHK(c, hipGetLastError());
         return FE_OK;
@@ -3255,7 +3257,7 @@ int server_launch_chain(fe_server *sv, fe_server::Lane &ln)
     launch_chain_block(blk.at(ar), P<int>(ln.statd), s);
     HIPCHK(c, hipMemcpyAsync(ln.hout, ln.outd.p, (size_t)R * 2 * M * sizeof(int),
                              hipMemcpyDeviceToHost, s));
-    HIPCHK(c, hipMemcpyAsync(ln.hout + (size_t)R * 2 * M, ln.statd.p, sizeof(int),
+    HIPCHK(c, hipMemcpyAsync(ln.hout + (size_t)R * 2 * M, P<int>(ln.statd) + 1, sizeof(int),
                              hipMemcpyDeviceToHost, s));
     HIPCHK(c, hipEventRecord(ln.done, s));
     HIPCHK(c, hipGetLastError());
@@ -3746,7 +3748,7 @@ extern "C" int fe_server_create(fe_ctx *c, const fe_server_config *cfg, const in
             return bail(rc);
         if ((rc = ensure(c, L.jobsd, (size_t)cfg->max_round * sizeof(BJob)))) return bail(rc);
         if ((rc = ensure(c, L.segd, ROUND_RESULTS * sizeof(int4)))) return bail(rc);
-        if ((rc = ensure(c, L.statd, sizeof(int)))) return bail(rc);
+        if ((rc = ensure(c, L.statd, 2 * sizeof(int)))) return bail(rc);
         if (deep_bytes > 0 && (rc = ensure(c, L.deepd, (size_t)deep_bytes))) return bail(rc);
         HIPCHK(c, hipHostMalloc((void **)&L.hout,
                                 ((size_t)cfg->max_round * 2 * M + 1) * sizeof(int)));
