@@ -101,7 +101,9 @@ struct ChainJob {
 
 inline unsigned seg_share(int P) { return 0xffffffffu / (unsigned)P; }
 
-enum ChainMode { CHAIN_EXACT = 0, CHAIN_RELAXED = 1, CHAIN_TWO_PASS = 2 };
+// (CHAIN_SURVIVORS: exact counts where upper, which is there already, is at least
+// theta; -1 elsewhere)
+enum ChainMode { CHAIN_EXACT = 0, CHAIN_RELAXED = 1, CHAIN_TWO_PASS = 2, CHAIN_SURVIVORS = 3 };
 
 // Validates the streams and (rows.M > 0) the candidate rows into *status, and
 // starts the index with the per-chunk type histograms (T = 0 in the plan:

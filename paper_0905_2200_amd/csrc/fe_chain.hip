@@ -763,7 +763,7 @@ __global__ __launch_bounds__(WAVE, chain_waves(EMAX)) void k_chain(ChainJob j, c
     const int per = blocks / XCDS;
     const int m = (b < per * XCDS ? b % XCDS * per + b / XCDS : b) << log2_rows;
     unsigned long long todo = 1;
-    if (MODE == CHAIN_EXACT && j.P > 1 && j.upper) {
+    if (MODE == CHAIN_EXACT && j.upper) {
         // survivors only
         const int at = m + __lane_id();
         todo = bal((int)__lane_id() < per_wave && at < M && j.upper[at < M ? at : 0] >= j.theta);
@@ -1088,6 +1088,10 @@ void launch_chain(const ChainJob &job, ChainMode mode, int nmax, const int *stat
     if (job.rows.M <= 0) return;
     if (mode == CHAIN_TWO_PASS && job.P == 1) return chain_mode<CHAIN_TWO_PASS>(job, nmax, status, s);
     ChainJob j = job;
+    if (mode == CHAIN_SURVIVORS) {
+        if (j.P == 1) launch_fill(j.exact, -1, j.rows.M, s);  // (else k_stitch does)
+        return chain_mode<CHAIN_EXACT>(j, nmax, status, s);
+    }
     if (mode != CHAIN_EXACT) chain_mode<CHAIN_RELAXED>(j, nmax, status, s);
     if (mode != CHAIN_RELAXED) {
         // (exact alone: every candidate is taken)

@@ -826,14 +826,18 @@ bool event_by_event(int T, int M, int nmax, double f)
     return T == 1 || f < 1.0 || f * hops * std::sqrt(hops) >= 18.0 * T;
 }
 
-// Decides that for a call whose stream and table it checks (both synchronise;
-// such calls take milliseconds).  si: the stream's, for the other kernels.
+// Decides that; si is then the stream's, for the other kernels.  Calls that it
+// may concern have their stream and table checked (both synchronise; such calls
+// take milliseconds).
 int few_types_rule(fe_ctx *c, const int *ids, const int *ticks, int n, int num_types,
                    const CandIn &cin, int M, StreamInfo &si, bool &events)
 {
     int rc;
     hipStream_t s = c->stream;
     events = false;
+    if (num_types > FEW_TYPES || cin.nmax == 1 || M < FEW_TYPES_ROWS || n < 16384 ||
+        (int64_t)M * (3 * cin.nmax - 2) >= (int64_t)1 << 30)
+        return FE_OK;
     if ((rc = stream_info(c, ids, ticks, n, num_types, si))) return rc;
     if ((rc = ensure(c, c->small, sizeof(int)))) return rc;
     IndexSet none;
@@ -866,7 +870,7 @@ int chain_call(fe_ctx *c, const int *ids, const int *ticks, int64_t n, int num_t
     taken = false;
     const IndexPlan ip = index_plan(n, num_types, true);
     if (!index_room(c, ip) || ensure(c, c->cidx, (size_t)ip.ints * sizeof(int))) return FE_OK;
-    const int Pn = seg_room(c, ip, M, chain_P(c, M, n, num_types, cin.nmax, mode == CHAIN_EXACT));
+    const int Pn = seg_room(c, ip, M, chain_P(c, M, n, num_types, cin.nmax, mode == CHAIN_EXACT || mode == CHAIN_SURVIVORS));
     if ((rc = ensure_host(c, 4))) return rc;
     if (!c->checked)
         HIPCHK(c, hipEventCreateWithFlags(&c->checked, hipEventDisableTiming));
@@ -892,9 +896,9 @@ int chain_call(fe_ctx *c, const int *ids, const int *ticks, int64_t n, int num_t
     c->stats.map_launches += mode == CHAIN_TWO_PASS ? 2 : 1;
     c->stats.segments_max = std::max<int64_t>(c->stats.segments_max, Pn);
     {
-        const char *name = mode == CHAIN_EXACT     ? "map_exact_chain"
-                           : mode == CHAIN_RELAXED ? "map_relaxed_chain"
-                                                   : "map_two_pass_chain";
+        const char *name = mode == CHAIN_RELAXED    ? "map_relaxed_chain"
+                           : mode == CHAIN_TWO_PASS ? "map_two_pass_chain"
+                                                    : "map_exact_chain";
         KTimer kt(c, name, (double)M * (double)n);
         launch_chain(j, mode, cin.nmax, st, s);
         if (nsurv) launch_count_ge(upper, M, theta, nsurv, st, s);
@@ -1194,8 +1198,7 @@ extern "C" int fe_count(fe_ctx *c, const int32_t *ids, const int32_t *ticks, int
     CandIn cin{types, len, lo, hi, nmax};
     bool taken = false, events = M == 0 || !chain_takes(c, n, num_types);
     StreamInfo si{};
-    if (!events && mode == FE_RELAXED && num_types <= FEW_TYPES && nmax > 1 &&
-        M >= FEW_TYPES_ROWS && n >= 16384 && (int64_t)M * (3 * nmax - 2) < (int64_t)1 << 30 &&
+    if (!events && mode == FE_RELAXED &&
         (rc = few_types_rule(c, ids, ticks, (int)n, num_types, cin, M, si, events)))
         return rc;
     if (!events)
@@ -1277,16 +1280,21 @@ extern "C" int fe_count_two_pass(fe_ctx *c, const int32_t *ids, const int32_t *t
     HIPCHK(c, hipSetDevice(c->device));
     c->stats = fe_stats{};
     CandIn cin{types, len, lo, hi, nmax};
-    bool taken = false;
-    if (M > 0 && chain_takes(c, n, num_types))
-        rc = chain_call(c, ids, ticks, n, num_types, cin, M, CHAIN_TWO_PASS, theta, upper_out,
-                        exact_out, n_survivors_out, taken);
+    bool taken = false, events = false;
+    StreamInfo si{};
+    if (M > 0 && chain_takes(c, n, num_types)) {
+        if ((rc = few_types_rule(c, ids, ticks, (int)n, num_types, cin, M, si, events))) return rc;
+        if (events && (rc = count_impl(c, ids, ticks, si, num_types, cin, M, FE_RELAXED, upper_out)))
+            return rc;
+        rc = chain_call(c, ids, ticks, n, num_types, cin, M,
+                        events ? CHAIN_SURVIVORS : CHAIN_TWO_PASS, theta, upper_out, exact_out,
+                        n_survivors_out, taken);
+    }
     if (taken) {
         c->stats.last_call_ms = now_ms() - t0;
         return rc;
     }
-    StreamInfo si;
-    if ((rc = stream_info(c, ids, ticks, (int)n, num_types, si))) return rc;
+    if (si.n == 0 && (rc = stream_info(c, ids, ticks, (int)n, num_types, si))) return rc;
     rc = two_pass_impl(c, ids, ticks, si, num_types, cin, M, theta, upper_out, exact_out,
                        n_survivors_out);
     c->stats.last_call_ms = now_ms() - t0;

@@ -533,3 +533,27 @@ def test_relaxed_rows_over_few_types(ctx, fe, T, rows):
         ctx.count(ids, ticks.flip(0), T, many, RELAXED)
     assert e.value.code == fe.FE_EUNSORTED
     assert np.array_equal(ctx.count(ids, ticks, T, many, RELAXED).cpu().numpy(), got)
+
+
+@pytest.mark.parametrize("T,gap", [(1, 3), (2, 300), (3, 3), (4, 2), (4, 40)])
+@pytest.mark.parametrize("rows", [1500, 9000])
+def test_two_passes_over_few_types(ctx, T, gap, rows):
+    # the relaxed pass of either kind, then the survivors: all, some and none
+    rng = np.random.default_rng(100 * T + gap + rows)
+    n = 17_000
+    eps = synth.random_episodes(rng, 60, T, 6, [(0, 150), (30, 180), (0, 90)], n_min=2)
+    cand = synth.pack(eps)
+    many = synth.pack([eps[i % len(eps)] for i in range(rows)])
+    at = np.arange(rows) % len(eps)
+    ids_h = rng.integers(0, T, n).astype(np.int32)
+    ticks_h = np.sort(rng.integers(0, gap * n // T, n)).astype(np.int32)
+    ids, ticks = ctx.stream_tensors(ids_h, ticks_h)
+    up = oracle_counts(ids_h, ticks_h, T, cand, RELAXED)
+    for theta in (0, 1, int(np.median(up)), int(up.max()) + 1):
+        banner("two passes over few types: T=%d gap=%d rows=%d theta=%d" % (T, gap, rows, theta))
+        wu, we = oracle.two_pass(ids_h, ticks_h, T, cand["types"], cand["len"], cand["lo"],
+                                 cand["hi"], theta, projection=True)
+        gu, ge, ns = ctx.count_two_pass(ids, ticks, T, many, theta)
+        assert np.array_equal(gu.cpu().numpy(), wu[at])
+        assert np.array_equal(ge.cpu().numpy(), we[at])
+        assert int(ns.item()) == int((wu[at] >= theta).sum())
