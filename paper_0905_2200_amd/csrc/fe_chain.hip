@@ -672,12 +672,15 @@ __device__ __forceinline__ int seg_at(const ChainJob &j, int c, int p)
 // need 2.5 KB of LDS a wave, so their walks keep to eight waves' scalar
 // registers, the rest of them in vector lanes: 14.5 -> 12.3 ms for the 1e5
 // rows above (5.7 -> 7.6 waves resident).  Tables of four and five (EMAX = 3; 3
-// and 4 KB) do so where the launch has the waves: 30 000 rows of 4 nodes over
-// 3e6 events (11 segments) 1.13 -> 1.05 ms exact, 1.30 -> 1.17 relaxed; 8000
-// rows (3 segments) 0.22 -> 0.23 and 3000 rows 0.11 -> 0.12 exact, which take
-// the others' kernel.  Longer tables have LDS for five waves only, and 2% more
-// time with fewer registers.
-constexpr int64_t EIGHT_WAVES = 1 << 17;
+// and 4 KB) do so where the launch has the waves.  Eight waves' registers / the
+// others', exact and relaxed ms by waves, 4 nodes: 3e5 events of 200 types, 12 000
+// waves 0.175 / 0.163 and 0.194 / 0.188, 30 000 0.230 / 0.235 and 0.272 / 0.289; 1e6
+// of 64 types, 24 000 waves 0.448 / 0.444 and 0.593 / 0.666, 36 000 0.577 / 0.595 and
+// 0.787 / 0.866, 180 000 2.06 / 2.24 and 2.88 / 3.32; 3e6 of 128 types, 44 000 waves
+// 0.453 / 0.480 and 0.555 / 0.595; 5 nodes the same.  Longer tables take the general
+// kernel, whose scalar registers hold seven waves; of six nodes they have LDS for
+// eight (5 KB a wave), of eight for five (7 KB).
+constexpr int64_t EIGHT_WAVES = 1 << 15;
 constexpr int chain_waves(int emax) { return emax <= 3 ? 8 : 1; }
 
 // One wave per (segment, candidate).  P = 1 writes the counts; P > 1 the
@@ -809,14 +812,14 @@ __global__ __launch_bounds__(WAVE, chain_waves(EMAX)) void k_chains(const ChainJ
     extern __shared__ int lds[];
     const int64_t item = grid_item();
     if (item >= total) return;
-    const int st = *status;
     int m;
-    ChainJob j = job_at(jobs, first, njobs, item, m);
-    if (__builtin_expect(st != 0, 0)) {
+    if (__builtin_expect(*status != 0, 0)) {
         // (no caller waits for the checks of a batch's run)
+        const ChainJob j = job_at(jobs, first, njobs, item, m);
         if (__lane_id() == 0) j.upper[m] = j.exact[m] = -1;
         return;
     }
+    ChainJob j = job_at(jobs, first, njobs, item, m);
     j.seg = nullptr;
     j.P = 1;
     chain_item<MODE, EMAX>(j, m, 0, lds);
@@ -1498,7 +1501,9 @@ __global__ __launch_bounds__(256) void k_order(const int *__restrict__ F, int w,
         order[atomicAdd(&sh[F[(int64_t)a * w + w - 1]], 1)] = a;
 }
 
-// Waves a SIMD is given registers for, by length (2, 3, more shared nodes).
+// Waves a SIMD is given registers for, by length (2, 3, more shared nodes).  Two
+// of the kernels keep a few vector registers in scratch for it: relaxed, two shared
+// nodes, 12 (36 B a lane); exact, three, 4 (20 B).
 constexpr int sib_waves(bool rel, int emax) { return emax == 1 ? 7 : emax == 2 && !rel ? 6 : 5; }
 
 // One wave per frequent episode and QW mask words (grid z), by the episodes'
