@@ -50,8 +50,9 @@
  *   per-type event lists of the stream, which each call builds in library
  *   workspace (about 16 B per event), and need no lists of their own; calls
  *   those do not take (FE_PARAM_TYPE_DISPATCH = 0, FE_PARAM_SEGMENTS > 0,
- *   more than 4096 types or about 2^29 events, or no memory for them) run the
- *   machines event by event.  There, Algorithm 1's list for hop k matters
+ *   more than 4096 types or about 2^29 events, no memory for them or more than
+ *   FE_PARAM_LIST_BYTES), and relaxed counts of many candidates over up to 4
+ *   types where that is faster, run the machines event by event.  There, Algorithm 1's list for hop k matters
  *   only through the ticks that pass its test, a union of windows of which
  *   at most hi_k/(hi_k-lo_k+1)+1 are live at once.  Candidates whose hops
  *   all have at most 8 live windows keep their lists in registers; the
@@ -94,9 +95,11 @@ typedef enum fe_param {
     FE_PARAM_TARGET_WAVES = 1, /* waves the automatic P aims for per launch
                                 (default 16384: two generations of 8 waves
                                 per SIMD on 256 CUs)                          */
-    FE_PARAM_MIN_SEG_EVENTS = 2, /* smallest segment the automatic P allows   */
-    FE_PARAM_CONCAT_TREE = 3, /* 1 = wave-shuffle tree Concatenate when P >= 16,
-                                 0 = per-candidate sequential walk             */
+    FE_PARAM_MIN_SEG_EVENTS = 2, /* smallest segment the automatic P allows
+                                 (event by event; not over per-type lists)     */
+    FE_PARAM_CONCAT_TREE = 3, /* event by event: 1 = wave-shuffle tree
+                                 Concatenate when P >= 16, 0 = per-candidate
+                                 sequential walk                               */
     FE_PARAM_TIMING = 4,     /* 1 = time every kernel launch with HIP events on
                                 the context's stream (fe_get_kernel_stats)     */
     FE_PARAM_TYPE_DISPATCH = 5, /* 1 (default) = per-type dispatch: a candidate
@@ -108,7 +111,9 @@ typedef enum fe_param {
                                 N-1 types, those events wave-wide plus each
                                 lane's own last-type events); 0 = every event
                                 through every lane.  Read at each count call,
-                                at fe_batch_create and at each server round.
+                                at fe_batch_create, at fe_server_submit (lists
+                                or event by event) and, for the requests
+                                counted event by event, at each server round.
                                 Counts are identical either way.              */
     FE_PARAM_CROSSOVER_A = 6, /* hybrid rule (Algorithm 2, Eq. 2), exact       */
     FE_PARAM_CROSSOVER_B = 7, /* counter: a group of tiles >= A/N + B tiles of
@@ -158,9 +163,10 @@ typedef enum fe_param {
                                 defaults 9699 and 6165 (same fit)             */
     FE_PARAM_PASS1_COST = 13, /* cost of the relaxed pass per candidate, in
                                 thousandths of the exact pass's (default
-                                1000: on the mining workload's level 4 the
-                                relaxed pass takes as long as the exact one
-                                with shared lists); used by
+                                1000, no less than the exact pass's: over
+                                per-type lists a level's relaxed pass takes 2
+                                to 5 times as long, event by event with shared
+                                lists as long); used by
                                 FE_PARAM_ELIMINATION = 2                      */
     FE_PARAM_SAMPLE_MIN = 14, /* smallest level sampled by FE_PARAM_ELIMINATION
                                 = 2 (default 131072 candidates)                */
@@ -211,12 +217,10 @@ int fe_validate(fe_ctx *ctx, const int32_t *ids, const int32_t *ticks,
 
 /* Count every candidate over the stream (Algorithm 1 for FE_EXACT,
  * Algorithm 3 for FE_RELAXED): by chains of events over per-type lists of
- * the stream, built by the call, or (FE_PARAM_TYPE_DISPATCH = 0, segments
- * asked for, more than 4096 types, more than about 2^29 events, or no memory for
- * the lists) event by event; over P segments (MapConcatenate, Sec. 5.2.2)
+ * the stream, built by the call, or (see above) event by event; over P segments (MapConcatenate, Sec. 5.2.2)
  * with exact stitching where the candidates alone do not fill the device.
  * counts_out: device int32[M], in candidate order.  Synchronises once (input
- * checks). */
+ * checks; up to 4 types and 1024 or more candidates: more often). */
 int fe_count(fe_ctx *ctx, const int32_t *ids, const int32_t *ticks, int64_t n,
              int32_t num_types, const int32_t *types, const int32_t *len,
              const int32_t *lo, const int32_t *hi, int32_t M, int32_t nmax,
@@ -268,7 +272,8 @@ int fe_count_resume(fe_ctx *ctx, const int32_t *ids, const int32_t *ticks, int64
  * count; candidates with upper < theta are dropped (exact_out[m] = -1);
  * exact_out[m] = exact count for the others.  *n_survivors_out (device
  * int32) receives the number kept.  All outputs are device pointers.
- * Synchronises once (input checks; event by event: each pass's grouping). */
+ * Synchronises once (input checks; event by event, and as fe_count for few
+ * types: each pass's grouping). */
 int fe_count_two_pass(fe_ctx *ctx, const int32_t *ids, const int32_t *ticks,
                       int64_t n, int32_t num_types, const int32_t *types,
                       const int32_t *len, const int32_t *lo,
@@ -367,7 +372,8 @@ typedef struct fe_batch_tuning {
 /* Plan the two-pass count (Algorithm 4) of R recordings as one batch:
  * validates every stream and candidate table (synchronises) and lays out the
  * recordings' per-type lists, which each run builds anew before one launch
- * counts every candidate of every recording, the longest recordings first.
+ * counts every candidate of every recording, the longest recordings first (few
+ * candidates over long recordings: in segments, a few launches a pass).
  * With FE_PARAM_TYPE_DISPATCH = 0, more than 4096 types or no memory for the
  * lists it instead tiles every
  * recording's candidates, splits long recordings into MapConcatenate
