@@ -68,8 +68,9 @@ struct IndexSet {
     int64_t scan = 0;           // counts of a stream indexed alone
     int *scan_scratch = nullptr;
 };
-// blocks a type that fill the bucket tables
-int index_parts(const IndexJob &j);
+// blocks a type that fill the bucket tables of a stream of T types (types: of all
+// that are indexed together)
+int index_parts(int n, int T, int types);
 IndexSet index_set(const IndexPlan &p, const IndexJob &j, int *base);
 
 // Candidate rows with strides: node k of candidate m has type

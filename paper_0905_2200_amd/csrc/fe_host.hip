@@ -2520,10 +2520,10 @@ ChainBlock chain_block(std::vector<IndexJob> &ij, const std::vector<ChainJob> &c
         x.chunks += ij[r].nch;
         x.types += ij[r].T;
         x.most_types = std::max(x.most_types, ij[r].T);
-        x.parts = std::max(x.parts, index_parts(ij[r]));
         row[r + 1] = row[r] + cj[r].rows.M;
         item[r + 1] = item[r] + (int64_t)cj[r].rows.M * cj[r].P;
     }
+    for (const IndexJob &j : ij) x.parts = std::max(x.parts, index_parts(j.n, j.T, x.types));
     b.rows = row[R];
     b.items = item[R];
     b.nmax = nmax;

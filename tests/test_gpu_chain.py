@@ -557,3 +557,55 @@ def test_two_passes_over_few_types(ctx, T, gap, rows):
         assert np.array_equal(gu.cpu().numpy(), wu[at])
         assert np.array_equal(ge.cpu().numpy(), we[at])
         assert int(ns.item()) == int((wu[at] >= theta).sum())
+
+
+@pytest.mark.parametrize("T,n,hot", [(300, 60_000, 1), (2000, 40_000, 2), (4096, 20_000, 1), (7, 33_000, 1)])
+def test_types_of_most_events(ctx, fe, T, n, hot):
+    # lists far longer than the average, whose tables several blocks fill
+    rng = np.random.default_rng(T + n)
+    ids_h = np.where(rng.random(n) < 0.95, rng.integers(T - hot, T, n),
+                     rng.integers(0, T, n)).astype(np.int32)
+    ticks_h = np.sort(rng.integers(0, 20 * n, n)).astype(np.int32)
+    eps = synth.random_episodes(rng, 150, T, 4, IVS, n_min=1)
+    eps += [((T - 1,) * k, (0,) * (k - 1), (30,) * (k - 1)) for k in (1, 2, 3, 4)]
+    eps += [((T - 1, int(e), T - 1), (0, 5), (300, 400)) for e in rng.integers(0, T, 60)]
+    cand = synth.pack(eps)
+    banner("types of most events: T=%d" % T)
+    _check(ctx, ids_h, ticks_h, T, cand, "T=%d" % T)
+    ids, ticks = ctx.stream_tensors(ids_h, ticks_h)
+    wu, we = oracle.two_pass(ids_h, ticks_h, T, cand["types"], cand["len"], cand["lo"],
+                             cand["hi"], 3, projection=True)
+    b = fe.Batch(ctx, [{"ids": ids, "ticks": ticks, "num_types": T,
+                        "cand": ctx.cand_tensors(cand), "theta": 3}] * 3)
+    b.run()
+    ctx.sync()
+    for r in range(3):
+        assert np.array_equal(b.upper[r].cpu().numpy(), wu)
+        assert np.array_equal(b.exact[r].cpu().numpy(), we)
+    b.close()
+
+
+def test_types_of_most_events_cost(ctx, fe):
+    # the index of a stream with two types of nine tenths of its events takes no
+    # more than three times that of an even one
+    import time
+    rng = np.random.default_rng(12)
+    T, n = 1000, 1_000_000
+    cand = ctx.cand_tensors(synth.pack([((3, 5), (0,), (50,))]))
+    best = []
+    for hot in (False, True):
+        ids_h = rng.integers(0, T, n)
+        if hot:
+            ids_h = np.where(rng.random(n) < 0.9, rng.integers(0, 2, n), ids_h)
+        ids, ticks = ctx.stream_tensors(ids_h.astype(np.int32),
+                                        np.sort(rng.integers(0, 8 * n, n)).astype(np.int32))
+        t = []
+        for _ in range(6):
+            ctx.torch.cuda.synchronize()
+            a = time.perf_counter()
+            ctx.count(ids, ticks, T, cand, EXACT)
+            ctx.torch.cuda.synchronize()
+            t.append(time.perf_counter() - a)
+        best.append(min(t))
+    banner("even %.0f us, uneven %.0f us" % (best[0] * 1e6, best[1] * 1e6))
+    assert best[1] < 3 * best[0]
