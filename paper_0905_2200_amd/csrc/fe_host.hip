@@ -1196,15 +1196,22 @@ extern "C" int fe_count(fe_ctx *c, const int32_t *ids, const int32_t *ticks, int
     HIPCHK(c, hipSetDevice(c->device));
     c->stats = fe_stats{};
     CandIn cin{types, len, lo, hi, nmax};
-    bool taken = false, events = M == 0 || !chain_takes(c, n, num_types);
+    bool taken = false, events = false;
     StreamInfo si{};
-    if (!events && mode == FE_RELAXED &&
-        (rc = few_types_rule(c, ids, ticks, (int)n, num_types, cin, M, si, events)))
-        return rc;
-    if (!events)
-        rc = chain_call(c, ids, ticks, n, num_types, cin, M,
-                        mode == FE_EXACT ? CHAIN_EXACT : CHAIN_RELAXED, 0, counts_out, counts_out,
-                        nullptr, taken);
+    if (M > 0 && chain_takes(c, n, num_types)) {
+        if (mode == FE_RELAXED &&
+            (rc = few_types_rule(c, ids, ticks, (int)n, num_types, cin, M, si, events)))
+            return rc;
+        if (events) {
+            // (without memory for it, the lists)
+            rc = count_impl(c, ids, ticks, si, num_types, cin, M, mode, counts_out);
+            taken = rc != FE_ENOMEM;
+        }
+        if (!taken)
+            rc = chain_call(c, ids, ticks, n, num_types, cin, M,
+                            mode == FE_EXACT ? CHAIN_EXACT : CHAIN_RELAXED, 0, counts_out,
+                            counts_out, nullptr, taken);
+    }
     if (!taken) {
         if (si.n == 0 && (rc = stream_info(c, ids, ticks, (int)n, num_types, si))) return rc;
         rc = count_impl(c, ids, ticks, si, num_types, cin, M, mode, counts_out);
@@ -1284,8 +1291,11 @@ extern "C" int fe_count_two_pass(fe_ctx *c, const int32_t *ids, const int32_t *t
     StreamInfo si{};
     if (M > 0 && chain_takes(c, n, num_types)) {
         if ((rc = few_types_rule(c, ids, ticks, (int)n, num_types, cin, M, si, events))) return rc;
-        if (events && (rc = count_impl(c, ids, ticks, si, num_types, cin, M, FE_RELAXED, upper_out)))
-            return rc;
+        if (events) {
+            rc = count_impl(c, ids, ticks, si, num_types, cin, M, FE_RELAXED, upper_out);
+            if (rc && rc != FE_ENOMEM) return rc;
+            events = rc == FE_OK;
+        }
         rc = chain_call(c, ids, ticks, n, num_types, cin, M,
                         events ? CHAIN_SURVIVORS : CHAIN_TWO_PASS, theta, upper_out, exact_out,
                         n_survivors_out, taken);
