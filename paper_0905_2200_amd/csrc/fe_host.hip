@@ -814,7 +814,7 @@ int wait_checks(fe_ctx *c)
 //   4 types    20 Hz, 5 nodes 4.5 / 3.3;  100 Hz, 8 nodes 34 / 63;  300 Hz, 5 nodes
 //              34 / 39, 8 nodes 64 / 39;  1 kHz, 3 nodes 14 / 15, 8 nodes 69 / 39
 //   8 types    20 Hz, 5 nodes 2.2 / 2.5;  1 kHz, 8 nodes 35 / 39
-// (exact, the lists take a tenth or less of the others' time everywhere.)  At
+// (exact, the lists take a quarter of the others' time at most.)  At
 // 2000 rows the few rows' segments fill the device: 1 type 20 Hz, 5 nodes 2.9 /
 // 1.0, 100 Hz 8.6 / 27, 1 kHz 51 / 22; 2 types 20 Hz 1.2 / 0.72, 1 kHz 22 / 22.
 constexpr int FEW_TYPES = 4;
