@@ -814,28 +814,48 @@ int wait_checks(fe_ctx *c)
 //   4 types    20 Hz, 5 nodes 4.5 / 3.3;  100 Hz, 8 nodes 34 / 63;  300 Hz, 5 nodes
 //              34 / 39, 8 nodes 64 / 39;  1 kHz, 3 nodes 14 / 15, 8 nodes 69 / 39
 //   8 types    20 Hz, 5 nodes 2.2 / 2.5;  1 kHz, 8 nodes 35 / 39
-// (exact, the lists take a quarter of the others' time at most.)  At
-// 2000 rows the few rows' segments fill the device: 1 type 20 Hz, 5 nodes 2.9 /
-// 1.0, 100 Hz 8.6 / 27, 1 kHz 51 / 22; 2 types 20 Hz 1.2 / 0.72, 1 kHz 22 / 22.
+// (exact, the lists take a quarter of the others' time at most.)  Long streams, 10 000
+// rows over 2e6 events: 1 type 20 Hz, 5 nodes 127 / 23; 2 types 100 Hz, 8 nodes 329 /
+// 478, 1 kHz, 3 nodes 221 / 140; 4 types 1 kHz, 3 nodes 97 / 137, 8 nodes 447 / 358.
+// Small calls, 20 000 rows over 2e4 events, 20 Hz, 5 nodes: 1 type 2.7 / 0.9, 4 types
+// 0.56 / 0.72.  Below 8192 rows the few rows' segments fill the device, and the lists
+// lose where most segments are run again, 8 nodes: 200 000 events, 2000 rows, 1 kHz, 1
+// type 85 / 34; 64 rows, 3 kHz, 1 type 165 / 32, 2 types 116 / 32, 4 types 1.3 / 34.  2 types at 1 kHz go either way, 64 rows 53 / 31, 200 rows over 2e6 events 240 /
+// 330: the lists.  Below 1024 rows a short stream is not asked about: a call of 0.1 ms
+// would wait for the answer first (one dense type loses: 200 rows over 2e4 events, 3
+// kHz, 8 nodes 23 / 4.5).
 constexpr int FEW_TYPES = 4;
 constexpr int FEW_TYPES_ROWS = 1024, MANY_ROWS = 8192;
-bool event_by_event(int T, int M, int nmax, double f)
+constexpr double SPARSE_WORK = 1e8, DENSE_WORK = 1 << 25;  // rows x events of a list
+
+bool event_by_event(int T, int M, int nmax, double work, double f)
 {
-    const double hops = nmax - 1;
-    if (M < MANY_ROWS) return (T <= 2 && f < 1.0) || (T == 1 && f >= 16.0 && nmax > 2);
-    return T == 1 || f < 1.0 || f * hops * std::sqrt(hops) >= 18.0 * T;
+    const double hops = nmax - 1, deep = f * hops * std::sqrt(hops);
+    if (f < 1.0) return work >= SPARSE_WORK * T;
+    if (M >= MANY_ROWS) return T == 1 || deep >= 26.0 * T;
+    if (f < 16.0 || nmax == 2) return false;
+    return T == 1 ? M >= FEW_TYPES_ROWS || deep >= 150.0 : T == 2 && deep >= 1000.0;
+}
+
+// Whether the rule can say so at all, before it costs a wait.
+bool few_types_asks(int T, int M, int n, int nmax, double work)
+{
+    if (T > FEW_TYPES || nmax == 1 || n < (M < FEW_TYPES_ROWS ? 32768 : 16384)) return false;
+    if (work >= SPARSE_WORK * T) return true;
+    if (M >= MANY_ROWS) return work >= DENSE_WORK;
+    return (T == 1 && nmax > 2) || (T == 2 && nmax > 3);
 }
 
 // Decides that; si is then the stream's, for the other kernels.  Calls that it
-// may concern have their stream and table checked (both synchronise; such calls
-// take milliseconds).
+// may concern have their stream and table checked, and wait for both.
 int few_types_rule(fe_ctx *c, const int *ids, const int *ticks, int n, int num_types,
                    const CandIn &cin, int M, StreamInfo &si, bool &events)
 {
     int rc;
     hipStream_t s = c->stream;
     events = false;
-    if (num_types > FEW_TYPES || cin.nmax == 1 || M < FEW_TYPES_ROWS || n < 16384 ||
+    const double work = (double)M * n / num_types;
+    if (!few_types_asks(num_types, M, n, cin.nmax, work) ||
         (int64_t)M * (3 * cin.nmax - 2) >= (int64_t)1 << 30)
         return FE_OK;
     if ((rc = stream_info(c, ids, ticks, n, num_types, si))) return rc;
@@ -855,7 +875,7 @@ int few_types_rule(fe_ctx *c, const int *ids, const int *ticks, int n, int num_t
         return fail(c, status_code(bits), "%s", status_text(bits));
     }
     const double hop = (double)W / (cin.nmax - 1);
-    events = event_by_event(num_types, M, cin.nmax, hop * n / ((double)si.span * num_types));
+    events = event_by_event(num_types, M, cin.nmax, work, hop * n / ((double)si.span * num_types));
     return FE_OK;
 }
 

@@ -497,6 +497,32 @@ def test_many_types_cost_in_a_batch(ctx, fe):
     assert both < 2 * lone
 
 
+@pytest.mark.parametrize("n", [32_767, 32_768])
+@pytest.mark.parametrize("T", [1, 2, 3])
+@pytest.mark.parametrize("rows", [16, 1023])
+def test_relaxed_few_rows_over_dense_few_types(ctx, fe, n, T, rows):
+    # few rows with long dense windows: one or two types are counted event by event
+    # from a stream length on, three stay with the lists
+    rng = np.random.default_rng(100 * T + rows)
+    eps = synth.random_episodes(rng, 16, T, 6, [(0, 150), (30, 180)])
+    cand = synth.pack(eps)
+    many = synth.pack([eps[i % len(eps)] for i in range(rows)])
+    ids_h = rng.integers(0, T, n).astype(np.int32)
+    ticks_h = np.sort(rng.integers(0, n // T, n)).astype(np.int32)  # one of a type a tick
+    ids, ticks = ctx.stream_tensors(ids_h, ticks_h)
+    banner("few rows over few dense types: n=%d T=%d rows=%d" % (n, T, rows))
+    ctx.set_param(fe.PARAM_TIMING, 1)
+    try:
+        ctx.reset_kernel_stats()
+        got = ctx.count(ids, ticks, T, many, RELAXED).cpu().numpy()
+        lists = "map_relaxed_chain" in ctx.kernel_stats()
+    finally:
+        ctx.set_param(fe.PARAM_TIMING, 0)
+    want = oracle_counts(ids_h, ticks_h, T, cand, RELAXED)
+    assert np.array_equal(got, want[np.arange(rows) % len(eps)])
+    assert lists == (n < 32_768 or T == 3)
+
+
 @pytest.mark.parametrize("T", [1, 2, 3, 4, 5])
 @pytest.mark.parametrize("rows", [1023, 1024, 8191, 8192])
 def test_relaxed_rows_over_few_types(ctx, fe, T, rows):
